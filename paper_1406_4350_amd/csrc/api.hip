@@ -52,6 +52,8 @@ struct cheb_plan_s {
   int fft_batch = 1;
   HalfPlanes hproj, hback;                  // mixed plans: split planes of P (set with the projectors)
   bool split_gemm = true;                   // mixed plans: FP16 hi/lo split MFMA for P^H x and P w
+  RnsOperand rproj, rback;                  // FP64 plans: residue planes of P for P^H x and for P w (large plans)
+  bool rns_ok = false;                      // the planes hold the projectors (false: P unfit, FP64 products only)
   bool rr_refine = true;                    // warm-started refinement before the library eigensolver
   // Projections carried through the recurrence (reuse trick) are recomputed from the vectors every `resync`
   // steps (0: never); drift_on measures ||p_carried - P^H psi|| / ||P^H psi|| before every step of the filter
@@ -203,11 +205,23 @@ struct Persist {
   int4* col; int* ent; int4* xline; int4* pinfo; int2* dent; void* tw; void* kin; void* Vt; void* P; double* D; double* Q; c128* G; c128* Cinv; c128* Cmat; c128* Minv;
   _Float16* Hproj;  // mixed plans: FP16 hi/lo planes of P for P^H x (rows = projectors, k = plane waves)
   _Float16* Hback;  // and for P w (rows = plane waves, k = projectors)
+  int8_t *Rproj, *Rback;   // large FP64 plans: residue planes of P (rows = projectors; rows = plane waves)
+  double *Rpinv, *Rbinv;   // and the inverse scales of their rows
   int* gmap; int2* gpair;  // Gamma point maps
   size_t bytes;
 };
 
 inline long pad32(long k) { return (k + 31) / 32 * 32; }
+
+// Whether a plan holds the residue planes of its projectors: FP64 plans whose products over 1024 bands pay on the INT8
+// matrix cores, up to 64 GiB of planes (90 bytes per entry of P; 41 GB of the GPU's 288 at 137 065 x 3328). Gamma
+// plans take one or two real products per complex one instead of three and stay on the FP64 matrix cores.
+constexpr size_t kRnsPlaneCap = size_t(64) << 30;
+bool rns_planned(int npw, int nproj, int prec, int gamma) {
+  if (prec != CHEB_FP64 || gamma || nproj <= 0) return false;
+  if (!rns_pays(nproj, 1024, npw) && !rns_pays(npw, 1024, nproj)) return false;
+  return 3 * kRnsMods * (size_t(nproj) * rns_ld(npw) + size_t(npw) * rns_ld(nproj)) <= kRnsPlaneCap;
+}
 
 // Carves the persistent buffer (base == nullptr: only measures)
 Persist persist_layout(void* base, int n, int npw, int npf, int ncol, int rx, int nproj, size_t dsize, int overlap,
@@ -235,6 +249,14 @@ Persist persist_layout(void* base, int n, int npw, int npf, int ncol, int rx, in
     l.Hproj = b.take<_Float16>(4 * size_t(nproj) * pad32(npw));
     l.Hback = b.take<_Float16>(4 * size_t(npw) * pad32(nproj));
   }
+  l.Rproj = l.Rback = nullptr;
+  l.Rpinv = l.Rbinv = nullptr;
+  if (rns_planned(npw, nproj, prec, gamma)) {
+    l.Rproj = b.take<int8_t>(3 * kRnsMods * size_t(nproj) * rns_ld(npw));
+    l.Rback = b.take<int8_t>(3 * kRnsMods * size_t(npw) * rns_ld(nproj));
+    l.Rpinv = b.take<double>(nproj);
+    l.Rbinv = b.take<double>(npw);
+  }
   l.gmap = gamma ? b.take<int>(npf) : nullptr;
   l.gpair = gamma ? b.take<int2>(npw) : nullptr;
   l.bytes = b.off;
@@ -256,6 +278,16 @@ size_t part_elems(int M, int N, int K) {
 size_t upper_part_elems(int N, int K) {
   const int s = gemm_upper_splits(N, K);
   return s > 1 ? size_t(s) * N * N : 0;
+}
+
+// Columns taken at a time by a product on the INT8 matrix cores, whose residue planes (45 bytes per complex entry of
+// the operand and of the result) are scratch: about equal pieces of at most kRnsChunk columns, whole tiles of 256.
+constexpr int kRnsChunk = 1024;
+constexpr int kRnsGramChunk = 512;  // and by P^H P, whose set-up has no other large scratch
+long rns_chunk(int nb) {
+  const long pieces = (nb + kRnsChunk - 1) / kRnsChunk;
+  const long per = (nb + pieces - 1) / pieces;
+  return std::min<long>(nb, (per + 255) / 256 * 256);
 }
 
 // Scratch of the FFT passes: two disk-column buffers for a batch of bands.
@@ -285,6 +317,12 @@ struct Ws {
   c128 *cp = nullptr, *cq = nullptr, *cr = nullptr;  // iterative capacitance solve: right side, solution, residual
   c128* pfresh = nullptr;  // projections recomputed from the vectors (drift monitor)
   double* dcol = nullptr;  // per-band relative drift
+  // products on the INT8 matrix cores: flag, scales and inverse scales of the call's operand, its residue planes, the
+  // products' planes (both for at most kRnsChunk columns at a time; null where no product of the call takes them)
+  int* rflag = nullptr;
+  double *rscale = nullptr, *rinv = nullptr;
+  int8_t *rB = nullptr, *rC = nullptr;
+  size_t rB_bytes = 0, rC_bytes = 0;
   void* Xs = nullptr;   // band-sorted copy for the per-band degree filter
   int* lidx = nullptr;  // its gather / scatter indices (3 nb)
   void* solver = nullptr;
@@ -446,6 +484,14 @@ cheb_status ws_layout(cheb_plan p, int op, int nb, void* base, Ws* w) {
     case CHEB_OP_SETUP: {
       w->Hs = b.take<c128>(size_t(std::max(np, 1)) * std::max(np, 1));  // staging of C
       w->flags = b.take<int>(4);
+      if (p->rproj.base) {
+        // scales, the flag, and for P^H P the sums of a piece of the projectors and its product's planes
+        const size_t n = size_t(std::min(np, kRnsGramChunk));
+        w->rflag = b.take<int>(1);
+        w->rscale = b.take<double>(std::max(np, p->npw));
+        w->rB = b.take<int8_t>(kRnsMods * n * rns_ld(p->npw));
+        w->rC = b.take<int8_t>(3 * kRnsMods * n * rns_ldc(np));
+      }
       part = part_elems(np, np, p->npw);
       CHK(solver_query(p, CHEB_OP_SETUP, np, &w->solver_bytes));
       w->solver = b.take<char>(std::max<size_t>(w->solver_bytes, 1));
@@ -468,6 +514,32 @@ cheb_status ws_layout(cheb_plan p, int op, int nb, void* base, Ws* w) {
     w->cp = b.take<c128>(pp);
     w->cq = b.take<c128>(pp);
     w->cr = b.take<c128>(pp);
+  }
+  if (p->rproj.base && op != CHEB_OP_SETUP && op != CHEB_OP_BOUND) {
+    const size_t before = b.off;
+    const size_t n = size_t(rns_chunk(std::max(nb, 1)));
+    if (rns_pays(np, nb, p->npw)) {
+      w->rB_bytes = 3 * kRnsMods * n * rns_ld(p->npw);
+      w->rC_bytes = 3 * kRnsMods * n * rns_ldc(np);
+    }
+    if (rns_pays(p->npw, nb, np)) {
+      w->rB_bytes = std::max<size_t>(w->rB_bytes, 3 * kRnsMods * n * rns_ld(np));
+      w->rC_bytes = std::max<size_t>(w->rC_bytes, 3 * kRnsMods * n * rns_ldc(p->npw));
+    }
+    if (w->rB_bytes > 0) {
+      w->rflag = b.take<int>(1);
+      w->rscale = b.take<double>(nb);
+      w->rinv = b.take<double>(nb);
+      w->rB = b.take<int8_t>(w->rB_bytes);
+      w->rC = b.take<int8_t>(w->rC_bytes);
+      // cheb_apply_H_noalloc lends a fixed scratch: what fits it without these buffers is computed without them,
+      // there and in cheb_apply_H alike
+      if (op == CHEB_OP_H && before <= kNoAllocScratchBytes && b.off > kNoAllocScratchBytes) {
+        b.off = before;
+        w->rB = w->rC = nullptr;
+        w->rB_bytes = w->rC_bytes = 0;
+      }
+    }
   }
   w->total = b.off;
   return CHEB_OK;
@@ -684,6 +756,42 @@ template <typename T> struct Ops {
     return CHEB_OK;
   }
 
+  // Whether a product with residue planes of the plan takes the INT8 matrix cores: where it pays and the workspace,
+  // which is laid out for the call's widest block, holds its planes (a narrower block of the same call takes the FP64
+  // product where the wide one did not need the planes)
+  bool use_rns(const Ws& w, int M, int nb, int K) const {
+    if (!std::is_same<T, double>::value || !w.rB || !p->rns_ok || !rns_pays(M, nb, K)) return false;
+    const size_t n = size_t(rns_chunk(nb));
+    return 3 * kRnsMods * n * rns_ld(K) <= w.rB_bytes && 3 * kRnsMods * n * rns_ldc(M) <= w.rC_bytes;
+  }
+
+  // out = op(A) B on the INT8 matrix cores (A: residue planes of the plan, B: K x nb), with the FP64 product behind it
+  // for an operand that the flag says is not fit for the integers (every product looks at its own operand)
+  template <typename Fallback>
+  cheb_status rns(GemmMode mode, int M, int nb, int K, const RnsOperand& A, const c128* B, long ldb, Epi<double> e,
+                  const Ws& w, Fallback&& fp64) {
+    HIPCHK(fill_zero_real<int>(w.rflag, 1, st));
+    HIPCHK(rns_scale_cols<double>(K, nb, B, ldb, w.rscale, w.rinv, w.rflag, st));
+    const long step = rns_chunk(nb), ld = rns_ld(K);
+    for (long n0 = 0; n0 < nb; n0 += step) {
+      const int cnt = int(std::min<long>(step, nb - n0));
+      const long plane = cnt * ld;
+      RnsOperand b;
+      b.base = w.rB; b.third = w.rB + 2 * kRnsMods * plane;
+      b.plane = b.third_plane = plane; b.ld = ld; b.inv = w.rinv + n0;
+      HIPCHK(rns_split_cols<double>(K, cnt, B + n0 * ldb, ldb, w.rscale + n0, w.rB, w.rB + 2 * kRnsMods * plane, nullptr,
+                                    plane, ld, w.rflag, st));
+      Epi<double> en = e;
+      en.out += n0 * e.ldo;
+      if (en.L) en.L += n0 * e.ldl;
+      if (en.U) en.U += n0 * e.ldu;
+      if (en.W) en.W += n0 * e.ldw;
+      HIPCHK(rns_product<double>(mode, M, cnt, K, A, b, w.rC, en, false, w.rflag, st));
+    }
+    HIPCHK(fp64(w.rflag));
+    return CHEB_OK;
+  }
+
   // pout (nproj x nb, c128) = P^H X. exact: FP64 MFMA whatever the plan precision (products of complex64
   // inputs are exact in FP64), for the Rayleigh-Ritz matrices of a mixed plan.
   bool use_split() const { return std::is_same<T, float>::value && p->split_gemm && p->hproj.p; }
@@ -698,6 +806,14 @@ template <typename T> struct Ops {
     e.real_only = p->gamma != 0;  // projections of real functions are real
     const double b = sizeof(C), np = p->nproj, npw = p->npw;
     Timed t(p, st, CHEB_T_PROJECT, (npw * np + npw * nb) * b + np * nb * 16.0, 8.0 * np * nb * npw);
+    if constexpr (std::is_same<T, double>::value) {
+      if (use_rns(w, p->nproj, nb, p->npw))
+        return rns(GEMM_CN, p->nproj, nb, p->npw, p->rproj, X, ldx, e, w, [&](const int* pred) {
+          return gemm<double, double, double, double>(GEMM_CN, p->nproj, nb, p->npw, P(), p->npw, X, ldx, e,
+                                                      gemm_pick_splits(p->nproj, nb, p->npw), w.part, st, ROLE_PROJECT,
+                                                      false, pred);
+        });
+    }
     if (exact) {
       HIPCHK((gemm<double, T, T, double>(GEMM_CN, p->nproj, nb, p->npw, P(), p->npw, X, ldx, e,
                                          gemm_pick_splits(p->nproj, nb, p->npw), w.part, st, ROLE_PROJECT)));
@@ -733,6 +849,13 @@ template <typename T> struct Ops {
     const double vecs = 1.0 + (e.L ? 1 : 0) + (e.U ? 1 : 0) + (e.W ? 1 : 0);
     if (ldw <= 0) ldw = p->nproj;
     Timed t(p, st, CHEB_T_BACKPROJECT, npw * np * b + np * nb * 16.0 + vecs * npw * nb * b, 8.0 * npw * nb * np);
+    if constexpr (std::is_same<T, double>::value) {
+      if (use_rns(w, p->npw, nb, p->nproj))
+        return rns(GEMM_NN, p->npw, nb, p->nproj, p->rback, wv, ldw, e, w, [&](const int* pred) {
+          return gemm<double, double, double, double>(GEMM_NN, p->npw, nb, p->nproj, P(), p->npw, wv, ldw, e, 1, nullptr,
+                                                      st, ROLE_BACKPROJECT, false, pred);
+        });
+    }
     if (use_split()) {
       if constexpr (std::is_same<T, float>::value) {
         // the small projector-space operand split once into FP16 planes (not once per block and K tile)
@@ -1995,6 +2118,13 @@ cheb_status cheb_plan_create(const cheb_desc* d, void* persistent, size_t bytes,
   p->D = l.D; p->Q = l.Q; p->G = l.G; p->Cinv = l.Cinv; p->Cmat = l.Cmat; p->Minv = l.Minv;
   p->hproj.p = l.Hproj; p->hproj.rows = nproj; p->hproj.ld = pad32(d->npw);
   p->hback.p = l.Hback; p->hback.rows = d->npw; p->hback.ld = pad32(nproj);
+  if (l.Rproj) {
+    const long lp = rns_ld(d->npw), lb = rns_ld(nproj);
+    p->rproj.base = l.Rproj; p->rproj.third = l.Rproj + 2 * kRnsMods * nproj * lp;
+    p->rproj.plane = p->rproj.third_plane = nproj * lp; p->rproj.ld = lp; p->rproj.inv = l.Rpinv;
+    p->rback.base = l.Rback; p->rback.third = l.Rback + 2 * kRnsMods * d->npw * lb;
+    p->rback.plane = p->rback.third_plane = d->npw * lb; p->rback.ld = lb; p->rback.inv = l.Rbinv;
+  }
 
   // host-side index maps
   std::vector<int4> col(ncol);
@@ -2199,11 +2329,48 @@ cheb_status cheb_set_projectors(cheb_plan p, const void* P, int ldp, const doubl
     HIPCHK(split_planes(Pd, ldp, p->npw, np, false, sA, const_cast<_Float16*>(p->hproj.p), p->hproj.rows, p->hproj.ld, st));
     HIPCHK(split_planes(Pd, ldp, p->npw, np, true, sA, const_cast<_Float16*>(p->hback.p), p->hback.rows, p->hback.ld, st));
   }
-  // G = P^H P in FP64 from the caller's complex128 projectors
+  p->rns_ok = false;
+  // where the planes are laid out, residues of P: rows = projectors (with the differences, for P^H x) and rows = plane
+  // waves (with the sums)
+  auto mut = [](const auto* q) { return const_cast<std::remove_const_t<std::remove_pointer_t<decltype(q)>>*>(q); };
+  if (p->rproj.base) {
+    int unfit = 0;
+    HIPCHK(fill_zero_real<int>(w.rflag, 1, st));
+    HIPCHK(rns_scale_rows<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rback.inv), w.rflag, st));
+    HIPCHK(rns_split_rows<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rback.base), mut(p->rback.third),
+                                  p->rback.plane, p->rback.ld, w.rflag, st));
+    HIPCHK(rns_scale_cols<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rproj.inv), w.rflag, st));
+    HIPCHK(rns_split_cols<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rproj.base), nullptr, mut(p->rproj.third),
+                                  p->rproj.plane, p->rproj.ld, w.rflag, st));
+    HIPCHK(hipMemcpyAsync(&unfit, w.rflag, sizeof(int), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    p->rns_ok = !unfit;
+  }
+  // G = P^H P in FP64 from the caller's complex128 projectors; on the INT8 matrix cores by pieces of the columns, each
+  // down to its diagonal block (3328 projectors, 137 065 plane waves: cheb_set_projectors 87 ms, planes included, instead
+  // of 169; 1664 and 57 777: 20 instead of 26)
   Epi<double> eg;
   eg.out = p->G; eg.ldo = np; eg.real_only = p->gamma != 0;
-  HIPCHK((gemm<double, double, double, double>(GEMM_CN, np, np, p->npw, Pd, ldp, Pd, ldp, eg,
-                                               gemm_pick_splits(np, np, p->npw), w.part, st)));
+  if (p->rns_ok && rns_pays(np, std::min(np, kRnsGramChunk), p->npw)) {
+    for (int n0 = 0; n0 < np; n0 += kRnsGramChunk) {
+      const int cnt = std::min(kRnsGramChunk, np - n0);
+      RnsOperand b = p->rproj;
+      b.base += long(n0) * b.ld;
+      b.inv += n0;
+      const long plane = cnt * b.ld;
+      HIPCHK(rns_split_cols<double>(p->npw, cnt, Pd + long(n0) * ldp, ldp, w.rscale + n0, nullptr, w.rB, nullptr, plane,
+                                    b.ld, w.rflag, st));
+      b.third = w.rB;
+      b.third_plane = plane;
+      Epi<double> ec = eg;
+      ec.out += long(n0) * np;
+      HIPCHK(rns_product<double>(GEMM_CN, n0 + cnt, cnt, p->npw, p->rproj, b, w.rC, ec, false, w.rflag, st));
+    }
+    HIPCHK(hermitian_lower(np, p->G, np, st));
+  } else {
+    HIPCHK((gemm<double, double, double, double>(GEMM_CN, np, np, p->npw, Pd, ldp, Pd, ldp, eg,
+                                                 gemm_pick_splits(np, np, p->npw), w.part, st)));
+  }
   if (p->has_overlap) {
     HIPCHK(hipMemcpyAsync(p->Q, Q, sizeof(double) * np, hipMemcpyDeviceToDevice, st));
     HIPCHK(capacitance(np, p->G, p->Q, p->Cinv, st));

@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "gemm_common.h"
 #include "kernels.h"
 
 namespace chebfd {
@@ -31,49 +32,7 @@ template <> struct Mfma<float> {
 // and 32 and paddings of 1 to 16 (a padding of 16 puts the transposed tile stores on one bank)
 constexpr int BM = 64, BN = 64, BK = 32, PAD = 1, NT = 256;
 
-// Block placement. The hardware deals the blocks of a launch to the 8 XCDs in turn (block i to XCD i mod 8),
-// each XCD with its own L2. Physical block i takes the logical item that gives each XCD one contiguous run of
-// items. Items are numbered split by split; inside a split, in groups of `grp` M tiles, and inside a group with
-// the M tile fastest. With grp = 8 the blocks an XCD holds at once (32 to 64) cover a square-ish patch of up to 8
-// M tiles by 4 to 8 N tiles, so each slice of A and of B they read is shared by several resident blocks in the
-// XCD's L2: the rule for long contractions (K >= M: projections, Gram matrices), where both operands stream
-// K-long slices. With grp = 1 the N tile runs fastest and each M tile's slice of A is read once, by all N tiles
-// at the same time: the rule for tall, short-K products (back-projection, rotation), whose A dwarfs B.
-constexpr int kTileGroup = 8;
-constexpr int kUpperTiles = -1;  // group value of the upper-triangle tile order (Hermitian products)
-__host__ __device__ inline void gemm_tile_of(int i, int total, int tm, int tn, int grp, int& bx, int& by, int& bz) {
-  const int q = total / 8, rem = total % 8, k = i % 8, j = i / 8;
-  const int L = (k < rem ? k * (q + 1) : rem * (q + 1) + (k - rem) * q) + j;
-  if (grp == kUpperTiles) {  // the tiles bx <= by of a square grid, column by column: t = by (by + 1) / 2 + bx
-    const int per = tm * (tm + 1) / 2;
-    bz = L / per;
-    const int t = L - bz * per;
-    int c = int((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
-    while (c * (c + 1) / 2 > t) --c;
-    while ((c + 1) * (c + 2) / 2 <= t) ++c;
-    by = c;
-    bx = t - c * (c + 1) / 2;
-    return;
-  }
-  const int per = tm * tn;
-  bz = L / per;
-  const int t = L - bz * per;
-  const int first = (t / (grp * tn)) * grp;
-  const int gm = tm - first < grp ? tm - first : grp;  // M tiles in this group (fewer in the last)
-  const int r = t - first * tn;
-  bx = first + r % gm;
-  by = r / gm;
-}
 inline int tile_group(int M, int K) { return K >= M ? kTileGroup : 1; }
-
-template <typename E>
-__device__ __forceinline__ void epi_store(const Epi<E>& e, long m, long n, double re, double im) {
-  double xr = e.alpha * re, xi = e.alpha * im;
-  if (e.L) { cx<E> v = e.L[m + n * e.ldl]; xr += e.bL * double(v.x); xi += e.bL * double(v.y); }
-  if (e.U) { cx<E> v = e.U[m + n * e.ldu]; xr += e.bU * double(v.x); xi += e.bU * double(v.y); }
-  if (e.W) { cx<E> v = e.W[m + n * e.ldw]; xr += e.bW * double(v.x); xi += e.bW * double(v.y); }
-  e.out[m + n * e.ldo] = cx<E>{E(xr), e.real_only ? E(0) : E(xi)};
-}
 
 // Epilogue operands moved into the leading slots (L, then U, then W) and counted: 0, 1 or 3 slots in use, a
 // second operand without a third repeated in the third slot with weight 0 (it is a finite input). The tiled
@@ -157,9 +116,11 @@ __device__ __forceinline__ void epi_blocks(const Epi<E>& epi, int M, int N, long
 template <typename T, typename EA, typename EB, typename EO, int MODE, int ROLE, int NE>
 __global__ __launch_bounds__(NT, 2) void k_gemm(int M, int N, int K, int kchunk, const cx<EA>* __restrict__ A,
                                              long lda, const cx<EB>* __restrict__ B, long ldb, Epi<EO> epi,
-                                             c128* __restrict__ part, int grp) {
+                                             c128* __restrict__ part, int grp,
+                                             const int* __restrict__ pred) {
   constexpr bool G3 = sizeof(T) == 8;
   __shared__ T Ar[BK][BM + PAD], Ai[BK][BM + PAD], Br[BK][BN + PAD], Bi[BK][BN + PAD];
+  if (pred && !*pred) return;
   using acc_t = typename Mfma<T>::acc;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
@@ -324,7 +285,8 @@ __global__ __launch_bounds__(NT, 2) void k_gemm(int M, int N, int K, int kchunk,
 // upper: only the elements of tiles bx <= by (the others' partials were not written)
 template <typename EO>
 __global__ __launch_bounds__(256) void k_reduce(int M, int N, int splits, const c128* __restrict__ part, Epi<EO> epi,
-                                                int upper = 0) {
+                                                int upper = 0, const int* __restrict__ pred = nullptr) {
+  if (pred && !*pred) return;
   const long total = long(M) * N;
   for (long t = blockIdx.x * long(blockDim.x) + threadIdx.x; t < total; t += long(gridDim.x) * blockDim.x) {
     const long n = t / M, m = t - n * M;
@@ -739,12 +701,14 @@ int gemm_pick_splits(int M, int N, int K) {
 
 template <typename T, typename EA, typename EB, typename EO>
 hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, const cx<EB>* B, long ldb,
-                const Epi<EO>& epi, int splits, c128* part, hipStream_t st, GemmRole role, bool upper) {
+                const Epi<EO>& epi, int splits, c128* part, hipStream_t st, GemmRole role, bool upper,
+                const int* pred) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (upper && M != N) return hipErrorInvalidValue;
   if constexpr (std::is_same<T, double>::value && std::is_same<EA, double>::value && std::is_same<EB, double>::value) {
     const long blocks = long((M + 15) / 16) * ((N + 15) / 16);
     if (K <= SKMAX && blocks <= SBLKMAX) {  // splits and part are not used
+      if (pred) return hipErrorInvalidValue;  // too small for a product that has another route
       int kc = (std::max(K, 0) + SW - 1) / SW;
       kc = std::max(SKG, ((kc + SKG - 1) / SKG) * SKG);
       if (mode == GEMM_CN)
@@ -773,13 +737,13 @@ hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, c
     constexpr int MO = decltype(modec)::value, RO = decltype(rolec)::value;
     if (ne == 0 || use_part)
       hipLaunchKernelGGL((k_gemm<T, EA, EB, EO, MO, RO, 0>), grid, dim3(NT), 0, st, M, N, K, kchunk, A, lda, B, ldb, en, pp,
-                         grp);
+                         grp, pred);
     else if (ne == 1)
       hipLaunchKernelGGL((k_gemm<T, EA, EB, EO, MO, RO, 1>), grid, dim3(NT), 0, st, M, N, K, kchunk, A, lda, B, ldb, en, pp,
-                         grp);
+                         grp, pred);
     else
       hipLaunchKernelGGL((k_gemm<T, EA, EB, EO, MO, RO, 3>), grid, dim3(NT), 0, st, M, N, K, kchunk, A, lda, B, ldb, en, pp,
-                         grp);
+                         grp, pred);
   };
   using CN = std::integral_constant<int, GEMM_CN>;
   using NNm = std::integral_constant<int, GEMM_NN>;
@@ -794,7 +758,8 @@ hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, c
   const long total = long(M) * N;
   int blocks = int((total + 255) / 256);
   if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL((k_reduce<EO>), dim3(blocks), dim3(256), 0, st, M, N, splits, part, epi, upper ? 1 : 0);
+  hipLaunchKernelGGL((k_reduce<EO>), dim3(blocks), dim3(256), 0, st, M, N, splits, part, epi, upper ? 1 : 0,
+                     pred);
   return hipGetLastError();
 }
 
@@ -1046,7 +1011,7 @@ template hipError_t column_scales<double>(long, int, const c128*, long, float*, 
 
 #define INST(T, EA, EB, EO)                                                                               \
   template hipError_t gemm<T, EA, EB, EO>(GemmMode, int, int, int, const cx<EA>*, long, const cx<EB>*, long, \
-                                          const Epi<EO>&, int, c128*, hipStream_t, GemmRole, bool);
+                                          const Epi<EO>&, int, c128*, hipStream_t, GemmRole, bool, const int*);
 INST(double, double, double, double)
 INST(float, float, float, float)
 INST(float, float, double, float)

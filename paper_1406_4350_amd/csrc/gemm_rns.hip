@@ -1,0 +1,582 @@
+// Large FP64 complex products on the INT8 matrix cores, by exact integer arithmetic in a residue number system.
+//
+// The FP64 matrix cores do 78.6 TFLOP/s and the INT8 ones about 5 POP/s, 64 times as much. Each operand vector (a row
+// of op(A), a column of B) is scaled by a power of two to a 2-norm in (2^56, 2^57] and rounded to integers; the
+// product of the integer matrices is computed exactly, modulo kRnsMods pairwise coprime numbers p below 2^8, as one
+// int8 x int8 -> int32 product per modulus and real product; the Chinese remainder theorem gives the integers back.
+// By Cauchy-Schwarz every entry (real or imaginary) is below 2^114 <= prod p / 4 in magnitude, so nothing overflows
+// whatever the data, and the only errors are the roundings of the operands (1/2 in integers of norm 2^56 ... 2^57) and
+// one rounding of the result: about 2^-58 |a| |b| per entry, where a chain of K / 4 FP64 MFMAs leaves about
+// 2^-53 0.3 sqrt(chain / K) |a| |b| (chain: the K range that one accumulator sums).
+//
+// A complex product takes three real ones, P1 = a_r b_r, P2 = a_i b_i, P3 = (a_r + s a_i)(b_r + b_i), re = P1 - s P2,
+// im = P3 - P1 - s P2 (s = -1 for conj(a) b, 1 for a b): exact here, since everything is modulo p.
+// Operands arrive as int8 planes (per modulus: residues of the real parts, of the imaginary parts and of the sum),
+// K contiguous; the projectors' planes are laid out once with the plan, the other operand's per call.
+#include <algorithm>
+
+#include "gemm_common.h"
+#include "kernels.h"
+
+namespace chebfd {
+namespace {
+
+constexpr int L = kRnsMods;
+// 256, then the largest numbers below 242 that are pairwise coprime: residues of the odd ones lie within +-120, which
+// leaves the one-step reductions below (error at most 6) inside the int8 range
+constexpr int kP[15] = {256, 241, 239, 235, 233, 229, 227, 223, 221, 217, 211, 209, 199, 197, 193};
+static_assert(L <= 15, "moduli");
+
+typedef unsigned __int128 u128;
+constexpr u128 rns_modulus() {
+  u128 m = 1;
+  for (int l = 0; l < L; ++l) m *= u128(kP[l]);
+  return m;
+}
+constexpr int rns_bits() {  // M < 2^bits
+  int b = 0;
+  for (u128 m = rns_modulus(); m; m >>= 1) ++b;
+  return b;
+}
+constexpr bool rns_coprime() {
+  for (int i = 0; i < L; ++i)
+    for (int j = 0; j < i; ++j) {
+      int a = kP[i], b = kP[j];
+      while (b) { const int t = a % b; a = b; b = t; }
+      if (a != 1) return false;
+    }
+  return true;
+}
+static_assert(rns_coprime(), "moduli must be pairwise coprime");
+// operand norms: 2^kNormExp per operand, twice that two bits below M
+constexpr int kNormExp = (rns_bits() - 1 - 2) / 2;
+static_assert(kNormExp <= 57, "the split takes integers up to 2^57");
+
+constexpr double u128_to_double(u128 v) {  // exact for values of at most 53 significant bits
+  double r = 0.0, f = 1.0;
+  for (; v; v >>= 32, f *= 4294967296.0) r += f * double(unsigned(v & 0xffffffffu));
+  return r;
+}
+// Weights w_l = (M / p_l) ((M / p_l)^-1 mod p_l) of the Chinese remainder theorem in two parts of 40 bits, w1 a
+// multiple of 2^(bits - 40) and w2 of 2^(bits - 80); the rest (below 2^(bits - 80)) is some 2^-8 of the rounding error
+// of the operands. Sums of kRnsMods such parts times residues (at most 384 in magnitude) are exact in FP64.
+struct Crt {
+  double w1[L], w2[L], m1, m2, minv;
+};
+constexpr Crt make_crt() {
+  Crt c{};
+  const u128 M = rns_modulus();
+  constexpr int s1 = rns_bits() - 40, s2 = rns_bits() - 80;
+  for (int l = 0; l < L; ++l) {
+    const u128 q = M / u128(kP[l]);
+    const int r = int(q % u128(kP[l]));
+    int inv = 1;
+    while ((r * inv) % kP[l] != 1) ++inv;
+    const u128 w = q * u128(inv);
+    c.w1[l] = u128_to_double((w >> s1) << s1);
+    c.w2[l] = u128_to_double(((w & ((u128(1) << s1) - 1)) >> s2) << s2);
+  }
+  c.m1 = u128_to_double((M >> s1) << s1);
+  c.m2 = u128_to_double(((M & ((u128(1) << s1) - 1)) >> s2) << s2);
+  c.minv = 1.0 / (c.m1 + c.m2);
+  return c;
+}
+constexpr Crt kCrt = make_crt();
+constexpr int sym_mod(long long v, int p) {
+  int r = int(v % p);
+  if (r < 0) r += p;
+  return r > p / 2 ? r - p : r;
+}
+
+struct ModTab { int p[16]; float inv[16]; int c16[16]; };  // c16 = 2^16 mod p
+constexpr ModTab make_tab() {
+  ModTab t{};
+  for (int l = 0; l < 15; ++l) { t.p[l] = kP[l]; t.inv[l] = 1.0f / float(kP[l]); t.c16[l] = sym_mod(1 << 16, kP[l]); }
+  return t;
+}
+__constant__ ModTab kTab = make_tab();
+
+// x - p round(x / p) for |x| < 2^22 p: the float product added to 1.5 2^23 leaves the rounded quotient in the low
+// mantissa bits. Exact up to the rounding of x to float: |result| <= p / 2 + 2^-24 |x| + |x - float(x)|.
+constexpr float kMagic = 12582912.0f;
+constexpr int kMagicBits = 0x4B400000;
+__device__ __forceinline__ int mod_step(int x, int p, float inv) {
+  const int q = __float_as_int(fmaf(float(x), inv, kMagic)) - kMagicBits;
+  return x - __mul24(q, p);
+}
+// the low byte of the same: the constant of kMagicBits drops out modulo 256
+__device__ __forceinline__ unsigned mod_byte(int x, int p, float inv) {
+  return unsigned(x - __mul24(__float_as_int(fmaf(float(x), inv, kMagic)), p));
+}
+__device__ __forceinline__ unsigned pack4(unsigned a, unsigned b, unsigned c, unsigned d) {  // low bytes
+  const unsigned lo = __builtin_amdgcn_perm(b, a, 0x0c0c0400u), hi = __builtin_amdgcn_perm(d, c, 0x04000c0cu);
+  return lo | hi;
+}
+
+// ---- scales ------------------------------------------------------------------------------------------------
+// A vector of norm f 2^x (f in [1/2, 1)) is scaled by 2^(kNormExp - x). flag[0] = 1 for a vector with a NaN or Inf,
+// or whose largest entry is not 0 and outside [1e-130, 1e130]: its product is left to the FP64 matrix cores.
+__device__ __forceinline__ void set_scale(double ss, double mx, double* scale, double* inv, int* flag) {
+  const bool zero = mx == 0.0 && ss == 0.0;
+  const bool ok = zero || (mx >= 1e-130 && mx <= 1e130 && ss < 1e300);
+  if (!ok) *flag = 1;
+  int x = 0;
+  if (ok && !zero) (void)frexp(sqrt(ss), &x);
+  *scale = ldexp(1.0, kNormExp - x);
+  *inv = ldexp(1.0, x - kNormExp);
+}
+
+constexpr int NST = 1024;
+template <typename E>
+__global__ __launch_bounds__(NST) void k_rns_colnorm(long K, const cx<E>* __restrict__ B, long ldb, double* scale,
+                                                     double* inv, int* flag) {
+  __shared__ double rs[NST / 64], rm[NST / 64];
+  const cx<E>* col = B + long(blockIdx.x) * ldb;
+  double ss = 0.0, mx = 0.0;
+  for (long i = threadIdx.x; i < K; i += NST) {
+    const cx<E> v = col[i];
+    const double x = double(v.x), y = double(v.y);
+    ss += x * x + y * y;
+    mx = fmax(mx, fmax(fabs(x), fabs(y)));
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) { ss += __shfl_xor(ss, o, 64); mx = fmax(mx, __shfl_xor(mx, o, 64)); }
+  if ((threadIdx.x & 63) == 0) { rs[threadIdx.x >> 6] = ss; rm[threadIdx.x >> 6] = mx; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < NST / 64; ++w) { ss += rs[w]; mx = fmax(mx, rm[w]); }
+    set_scale(ss, mx, scale + blockIdx.x, inv + blockIdx.x, flag);
+  }
+}
+
+// rows of an M x K matrix stored with the rows contiguous: one thread per row
+template <typename E>
+__global__ __launch_bounds__(256) void k_rns_rownorm(long M, int K, const cx<E>* __restrict__ A, long lda,
+                                                     double* scale, double* inv, int* flag) {
+  const long m = long(blockIdx.x) * 256 + threadIdx.x;
+  if (m >= M) return;
+  double ss = 0.0, mx = 0.0;
+#pragma unroll 8
+  for (int k = 0; k < K; ++k) {
+    const cx<E> v = A[m + long(k) * lda];
+    const double x = double(v.x), y = double(v.y);
+    ss += x * x + y * y;
+    mx = fmax(mx, fmax(fabs(x), fabs(y)));
+  }
+  set_scale(ss, mx, scale + m, inv + m, flag);
+}
+
+// ---- operands to residues ------------------------------------------------------------------------------------
+// y = d2 2^40 + d1 2^22 + d0 with |d2|, |d1| <= 2^17, |d0| <= 2^21 for |y| <= 2^57, y rounded to an integer
+struct Digits { int d2, d1, d0; };
+__device__ __forceinline__ Digits digits(double y) {
+  const double h = rint(y * 0x1p-40);
+  const double r = fma(-h, 0x1p40, y);
+  const double g = rint(r * 0x1p-22);
+  return {int(h), int(g), int(rint(fma(-g, 0x1p22, r)))};
+}
+// residues modulo kP[l] of NV complex integers, as bytes packed by four: re, im and the sums re + im, re - im (each
+// third plane only where asked for). |d2 c2 + d1 c1 + d0| <= 2^25.1, so one step leaves at most p / 2 + 4.
+template <int NV, bool SUM, bool DIFF>
+__device__ __forceinline__ void residues(int l, const Digits (&re)[NV], const Digits (&im)[NV], unsigned (&pr)[NV / 4],
+                                         unsigned (&pi)[NV / 4], unsigned (&ps)[NV / 4], unsigned (&pd)[NV / 4]) {
+  const int p = kP[l];
+  const float inv = 1.0f / float(p);
+  const int c2 = sym_mod(1ll << 40, p), c1 = sym_mod(1ll << 22, p);
+#pragma unroll
+  for (int g = 0; g < NV / 4; ++g) {
+    int r[4], i[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const Digits& a = re[4 * g + j];
+      const Digits& b = im[4 * g + j];
+      r[j] = mod_step(__mul24(a.d2, c2) + __mul24(a.d1, c1) + a.d0, p, inv);
+      i[j] = mod_step(__mul24(b.d2, c2) + __mul24(b.d1, c1) + b.d0, p, inv);
+    }
+    pr[g] = pack4(unsigned(r[0]), unsigned(r[1]), unsigned(r[2]), unsigned(r[3]));
+    pi[g] = pack4(unsigned(i[0]), unsigned(i[1]), unsigned(i[2]), unsigned(i[3]));
+    if constexpr (SUM)
+      ps[g] = pack4(mod_byte(r[0] + i[0], p, inv), mod_byte(r[1] + i[1], p, inv), mod_byte(r[2] + i[2], p, inv),
+                    mod_byte(r[3] + i[3], p, inv));
+    if constexpr (DIFF)
+      pd[g] = pack4(mod_byte(r[0] - i[0], p, inv), mod_byte(r[1] - i[1], p, inv), mod_byte(r[2] - i[2], p, inv),
+                    mod_byte(r[3] - i[3], p, inv));
+  }
+}
+
+// Vectors contiguous along k (columns of B, columns of A under a conjugate transpose): 4 k per thread, so a wave
+// reads 4 KB and writes 256 bytes of each plane. Bound by memory: 16 bytes read, 3 kRnsMods written per element.
+template <typename E, bool SUM, bool DIFF>
+__global__ __launch_bounds__(256) void k_rns_split(long K, const cx<E>* __restrict__ B, long ldb,
+                                                   const double* __restrict__ scale, int8_t* __restrict__ base,
+                                                   int8_t* __restrict__ sum, int8_t* __restrict__ diff, long plane,
+                                                   long ld, const int* __restrict__ flag) {
+  if (*flag) return;
+  const long k = (long(blockIdx.x) * 256 + threadIdx.x) * 4;
+  const long n = blockIdx.y;
+  if (k >= ld) return;
+  const double s = scale[n];
+  const cx<E>* col = B + n * ldb;
+  Digits re[4], im[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const cx<E> v = col[min(k + j, K - 1)];
+    const bool in = k + j < K;
+    re[j] = digits(in ? double(v.x) * s : 0.0);
+    im[j] = digits(in ? double(v.y) * s : 0.0);
+  }
+  const long at = n * ld + k;
+#pragma unroll
+  for (int l = 0; l < L; ++l) {
+    unsigned pr[1], pi[1], ps[1], pd[1];
+    residues<4, SUM, DIFF>(l, re, im, pr, pi, ps, pd);
+    if (base) {
+      *reinterpret_cast<unsigned*>(base + (2 * l) * plane + at) = pr[0];
+      *reinterpret_cast<unsigned*>(base + (2 * l + 1) * plane + at) = pi[0];
+    }
+    if constexpr (SUM) *reinterpret_cast<unsigned*>(sum + l * plane + at) = ps[0];
+    if constexpr (DIFF) *reinterpret_cast<unsigned*>(diff + l * plane + at) = pd[0];
+  }
+}
+
+// Vectors strided along k (rows of A, stored with the rows contiguous): a block takes 64 rows by 64 k, lane = row,
+// 16 k per thread, so reads are 1 KB per wave and k, and each row of each plane is written 16 bytes at a time.
+template <typename E>
+__global__ __launch_bounds__(256) void k_rns_split_rows(long M, int K, const cx<E>* __restrict__ A, long lda,
+                                                        const double* __restrict__ scale, int8_t* __restrict__ base,
+                                                        int8_t* __restrict__ sum, long plane, long ld,
+                                                        const int* __restrict__ flag) {
+  if (*flag) return;
+  const long m = long(blockIdx.x) * 64 + (threadIdx.x & 63);
+  const int k0 = int(blockIdx.y) * 64 + (threadIdx.x >> 6) * 16;
+  if (m >= M || k0 >= ld) return;
+  const double s = scale[m];
+  Digits re[16], im[16];
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const cx<E> v = A[m + long(min(k0 + j, K - 1)) * lda];
+    const bool in = k0 + j < K;
+    re[j] = digits(in ? double(v.x) * s : 0.0);
+    im[j] = digits(in ? double(v.y) * s : 0.0);
+  }
+  const long at = m * ld + k0;
+#pragma unroll
+  for (int l = 0; l < L; ++l) {
+    unsigned pr[4], pi[4], ps[4], pd[4];
+    residues<16, true, false>(l, re, im, pr, pi, ps, pd);
+    *reinterpret_cast<uint4*>(base + (2 * l) * plane + at) = uint4{pr[0], pr[1], pr[2], pr[3]};
+    *reinterpret_cast<uint4*>(base + (2 * l + 1) * plane + at) = uint4{pi[0], pi[1], pi[2], pi[3]};
+    *reinterpret_cast<uint4*>(sum + l * plane + at) = uint4{ps[0], ps[1], ps[2], ps[3]};
+  }
+}
+
+// ---- the int8 products ---------------------------------------------------------------------------------------
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int RT = 256;         // output tile (both ways), 4 waves of 128 x 128
+constexpr int RK = kRnsKTile;   // k per LDS stage
+constexpr int RCH = RK / 16;    // 16-byte chunks of a stage row
+constexpr int kStageBytes = 2 * RT * RK;
+// |accumulator| <= 120^2 k (modulo 256 it may wrap): K up to kRnsMaxK fits int32, and up to kDirectK the one-byte
+// reduction takes it as it is; beyond, its upper half is folded first: |x| <= 2^15 120 + 2^16, exact as a float
+constexpr int kDirectK = 4608;
+static_assert(long(kRnsMaxK) * 120 * 120 < (1l << 31), "accumulator range");
+static_assert(long(kDirectK) * 120 * 120 <= (1l << 26), "accumulator range of the one-byte reduction");
+
+// chunk c of stage row r sits at chunk c ^ (r / 2 % 8): 16 consecutive rows read at one c touch all 64 LDS banks
+__device__ __forceinline__ int stage_at(int r, int c) { return r * RK + ((c ^ ((r >> 1) & 7)) << 4); }
+
+// C[z][n][m] (residues as int8, m contiguous, ldc) = sum_k A_z[m][k] B_z[n][k] modulo kP[z / 3], z = 3 l + product.
+// One wave per SIMD holds a 128 x 128 tile (256 accumulators) on the 32x32x32 int8 MFMA; the LDS holds two stages of
+// 128 k. While tile t is multiplied, tile t + 1 goes from registers to the other stage and tile t + 2 is requested
+// from memory, one 16-byte access behind each MFMA (sched_group_barrier), and the fragments of the next 32 k are read
+// one step ahead, across the one barrier of the tile: the MFMAs never wait on a whole group of loads. Measured at
+// 3328 x 512 x 32768, 45 products: 2070 TOP/s against 1890 without the two stages as separate arrays (the compiler
+// then orders reads behind writes), 1560 without the interleaving, and 3100 for the MFMAs alone (power-limited).
+__global__ __launch_bounds__(256, 1) void k_rns_gemm(int M, int N, int nt, RnsOperand A, RnsOperand B,
+                                                     int8_t* __restrict__ C, long ldc, long zc, int upper,
+                                                     const int* __restrict__ flag) {
+  __shared__ __align__(16) int8_t S0[kStageBytes], S1[kStageBytes];
+  if (*flag) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tm = (M + RT - 1) / RT, tn = (N + RT - 1) / RT;
+  // one contiguous run of tiles per XCD, the N tile fastest: the blocks an XCD holds at once share their operands in L2
+  int bx, by, z;
+  gemm_tile_of(blockIdx.x, gridDim.x, tm, tn, upper ? kUpperTiles : 1, bx, by, z);
+  const int m0 = bx * RT, n0 = by * RT, l = z / 3, c3 = z - 3 * l;
+  const int8_t* Az = c3 < 2 ? A.base + (2 * l + c3) * A.plane : A.third + l * A.third_plane;
+  const int8_t* Bz = c3 < 2 ? B.base + (2 * l + c3) * B.plane : B.third + l * B.third_plane;
+
+  // loaders: 16-byte chunk tid % 8 of rows tid / 8 + 32 i of each tile, rows past M or N clamped (they feed only outputs
+  // that are not used); 32-bit offsets from the tiles' first rows
+  constexpr int NL = 2 * RT * RCH / 256;
+  static_assert(RCH == 8 && NL == 16, "loader roles");
+  const int8_t* Ab = Az + long(m0) * A.ld;
+  const int8_t* Bb = Bz + long(n0) * B.ld;
+  unsigned src[NL];
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    const int row = (i & 7) * 32 + (tid >> 3);
+    src[i] = unsigned(i < 8 ? min(row, M - 1 - m0) : min(row, N - 1 - n0)) * unsigned(A.ld) + (tid & 7) * 16;
+  }
+  const int dst = stage_at(tid >> 3, tid & 7);  // + 32 i rows: the swizzle repeats every 16 rows
+  i32x4 g[NL];
+  const int wm = (wave & 1) * 128, wn = (wave >> 1) * 128, fr = lane & 31, fh = lane >> 5;
+  constexpr int KS = RK / 32;
+  i32x16 acc[4][4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0;
+  auto load_i = [&](int i, int k0) { g[i] = *reinterpret_cast<const i32x4*>((i < 8 ? Ab : Bb) + k0 + src[i]); };
+  auto put_i = [&](int i, int8_t* S) { *reinterpret_cast<i32x4*>(S + dst + i * 32 * RK) = g[i]; };
+  // the int8 MFMA takes row (lane % 32) of either operand at 16 (lane / 32) ... + 15 of its 32 k
+  auto frag = [&](const int8_t* S, int ks, i32x4(&fa)[4], i32x4(&fb)[4]) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      fa[a] = *reinterpret_cast<const i32x4*>(S + stage_at(wm + 32 * a + fr, 2 * ks + fh));
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      fb[a] = *reinterpret_cast<const i32x4*>(S + stage_at(RT + wn + 32 * a + fr, 2 * ks + fh));
+  };
+  auto mul = [&](const i32x4(&fa)[4], const i32x4(&fb)[4]) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[a], fb[b], acc[a][b], 0, 0, 0);
+  };
+#pragma unroll
+  for (int i = 0; i < NL; ++i) load_i(i, 0);
+#pragma unroll
+  for (int i = 0; i < NL; ++i) put_i(i, S0);
+#pragma unroll
+  for (int i = 0; i < NL; ++i) load_i(i, min(1, nt - 1) * RK);
+  __syncthreads();
+  i32x4 fa[2][4], fb[2][4];
+  frag(S0, 0, fa[0], fb[0]);
+  // tile t from stage Sa; the last tiles request (and store) the last tile again, which nothing reads
+  auto step = [&](int t, int8_t* Sa, int8_t* Sb) {
+    const int kn = min(t + 2, nt - 1) * RK;
+    constexpr int PER = (NL + KS - 2) / (KS - 1);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      if (ks + 1 < KS) {
+        frag(Sa, ks + 1, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
+#pragma unroll
+        for (int i = ks * PER; i < (ks + 1) * PER && i < NL; ++i) { put_i(i, Sb); load_i(i, kn); }
+        mul(fa[ks & 1], fb[ks & 1]);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {  // MFMA, LDS read, MFMA, LDS write, global load
+          __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+        }
+      } else {
+        __syncthreads();
+        frag(Sb, 0, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
+        mul(fa[ks & 1], fb[ks & 1]);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          __builtin_amdgcn_sched_group_barrier(0x8, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+      }
+    }
+  };
+  const int p = kTab.p[l];
+  const float inv = kTab.inv[l];
+  int it = 0;
+  for (; it + 1 < nt; it += 2) { step(it, S0, S1); step(it + 1, S1, S0); }
+  if (it < nt) step(it, S0, S1);
+
+  // bytes through the wave's own 16 KB of LDS (row n: 8 chunks of 16 m) to 128-byte rows.
+  // Accumulator v of a lane: row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane % 32 of its 32 x 32 block.
+  __syncthreads();
+  int8_t* W = S0 + wave * 128 * 128;
+  const int c16 = kTab.c16[l];
+  auto bytes = [&](auto fold) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+#pragma unroll
+        for (int v = 0; v < 16; v += 4) {
+          unsigned x[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            int y = acc[a][b][v + j];
+            if constexpr (decltype(fold)::value) y = __mul24(y >> 16, c16) + (y & 0xffff);
+            x[j] = mod_byte(y, p, inv);
+          }
+          const int m = 32 * a + 2 * v + 4 * fh, n = 32 * b + fr;
+          *reinterpret_cast<unsigned*>(W + stage_at(n, m >> 4) + (m & 15)) = pack4(x[0], x[1], x[2], x[3]);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // one block at a time: all 256 at once would not fit the registers
+      }
+  };
+  if (nt * RK > kDirectK) bytes(std::true_type{});
+  else bytes(std::false_type{});
+  __syncthreads();
+  const int cc = lane & 7, rr = lane >> 3;
+  const long m = m0 + wm + 16 * cc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int n = 8 * i + rr;
+    const i32x4 v = *reinterpret_cast<const i32x4*>(W + stage_at(n, cc));
+    if (n0 + wn + n < N && m < ldc) *reinterpret_cast<i32x4*>(C + z * zc + long(n0 + wn + n) * ldc + m) = v;
+  }
+}
+static_assert(kStageBytes == 4 * 128 * 128, "the output bytes of a block fill one stage");
+
+// ---- residues to results -------------------------------------------------------------------------------------
+// 4 m per thread from the 3 kRnsMods planes (256 bytes of each per wave), then the epilogue with m across the lanes
+// (through LDS). Bound by memory.
+template <typename EO>
+__global__ __launch_bounds__(256) void k_rns_finish(int M, int N, const int8_t* __restrict__ C, long ldc, long zc,
+                                                    const double* __restrict__ ia, const double* __restrict__ ib,
+                                                    int sg, int upper, Epi<EO> epi, const int* __restrict__ flag) {
+  __shared__ c128 buf[1024];
+  if (*flag) return;
+  const long mb = long(blockIdx.x) * 1024, n = blockIdx.y;
+  if (upper && mb / RT > n / RT) return;
+  const int t = threadIdx.x;
+  const long m4 = mb + 4 * t;
+  if (m4 < ldc) {
+    const int8_t* c = C + n * ldc + m4;
+    unsigned w[3 * L];
+#pragma unroll
+    for (int z = 0; z < 3 * L; ++z) w[z] = *reinterpret_cast<const unsigned*>(c + z * zc);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      double r1 = 0.0, r2 = 0.0, i1 = 0.0, i2 = 0.0;
+#pragma unroll
+      for (int l = 0; l < L; ++l) {
+        const int x1 = int(w[3 * l] << (24 - 8 * j)) >> 24, x2 = sg * (int(w[3 * l + 1] << (24 - 8 * j)) >> 24),
+                  x3 = int(w[3 * l + 2] << (24 - 8 * j)) >> 24;
+        const double re = double(x1 - x2), im = double(x3 - x1 - x2);
+        r1 = fma(re, kCrt.w1[l], r1);
+        r2 = fma(re, kCrt.w2[l], r2);
+        i1 = fma(im, kCrt.w1[l], i1);
+        i2 = fma(im, kCrt.w2[l], i2);
+      }
+      const double qr = rint(r1 * kCrt.minv), qi = rint(i1 * kCrt.minv);
+      buf[4 * t + j] = c128{fma(-qr, kCrt.m1, r1) + fma(-qr, kCrt.m2, r2), fma(-qi, kCrt.m1, i1) + fma(-qi, kCrt.m2, i2)};
+    }
+  }
+  __syncthreads();
+  const double sb = ib[n];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const long m = mb + 256 * j + t;
+    if (m < M && !(upper && m / RT > n / RT)) {
+      const double s = ia[m];
+      const c128 v = buf[256 * j + t];
+      epi_store(epi, m, n, v.x * s * sb, v.y * s * sb);
+    }
+  }
+}
+
+}  // namespace
+
+// Microseconds of both routes, from what they measured: the FP64 tiles at 55 TFLOP/s executed on whole 64 x 64 tiles
+// (43 to 62 over the sizes below); the int8 tiles at 0.0140 us per k and 3.5 us for filling and emptying them, or the
+// A planes read once at 4.2 TB/s where few columns share them; the operand scaled and split, the results' residues read.
+//   M x N x K              FP64    INT8     (us, INT8 with the scaling, the split of B and the epilogue)
+//   3328 x 512 x 137065   23038   10829     137065 x 512 x 3328   23321   11099
+//   3328 x 128 x 137065    9851    6039     137065 x 128 x 3328    6167    5531
+//   3328 x  64 x 137065    6054    5632     137065 x  64 x 3328    3565    5241
+//   1664 x 700 x 57777     7044    3795     57777 x 700 x 1664     7190    3994
+//    832 x 512 x 57777     4151    1968     57777 x 512 x 832      2873    2010
+//    512 x 512 x 17077      614     380     17077 x 512 x 512       598     513
+//    512 x 256 x 17077      309     287     17077 x 256 x 512       333     284
+bool rns_pays(int M, int N, int K) {
+  if (M <= 0 || N <= 0 || K <= 0 || K > kRnsMaxK) return false;
+  const double m = M, n = N, k = double(rns_ld(K));
+  const double tiles = double((M + RT - 1) / RT) * double((N + RT - 1) / RT) * 3 * L;
+  const double m64 = (M + 63) / 64 * 64, n64 = (N + 63) / 64 * 64;
+  const double fp64 = 6.0 * m64 * n64 * K / 55e6;
+  const double rounds = std::max(1.0, tiles / 256 + 0.3);
+  const double gemm = std::max(rounds * (0.0140 * k + 3.5), 3.0 * L * m * k / 4.2e6);
+  return gemm + 77.0 * n * (k + m) / 4.6e6 + 20.0 < 0.9 * fp64;
+}
+
+template <typename E>
+hipError_t rns_scale_cols(long K, int N, const cx<E>* B, long ldb, double* scale, double* inv, int* flag,
+                          hipStream_t st) {
+  if (N <= 0) return hipSuccess;
+  hipLaunchKernelGGL((k_rns_colnorm<E>), dim3(N), dim3(NST), 0, st, K, B, ldb, scale, inv, flag);
+  return hipGetLastError();
+}
+
+template <typename E>
+hipError_t rns_scale_rows(long M, int K, const cx<E>* A, long lda, double* scale, double* inv, int* flag,
+                          hipStream_t st) {
+  if (M <= 0) return hipSuccess;
+  hipLaunchKernelGGL((k_rns_rownorm<E>), dim3(unsigned((M + 255) / 256)), dim3(256), 0, st, M, K, A, lda, scale, inv,
+                     flag);
+  return hipGetLastError();
+}
+
+template <typename E>
+hipError_t rns_split_cols(long K, int N, const cx<E>* B, long ldb, const double* scale, int8_t* base, int8_t* sum,
+                          int8_t* diff, long plane, long ld, const int* flag, hipStream_t st) {
+  if (N <= 0) return hipSuccess;
+  if (K <= 0 || N > 65535 || ld != rns_ld(K) || plane < N * ld || !(sum || diff)) return hipErrorInvalidValue;
+  const dim3 grid(unsigned((ld / 4 + 255) / 256), unsigned(N));
+  if (sum && diff)
+    hipLaunchKernelGGL((k_rns_split<E, true, true>), grid, dim3(256), 0, st, K, B, ldb, scale, base, sum, diff, plane,
+                       ld, flag);
+  else if (sum)
+    hipLaunchKernelGGL((k_rns_split<E, true, false>), grid, dim3(256), 0, st, K, B, ldb, scale, base, sum, diff, plane,
+                       ld, flag);
+  else
+    hipLaunchKernelGGL((k_rns_split<E, false, true>), grid, dim3(256), 0, st, K, B, ldb, scale, base, sum, diff, plane,
+                       ld, flag);
+  return hipGetLastError();
+}
+
+template <typename E>
+hipError_t rns_split_rows(long M, int K, const cx<E>* A, long lda, const double* scale, int8_t* base, int8_t* sum,
+                          long plane, long ld, const int* flag, hipStream_t st) {
+  if (M <= 0) return hipSuccess;
+  if (K <= 0 || ld != rns_ld(K) || plane < M * ld || !sum || ld / 64 > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_rns_split_rows<E>), dim3(unsigned((M + 63) / 64), unsigned(ld / 64)), dim3(256), 0, st, M, K, A,
+                     lda, scale, base, sum, plane, ld, flag);
+  return hipGetLastError();
+}
+
+template <typename EO>
+hipError_t rns_product(GemmMode mode, int M, int N, int K, const RnsOperand& A, const RnsOperand& B, int8_t* C,
+                       const Epi<EO>& epi, bool upper, const int* flag, hipStream_t st) {
+  if (M <= 0 || N <= 0) return hipSuccess;
+  if (K <= 0 || K > kRnsMaxK || N > 65535 || A.ld != rns_ld(K) || B.ld != A.ld || (upper && M != N)) return hipErrorInvalidValue;
+  const long ldc = rns_ldc(M), zc = ldc * N;
+  const long tm = (M + RT - 1) / RT, tn = (N + RT - 1) / RT;
+  const long tiles = upper ? tm * (tm + 1) / 2 : tm * tn;
+  hipLaunchKernelGGL(k_rns_gemm, dim3(unsigned(tiles * 3 * L)), dim3(256), 0, st, M, N, int(A.ld / RK), A, B, C, ldc,
+                     zc, upper ? 1 : 0, flag);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_rns_finish<EO>), dim3(unsigned((M + 1023) / 1024), unsigned(N)), dim3(256), 0, st, M, N, C, ldc,
+                     zc, A.inv, B.inv, mode == GEMM_CN ? -1 : 1, upper ? 1 : 0, epi, flag);
+  return hipGetLastError();
+}
+
+#define INST(E)                                                                                                       \
+  template hipError_t rns_scale_cols<E>(long, int, const cx<E>*, long, double*, double*, int*, hipStream_t);          \
+  template hipError_t rns_scale_rows<E>(long, int, const cx<E>*, long, double*, double*, int*, hipStream_t);          \
+  template hipError_t rns_split_cols<E>(long, int, const cx<E>*, long, const double*, int8_t*, int8_t*, int8_t*, long, \
+                                        long, const int*, hipStream_t);                                               \
+  template hipError_t rns_split_rows<E>(long, int, const cx<E>*, long, const double*, int8_t*, int8_t*, long, long,    \
+                                        const int*, hipStream_t);                                                     \
+  template hipError_t rns_product<E>(GemmMode, int, int, int, const RnsOperand&, const RnsOperand&, int8_t*,          \
+                                     const Epi<E>&, bool, const int*, hipStream_t);
+INST(double)
+#undef INST
+
+}  // namespace chebfd

@@ -28,10 +28,12 @@ enum GemmRole { ROLE_SMALL = 0, ROLE_PROJECT = 1, ROLE_BACKPROJECT = 2, ROLE_SUB
 // deterministic reduction applies the epilogue; splits == 1: the epilogue is applied directly.
 // upper = true (M = N, a Hermitian result): only the 64 x 64 output tiles with row tile <= column tile are
 // computed (the others are not written; hermitian_lower fills them), splits from gemm_upper_splits.
+// pred (device): the product is computed only where *pred is not 0 (the other route of a product that took
+// rns_product; hipErrorInvalidValue at the sizes of the small GEMM, which have no other route).
 template <typename T, typename EA, typename EB, typename EO>
 hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, const cx<EB>* B, long ldb,
                 const Epi<EO>& epi, int splits, c128* part, hipStream_t st, GemmRole role = ROLE_SMALL,
-                bool upper = false);
+                bool upper = false, const int* pred = nullptr);
 int gemm_upper_splits(int N, int K);
 // A[i][j] = conj(A[j][i]) for i > j (n x n, column-major)
 hipError_t hermitian_lower(int n, c128* A, long lda, hipStream_t st);
@@ -84,6 +86,44 @@ hipError_t column_maxabs(long rows, int ncols, const c128* X, long ldx, double* 
 // (k runs down X's column); transpose = true: plane row r = row r of X (k runs along X's row).
 hipError_t split_planes(const c128* X, long ldx, int rows_x, int cols_x, bool transpose, double scale,
                         _Float16* planes, long prow, long pld, hipStream_t st);
+
+// ---- large FP64 complex products on the INT8 matrix cores ---------------------------------------------------
+// Operands as residues modulo kRnsMods coprime numbers (see gemm_rns.hip): int8 planes [2 l] (real parts) and
+// [2 l + 1] (imaginary parts) at base + i plane, the sums' (or differences') plane l at third + l third_plane; row r of a
+// plane at r ld, its K values contiguous and padded with zeros to ld = rns_ld(K). inv[r] undoes the row's scale.
+constexpr int kRnsMods = 15, kRnsKTile = 128, kRnsMaxK = 149120;
+inline long rns_ld(long K) { return (K + kRnsKTile - 1) / kRnsKTile * kRnsKTile; }
+inline long rns_ldc(long M) { return (M + 15) / 16 * 16; }
+struct RnsOperand {
+  const int8_t* base = nullptr;
+  const int8_t* third = nullptr;
+  long plane = 0, third_plane = 0, ld = 0;
+  const double* inv = nullptr;
+};
+// whether the INT8 matrix cores are the faster ones for an M x N x K product whose A is already split
+bool rns_pays(int M, int N, int K);
+// Power-of-two scales of the columns (K x N, ldb) or rows (M x K, lda) of a matrix and their inverses; *flag = 1 (else
+// untouched) if a vector is not fit for the integers (NaN, Inf, entries beyond 1e+-130): every rns call below then
+// returns without effect, and the product is left to gemm() with pred = flag.
+template <typename E>
+hipError_t rns_scale_cols(long K, int N, const cx<E>* B, long ldb, double* scale, double* inv, int* flag,
+                          hipStream_t st);
+template <typename E>
+hipError_t rns_scale_rows(long M, int K, const cx<E>* A, long lda, double* scale, double* inv, int* flag,
+                          hipStream_t st);
+// Residue planes of scaled columns (row n of a plane = column n; base null: not written) with the sums re + im, the
+// differences re - im or both (null: not written), and of scaled rows (row m = row m) with the sums.
+template <typename E>
+hipError_t rns_split_cols(long K, int N, const cx<E>* B, long ldb, const double* scale, int8_t* base, int8_t* sum,
+                          int8_t* diff, long plane, long ld, const int* flag, hipStream_t st);
+template <typename E>
+hipError_t rns_split_rows(long M, int K, const cx<E>* A, long lda, const double* scale, int8_t* base, int8_t* sum,
+                          long plane, long ld, const int* flag, hipStream_t st);
+// out (M x N) = conj(A)^T B (GEMM_CN, A's third planes the differences) or A B (GEMM_NN, the sums; B's always the
+// sums) with the epilogue of gemm(); upper as there. C: 3 kRnsMods N rns_ldc(M) bytes of scratch. N <= 65535.
+template <typename EO>
+hipError_t rns_product(GemmMode mode, int M, int N, int K, const RnsOperand& A, const RnsOperand& B, int8_t* C,
+                       const Epi<EO>& epi, bool upper, const int* flag, hipStream_t st);
 
 // ---- FFT passes (per batch of bands) -------------------------------------------------------------------
 struct FftGeom {
