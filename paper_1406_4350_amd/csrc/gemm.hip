@@ -601,6 +601,188 @@ __global__ __launch_bounds__(HTile<TB>::NT) void k_gemm_h(int M, int N, int K, i
   }
 }
 
+// ---- the 128 tiles with both operands as planes -----------------------------------------------------------------
+// Same products as k_gemm_h for TB = 128, pre-split B. One wave per SIMD holds a 64 x 64 complex tile (2 x 2 blocks of the
+// 32x32x16 MFMA, 128 accumulators); the LDS holds two stages of 32 k (1024 plane rows of 64 bytes, 64 KB each). While
+// tile t is multiplied, tile t + 1 goes from registers to the other stage and tile t + 2 is requested from memory, one
+// 16-byte access behind each MFMA or two (sched_group_barrier), and the fragments of the next 16 k are read one step
+// ahead, across the one barrier of the tile. The epilogue passes through LDS so that its operands are read and written
+// with m across the lanes. Bound by power: the matrix cores are 62% busy at 1.5 to 1.6 GHz (8 waves of 64 x 32 tiles
+// without the interleaving: 45 to 50% at 1.9 to 2.0 GHz), 1.06 PFLOP/s executed. 3328 x 1024 x 137065 12.0 -> 10.6 ms,
+// 137065 x 1024 x 3328 with three epilogue operands 12.4 -> 10.6 ms.
+constexpr int PT = 128, PKB = 2 * HBK;       // output tile; bytes of a stage row
+constexpr int kPStage = 2 * 4 * PT * PKB;    // A planes, then B planes
+// chunk c (16 bytes) of stage row r sits at chunk c ^ (r / 4 % 4): 16 consecutive rows read at one c touch all 64 banks
+__device__ __forceinline__ int pstage_at(int r, int c) { return r * PKB + ((c ^ ((r >> 2) & 3)) << 4); }
+typedef float f16v __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ f16v mul3(h8 xh, h8 xl, h8 yh, h8 yl, f16v acc) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(xh, yh, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(xh, yl, acc, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(xl, yh, acc, 0, 0, 0);
+}
+
+template <typename EO, int MODE, int ROLE, int NE>
+__global__ __launch_bounds__(256, 1) void k_gemm_hp(int M, int N, int K, int kchunk, const _Float16* __restrict__ Ap,
+                                                   long arows, long ald, double ainv, const _Float16* __restrict__ Bp,
+                                                   long brows, long bld, const float* __restrict__ bsc, Epi<EO> epi,
+                                                   c128* __restrict__ part, int grp) {
+  __shared__ __align__(16) int8_t S0[kPStage], S1[kPStage];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int bx, by, bz;
+  gemm_tile_of(blockIdx.x, gridDim.x, (M + PT - 1) / PT, (N + PT - 1) / PT, grp, bx, by, bz);
+  const int m0 = bx * PT, n0 = by * PT;
+  const int kbeg = bz * kchunk;
+  const int nt = (min(K, kbeg + kchunk) - kbeg + HBK - 1) / HBK;  // K is padded with zeros to whole tiles
+
+  // loaders: chunk tid % 4 of rows tid / 4 + 64 (i % 2) of plane i / 2 of A, then of B, rows past M or N clamped (they
+  // feed only outputs that are not stored)
+  constexpr int NL = 16;
+  const int8_t* base[8];
+#pragma unroll
+  for (int pl = 0; pl < 4; ++pl) {
+    base[pl] = reinterpret_cast<const int8_t*>(Ap + (pl * arows + m0) * ald + kbeg);
+    base[4 + pl] = reinterpret_cast<const int8_t*>(Bp + (pl * brows + n0) * bld + kbeg);
+  }
+  unsigned off[4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int row = 64 * h + (tid >> 2);
+    off[h] = unsigned(min(row, M - 1 - m0)) * unsigned(2 * ald) + (tid & 3) * 16;
+    off[2 + h] = unsigned(min(row, N - 1 - n0)) * unsigned(2 * bld) + (tid & 3) * 16;
+  }
+  const int dst = pstage_at(tid >> 2, tid & 3);  // + 64 i rows: the swizzle repeats every 16 rows
+  h8 g[NL];
+  auto load_i = [&](int i, int t) {
+    g[i] = *reinterpret_cast<const h8*>(base[i >> 1] + t * PKB + off[(i >> 3) * 2 + (i & 1)]);
+  };
+  auto put_i = [&](int i, int8_t* S) { *reinterpret_cast<h8*>(S + dst + i * 64 * PKB) = g[i]; };
+  const int wm = (wave & 1) * 64, wn = (wave >> 1) * 64, fr = lane & 31, fh = lane >> 5;
+  f16v cr[2][2], ci[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) { cr[i][j][v] = 0.f; ci[i][j][v] = 0.f; }
+  // lane l of the MFMA holds row l % 32 at k = 8 (l / 32) ... + 7 of its 16
+  auto frag = [&](const int8_t* S, int ks, h8(&fa)[2][4], h8(&fb)[2][4]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int pl = 0; pl < 4; ++pl) {
+        fa[i][pl] = *reinterpret_cast<const h8*>(S + pstage_at(pl * PT + wm + 32 * i + fr, 2 * ks + fh));
+        fb[i][pl] = *reinterpret_cast<const h8*>(S + pstage_at((4 + pl) * PT + wn + 32 * i + fr, 2 * ks + fh));
+      }
+  };
+  auto mul = [&](const h8(&fa)[2][4], const h8(&fb)[2][4]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const h8 nih = -fa[i][2], nil = -fa[i][3];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        cr[i][j] = mul3(fa[i][0], fa[i][1], fb[j][0], fb[j][1], cr[i][j]);
+        ci[i][j] = mul3(fa[i][0], fa[i][1], fb[j][2], fb[j][3], ci[i][j]);
+        if (MODE == GEMM_CN) {  // conj(a) b: re += ar br + ai bi, im += ar bi - ai br
+          cr[i][j] = mul3(fa[i][2], fa[i][3], fb[j][2], fb[j][3], cr[i][j]);
+          ci[i][j] = mul3(nih, nil, fb[j][0], fb[j][1], ci[i][j]);
+        } else {  // a b: re += ar br - ai bi, im += ar bi + ai br
+          cr[i][j] = mul3(nih, nil, fb[j][2], fb[j][3], cr[i][j]);
+          ci[i][j] = mul3(fa[i][2], fa[i][3], fb[j][0], fb[j][1], ci[i][j]);
+        }
+      }
+    }
+  };
+  if (nt > 0) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) load_i(i, 0);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) put_i(i, S0);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) load_i(i, min(1, nt - 1));
+    __syncthreads();
+    h8 fa[2][2][4], fb[2][2][4];
+    frag(S0, 0, fa[0], fb[0]);
+    // tile t from stage Sa; the last tiles request (and store) the last tile again, which nothing reads
+    auto step = [&](int t, int8_t* Sa, int8_t* Sb) {
+      const int tn = min(t + 2, nt - 1);
+      frag(Sa, 1, fa[1], fb[1]);
+#pragma unroll
+      for (int i = 0; i < NL; ++i) { put_i(i, Sb); load_i(i, tn); }
+      mul(fa[0], fb[0]);
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+      }
+      __syncthreads();
+      frag(Sb, 0, fa[0], fb[0]);
+      mul(fa[1], fb[1]);
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 3, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+    };
+    int it = 0;
+    for (; it + 1 < nt; it += 2) { step(it, S0, S1); step(it + 1, S1, S0); }
+    if (it < nt) step(it, S0, S1);
+    __syncthreads();
+  }
+
+  // 32 columns at a time through the wave's own 32 KB: element (m, n) at float2 64 n + (m ^ (n % 16) * 2), so that the
+  // 32 columns written at one m spread over the banks. Accumulator v of a lane: row 8 (v / 4) + 4 (lane / 32) + v % 4,
+  // column lane % 32 of its 32 x 32 block.
+  float2* W = reinterpret_cast<float2*>((wave & 2 ? S1 : S0) + (wave & 1) * (kPStage / 2));
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int m = 32 * i + 8 * (v >> 2) + 4 * fh + (v & 3), n = 32 * j + fr;
+        W[64 * n + (m ^ ((n & 15) * 2))] = float2{cr[i][j][v], ci[i][j][v]};
+      }
+  __syncthreads();
+  const long m = m0 + wm + lane;
+  const long mc = min(m, long(M) - 1);
+  const int nn = min(64, N - n0 - wn);
+  constexpr int NS = NE > 0 ? NE : 1, NU = 4;
+  const cx<EO>* src[3] = {epi.L, epi.U, epi.W};
+  const long lds[3] = {epi.ldl, epi.ldu, epi.ldw};
+  const double bet[3] = {epi.bL, epi.bU, epi.bW};
+  for (int q = 0; q < nn; q += NU) {
+    cx<EO> in[NU][NS];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const long n = n0 + wn + min(q + u, nn - 1);
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+        if constexpr (NE > 0) in[u][s] = src[s][mc + n * lds[s]];
+    }
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int c = min(q + u, nn - 1);
+      const long n = n0 + wn + c;
+      const float2 x = W[64 * c + (lane ^ ((c & 15) * 2))];
+      const double f = ainv / double(bsc[n]);
+      if (part) {
+        if (m < M && q + u < nn) part[(long(bz) * N + n) * M + m] = c128{f * double(x.x), f * double(x.y)};
+      } else {
+        const double fa = epi.alpha * f;
+        double xr = fa * double(x.x), xi = fa * double(x.y);
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+          if constexpr (NE > 0) { xr += bet[s] * double(in[u][s].x); xi += bet[s] * double(in[u][s].y); }
+        if (m < M && q + u < nn) epi.out[m + n * epi.ldo] = cx<EO>{EO(xr), epi.real_only ? EO(0) : EO(xi)};
+      }
+    }
+  }
+}
+
 // one 1024-thread block per column (16 waves per CU keep enough loads in flight), max over lanes by shuffles
 constexpr int CST = 1024;
 template <typename E>
@@ -940,17 +1122,20 @@ hipError_t gemm_h_pre(GemmMode mode, int M, int N, int K, const HalfPlanes& A, c
   c128* np = use_part ? part : nullptr;
   auto launch = [&](auto tbc, auto modec, auto rolec) {
     constexpr int T = decltype(tbc)::value, MO = decltype(modec)::value, RO = decltype(rolec)::value;
-    const dim3 grid(((M + T - 1) / T) * ((N + T - 1) / T) * splits), block(HTile<T>::NT);
+    const dim3 grid(((M + T - 1) / T) * ((N + T - 1) / T) * splits);
     const int grp = tile_group(M, K);
-    if (ne == 0 || use_part)
-      hipLaunchKernelGGL((k_gemm_h<T, double, EO, MO, RO, 0, true>), grid, block, 0, st, M, N, K, kchunk, A.p,
-                         A.rows, A.ld, A.inv_scale, nb64, 0L, Bp.p, Bp.rows, Bp.ld, bscale, en, np, grp);
-    else if (ne == 1)
-      hipLaunchKernelGGL((k_gemm_h<T, double, EO, MO, RO, 1, true>), grid, block, 0, st, M, N, K, kchunk, A.p,
-                         A.rows, A.ld, A.inv_scale, nb64, 0L, Bp.p, Bp.rows, Bp.ld, bscale, en, np, grp);
-    else
-      hipLaunchKernelGGL((k_gemm_h<T, double, EO, MO, RO, 3, true>), grid, block, 0, st, M, N, K, kchunk, A.p,
-                         A.rows, A.ld, A.inv_scale, nb64, 0L, Bp.p, Bp.rows, Bp.ld, bscale, en, np, grp);
+    auto go = [&](auto nec) {
+      constexpr int NEC = decltype(nec)::value;
+      if constexpr (T == PT)
+        hipLaunchKernelGGL((k_gemm_hp<EO, MO, RO, NEC>), grid, dim3(256), 0, st, M, N, K, kchunk, A.p, A.rows, A.ld,
+                           A.inv_scale, Bp.p, Bp.rows, Bp.ld, bscale, en, np, grp);
+      else
+        hipLaunchKernelGGL((k_gemm_h<T, double, EO, MO, RO, NEC, true>), grid, dim3(HTile<T>::NT), 0, st, M, N, K,
+                           kchunk, A.p, A.rows, A.ld, A.inv_scale, nb64, 0L, Bp.p, Bp.rows, Bp.ld, bscale, en, np, grp);
+    };
+    if (ne == 0 || use_part) go(std::integral_constant<int, 0>{});
+    else if (ne == 1) go(std::integral_constant<int, 1>{});
+    else go(std::integral_constant<int, 3>{});
   };
   using CN = std::integral_constant<int, GEMM_CN>;
   using NNm = std::integral_constant<int, GEMM_NN>;
