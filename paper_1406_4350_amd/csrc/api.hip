@@ -693,6 +693,10 @@ template <typename T> struct Ops {
     const double n = p->n, nx = 2.0 * p->rx + 1.0;
     return n * ((2.0 * nx + 2.0 * n) * 5.0 * n * std::log2(n) + 2.0 * n * n);
   }
+  // Gamma point: projections and subspace matrices of real functions are real, so their products keep real parts only
+  // and the products with them have a real right side
+  GemmForm re_form() const { return p->gamma ? FORM_RE : FORM_FULL; }
+  GemmForm b_form() const { return p->gamma ? FORM_B_REAL : FORM_FULL; }
   const C* P() const { return static_cast<const C*>(p->P); }
 
   // out = (K + V_loc) X, batched over bands through the disk-column buffers
@@ -816,7 +820,8 @@ template <typename T> struct Ops {
     }
     if (exact) {
       HIPCHK((gemm<double, T, T, double>(GEMM_CN, p->nproj, nb, p->npw, P(), p->npw, X, ldx, e,
-                                         gemm_pick_splits(p->nproj, nb, p->npw), w.part, st, ROLE_PROJECT)));
+                                         gemm_pick_splits(p->nproj, nb, p->npw), w.part, st, ROLE_PROJECT, false,
+                                         nullptr, re_form())));
     } else if (use_split()) {
       if constexpr (std::is_same<T, float>::value) {
         HIPCHK(column_scales<float>(p->npw, nb, X, ldx, w.bsc, st));
@@ -838,7 +843,8 @@ template <typename T> struct Ops {
       }
     } else {
       HIPCHK((gemm<T, T, T, double>(GEMM_CN, p->nproj, nb, p->npw, P(), p->npw, X, ldx, e,
-                                    gemm_pick_splits(p->nproj, nb, p->npw), w.part, st, ROLE_PROJECT)));
+                                    gemm_pick_splits(p->nproj, nb, p->npw), w.part, st, ROLE_PROJECT, false, nullptr,
+                                    re_form())));
     }
     return CHEB_OK;
   }
@@ -871,7 +877,7 @@ template <typename T> struct Ops {
       }
     } else {
       HIPCHK((gemm<T, T, double, T>(GEMM_NN, p->npw, nb, p->nproj, P(), p->npw, wv, ldw, e, 1, nullptr, st,
-                                    ROLE_BACKPROJECT)));
+                                    ROLE_BACKPROJECT, false, nullptr, b_form())));
     }
     return CHEB_OK;
   }
@@ -1111,11 +1117,11 @@ template <typename T> struct Ops {
     // the strictly lower part is their conjugate transpose (the eigensolver reads one triangle; the refinement
     // the whole matrices)
     HIPCHK((gemm<double, T, T, double>(GEMM_CN, nb, nb, p->npw, X, ldx, loc, npw, eh,
-                                       gemm_upper_splits(nb, p->npw), w.part, st, ROLE_SUBSPACE, true)));
+                                       gemm_upper_splits(nb, p->npw), w.part, st, ROLE_SUBSPACE, true, nullptr, re_form())));
     Epi<double> es;
     es.out = w.Ss; es.ldo = nb; es.real_only = p->gamma != 0;
     HIPCHK((gemm<double, T, T, double>(GEMM_CN, nb, nb, p->npw, X, ldx, X, ldx, es,
-                                       gemm_upper_splits(nb, p->npw), w.part, st, ROLE_SUBSPACE, true)));
+                                       gemm_upper_splits(nb, p->npw), w.part, st, ROLE_SUBSPACE, true, nullptr, re_form())));
     if (np > 0) {
       Epi<double> e2;
       e2.out = w.Hs; e2.ldo = nb; e2.L = w.Hs; e2.ldl = nb; e2.bL = 1.0;

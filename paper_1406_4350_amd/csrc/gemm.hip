@@ -28,8 +28,8 @@ template <> struct Mfma<float> {
   }
 };
 
-// K tiles of 32 and rows padded by one element: measured best on the paw48 projector shapes among K tiles of 16
-// and 32 and paddings of 1 to 16 (a padding of 16 puts the transposed tile stores on one bank)
+// split-K chunks are multiples of BK = 32; LDS rows padded by one element (a padding of 16 puts the transposed tile
+// stores on one bank)
 constexpr int BM = 64, BN = 64, BK = 32, PAD = 1, NT = 256;
 
 inline int tile_group(int M, int K) { return K >= M ? kTileGroup : 1; }
@@ -109,17 +109,32 @@ __device__ __forceinline__ void epi_blocks(const Epi<E>& epi, int M, int N, long
 // One 64 x 64 complex output tile per block of 4 waves; wave w owns the 32 x 32 quadrant
 // (w & 1, w >> 1) as 2 x 2 MFMA blocks. FP64 tiles take three real products per complex product
 // (P1 = a_r b_r, P2 = a_i b_i, P3 = (a_r + s a_i)(b_r + b_i) with s = 1 for a b and s = -1 for conj(a) b:
-// re = P1 - s P2, im = P3 - P1 - s P2), the sums formed in registers from the real and imaginary planes
-// (storing them as two more LDS planes measured 9% slower); FP32 tiles keep the four-product form, whose
+// re = P1 - s P2, im = P3 - P1 - s P2), the sums formed in registers from the real and imaginary parts
+// (storing them as two more LDS planes measured 9% slower), or two where FORM says so (FORM_RE: only the real part is
+// wanted, P1 and P2; FORM_B_REAL: b is real, a_r b_r and a_i b_r); FP32 tiles keep the four-product form, whose
 // rounding does not grow with the magnitude of the other component.
+//
+// The LDS holds two stages of GK = 16 k (separate arrays, so that the compiler need not order the reads of one behind
+// the writes of the other; two blocks per CU). While tile t is multiplied, tile t + 1 goes from registers to the other
+// stage and tile t + 2 is requested from memory, each access behind an MFMA (sched_group_barrier), and the fragments of
+// the next 4 k are read one step ahead, across the one barrier of the tile: small products, with one or two waves per
+// SIMD, have nobody else to hide these latencies behind. Against one stage of 32 k filled between two barriers:
+// 256 x 256 x 7153 (16 splits) 66 -> 49 us, 7153 x 256 x 256 with three epilogue operands 80 -> 77 us (its operands'
+// traffic, 146 MB, is not overlapped: all its blocks are resident at once); the two-product forms at 64^3, Gamma point:
+// 512 x 301 x 8539 262 -> 176 us, 8539 x 301 x 512 210 -> 145 us.
 // ROLE only separates kernel names per use (projection, back-projection, small, subspace) for profiling.
-template <typename T, typename EA, typename EB, typename EO, int MODE, int ROLE, int NE>
+constexpr int GK = 16;
+static_assert(BK % GK == 0, "splits are whole tiles");
+template <typename T, typename EA, typename EB, typename EO, int MODE, int ROLE, int NE, int FORM>
 __global__ __launch_bounds__(NT, 2) void k_gemm(int M, int N, int K, int kchunk, const cx<EA>* __restrict__ A,
                                              long lda, const cx<EB>* __restrict__ B, long ldb, Epi<EO> epi,
                                              c128* __restrict__ part, int grp,
                                              const int* __restrict__ pred) {
   constexpr bool G3 = sizeof(T) == 8;
-  __shared__ T Ar[BK][BM + PAD], Ai[BK][BM + PAD], Br[BK][BN + PAD], Bi[BK][BN + PAD];
+  static_assert(G3 || FORM == FORM_FULL, "the two-product forms are FP64");
+  constexpr int SZ = GK * (BM + PAD);
+  static_assert(BM == BN, "one stage layout");
+  __shared__ cx<T> A0[SZ], B0[SZ], A1[SZ], B1[SZ];
   if (pred && !*pred) return;
   using acc_t = typename Mfma<T>::acc;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -130,6 +145,7 @@ __global__ __launch_bounds__(NT, 2) void k_gemm(int M, int N, int K, int kchunk,
   const long m0 = long(bx) * BM, n0 = long(by) * BN;
   const int kbeg = bz * kchunk;
   const int kend = min(K, kbeg + kchunk);
+  const int nt = (kend - kbeg + GK - 1) / GK;
 
   acc_t cr[2][2], ci[2][2], c3[2][2];
 #pragma unroll
@@ -139,114 +155,125 @@ __global__ __launch_bounds__(NT, 2) void k_gemm(int M, int N, int K, int kchunk,
 #pragma unroll
       for (int v = 0; v < 4; ++v) { cr[i][j][v] = T(0); ci[i][j][v] = T(0); c3[i][j][v] = T(0); }
 
-  // global -> registers for one K tile (raw storage type, so that the loads stay in flight while the previous
-  // tile is multiplied), registers -> LDS planes converted to the MFMA type
-  constexpr int RA = (BM * BK) / NT, RBn = (BN * BK) / NT;
-  cx<EA> va[RA];
-  cx<EB> vb[RBn];
-  auto load_tile = [&](int k0) {
+  // global -> registers for one K tile (raw storage type), registers -> LDS converted to the MFMA type. Rows past M
+  // and columns past N are read clamped (they feed only outputs that are not stored), k past the end clamped and
+  // zeroed by value: a load under a condition would be waited for before the MFMAs.
+  constexpr int RL = (BM * GK) / NT;
+  cx<EA> va[RL];
+  cx<EB> vb[RL];
+  // A: k fastest for a conjugate transpose (as stored), row fastest else; B: k fastest
+  const int ak = MODE == GEMM_CN ? tid % GK : tid / BM, am = MODE == GEMM_CN ? tid / GK : tid % BM;
+  constexpr int AKS = MODE == GEMM_CN ? 0 : NT / BM, AMS = MODE == GEMM_CN ? NT / GK : 0;
+  const int bk = tid % GK, bn = tid / GK;
+  const cx<EA>* arow[RL];
+  const cx<EB>* bcol[RL];
 #pragma unroll
-    for (int r = 0; r < RA; ++r) {
-      const int idx = tid + r * NT;
-      int kk, mm;
-      if (MODE == GEMM_CN) { kk = idx % BK; mm = idx / BK; }
-      else { mm = idx % BM; kk = idx / BM; }
-      const long gm = m0 + mm;
-      const int gk = k0 + kk;
-      cx<EA> v = {EA(0), EA(0)};
-      if (gm < M && gk < kend) v = (MODE == GEMM_CN) ? A[gk + gm * lda] : A[gm + long(gk) * lda];
-      va[r] = v;
-    }
+  for (int r = 0; r < RL; ++r) {
+    const long gm = min(m0 + am + r * AMS, long(M) - 1);
+    arow[r] = MODE == GEMM_CN ? A + gm * lda : A + gm;
+    bcol[r] = B + min(n0 + bn + r * (NT / GK), long(N) - 1) * ldb;
+  }
+  auto load_r = [&](int r, int k0) {
+    const int ka = min(k0 + ak + r * AKS, kend - 1), kb = min(k0 + bk, kend - 1);
+    va[r] = MODE == GEMM_CN ? arow[r][ka] : arow[r][long(ka) * lda];
+    vb[r] = bcol[r][kb];
+  };
+  auto put_r = [&](int r, int k0, cx<T>* As, cx<T>* Bs) {
+    const bool oa = k0 + ak + r * AKS < kend, ob = k0 + bk < kend;
+    As[(ak + r * AKS) * (BM + PAD) + am + r * AMS] = cx<T>{oa ? T(va[r].x) : T(0), oa ? T(va[r].y) : T(0)};
+    Bs[bk * (BN + PAD) + bn + r * (NT / GK)] = cx<T>{ob ? T(vb[r].x) : T(0), ob ? T(vb[r].y) : T(0)};
+  };
+  auto frag = [&](const cx<T>* As, const cx<T>* Bs, int ks, cx<T>(&a)[2], cx<T>(&b)[2]) {
 #pragma unroll
-    for (int r = 0; r < RBn; ++r) {
-      const int idx = tid + r * NT;
-      const int kk = idx % BK, nn = idx / BK;
-      const long gn = n0 + nn;
-      const int gk = k0 + kk;
-      cx<EB> v = {EB(0), EB(0)};
-      if (gn < N && gk < kend) v = B[gk + gn * ldb];
-      vb[r] = v;
+    for (int i = 0; i < 2; ++i) {
+      a[i] = As[(4 * ks + lk) * (BM + PAD) + wm + 16 * i + li];
+      b[i] = Bs[(4 * ks + lk) * (BN + PAD) + wn + 16 * i + li];
     }
   };
-  auto store_tile = [&]() {
+  auto mul = [&](const cx<T>(&a)[2], const cx<T>(&b)[2]) {
+    if constexpr (G3) {
+      // cr <- P1, ci <- P2, c3 <- P3
+      T as[2], bs[2];
 #pragma unroll
-    for (int r = 0; r < RA; ++r) {
-      const int idx = tid + r * NT;
-      int kk, mm;
-      if (MODE == GEMM_CN) { kk = idx % BK; mm = idx / BK; }
-      else { mm = idx % BM; kk = idx / BM; }
-      Ar[kk][mm] = T(va[r].x);
-      Ai[kk][mm] = T(va[r].y);
-    }
+      for (int i = 0; i < 2; ++i) {
+        as[i] = MODE == GEMM_CN ? a[i].x - a[i].y : a[i].x + a[i].y;
+        bs[i] = b[i].x + b[i].y;
+      }
 #pragma unroll
-    for (int r = 0; r < RBn; ++r) {
-      const int idx = tid + r * NT;
-      const int kk = idx % BK, nn = idx / BK;
-      Br[kk][nn] = T(vb[r].x);
-      Bi[kk][nn] = T(vb[r].y);
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          cr[i][j] = Mfma<T>::run(a[i].x, b[j].x, cr[i][j]);
+          ci[i][j] = Mfma<T>::run(a[i].y, FORM == FORM_B_REAL ? b[j].x : b[j].y, ci[i][j]);
+          if constexpr (FORM == FORM_FULL) c3[i][j] = Mfma<T>::run(as[i], bs[j], c3[i][j]);
+        }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          if (MODE == GEMM_CN) {  // conj(a) b
+            cr[i][j] = Mfma<T>::run(a[i].x, b[j].x, cr[i][j]);
+            cr[i][j] = Mfma<T>::run(a[i].y, b[j].y, cr[i][j]);
+            ci[i][j] = Mfma<T>::run(a[i].x, b[j].y, ci[i][j]);
+            ci[i][j] = Mfma<T>::run(-a[i].y, b[j].x, ci[i][j]);
+          } else {  // a b
+            cr[i][j] = Mfma<T>::run(a[i].x, b[j].x, cr[i][j]);
+            cr[i][j] = Mfma<T>::run(-a[i].y, b[j].y, cr[i][j]);
+            ci[i][j] = Mfma<T>::run(a[i].x, b[j].y, ci[i][j]);
+            ci[i][j] = Mfma<T>::run(a[i].y, b[j].x, ci[i][j]);
+          }
+        }
     }
   };
 
-  if (kbeg < kend) {
-    load_tile(kbeg);
-    store_tile();
-  }
-  __syncthreads();
-  for (int k0 = kbeg; k0 < kend; k0 += BK) {
-    const bool more = k0 + BK < kend;
-    if (more) load_tile(k0 + BK);  // in flight while this tile is multiplied
+  if (nt > 0) {
+    constexpr int KS = GK / 4;
+    static_assert(KS == 4 && RL == 4, "interleaving below");
+    auto at = [&](int t) { return kbeg + min(t, nt - 1) * GK; };
 #pragma unroll
-    for (int ks = 0; ks < BK; ks += 4) {
-      T ar[2], ai[2], br[2], bi[2];
+    for (int r = 0; r < RL; ++r) load_r(r, kbeg);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        ar[i] = Ar[ks + lk][wm + 16 * i + li];
-        ai[i] = Ai[ks + lk][wm + 16 * i + li];
-        br[i] = Br[ks + lk][wn + 16 * i + li];
-        bi[i] = Bi[ks + lk][wn + 16 * i + li];
-      }
-      if constexpr (G3) {
-        // cr <- P1, ci <- P2, c3 <- P3
-        T as[2], bs[2];
+    for (int r = 0; r < RL; ++r) put_r(r, kbeg, A0, B0);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          as[i] = MODE == GEMM_CN ? ar[i] - ai[i] : ar[i] + ai[i];
-          bs[i] = br[i] + bi[i];
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            cr[i][j] = Mfma<T>::run(ar[i], br[j], cr[i][j]);
-            ci[i][j] = Mfma<T>::run(ai[i], bi[j], ci[i][j]);
-            c3[i][j] = Mfma<T>::run(as[i], bs[j], c3[i][j]);
-          }
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            if (MODE == GEMM_CN) {  // conj(a) b
-              cr[i][j] = Mfma<T>::run(ar[i], br[j], cr[i][j]);
-              cr[i][j] = Mfma<T>::run(ai[i], bi[j], cr[i][j]);
-              ci[i][j] = Mfma<T>::run(ar[i], bi[j], ci[i][j]);
-              ci[i][j] = Mfma<T>::run(-ai[i], br[j], ci[i][j]);
-            } else {  // a b
-              cr[i][j] = Mfma<T>::run(ar[i], br[j], cr[i][j]);
-              cr[i][j] = Mfma<T>::run(-ai[i], bi[j], cr[i][j]);
-              ci[i][j] = Mfma<T>::run(ar[i], bi[j], ci[i][j]);
-              ci[i][j] = Mfma<T>::run(ai[i], br[j], ci[i][j]);
-            }
-          }
-        }
-      }
-    }
+    for (int r = 0; r < RL; ++r) load_r(r, at(1));
     __syncthreads();
-    if (more) {
-      store_tile();
-      __syncthreads();
-    }
+    cx<T> fa[2][2], fb[2][2];
+    frag(A0, B0, 0, fa[0], fb[0]);
+    // tile t from stage (As, Bs); the last tiles request (and store) the last tile again, which nothing reads
+    auto step = [&](int t, cx<T>* As, cx<T>* Bs, cx<T>* An, cx<T>* Bn) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        if (ks + 1 < KS) {
+          frag(As, Bs, ks + 1, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
+#pragma unroll
+          for (int r = ks; r < RL; r += KS - 1)
+            if (r < RL) { put_r(r, at(t + 1), An, Bn); load_r(r, at(t + 2)); }
+          mul(fa[ks & 1], fb[ks & 1]);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {  // MFMA, LDS read, MFMA, LDS write, MFMA, global load
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            if constexpr (FORM == FORM_FULL) __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+          }
+        } else {
+          __syncthreads();
+          frag(An, Bn, 0, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
+          mul(fa[ks & 1], fb[ks & 1]);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            __builtin_amdgcn_sched_group_barrier(0x8, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          }
+        }
+      }
+    };
+    int it = 0;
+    for (; it + 1 < nt; it += 2) { step(it, A0, B0, A1, B1); step(it + 1, A1, B1, A0, B0); }
+    if (it < nt) step(it, A0, B0, A1, B1);
   }
 
   if constexpr (G3) {
@@ -258,8 +285,12 @@ __global__ __launch_bounds__(NT, 2) void k_gemm(int M, int N, int K, int kchunk,
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const T p1 = cr[i][j][v], p2 = ci[i][j][v], p3 = c3[i][j][v];
-          cr[i][j][v] = p1 - sg * p2;
-          ci[i][j][v] = p3 - p1 - sg * p2;
+          if constexpr (FORM == FORM_B_REAL) {
+            ci[i][j][v] = sg * p2;  // a_i b_r, negated under conj(a)
+          } else {
+            cr[i][j][v] = p1 - sg * p2;
+            ci[i][j][v] = FORM == FORM_FULL ? p3 - p1 - sg * p2 : T(0);
+          }
         }
   }
   // accumulator v of a lane holds column li of each 16 x 16 block, row 4*lk + v for the f32 MFMA and
@@ -884,7 +915,7 @@ int gemm_pick_splits(int M, int N, int K) {
 template <typename T, typename EA, typename EB, typename EO>
 hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, const cx<EB>* B, long ldb,
                 const Epi<EO>& epi, int splits, c128* part, hipStream_t st, GemmRole role, bool upper,
-                const int* pred) {
+                const int* pred, GemmForm form) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (upper && M != N) return hipErrorInvalidValue;
   if constexpr (std::is_same<T, double>::value && std::is_same<EA, double>::value && std::is_same<EB, double>::value) {
@@ -915,17 +946,26 @@ hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, c
   c128* pp = use_part ? part : nullptr;
   Epi<EO> en = epi;
   const int ne = epi_slots(en);
+  auto go = [&](auto modec, auto rolec, auto nec, auto formc) {
+    constexpr int MO = decltype(modec)::value, RO = decltype(rolec)::value, NEC = decltype(nec)::value,
+                  FO = decltype(formc)::value;
+    hipLaunchKernelGGL((k_gemm<T, EA, EB, EO, MO, RO, NEC, FO>), grid, dim3(NT), 0, st, M, N, K, kchunk, A, lda, B, ldb,
+                       en, pp, grp, pred);
+  };
   auto launch = [&](auto modec, auto rolec) {
     constexpr int MO = decltype(modec)::value, RO = decltype(rolec)::value;
-    if (ne == 0 || use_part)
-      hipLaunchKernelGGL((k_gemm<T, EA, EB, EO, MO, RO, 0>), grid, dim3(NT), 0, st, M, N, K, kchunk, A, lda, B, ldb, en, pp,
-                         grp, pred);
-    else if (ne == 1)
-      hipLaunchKernelGGL((k_gemm<T, EA, EB, EO, MO, RO, 1>), grid, dim3(NT), 0, st, M, N, K, kchunk, A, lda, B, ldb, en, pp,
-                         grp, pred);
-    else
-      hipLaunchKernelGGL((k_gemm<T, EA, EB, EO, MO, RO, 3>), grid, dim3(NT), 0, st, M, N, K, kchunk, A, lda, B, ldb, en, pp,
-                         grp, pred);
+    auto by_ne = [&](auto formc) {
+      if (ne == 0 || use_part) go(modec, rolec, std::integral_constant<int, 0>{}, formc);
+      else if (ne == 1) go(modec, rolec, std::integral_constant<int, 1>{}, formc);
+      else go(modec, rolec, std::integral_constant<int, 3>{}, formc);
+    };
+    if constexpr (sizeof(T) == 8 && RO != 0) {
+      // real parts of conjugate products (projections, Grams), real right sides of plain ones (back-projection,
+      // rotation)
+      if (MO == GEMM_CN && form == FORM_RE) return by_ne(std::integral_constant<int, MO == GEMM_CN ? FORM_RE : FORM_FULL>{});
+      if (MO == GEMM_NN && form == FORM_B_REAL) return by_ne(std::integral_constant<int, MO == GEMM_NN ? FORM_B_REAL : FORM_FULL>{});
+    }
+    by_ne(std::integral_constant<int, FORM_FULL>{});
   };
   using CN = std::integral_constant<int, GEMM_CN>;
   using NNm = std::integral_constant<int, GEMM_NN>;
@@ -1196,7 +1236,7 @@ template hipError_t column_scales<double>(long, int, const c128*, long, float*, 
 
 #define INST(T, EA, EB, EO)                                                                               \
   template hipError_t gemm<T, EA, EB, EO>(GemmMode, int, int, int, const cx<EA>*, long, const cx<EB>*, long, \
-                                          const Epi<EO>&, int, c128*, hipStream_t, GemmRole, bool, const int*);
+                                          const Epi<EO>&, int, c128*, hipStream_t, GemmRole, bool, const int*, GemmForm);
 INST(double, double, double, double)
 INST(float, float, float, float)
 INST(float, float, double, float)

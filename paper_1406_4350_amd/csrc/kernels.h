@@ -17,6 +17,10 @@ template <typename E> struct Epi {
 };
 
 enum GemmMode { GEMM_CN = 0, GEMM_NN = 1 };
+// FORM_RE: the caller keeps only the real part of conj(A)^T B (the imaginary part of the result is 0); FORM_B_REAL: the
+// imaginary part of B in A B is 0 or to be taken as 0. Two real products per complex one instead of three; taken by the
+// tiled FP64 products of the matching mode, ignored (the full product) by the others.
+enum GemmForm { FORM_FULL = 0, FORM_RE = 1, FORM_B_REAL = 2 };
 // separate kernel instances per use, so that profiles tell them apart
 enum GemmRole { ROLE_SMALL = 0, ROLE_PROJECT = 1, ROLE_BACKPROJECT = 2, ROLE_SUBSPACE = 3 };
 
@@ -33,7 +37,7 @@ enum GemmRole { ROLE_SMALL = 0, ROLE_PROJECT = 1, ROLE_BACKPROJECT = 2, ROLE_SUB
 template <typename T, typename EA, typename EB, typename EO>
 hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, const cx<EB>* B, long ldb,
                 const Epi<EO>& epi, int splits, c128* part, hipStream_t st, GemmRole role = ROLE_SMALL,
-                bool upper = false, const int* pred = nullptr);
+                bool upper = false, const int* pred = nullptr, GemmForm form = FORM_FULL);
 int gemm_upper_splits(int N, int K);
 // A[i][j] = conj(A[j][i]) for i > j (n x n, column-major)
 hipError_t hermitian_lower(int n, c128* A, long lda, hipStream_t st);
