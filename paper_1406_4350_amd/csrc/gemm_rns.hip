@@ -293,7 +293,10 @@ __device__ __forceinline__ int stage_at(int r, int c) { return r * RK + ((c ^ ((
 // from memory, one 16-byte access behind each MFMA (sched_group_barrier), and the fragments of the next 32 k are read
 // one step ahead, across the one barrier of the tile: the MFMAs never wait on a whole group of loads. Measured at
 // 3328 x 512 x 32768, 45 products: 2070 TOP/s against 1890 without the two stages as separate arrays (the compiler
-// then orders reads behind writes), 1560 without the interleaving, and 3100 for the MFMAs alone (power-limited).
+// then orders reads behind writes), 1560 without the interleaving, and 3100 for the MFMAs alone: power is
+// the limit (matrix cores 70% busy at 1.5 GHz). Loads straight to LDS measured 5% slower; persistent blocks that request
+// the next output tile's operands during the last k tiles of this one left too few registers for the reduction of the
+// accumulators and took 31 instead of 22 us per tile at 1024 k.
 __global__ __launch_bounds__(256, 1) void k_rns_gemm(int M, int N, int nt, RnsOperand A, RnsOperand B,
                                                      int8_t* __restrict__ C, long ldc, long zc, int upper,
                                                      const int* __restrict__ flag) {
@@ -483,23 +486,23 @@ __global__ __launch_bounds__(256) void k_rns_finish(int M, int N, const int8_t* 
 
 }  // namespace
 
-// Microseconds of both routes, from what they measured: the FP64 tiles at 55 TFLOP/s executed on whole 64 x 64 tiles
-// (43 to 62 over the sizes below); the int8 tiles at 0.0140 us per k and 3.5 us for filling and emptying them, or the
+// Microseconds of both routes, from what they measured: the FP64 tiles at 60 TFLOP/s executed on whole 64 x 64 tiles
+// (47 to 66 over the sizes below); the int8 tiles at 0.0140 us per k and 3.5 us for filling and emptying them, or the
 // A planes read once at 4.2 TB/s where few columns share them; the operand scaled and split, the results' residues read.
 //   M x N x K              FP64    INT8     (us, INT8 with the scaling, the split of B and the epilogue)
-//   3328 x 512 x 137065   23038   10829     137065 x 512 x 3328   23321   11099
-//   3328 x 128 x 137065    9851    6039     137065 x 128 x 3328    6167    5531
-//   3328 x  64 x 137065    6054    5632     137065 x  64 x 3328    3565    5241
-//   1664 x 700 x 57777     7044    3795     57777 x 700 x 1664     7190    3994
-//    832 x 512 x 57777     4151    1968     57777 x 512 x 832      2873    2010
-//    512 x 512 x 17077      614     380     17077 x 512 x 512       598     513
-//    512 x 256 x 17077      309     287     17077 x 256 x 512       333     284
+//   3328 x 512 x 137065   21213   10446     137065 x 512 x 3328   21209   10901
+//   3328 x 128 x 137065    9255    5770     137065 x 128 x 3328    5520    5416
+//   3328 x  64 x 137065    5698    5438     137065 x  64 x 3328    3206    5133
+//   1664 x 700 x 57777     6446    3697     57777 x 700 x 1664     6292    3955
+//    832 x 512 x 57777     3793    1943     57777 x 512 x 832      2746    2066
+//    512 x 512 x 17077      481     368     17077 x 512 x 512       531     514
+//    512 x 256 x 17077      246     277     17077 x 256 x 512       291     280
 bool rns_pays(int M, int N, int K) {
   if (M <= 0 || N <= 0 || K <= 0 || K > kRnsMaxK) return false;
   const double m = M, n = N, k = double(rns_ld(K));
   const double tiles = double((M + RT - 1) / RT) * double((N + RT - 1) / RT) * 3 * L;
   const double m64 = (M + 63) / 64 * 64, n64 = (N + 63) / 64 * 64;
-  const double fp64 = 6.0 * m64 * n64 * K / 55e6;
+  const double fp64 = 6.0 * m64 * n64 * K / 60e6;
   const double rounds = std::max(1.0, tiles / 256 + 0.3);
   const double gemm = std::max(rounds * (0.0140 * k + 3.5), 3.0 * L * m * k / 4.2e6);
   return gemm + 77.0 * n * (k + m) / 4.6e6 + 20.0 < 0.9 * fp64;
