@@ -802,9 +802,12 @@ template <typename T> struct Ops {
 
   // pout (nproj x nb, c128) = P^H X. exact: FP64 MFMA whatever the plan precision (products of complex64
   // inputs are exact in FP64), for the Rayleigh-Ritz matrices of a mixed plan. Otherwise a mixed plan uses
-  // the FP16 hi/lo split MFMA on X scaled per band by a power of two (FP32-level accuracy).
-  cheb_status project(const C* X, long ldx, int nb, c128* pout, const Ws& w, bool exact = false, long ldo = 0) {
+  // the FP16 hi/lo split MFMA on X scaled per band by a power of two (FP32-level accuracy). from (ld ldo, may be pout):
+  // pout = from - P^H X instead.
+  cheb_status project(const C* X, long ldx, int nb, c128* pout, const Ws& w, bool exact = false, long ldo = 0,
+                      const c128* from = nullptr) {
     Epi<double> e;
+    if (from) { e.alpha = -1.0; e.L = from; e.ldl = ldo > 0 ? ldo : p->nproj; e.bL = 1.0; }
     e.out = pout;
     e.ldo = ldo > 0 ? ldo : p->nproj;
     e.real_only = p->gamma != 0;  // projections of real functions are real
@@ -824,12 +827,11 @@ template <typename T> struct Ops {
                                          nullptr, re_form())));
     } else if (use_split()) {
       if constexpr (std::is_same<T, float>::value) {
-        HIPCHK(column_scales<float>(p->npw, nb, X, ldx, w.bsc, st));
         const int splits = gemm_h_pick_splits(p->nproj, nb, p->npw);
         if (w.hx) {
           // the filters' workspaces hold the bands split once into FP16 planes (the same values the GEMM would
           // split on the fly), which the GEMM then reads as plain 16-byte rows
-          HIPCHK(split_columns(p->npw, nb, X, ldx, w.bsc, w.hx, w.hx_ld, st));
+          HIPCHK(scale_split_columns<float>(p->npw, nb, X, ldx, w.bsc, w.hx, w.hx_ld, st));
           HalfPlanes xp;
           xp.p = w.hx;
           xp.rows = nb;
@@ -837,6 +839,7 @@ template <typename T> struct Ops {
           HIPCHK((gemm_h_pre<double>(GEMM_CN, p->nproj, nb, p->npw, p->hproj, xp, w.bsc, e, splits, w.part, st,
                                      ROLE_PROJECT)));
         } else {
+          HIPCHK(column_scales<float>(p->npw, nb, X, ldx, w.bsc, st));
           HIPCHK((gemm_h<float, double>(GEMM_CN, p->nproj, nb, p->npw, p->hproj, X, ldx, w.bsc, e, splits, w.part,
                                         st, ROLE_PROJECT)));
         }
@@ -866,8 +869,7 @@ template <typename T> struct Ops {
       if constexpr (std::is_same<T, float>::value) {
         // the small projector-space operand split once into FP16 planes (not once per block and K tile)
         if (!w.hb) return fail(p, CHEB_ERR_STATE, "workspace laid out without the split back-projection operand");
-        HIPCHK(column_scales<double>(p->nproj, nb, wv, ldw, w.bsc, st));
-        HIPCHK(split_columns(p->nproj, nb, wv, ldw, w.bsc, w.hb, w.hb_ld, st));
+        HIPCHK(scale_split_columns<double>(p->nproj, nb, wv, ldw, w.bsc, w.hb, w.hb_ld, st));
         HalfPlanes bp;
         bp.p = w.hb;
         bp.rows = nb;
@@ -957,10 +959,11 @@ template <typename T> struct Ops {
   // One step of the recurrence (Alg. 2 inner loop): out = s1 (S^-1 H cur - c cur) - s2 prev, with the
   // projections p = P^H psi carried alongside (reuse trick, Sec. 5.1). out may alias prev (and pout pprev);
   // prev / pprev are unused for i = 1.
-  // loc_in: (K + V) cur given by the caller (ld npw), else computed here
+  // loc_in: (K + V) cur given by the caller (ld npw), else computed here. opened (plans with an overlap): the previous
+  // step left D p and Q^-1 D p of pcur in w.ploc; open_next: leave those of pout there for the next step.
   cheb_status filter_step(int i, const C* cur, long ldc, const C* prev, long ldp, C* out, long ldo,
                           const c128* pcur, const c128* pprev, c128* pout, int nb, double c, double r, const Ws& w,
-                          const C* loc_in = nullptr) {
+                          const C* loc_in = nullptr, bool opened = false, bool open_next = false) {
     const int np = p->nproj;
     const long npw = p->npw;
     const double s1 = (i == 1 ? 1.0 : 2.0) / r;
@@ -984,15 +987,18 @@ template <typename T> struct Ops {
     const long l2 = 2L * np;
     c128* pl = w.ploc;
     c128* dp = w.ploc + np;
-    CHK(project(loc, npw, nb, pl, w, false, l2));
-    HIPCHK(block_diag_apply(np, nb, p->pinfo, p->D, pcur, np, dp, l2, st));
     const c128* wv = dp;
     long ldw = l2;
     if (p->has_overlap) {
-      HIPCHK(overlap_rhs(np, nb, p->Q, dp, l2, pl, l2, pl, l2, st));  // u over p_loc, which is not needed after
+      // u = Q^-1 D p - p_loc comes out of the projection's epilogue, over Q^-1 D p
+      if (!opened) HIPCHK(overlap_open(np, nb, p->pinfo, p->D, p->Q, pcur, np, dp, pl, l2, st));
+      CHK(project(loc, npw, nb, pl, w, false, l2, pl));
       CHK(cinv(pl, l2, nb, w.w, np, w));
       wv = w.w;
       ldw = np;
+    } else {
+      CHK(project(loc, npw, nb, pl, w, false, l2));
+      HIPCHK(block_diag_apply(np, nb, p->pinfo, p->D, pcur, np, dp, l2, st));
     }
     // psi^i = s1 (loc + P w - c psi^(i-1)) - s2 psi^(i-2)
     Epi<T> e;
@@ -1003,8 +1009,8 @@ template <typename T> struct Ops {
     CHK(backproject(wv, nb, e, w, ldw));
     if (p->has_overlap) {
       // p^i = s1 (Q^-1 (D p - w) - c p^(i-1)) - s2 p^(i-2)
-      HIPCHK(overlap_recur(np, nb, p->Q, dp, l2, w.w, np, s1, c, pcur, np, s2, i > 1 ? pprev : nullptr, np, pout, np,
-                           st));
+      HIPCHK(overlap_close(np, nb, p->pinfo, p->D, p->Q, dp, pl, l2, w.w, np, s1, c, pcur, np, s2,
+                           i > 1 ? pprev : nullptr, np, pout, np, open_next, st));
       return CHEB_OK;
     }
     // p^i = s1 (p_loc + G w - c p^(i-1)) - s2 p^(i-2)
@@ -1022,6 +1028,7 @@ template <typename T> struct Ops {
   // rounded vectors, and the recurrence amplifies the drift like the bands it multiplies. With the drift monitor
   // on, the carried projections of cur are compared with P^H cur recomputed from the vector (FP64 products); at
   // the steps i = 1 + k * resync both carried projections are replaced by the projections of their vectors.
+  bool resync_at(int i) const { return i >= 2 && p->resync > 0 && (i - 1) % p->resync == 0; }
   cheb_status resync_step(int i, const C* cur, long ldc, c128* pcur, const C* prev, long ldp, c128* pprev, int nb,
                           const Ws& w) {
     const int np = p->nproj;
@@ -1035,7 +1042,7 @@ template <typename T> struct Ops {
       for (double v : h) p->drift_max = std::isnan(v) ? v : std::max(p->drift_max, v);
       p->drift_checks += 1;
     }
-    if (p->resync > 0 && (i - 1) % p->resync == 0) {
+    if (resync_at(i)) {
       CHK(project(cur, ldc, nb, pcur, w));
       if (i > 2) CHK(project(prev, ldp, nb, pprev, w));  // psi^0's projections are exact already
     }
@@ -1062,7 +1069,7 @@ template <typename T> struct Ops {
       const int ci = (i - 1) & 1, oi = i & 1;
       CHK(resync_step(i, buf[ci], ld[ci], pb[ci], buf[oi], ld[oi], pb[oi], nb, w));
       CHK(filter_step(i, buf[ci], ld[ci], buf[oi], ld[oi], buf[oi], ld[oi], pb[ci], pb[oi], pb[oi], nb, c, r, w,
-                      i == 1 ? hxin : nullptr));
+                      i == 1 ? hxin : nullptr, i > 1 && !resync_at(i), i < m && !resync_at(i + 1)));
     }
     if (m & 1) HIPCHK((convert_copy<T, T>(npw, nb, buf[1], npw, X, ldx, st)));
     return CHEB_OK;
@@ -1085,7 +1092,8 @@ template <typename T> struct Ops {
     for (int i = 1; i <= int(active.size()); ++i) {
       const int ci = (i - 1) & 1, oi = i & 1;
       CHK(resync_step(i, buf[ci], npw, pb[ci], buf[oi], npw, pb[oi], active[i - 1], w));
-      CHK(filter_step(i, buf[ci], npw, buf[oi], npw, buf[oi], npw, pb[ci], pb[oi], pb[oi], active[i - 1], c, r, w));
+      CHK(filter_step(i, buf[ci], npw, buf[oi], npw, buf[oi], npw, pb[ci], pb[oi], pb[oi], active[i - 1], c, r, w,
+                      nullptr, i > 1 && !resync_at(i), i < int(active.size()) && !resync_at(i + 1)));
     }
     const int* ev = idx + na;
     const int* od = ev + 2 * ne;

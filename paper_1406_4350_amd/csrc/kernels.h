@@ -65,12 +65,11 @@ struct HalfPlanes {
 template <typename EB, typename EO>
 hipError_t gemm_h(GemmMode mode, int M, int N, int K, const HalfPlanes& A, const cx<EB>* B, long ldb,
                   const float* bscale, const Epi<EO>& epi, int splits, c128* part, hipStream_t st, GemmRole role);
-// B split once, exactly as gemm_h splits it on the fly: planes [4][N][pld] of bscale[n] B[k][n] (Re hi, Re lo,
-// Im hi, Im lo; zero for K <= k < pld), pld >= K a multiple of 32
-hipError_t split_columns(int K, int N, const c128* B, long ldb, const float* bscale, _Float16* planes, long pld,
-                         hipStream_t st);
-hipError_t split_columns(int K, int N, const c64* B, long ldb, const float* bscale, _Float16* planes, long pld,
-                         hipStream_t st);
+// B scaled and split once, exactly as column_scales and the on-the-fly split of gemm_h: bscale[n], and planes [4][N][pld]
+// of bscale[n] B[k][n] (Re hi, Re lo, Im hi, Im lo; zero for K <= k < pld), pld >= K a multiple of 32
+template <typename E>
+hipError_t scale_split_columns(int K, int N, const cx<E>* B, long ldb, float* bscale, _Float16* planes, long pld,
+                               hipStream_t st);
 // gemm_h with B given as such planes (Bp.rows = N, Bp.ld = pld, Bp.inv_scale unused); splits > 1 sums split-K
 // partials in part as gemm_h does (same results as gemm_h with the same splits)
 template <typename EO>
@@ -186,13 +185,14 @@ hipError_t block_diag_apply_c(int nproj, int nb, const int4* pinfo, const c128* 
                               long ldo, bool accumulate, hipStream_t st);
 hipError_t diag_apply(int nproj, int nb, const double* d, const c128* in, long ldi, c128* out, long ldo,
                       hipStream_t st);
-// Projector-space steps of the filter with an overlap (S = I + P Q P^H, Q diagonal, C = Q^-1 + P^H P):
-// u = Q^-1 Dp - ploc (u may alias ploc), and out = s1 (Q^-1 (Dp - w) - c cur) - s2 prev (prev may be null)
-hipError_t overlap_rhs(int nproj, int nb, const double* Q, const c128* Dp, long ldd, const c128* ploc, long ldl,
-                       c128* u, long ldu, hipStream_t st);
-hipError_t overlap_recur(int nproj, int nb, const double* Q, const c128* Dp, long ldd, const c128* w, long ldw,
-                         double s1, double c, const c128* cur, long ldc, double s2, const c128* prev, long ldp,
-                         c128* out, long ldo, hipStream_t st);
+// Projector space of a filter step with an overlap (S = I + P Q P^H, Q diagonal, C = Q^-1 + P^H P): open: dp = D cur and
+// qdp = Q^-1 D cur (both ld ldd); close: out = s1 (Q^-1 (dp - w) - c cur) - s2 prev (prev may be null or out), and with
+// next the open of out for the following step.
+hipError_t overlap_open(int nproj, int nb, const int4* pinfo, const double* D, const double* Q, const c128* cur,
+                        long ldc, c128* dp, c128* qdp, long ldd, hipStream_t st);
+hipError_t overlap_close(int nproj, int nb, const int4* pinfo, const double* D, const double* Q, c128* dp, c128* qdp,
+                         long ldd, const c128* w, long ldw, double s1, double c, const c128* cur, long ldc, double s2,
+                         const c128* prev, long ldp, c128* out, long ldo, bool next, hipStream_t st);
 // out = a x + b y (+ c z), complex, any storage type
 template <typename E>
 hipError_t axpbypcz(long rows, int nb, double a, const cx<E>* x, long ldx, double b, const cx<E>* y, long ldy,

@@ -103,35 +103,65 @@ __global__ void k_block_diag_c(int nproj, int nb, const int4* __restrict__ pinfo
   }
 }
 
-// u = Q^-1 Dp - ploc (u may be ploc)
-__global__ void k_overlap_rhs(int nproj, int nb, const double* __restrict__ Q, const c128* __restrict__ Dp, long ldd,
-                              const c128* ploc, long ldl, c128* u, long ldu) {
-  const long total = long(nproj) * nb;
-  for (long t = blockIdx.x * long(blockDim.x) + threadIdx.x; t < total; t += long(gridDim.x) * blockDim.x) {
-    const int b = int(t / nproj), i = int(t - long(b) * nproj);
-    const c128 d = Dp[long(b) * ldd + i], l = ploc[long(b) * ldl + i];
-    const double q = Q[i];
-    u[long(b) * ldu + i] = c128{d.x / q - l.x, d.y / q - l.y};
+// Projector space of a filter step with an overlap (u = Q^-1 D p - P^H loc, w = C^-1 u, and the recurrence of the carried
+// projections p). The recurrence closes one step and D p and Q^-1 D p open the next one, of the same p: one kernel, one
+// block per band with the band's new p in LDS for the block-diagonal D (an atom's block needs p of all its projectors).
+// Bound by its launch at the small sizes (D p, u and the recurrence as kernels of their own took 4.8 us each at 256 x 256
+// and 256 bands, this one 5.0); u itself comes out of the projection's epilogue.
+constexpr int kStepProj = 4096;  // projectors whose p fits 64 KB of LDS
+template <bool RECUR, bool DIAG>
+__global__ __launch_bounds__(256) void k_overlap_step(int nproj, const int4* __restrict__ pinfo,
+                                                      const double* __restrict__ D, const double* __restrict__ Q,
+                                                      c128* dp, c128* qdp, long ldd, const c128* __restrict__ w,
+                                                      long ldw, double s1, double c, const c128* __restrict__ cur,
+                                                      long ldc, double s2, const c128* prev, long ldp, c128* out,
+                                                      long ldo) {
+  extern __shared__ c128 pcol[];
+  const long b = blockIdx.x;
+  for (int i = threadIdx.x; i < nproj; i += 256) {
+    const c128 x = cur[b * ldc + i];
+    if constexpr (RECUR) {  // out = s1 (Q^-1 (D p - w) - c cur) - s2 prev (prev may be null, and may be out)
+      const c128 d = dp[b * ldd + i], v = w[b * ldw + i];
+      const double q = Q[i];
+      double re = s1 * ((d.x - v.x) / q - c * x.x), im = s1 * ((d.y - v.y) / q - c * x.y);
+      if (prev) {
+        const c128 y = prev[b * ldp + i];
+        re -= s2 * y.x;
+        im -= s2 * y.y;
+      }
+      out[b * ldo + i] = c128{re, im};
+      if constexpr (DIAG) pcol[i] = c128{re, im};
+    } else {
+      pcol[i] = x;
+    }
+  }
+  if constexpr (DIAG) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < nproj; i += 256) {
+      const int4 pi = pinfo[i];  // {atom's first row, block size, block offset, 0}
+      const double* Drow = D + pi.z + long(i - pi.x) * pi.y;
+      double re = 0.0, im = 0.0;
+      for (int j = 0; j < pi.y; ++j) {
+        const c128 x = pcol[pi.x + j];
+        re += Drow[j] * x.x;
+        im += Drow[j] * x.y;
+      }
+      const double q = Q[i];
+      dp[b * ldd + i] = c128{re, im};
+      qdp[b * ldd + i] = c128{re / q, im / q};
+    }
   }
 }
 
-// out = s1 (Q^-1 (Dp - w) - c cur) - s2 prev (prev may be null)
-__global__ void k_overlap_recur(int nproj, int nb, const double* __restrict__ Q, const c128* __restrict__ Dp, long ldd,
-                                const c128* __restrict__ w, long ldw, double s1, double c, const c128* __restrict__ cur,
-                                long ldc, double s2, const c128* __restrict__ prev, long ldp, c128* __restrict__ out,
-                                long ldo) {
+// qdp = Q^-1 dp (more projectors than kStepProj)
+__global__ void k_overlap_scale(int nproj, int nb, const double* __restrict__ Q, const c128* __restrict__ dp,
+                                c128* __restrict__ qdp, long ldd) {
   const long total = long(nproj) * nb;
   for (long t = blockIdx.x * long(blockDim.x) + threadIdx.x; t < total; t += long(gridDim.x) * blockDim.x) {
     const int b = int(t / nproj), i = int(t - long(b) * nproj);
-    const c128 d = Dp[long(b) * ldd + i], v = w[long(b) * ldw + i], x = cur[long(b) * ldc + i];
+    const c128 d = dp[long(b) * ldd + i];
     const double q = Q[i];
-    double re = s1 * ((d.x - v.x) / q - c * x.x), im = s1 * ((d.y - v.y) / q - c * x.y);
-    if (prev) {
-      const c128 y = prev[long(b) * ldp + i];
-      re -= s2 * y.x;
-      im -= s2 * y.y;
-    }
-    out[long(b) * ldo + i] = c128{re, im};
+    qdp[long(b) * ldd + i] = c128{d.x / q, d.y / q};
   }
 }
 
@@ -367,20 +397,32 @@ hipError_t block_diag_apply_c(int nproj, int nb, const int4* pinfo, const c128* 
                      out, ldo, accumulate ? 1 : 0);
   return hipGetLastError();
 }
-hipError_t overlap_rhs(int nproj, int nb, const double* Q, const c128* Dp, long ldd, const c128* ploc, long ldl,
-                       c128* u, long ldu, hipStream_t st) {
+hipError_t overlap_open(int nproj, int nb, const int4* pinfo, const double* D, const double* Q, const c128* cur,
+                        long ldc, c128* dp, c128* qdp, long ldd, hipStream_t st) {
   if (nproj <= 0 || nb <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_overlap_rhs, dim3(nblocks(long(nproj) * nb)), dim3(256), 0, st, nproj, nb, Q, Dp, ldd, ploc, ldl,
-                     u, ldu);
+  if (nproj <= kStepProj) {
+    hipLaunchKernelGGL((k_overlap_step<false, true>), dim3(nb), dim3(256), size_t(nproj) * sizeof(c128), st, nproj, pinfo,
+                       D, Q, dp, qdp, ldd, nullptr, 0L, 0.0, 0.0, cur, ldc, 0.0, nullptr, 0L, nullptr, 0L);
+    return hipGetLastError();
+  }
+  const hipError_t e = block_diag_apply(nproj, nb, pinfo, D, cur, ldc, dp, ldd, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_overlap_scale, dim3(nblocks(long(nproj) * nb)), dim3(256), 0, st, nproj, nb, Q, dp, qdp, ldd);
   return hipGetLastError();
 }
-hipError_t overlap_recur(int nproj, int nb, const double* Q, const c128* Dp, long ldd, const c128* w, long ldw,
-                         double s1, double c, const c128* cur, long ldc, double s2, const c128* prev, long ldp,
-                         c128* out, long ldo, hipStream_t st) {
+hipError_t overlap_close(int nproj, int nb, const int4* pinfo, const double* D, const double* Q, c128* dp, c128* qdp,
+                         long ldd, const c128* w, long ldw, double s1, double c, const c128* cur, long ldc, double s2,
+                         const c128* prev, long ldp, c128* out, long ldo, bool next, hipStream_t st) {
   if (nproj <= 0 || nb <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_overlap_recur, dim3(nblocks(long(nproj) * nb)), dim3(256), 0, st, nproj, nb, Q, Dp, ldd, w, ldw,
+  if (next && nproj <= kStepProj) {
+    hipLaunchKernelGGL((k_overlap_step<true, true>), dim3(nb), dim3(256), size_t(nproj) * sizeof(c128), st, nproj, pinfo,
+                       D, Q, dp, qdp, ldd, w, ldw, s1, c, cur, ldc, s2, prev, ldp, out, ldo);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((k_overlap_step<true, false>), dim3(nb), dim3(256), 0, st, nproj, pinfo, D, Q, dp, qdp, ldd, w, ldw,
                      s1, c, cur, ldc, s2, prev, ldp, out, ldo);
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess || !next ? e : overlap_open(nproj, nb, pinfo, D, Q, out, ldo, dp, qdp, ldd, st);
 }
 hipError_t diag_apply(int nproj, int nb, const double* d, const c128* in, long ldi, c128* out, long ldo,
                       hipStream_t st) {
