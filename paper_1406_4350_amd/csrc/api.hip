@@ -50,6 +50,7 @@ struct cheb_plan_s {
   bool cap_blocks_ok = false;  // atom blocks inverted (all of size <= 32)
   bool have_V = false, have_P = false, have_D = false;
   int fft_batch = 1;
+  bool band_fits = false;  // small boxes: the transforms of a band in one launch (fft_band)
   HalfPlanes hproj, hback;                  // mixed plans: split planes of P (set with the projectors)
   bool split_gemm = true;                   // mixed plans: FP16 hi/lo split MFMA for P^H x and P w
   RnsOperand rproj, rback;                  // FP64 plans: residue planes of P for P^H x and for P w (large plans)
@@ -699,12 +700,20 @@ template <typename T> struct Ops {
   GemmForm b_form() const { return p->gamma ? FORM_B_REAL : FORM_FULL; }
   const C* P() const { return static_cast<const C*>(p->P); }
 
+  // The small boxes take the transforms of a band in one launch; the three passes while the kernel-class timers are on,
+  // which tell them apart.
+  bool one_pass() const { return p->band_fits && !p->prof_on; }
+
   // out = (K + V_loc) X, batched over bands through the disk-column buffers
   cheb_status hloc(const C* X, long ldx, int nb, C* out, long ldo, const FftWs& fw) {
     if (p->gamma) return hloc_gamma(X, ldx, nb, out, ldo, fw);
     const int fb = fft_batch_for(p, nb);
     const FftGeom g = geom();
     const C* tw = static_cast<const C*>(p->tw);
+    if (one_pass()) {
+      HIPCHK(fft_band<T>(g, tw, static_cast<const T*>(p->Vt), X, ldx, static_cast<const T*>(p->kin), out, ldo, nb, st));
+      return CHEB_OK;
+    }
     for (int b0 = 0; b0 < nb; b0 += fb) {
       const int cnt = std::min(fb, nb - b0);
       C* ca = static_cast<C*>(fw.a);
@@ -741,6 +750,15 @@ template <typename T> struct Ops {
       C* ca = static_cast<C*>(fw.a);
       C* cb = static_cast<C*>(fw.b);
       const double b = sizeof(C), colv = double(p->n) * p->ncol, npw = p->npw;
+      if (one_pass()) {
+        HIPCHK((gamma_pack<T>(p->npf, cnt, p->gmap, p->h0, X + long(b0) * ldx, ldx, ga, npf, st)));
+        FftGeom gf = g;
+        gf.npw = p->npf;  // the whole sphere's entries
+        HIPCHK(fft_band<T>(gf, tw, static_cast<const T*>(p->Vt), ga, npf, nullptr, gb, npf, npair, st));
+        HIPCHK((gamma_split<T>(p->npw, cnt, p->gpair, p->h0, gb, npf, static_cast<const T*>(p->kin),
+                               X + long(b0) * ldx, ldx, out + long(b0) * ldo, ldo, st)));
+        continue;
+      }
       {
         Timed t(p, st, CHEB_T_FFT_COL_INV, (cnt * npw + npair * (2.0 * npf + colv)) * b, 0.0);
         HIPCHK((gamma_pack<T>(p->npf, cnt, p->gmap, p->h0, X + long(b0) * ldx, ldx, ga, npf, st)));
@@ -2207,6 +2225,8 @@ cheb_status cheb_plan_create(const cheb_desc* d, void* persistent, size_t bytes,
     if ((e = hipStreamSynchronize(st))) return fail_hip(e, "sync");
   }
   if ((e = fft_prepare_attributes())) return fail_hip(e, "kernel attributes");
+  const FftGeom geom{p->n, p->ncol, p->npw, p->rx, p->col, p->ent, p->xline};
+  p->band_fits = mixed ? fft_band_fits<float>(geom) : fft_band_fits<double>(geom);
   if (rocblas_create_handle(&p->rb) != rocblas_status_success) {
     std::fprintf(stderr, "cheb_plan_create: rocblas_create_handle failed\n");
     return CHEB_ERR_HIP;

@@ -885,6 +885,185 @@ __global__ __launch_bounds__(NT) void k_col_fwd(int ncol, const int4* __restrict
   }
 }
 
+// ---- whole band in one block (N <= 16) ---------------------------------------------------------------------------
+// At the smallest boxes the three passes are three launches of 3 to 5 us each, and their disk columns fit LDS: one block
+// takes a band from the sphere to the sphere. The columns stay in LDS as z-lines; between their two transforms each wave
+// takes a z-plane by itself (no block barrier among the planes), with the plane in its own LDS as N x-lines of y-lines,
+// transformed in place: every sub-stage reads and writes the same slots with one lane, in the factorisation and the order
+// of operations of the three passes. V(r) of the plane is requested before its first stage. Bound by the latency of its
+// exchanges: 11.0 us at 16^3 for 16 bands, as the three kernels together (3.4 + 4.5 + 3.2 us), without two of their
+// launches (H X of 16 bands 26.8 -> 20.1 us); at 24^3, where a wave has three planes, 28.2 us against 16.9, so that box
+// keeps the three passes.
+template <int N, typename T> struct BandCfg {
+  static constexpr int N1 = LineSplit<N>::N1, N2 = LineSplit<N>::N2, PS = N2 + 1, LS = line_stride<N>();
+  static constexpr int NW = N;  // waves: one per plane
+  static constexpr int VT = (N * N1 + 63) / 64;  // V(r) tasks per lane
+};
+template <int N, typename T> constexpr size_t band_lds(int ncol, int nx) {
+  using C = BandCfg<N, T>;
+  return (size_t(ncol) * C::LS + size_t(C::NW) * N * C::LS + N) * sizeof(cx<T>) + 16 + size_t(nx) * 16;
+}
+
+template <int N, typename T>
+__global__ __launch_bounds__((64 * BandCfg<N, T>::NW)) void k_band(int ncol, int rx, int npw,
+                                                                  const int* __restrict__ ent,
+                                                                  const int4* __restrict__ xline,
+                                                                  const cx<T>* __restrict__ twg,
+                                                                  const T* __restrict__ Vt, const cx<T>* __restrict__ X,
+                                                                  long ldx, const T* __restrict__ kin,
+                                                                  cx<T>* __restrict__ out, long ldo, T scale) {
+  using C = BandCfg<N, T>;
+  constexpr int N1 = C::N1, N2 = C::N2, PS = C::PS, LS = C::LS, NW = C::NW, NTH = 64 * NW;
+  extern __shared__ unsigned char smem_raw[];
+  const int nx = 2 * rx + 1, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  cx<T>* lines = reinterpret_cast<cx<T>*>(smem_raw);  // [ncol][LS]
+  cx<T>* L = lines + size_t(ncol) * LS + size_t(wave) * N * LS;  // this wave's plane: x-line gx at gx mod N
+  cx<T>* tw = lines + size_t(ncol) * LS + size_t(NW) * N * LS;   // tw[k1 N2 + n2] = W_N^(n2 k1), forward sign
+  int4* XL = reinterpret_cast<int4*>(smem_raw + (((size_t(ncol) * LS + size_t(NW) * N * LS + N) * sizeof(cx<T>) + 15) & ~size_t(15)));
+  const cx<T> zero = {T(0), T(0)};
+  const long band = blockIdx.x;
+  const cx<T>* xb = X + band * ldx;
+  cx<T>* ob = out + band * ldo;
+
+  for (int t = tid; t < N; t += NTH) tw[t] = twg[((t % N2) * (t / N2)) % N];
+  for (int t = tid; t < nx; t += NTH) XL[t] = xline[t];
+  for (int t = tid; t < ncol * LS; t += NTH) lines[t] = zero;
+  __syncthreads();
+  for (int e = tid; e < npw; e += NTH) {
+    const int code = ent[e];
+    lines[(code >> 8) * LS + (code & 255)] = xb[e];
+  }
+  __syncthreads();
+  lds_fft<N, +1, T>(lines, ncol, LS, tw);
+
+  for (int z = wave; z < N; z += NW) {
+    T vr[C::VT][N2];
+#pragma unroll
+    for (int q = 0; q < C::VT; ++q) {
+      const int t = min(lane + 64 * q, N * N1 - 1), y = t / N1, a = t - y * N1;
+      const T* Vrow = Vt + (long(z) * N + y) * N + a;
+#pragma unroll
+      for (int b = 0; b < N2; ++b) vr[q][b] = Vrow[N1 * b];
+    }
+    // inverse y: x-lines to groups a of y = a + N1 b at slot PS a + b
+    for (int t = lane; t < nx * N2; t += 64) {
+      const int xi = t / N2, n2 = t - xi * N2;
+      const int4 xl = XL[xi];  // {first column, lowest gy, column count, 0}
+      cx<T> v[N1];
+#pragma unroll
+      for (int n1 = 0; n1 < N1; ++n1) {
+        const int j = freq<N>(N2 * n1 + n2) - xl.y;
+        const bool ok = j >= 0 && j < xl.z;
+        const cx<T> x = lines[(xl.x + (ok ? j : 0)) * LS + z];
+        v[n1] = cx<T>{ok ? x.x : T(0), ok ? x.y : T(0)};
+      }
+      Dft<N1, +1>::run(v);
+      cx<T>* p = L + ((xi - rx + N) % N) * LS + n2;
+#pragma unroll
+      for (int k1 = 0; k1 < N1; ++k1) p[PS * k1] = k1 ? cmul(v[k1], conj_if(tw[k1 * N2 + n2], true)) : v[0];
+    }
+    wave_sync();
+    for (int t = lane; t < nx * N1; t += 64) {
+      const int xi = t / N1, a = t - xi * N1;
+      cx<T>* p = L + ((xi - rx + N) % N) * LS + PS * a;
+      cx<T> v[N2];
+#pragma unroll
+      for (int b = 0; b < N2; ++b) v[b] = p[b];
+      Dft<N2, +1>::run(v);
+#pragma unroll
+      for (int b = 0; b < N2; ++b) p[b] = v[b];
+    }
+    wave_sync();
+    // per row y: inverse x, V(r), forward x, in place over the x-lines
+    for (int t = lane; t < N * N2; t += 64) {
+      const int y = t / N2, n2 = t - y * N2;
+      cx<T>* p = L + n2 * LS + PS * (y % N1) + y / N1;
+      cx<T> v[N1];
+#pragma unroll
+      for (int n1 = 0; n1 < N1; ++n1) {
+        const int gx = freq<N>(N2 * n1 + n2);
+        const bool ok = gx >= -rx && gx <= rx;
+        const cx<T> x = p[N2 * n1 * LS];
+        v[n1] = cx<T>{ok ? x.x : T(0), ok ? x.y : T(0)};
+      }
+      Dft<N1, +1>::run(v);
+#pragma unroll
+      for (int k1 = 0; k1 < N1; ++k1) p[N2 * k1 * LS] = k1 ? cmul(v[k1], conj_if(tw[k1 * N2 + n2], true)) : v[0];
+    }
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < C::VT; ++q) {
+      const int t = lane + 64 * q;
+      if (t < N * N1) {
+        const int y = t / N1, a = t - y * N1;
+        cx<T>* p = L + N2 * a * LS + PS * (y % N1) + y / N1;
+        cx<T> v[N2];
+#pragma unroll
+        for (int b = 0; b < N2; ++b) v[b] = p[b * LS];
+        Dft<N2, +1>::run(v);  // v[b] = psi(x = a + N1 b)
+#pragma unroll
+        for (int b = 0; b < N2; ++b) v[b] = cx<T>{v[b].x * vr[q][b], v[b].y * vr[q][b]};
+        Dft<N2, -1>::run(v);
+#pragma unroll
+        for (int kb = 0; kb < N2; ++kb) p[kb * LS] = kb ? cmul(v[kb], tw[a * N2 + kb]) : v[0];
+      }
+    }
+    wave_sync();
+    for (int t = lane; t < N * N2; t += 64) {
+      const int y = t / N2, n2 = t - y * N2;
+      cx<T>* p = L + n2 * LS + PS * (y % N1) + y / N1;
+      cx<T> v[N1];
+#pragma unroll
+      for (int a = 0; a < N1; ++a) v[a] = p[N2 * a * LS];
+      Dft<N1, -1>::run(v);
+#pragma unroll
+      for (int ka = 0; ka < N1; ++ka) p[N2 * ka * LS] = v[ka];
+    }
+    wave_sync();
+    // forward y, back to the columns
+    for (int t = lane; t < nx * N1; t += 64) {
+      const int xi = t / N1, a = t - xi * N1;
+      cx<T>* p = L + ((xi - rx + N) % N) * LS + PS * a;
+      cx<T> v[N2];
+#pragma unroll
+      for (int b = 0; b < N2; ++b) v[b] = p[b];
+      Dft<N2, -1>::run(v);
+#pragma unroll
+      for (int kb = 0; kb < N2; ++kb) p[kb] = kb ? cmul(v[kb], tw[a * N2 + kb]) : v[0];
+    }
+    wave_sync();
+    for (int t = lane; t < nx * N2; t += 64) {
+      const int xi = t / N2, n2 = t - xi * N2;
+      const int4 xl = XL[xi];
+      const cx<T>* p = L + ((xi - rx + N) % N) * LS + n2;
+      cx<T> v[N1];
+#pragma unroll
+      for (int a = 0; a < N1; ++a) v[a] = p[PS * a];
+      Dft<N1, -1>::run(v);
+#pragma unroll
+      for (int ka = 0; ka < N1; ++ka) {
+        const int j = freq<N>(n2 + N2 * ka) - xl.y;
+        if (j >= 0 && j < xl.z) lines[(xl.x + j) * LS + z] = v[ka];
+      }
+    }
+    wave_sync();  // the next plane overwrites this one
+  }
+  __syncthreads();
+
+  lds_fft<N, -1, T>(lines, ncol, LS, tw);
+  for (int e = tid; e < npw; e += NTH) {
+    const int code = ent[e];
+    const cx<T> v = lines[(code >> 8) * LS + (code & 255)];
+    if (kin) {
+      const cx<T> x = xb[e];
+      const T k = kin[e];
+      ob[e] = cx<T>{v.x * scale + k * x.x, v.y * scale + k * x.y};
+    } else {
+      ob[e] = cx<T>{v.x * scale, v.y * scale};
+    }
+  }
+}
+
 // ---- Gamma point: two real bands per complex transform --------------------------------------------------------
 // Stored Gamma vectors hold sqrt(2) c_G on the half sphere (c_0 at G = 0). gmap[e] = h | (conj << 30) gives, for
 // entry e of the whole sphere, the half-sphere entry h with G_e = G_h (conj = 0) or G_e = -G_h (conj = 1).
@@ -1058,6 +1237,37 @@ hipError_t fft_col_forward(const FftGeom& g, const cx<T>* tw, const cx<T>* colbu
   });
 }
 
+// one block per band from 8^3 to 16^3, where its LDS holds the columns and planes (spheres up to about a quarter of the
+// box; wider ones take the three passes)
+template <int N> constexpr bool band_box() { return N <= 16; }
+template <typename T> bool fft_band_fits(const FftGeom& g) {
+  bool fits = false;
+  (void)dispatch_n(g.n, [&](auto nc) {
+    constexpr int N = decltype(nc)::value;
+    if constexpr (band_box<N>()) fits = band_lds<N, T>(g.ncol, 2 * g.rx + 1) <= 160 * 1024;
+    return hipSuccess;
+  });
+  return fits;
+}
+template <typename T>
+hipError_t fft_band(const FftGeom& g, const cx<T>* tw, const T* Vt, const cx<T>* X, long ldx, const T* kin, cx<T>* out,
+                    long ldo, int nb, hipStream_t st) {
+  if (nb <= 0) return hipSuccess;
+  const T scale = T(1.0 / (double(g.n) * g.n * g.n));
+  return dispatch_n(g.n, [&](auto nc) {
+    constexpr int N = decltype(nc)::value;
+    if constexpr (band_box<N>()) {
+      const size_t lds = band_lds<N, T>(g.ncol, 2 * g.rx + 1);
+      if (lds > 160 * 1024) return hipErrorInvalidConfiguration;
+      hipLaunchKernelGGL((k_band<N, T>), dim3(unsigned(nb)), dim3(64 * BandCfg<N, T>::NW), lds, st, g.ncol, g.rx, g.npw,
+                         g.ent, g.xline, tw, Vt, X, ldx, kin, out, ldo, scale);
+      return hipGetLastError();
+    } else {
+      return hipErrorInvalidConfiguration;
+    }
+  });
+}
+
 size_t fft_plane_lds_bytes(int n, int rx, bool dbl) {
   size_t out = 0;
   (void)dispatch_n(n, [&](auto nc) {
@@ -1133,6 +1343,10 @@ hipError_t fft_prepare_attributes() {
     if constexpr (N == 128) set(reinterpret_cast<const void*>(&k_plane_half));
     else set(reinterpret_cast<const void*>(&k_plane<N, double>));
     set(reinterpret_cast<const void*>(&k_plane<N, float>));
+    if constexpr (band_box<N>()) {
+      set(reinterpret_cast<const void*>(&k_band<N, double>));
+      set(reinterpret_cast<const void*>(&k_band<N, float>));
+    }
     if constexpr (N <= 64) {
       set(reinterpret_cast<const void*>(&k_xdens<N, double>));
       set(reinterpret_cast<const void*>(&k_xdens<N, float>));
@@ -1146,6 +1360,12 @@ hipError_t fft_prepare_attributes() {
   return err;
 }
 
+template bool fft_band_fits<double>(const FftGeom&);
+template bool fft_band_fits<float>(const FftGeom&);
+template hipError_t fft_band<double>(const FftGeom&, const c128*, const double*, const c128*, long, const double*, c128*,
+                                     long, int, hipStream_t);
+template hipError_t fft_band<float>(const FftGeom&, const c64*, const float*, const c64*, long, const float*, c64*, long,
+                                    int, hipStream_t);
 template hipError_t cross_density<double>(const FftGeom&, const c128*, const c128*, const c128*, int, const double*,
                                           const double*, double, double*, double*, hipStream_t);
 template hipError_t cross_density<float>(const FftGeom&, const c64*, const c64*, const c64*, int, const double*,

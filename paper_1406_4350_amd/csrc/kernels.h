@@ -144,6 +144,11 @@ hipError_t fft_plane(const FftGeom& g, const cx<T>* tw, const T* Vt, const cx<T>
 template <typename T>
 hipError_t fft_col_forward(const FftGeom& g, const cx<T>* tw, const cx<T>* colbuf, const cx<T>* X, long ldx,
                            const T* kin, cx<T>* out, long ldo, int nb, hipStream_t st);
+// the three passes in one launch, one block per band, where fft_band_fits (small boxes); kin null: no kinetic term
+template <typename T> bool fft_band_fits(const FftGeom& g);
+template <typename T>
+hipError_t fft_band(const FftGeom& g, const cx<T>* tw, const T* Vt, const cx<T>* X, long ldx, const T* kin, cx<T>* out,
+                    long ldo, int nb, hipStream_t st);
 hipError_t fft_prepare_attributes();
 // dV[x][y][z] += coef n^-3 sum_b w_b Re(conj(a_b(r)) psi_b(r)) for nband bands of z-transformed disk columns ca, cb
 // (w = null: all weights 1); part: cross_density_part_doubles(n, nband) doubles of scratch. For n > 64 and ca != cb,
