@@ -323,10 +323,16 @@ __global__ __launch_bounds__(256) void k_reduce(int M, int N, int splits, const 
     const long n = t / M, m = t - n * M;
     if (upper && m / BM > n / BN) continue;
     double re = 0.0, im = 0.0;
-    for (int s = 0; s < splits; ++s) {
-      c128 v = part[long(s) * total + t];
-      re += v.x;
-      im += v.y;
+    // eight partials in flight at a time, added in order
+    for (int s0 = 0; s0 < splits; s0 += 8) {
+      c128 v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = part[long(min(s0 + j, splits - 1)) * total + t];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        re = s0 + j < splits ? re + v[j].x : re;
+        im = s0 + j < splits ? im + v[j].y : im;
+      }
     }
     epi_store(epi, m, n, re, im);
   }
@@ -336,18 +342,23 @@ __global__ __launch_bounds__(256) void k_reduce(int M, int N, int splits, const 
 // Products with at most a few hundred 16 x 16 output blocks and K of at most a thousand (the projector-space
 // matrices of Sec. 5.1 and the subspace matrices of the Rayleigh-Ritz step) fill only a few dozen 64 x 64 tiles:
 // the tiled kernel above then runs one wave per SIMD and needs split-K with a second reduction launch. Here one
-// block of 4 waves computes one 16 x 16 output block. Wave w takes the w-th quarter of K and reads its operand
+// block of SW waves computes one 16 x 16 output block. Wave w takes the w-th part of K and reads its operand
 // fragments straight from global memory (a few MB that stay in L2), the next load group in flight during the
-// MFMAs of the current one; the four partial blocks meet in LDS and are summed in a fixed order, so that the result does not depend on timing.
+// MFMAs of the current one; the partial blocks meet in LDS and are summed in a fixed order, so that the result does not depend on timing.
 //
 // Within a load group of 16 k, lane (li, lk) holds k = k0 + 4 s + lk for MFMA step s (the instruction's own k
 // order): the 4 lanes of one B column (and of one A column for conj(A)^T) read 64 contiguous bytes per load.
-constexpr int SKG = 16, SKMAX = 1024, SBLKMAX = 1024, SLD = 17, SW = 4;  // 8 waves per block measured slower
+//
+// Few blocks with a longer K (the projections and Grams of the small spheres) leave the chip idle while each block pulls
+// its whole K through one CU: K is then split over blocks too, and the partial blocks summed by k_reduce (65 x 41 x 925,
+// 15 blocks: 15.1 us in one launch, also with 16 waves per block; 8.4 us with 14 splits, the reduction included).
+constexpr int SKG = 16, SKMAX = 1024, SBLKMAX = 1024, SLD = 17, SW = 4;  // 8 waves per block measured slower at 256^3
 static_assert(SW >= 4, "the epilogue takes one thread per element of the 16 x 16 block");
 
 template <typename EO, int MODE>
 __global__ __launch_bounds__(64 * SW) void k_gemm_s(int M, int N, int K, int kchunk, const c128* __restrict__ A,
-                                                long lda, const c128* __restrict__ B, long ldb, Epi<EO> epi) {
+                                                long lda, const c128* __restrict__ B, long ldb, Epi<EO> epi,
+                                                c128* __restrict__ part) {
   __shared__ c128 red[SW][16 * SLD];
   using acc_t = Mfma<double>::acc;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -361,7 +372,7 @@ __global__ __launch_bounds__(64 * SW) void k_gemm_s(int M, int N, int K, int kch
   const c128* __restrict__ Ab = MODE == GEMM_CN ? A + amc * lda : A + amc;
   const long ask = MODE == GEMM_CN ? 1 : lda;  // A stride along k
   const c128* __restrict__ Bb = B + bnc * ldb;
-  const int kb = wave * kchunk, ke = min(K, kb + kchunk);
+  const int kb = (bz * SW + wave) * kchunk, ke = min(K, kb + kchunk);
   const int kfull = kb + (max(ke - kb, 0) / SKG) * SKG;  // end of the whole load groups
 
   acc_t p1, p2, p3;
@@ -442,7 +453,10 @@ __global__ __launch_bounds__(64 * SW) void k_gemm_s(int M, int N, int K, int kch
       im += x.y;
     }
     const long m = m0 + r, n = n0 + c;
-    if (m < M && n < N) epi_store(epi, m, n, re, im);
+    if (m < M && n < N) {
+      if (part) part[(long(bz) * N + n) * M + m] = c128{re, im};
+      else epi_store(epi, m, n, re, im);
+    }
   }
 }
 
@@ -961,16 +975,27 @@ hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, c
   if (upper && M != N) return hipErrorInvalidValue;
   if constexpr (std::is_same<T, double>::value && std::is_same<EA, double>::value && std::is_same<EB, double>::value) {
     const long blocks = long((M + 15) / 16) * ((N + 15) / 16);
-    if (K <= SKMAX && blocks <= SBLKMAX) {  // splits and part are not used
+    if (K <= SKMAX && blocks <= SBLKMAX) {
       if (pred) return hipErrorInvalidValue;  // too small for a product that has another route
-      int kc = (std::max(K, 0) + SW - 1) / SW;
+      // K over blocks as well where few of them meet a longer K: up to a block per CU, at least 64 k each
+      int s = 1;
+      if (part && K >= 512 && blocks <= 64) s = int(std::min<long>({long(std::max(splits, 1)), 256 / blocks, long(K / 64)}));
+      int kc = (std::max(K, 0) + SW * s - 1) / (SW * s);
       kc = std::max(SKG, ((kc + SKG - 1) / SKG) * SKG);
+      s = std::max(1, (K + SW * kc - 1) / (SW * kc));
+      c128* pp = s > 1 ? part : nullptr;
       if (mode == GEMM_CN)
-        hipLaunchKernelGGL((k_gemm_s<EO, GEMM_CN>), dim3(unsigned(blocks)), dim3(64 * SW), 0, st, M, N, K, kc, A, lda, B,
-                           ldb, epi);
+        hipLaunchKernelGGL((k_gemm_s<EO, GEMM_CN>), dim3(unsigned(blocks * s)), dim3(64 * SW), 0, st, M, N, K, kc, A, lda,
+                           B, ldb, epi, pp);
       else
-        hipLaunchKernelGGL((k_gemm_s<EO, GEMM_NN>), dim3(unsigned(blocks)), dim3(64 * SW), 0, st, M, N, K, kc, A, lda, B,
-                           ldb, epi);
+        hipLaunchKernelGGL((k_gemm_s<EO, GEMM_NN>), dim3(unsigned(blocks * s)), dim3(64 * SW), 0, st, M, N, K, kc, A, lda,
+                           B, ldb, epi, pp);
+      if (s > 1) {
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        const long total = long(M) * N;
+        hipLaunchKernelGGL((k_reduce<EO>), dim3(unsigned((total + 255) / 256)), dim3(256), 0, st, M, N, s, part, epi);
+      }
       return hipGetLastError();
     }
   }
