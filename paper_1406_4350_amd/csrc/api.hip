@@ -50,6 +50,7 @@ struct cheb_plan_s {
   bool cap_blocks_ok = false;  // atom blocks inverted (all of size <= 32)
   bool have_V = false, have_P = false, have_D = false;
   int fft_batch = 1;
+  bool narrow = false;     // every |gx| and |gy| of the sphere <= n / 4 (pruned plane pass)
   bool band_fits = false;  // small boxes: the transforms of a band in one launch (fft_band)
   HalfPlanes hproj, hback;                  // mixed plans: split planes of P (set with the projectors)
   bool split_gemm = true;                   // mixed plans: FP16 hi/lo split MFMA for P^H x and P w
@@ -340,7 +341,7 @@ int fft_batch_for(const cheb_plan_s* p, int nb) {
   // batches from cap / 2 to cap, take the one with the fewest rounds per band (the largest on a tie), so that the
   // last round of a launch does not leave blocks idle (15 bands at 128^3 FP64 are 1920 items on 256 blocks, 7.5
   // rounds; 14 are 7).
-  const long R = std::max(1, fft_plane_blocks(p->n, p->rx, p->prec == CHEB_FP64));
+  const long R = std::max(1, fft_plane_blocks(p->n, p->rx, p->narrow, p->prec == CHEB_FP64));
   const int per = p->gamma ? 2 : 1;  // bands per transform
   long best = long(cap), best_rounds = 0;
   for (long b = long(cap); b >= std::max<long>(1, long(cap) / 2); --b) {
@@ -686,7 +687,7 @@ template <typename T> struct Ops {
   using C = cx<T>;
   cheb_plan p;
   hipStream_t st;
-  FftGeom geom() const { return FftGeom{p->n, p->ncol, p->npw, p->rx, p->col, p->ent, p->xline}; }
+  FftGeom geom() const { return FftGeom{p->n, p->ncol, p->npw, p->rx, p->col, p->ent, p->xline, p->narrow}; }
   // algorithmic flops of one band's plane pass: on each of the n z-planes, 2 (2 rx + 1) y-transforms of the
   // nonzero x-lines and 2 n x-transforms of the rows, 5 n log2 n flops per complex length-n transform, and the
   // real-space product with V(r) (2 per point)
@@ -2179,6 +2180,8 @@ cheb_status cheb_plan_create(const cheb_desc* d, void* persistent, size_t bytes,
     if (xl.z == 0) { xl.x = cc; xl.y = g0[1]; }
     xl.z += 1;
   }
+  p->narrow = true;
+  for (int e = 0; e < npf; ++e) p->narrow = p->narrow && 4 * std::max(std::abs(G[3 * e]), std::abs(G[3 * e + 1])) <= d->n;
   std::vector<int4> pinfo(std::max(nproj, 1), int4{0, 0, 0, 0});
   size_t doff = 0;
   std::vector<int2> dent(std::max<size_t>(dsize, 1), int2{0, 0});
@@ -2225,7 +2228,7 @@ cheb_status cheb_plan_create(const cheb_desc* d, void* persistent, size_t bytes,
     if ((e = hipStreamSynchronize(st))) return fail_hip(e, "sync");
   }
   if ((e = fft_prepare_attributes())) return fail_hip(e, "kernel attributes");
-  const FftGeom geom{p->n, p->ncol, p->npw, p->rx, p->col, p->ent, p->xline};
+  const FftGeom geom{p->n, p->ncol, p->npw, p->rx, p->col, p->ent, p->xline, p->narrow};
   p->band_fits = mixed ? fft_band_fits<float>(geom) : fft_band_fits<double>(geom);
   if (rocblas_create_handle(&p->rb) != rocblas_status_success) {
     std::fprintf(stderr, "cheb_plan_create: rocblas_create_handle failed\n");

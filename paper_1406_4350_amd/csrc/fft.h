@@ -38,11 +38,39 @@ template <int R> struct SplitOf {  // smallest useful radix of R
   static constexpr int A = (R % 4 == 0 && R != 8) ? 4 : (R % 2 == 0 ? 2 : (R % 3 == 0 ? 3 : R));
 };
 
-// In-place DFT of length R on registers, natural order in and out.
+// bits of v[B n1 + n2], n1 < A, out of a mask over v
+constexpr unsigned sub_mask(unsigned zm, int A, int B, int n2) {
+  unsigned m = 0;
+  for (int n1 = 0; n1 < A; ++n1)
+    if (zm >> (B * n1 + n2) & 1u) m |= 1u << n1;
+  return m;
+}
+
+// In-place DFT of length R on registers, natural order in and out. ZM: bit n set where v[n] is known to be zero (taken as
+// zero whatever it holds); its additions are left out of the first radix-2 or radix-4 step.
 template <int R, int DIR> struct Dft {
-  template <typename T> __device__ __forceinline__ static void run(cx<T>* v) {
+  template <unsigned ZM = 0, typename T> __device__ __forceinline__ static void run(cx<T>* v) {
+    static_assert(ZM == 0 || R == 2 || (R == 3 && ZM == 2) || (R == 4 && ZM == 4) || R > 4, "no codelet for these zeros");
     if constexpr (R == 1) {
       return;
+    } else if constexpr (R == 3 && ZM == 2) {  // v[1] = 0
+      const T h = T(0.5), s3 = T(DIR * 0.86602540378443864676372317075294);
+      cx<T> a = v[0], c = v[2];
+      cx<T> m = {a.x - h * c.x, a.y - h * c.y}, r = {s3 * c.y, -s3 * c.x};
+      v[0] = a + c;
+      v[1] = m + r;
+      v[2] = m - r;
+    } else if constexpr (R == 2 && ZM != 0) {
+      if constexpr (ZM == 3) v[0] = v[1] = cx<T>{T(0), T(0)};
+      else if constexpr (ZM == 2) v[1] = v[0];
+      else { v[0] = v[1]; v[1] = cx<T>{-v[1].x, -v[1].y}; }
+    } else if constexpr (R == 4 && ZM == 4) {  // v[2] = 0
+      cx<T> a = v[0], c = v[1] + v[3], d = v[1] - v[3];
+      cx<T> di = DIR > 0 ? cx<T>{-d.y, d.x} : cx<T>{d.y, -d.x};
+      v[0] = a + c;
+      v[2] = a - c;
+      v[1] = a + di;
+      v[3] = a - di;
     } else if constexpr (R == 2) {
       cx<T> a = v[0], b = v[1];
       v[0] = a + b;
@@ -74,7 +102,8 @@ template <int R, int DIR> struct Dft {
         cx<T> y[A];
 #pragma unroll
         for (int n1 = 0; n1 < A; ++n1) y[n1] = v[B * n1 + n2];
-        Dft<A, DIR>::run(y);
+        constexpr unsigned zm = sub_mask(ZM, A, B, n2);
+        Dft<A, DIR>::template run<zm>(y);
         static_for<0, A>([&](auto k1c) {
           constexpr int k1 = decltype(k1c)::value;
           v[B * k1 + n2] = twc<R, n2 * k1, DIR>(y[k1]);

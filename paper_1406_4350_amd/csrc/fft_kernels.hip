@@ -82,6 +82,26 @@ template <typename T> __device__ __forceinline__ cx<T> conj_if(cx<T> w, bool c) 
 // signed frequency of FFT index k (|result| <= (N-1)/2 for the indices the sphere uses)
 template <int N> __device__ __forceinline__ int freq(int k) { return k <= (N - 1) / 2 ? k : k - N; }
 
+// Spheres within |gx|, |gy| <= N / 4 (any without aliasing in the box) leave whole first digits of the frequency unused:
+// with k = N2 n1 + n2, digit n1 holds a |freq(k)| <= N / 4 for some n2 or for none. PR kernels leave the loads, the additions and
+// the outputs of the empty digits out (3 of 8 at 64, 96 and 128, 2 of 6 at 48, 1 of 4 below): the plane pass of 8 filter
+// steps of 256 bands at 48^3 1.22 -> 1.14 ms (FP64) and 0.72 -> 0.68 ms (FP32), of one H X of 1024 bands at 96^3 5.74 ->
+// 5.38 ms, of 12 steps of 1024 bands at 128^3 in FP32 91.8 -> 86.4 ms.
+template <int N> constexpr bool digit_used(int n1) {
+  constexpr int N2 = LineSplit<N>::N2;
+  for (int n2 = 0; n2 < N2; ++n2) {
+    const int k = N2 * n1 + n2, g = k <= (N - 1) / 2 ? k : N - k;
+    if (4 * g <= N) return true;
+  }
+  return false;
+}
+template <int N, bool PR> constexpr unsigned digit_mask() {  // bit n1: digit n1 is empty
+  unsigned m = 0;
+  if (PR)
+    for (int n1 = 0; n1 < LineSplit<N>::N1; ++n1) m |= digit_used<N>(n1) ? 0u : 1u << n1;
+  return m;
+}
+
 // compute units of the current device (queried once per device)
 int compute_units() {
   static int cached[64] = {0};
@@ -135,6 +155,11 @@ template <int N, typename T> struct PlaneCfg {
   // loads one step ahead (see k_plane) where the LDS holds a single block per CU anyway; elsewhere the extra
   // registers would cost resident blocks
   static constexpr bool PF = N == 128 || (N == 96 && sizeof(T) == 8);
+  // the outermost x-lines apart (see k_plane) where that saves a round of groups at the radius N / 4: 31 lines in 4 groups
+  // at 64, one per wave, instead of 33 in 5; 63 in 16 at 128 instead of 65 in 17. The plane pass of 8 filter steps: 1.62 ->
+  // 1.47 ms at 64^3 (FP64, Gamma point), 96.5 -> 90.0 ms at 128^3 (FP32, 12 steps of 1024 bands); at 48^3, 4 groups or 3,
+  // 0.76 -> 0.72 ms in FP32 but 1.21 -> 1.23 in FP64; at 96^3, 10 groups either way, the extra code costs 4 to 9%.
+  static constexpr bool TRIM = N == 64 || N == 128 || (N == 48 && sizeof(T) == 4);
   static_assert(GL * N2 <= 64 && GL * N1 <= 64 && RPW <= GL, "one task per lane in every sub-stage");
 };
 
@@ -145,7 +170,7 @@ template <int N, typename T> constexpr size_t plane_lines_bytes(int nx) {
 }
 template <int N, typename T> constexpr size_t plane_lds(int nx) { return plane_lines_bytes<N, T>(nx) + size_t(nx) * 16; }
 
-template <int N, typename T>
+template <int N, typename T, bool PR>
 __global__ __launch_bounds__((64 * PlaneCfg<N, T>::NW)) void k_plane(int ncol, int rx, const int4* __restrict__ xline,
                                                                    const cx<T>* __restrict__ twg,
                                                                    const T* __restrict__ Vt,
@@ -153,6 +178,8 @@ __global__ __launch_bounds__((64 * PlaneCfg<N, T>::NW)) void k_plane(int ncol, i
                                                                    cx<T>* __restrict__ cout, int nitems) {
   using P = PlaneCfg<N, T>;
   constexpr int N1 = P::N1, N2 = P::N2, PS = P::PS, LS = P::LS, NW = P::NW, GL = P::GL, RPW = P::RPW;
+  constexpr unsigned ZM = digit_mask<N, PR>();
+  constexpr auto used = [](int d) { return (ZM >> d & 1u) == 0u; };
   extern __shared__ unsigned char smem_raw[];
   const int nx = 2 * rx + 1;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -173,8 +200,16 @@ __global__ __launch_bounds__((64 * PlaneCfg<N, T>::NW)) void k_plane(int ncol, i
   }
 #pragma unroll
   for (int k = 1; k < N2; ++k) twf[k] = twg[(a1 * k) % N];
-  const int ngroups = (nx + GL - 1) / GL;
   __syncthreads();
+  // The outermost x-lines (gx = -rx, rx) of a sphere of integer radius hold one column, at gy = 0: their inverse y
+  // transform is that value on every y, and their one forward output (gy = 0) the sum over y. The last wave sets and
+  // sums them directly, and the others go through the transforms in groups of GL.
+  const int trim = (P::TRIM && nx >= 3 && XL[0].z == 1 && XL[0].y == 0 && XL[nx - 1].z == 1 && XL[nx - 1].y == 0) ? 1 : 0;
+  const int xend = nx - trim;  // lines trim .. xend - 1 take the transforms
+  const int ngroups = (xend - trim + GL - 1) / GL;
+  const bool edge_wave = trim && wave == NW - 1;  // a wave with no more groups than any other
+  const int et = lane >> 5, es = lane & 31;        // edge line (0: gx = -rx, 1: gx = rx) and slot of a lane
+  const int exi = et ? nx - 1 : 0;
 
   // With PF, loads are issued one step ahead of their use and kept raw (the zero padding is selected at the use,
   // since a select right after the load would wait for it): the stage-A inputs of the next group (of the next
@@ -184,12 +219,13 @@ __global__ __launch_bounds__((64 * PlaneCfg<N, T>::NW)) void k_plane(int ncol, i
   cx<T> araw[N1];
   int aly = 0, alz = 0;  // lowest gy and column count of the prefetched x-line
   auto load_a = [&](const cx<T>* src, int g) {
-    const int xi = min(g * GL + u2, nx - 1);
+    const int xi = min(trim + g * GL + u2, xend - 1);
     const int4 xl = XL[xi];  // {first column, lowest gy, column count, 0}
     aly = xl.y;
     alz = xl.z;
 #pragma unroll
     for (int n1 = 0; n1 < N1; ++n1) {
+      if (!used(n1)) continue;
       const int j = freq<N>(N2 * n1 + n2) - xl.y;
       araw[n1] = src[xl.x + ((j >= 0 && j < xl.z) ? j : 0)];
     }
@@ -215,18 +251,19 @@ __global__ __launch_bounds__((64 * PlaneCfg<N, T>::NW)) void k_plane(int ncol, i
     // ---- A: inverse y ----
     for (int g = wave; g < ngroups; g += NW) {
       {
-        const int xi = g * GL + u2;
-        const bool mine = u2 < GL && xi < nx;
+        const int xi = trim + g * GL + u2;
+        const bool mine = u2 < GL && xi < xend;
         if constexpr (!P::PF) load_a(in, g);
         cx<T> v[N1];
 #pragma unroll
         for (int n1 = 0; n1 < N1; ++n1) {
+          if (!used(n1)) continue;
           const int j = freq<N>(N2 * n1 + n2) - aly;
           v[n1] = (j >= 0 && j < alz) ? araw[n1] : zero;
         }
         if constexpr (P::PF) load_a(in, min(g + NW, ngroups - 1));
         if (mine) {
-          Dft<N1, +1>::run(v);
+          Dft<N1, +1>::template run<ZM>(v);
           cx<T>* p = L + xi * LS + n2;
 #pragma unroll
           for (int k1 = 0; k1 < N1; ++k1) p[PS * k1] = k1 ? cmul(v[k1], twi[k1]) : v[0];
@@ -234,8 +271,8 @@ __global__ __launch_bounds__((64 * PlaneCfg<N, T>::NW)) void k_plane(int ncol, i
       }
       wave_sync();
       {
-        const int xi = g * GL + u1;
-        if (u1 < GL && xi < nx) {
+        const int xi = trim + g * GL + u1;
+        if (u1 < GL && xi < xend) {
           cx<T>* p = L + xi * LS + PS * a1;
           cx<T> v[N2];
 #pragma unroll
@@ -245,6 +282,11 @@ __global__ __launch_bounds__((64 * PlaneCfg<N, T>::NW)) void k_plane(int ncol, i
           for (int b = 0; b < N2; ++b) p[b] = v[b];  // y = a1 + N1 b
         }
       }
+    }
+    if (edge_wave) {  // the edge lines: their one value on every slot PS a + b
+      const cx<T> c = in[XL[exi].x];
+      cx<T>* p = L + exi * LS;
+      for (int e = es; e < N; e += 32) p[PS * (e / N2) + e % N2] = c;
     }
     __syncthreads();
 
@@ -258,12 +300,13 @@ __global__ __launch_bounds__((64 * PlaneCfg<N, T>::NW)) void k_plane(int ncol, i
         cx<T> v[N1];
 #pragma unroll
         for (int n1 = 0; n1 < N1; ++n1) {
+          if (!used(n1)) continue;
           const int gx = freq<N>(N2 * n1 + n2);
           const bool ok = gx >= -rx && gx <= rx;
           const cx<T> x = L[(ok ? gx + rx : 0) * LS + py];
           v[n1] = ok ? x : zero;
         }
-        Dft<N1, +1>::run(v);
+        Dft<N1, +1>::template run<ZM>(v);
         cx<T>* p = Rw + u2 * LS + n2;
 #pragma unroll
         for (int k1 = 0; k1 < N1; ++k1) p[PS * k1] = k1 ? cmul(v[k1], twi[k1]) : v[0];
@@ -292,6 +335,7 @@ __global__ __launch_bounds__((64 * PlaneCfg<N, T>::NW)) void k_plane(int ncol, i
         Dft<N1, -1>::run(v);
 #pragma unroll
         for (int ka = 0; ka < N1; ++ka) {
+          if (!used(ka)) continue;
           const int gx = freq<N>(n2 + N2 * ka);
           if (gx >= -rx && gx <= rx) L[(gx + rx) * LS + py] = v[ka];
         }
@@ -309,8 +353,8 @@ __global__ __launch_bounds__((64 * PlaneCfg<N, T>::NW)) void k_plane(int ncol, i
     // ---- C: forward y ----
     for (int g = wave; g < ngroups; g += NW) {
       {
-        const int xi = g * GL + u1;
-        if (u1 < GL && xi < nx) {
+        const int xi = trim + g * GL + u1;
+        if (u1 < GL && xi < xend) {
           cx<T>* p = L + xi * LS + PS * a1;
           cx<T> v[N2];
 #pragma unroll
@@ -322,8 +366,8 @@ __global__ __launch_bounds__((64 * PlaneCfg<N, T>::NW)) void k_plane(int ncol, i
       }
       wave_sync();
       {
-        const int xi = g * GL + u2;
-        if (u2 < GL && xi < nx) {
+        const int xi = trim + g * GL + u2;
+        if (u2 < GL && xi < xend) {
           const int4 xl = XL[xi];
           const cx<T>* p = L + xi * LS + n2;
           cx<T> v[N1];
@@ -332,11 +376,23 @@ __global__ __launch_bounds__((64 * PlaneCfg<N, T>::NW)) void k_plane(int ncol, i
           Dft<N1, -1>::run(v);
 #pragma unroll
           for (int ka = 0; ka < N1; ++ka) {
+            if (!used(ka)) continue;
             const int j = freq<N>(n2 + N2 * ka) - xl.y;
             if (j >= 0 && j < xl.z) out[xl.x + j] = v[ka];
           }
         }
       }
+    }
+    if (edge_wave) {  // the edge lines: the sum over y, 32 lanes per line
+      const cx<T>* p = L + exi * LS;
+      cx<T> acc = zero;
+      for (int e = es; e < N; e += 32) acc = acc + p[PS * (e / N2) + e % N2];
+#pragma unroll
+      for (int o = 16; o > 0; o >>= 1) {
+        acc.x += __shfl_xor(acc.x, o, 64);
+        acc.y += __shfl_xor(acc.y, o, 64);
+      }
+      if (es == 0) out[XL[exi].x] = acc;
     }
     __syncthreads();  // the next item overwrites the x-lines
   }
@@ -364,6 +420,7 @@ constexpr size_t half128_lines_bytes(int nx) {
 }
 constexpr size_t half128_lds(int nx) { return half128_lines_bytes(nx) + size_t(nx) * 16; }
 
+template <bool PR>
 __global__ __launch_bounds__(64 * Half128::NW) void k_plane_half(int ncol, int rx, const int4* __restrict__ xline,
                                                                  const c128* __restrict__ twg,
                                                                  const double* __restrict__ Vt,
@@ -373,6 +430,8 @@ __global__ __launch_bounds__(64 * Half128::NW) void k_plane_half(int ncol, int r
   using T = double;
   constexpr int N = H::N, N1 = H::N1, N2 = H::N2, PS = H::PS, LS = H::LS, LSH = H::LSH, GL = H::GL, NW = H::NW,
                 RPW = H::RPW;
+  constexpr unsigned ZM = digit_mask<N, PR>();
+  constexpr auto used = [](int d) { return (ZM >> d & 1u) == 0u; };
   extern __shared__ unsigned char smem_raw[];
   const int nx = 2 * rx + 1;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -399,11 +458,15 @@ __global__ __launch_bounds__(64 * Half128::NW) void k_plane_half(int ncol, int r
   __syncthreads();
   // The outermost x-lines (gx = -rx, rx) of a sphere of integer radius hold one column, at gy = 0: their inverse y
   // transform is that value on every y, and their one forward output (gy = 0) the sum over y. They are set and
-  // summed by the last wave directly, and the others go through the transforms in groups of GL, 63 lines in 16
-  // groups at 128^3 (two per wave) instead of 65 in 17 (a third round on one wave).
+  // summed by the last wave directly, and the others go through the transforms in groups of GW, 63 lines in 8
+  // groups at 128^3, one per wave.
   const int trim = (nx >= 3 && XL[0].z == 1 && XL[0].y == 0 && XL[nx - 1].z == 1 && XL[nx - 1].y == 0) ? 1 : 0;
   const int xend = nx - trim;  // lines trim .. xend - 1 take the transforms
-  const int ngroups = (xend - trim + GL - 1) / GL;
+  // lines per wave and group: two rounds of the stages of 16 tasks per line, whose loads overlap, and one of those of 4
+  // (with GL lines the 4-task stages ran on 16 of 64 lanes, twice). With the empty digits left out: 245 -> 205 us per
+  // launch of 14 bands.
+  constexpr int GW = 2 * GL;
+  const int ngroups = (xend - trim + GW - 1) / GW;
   const bool edge_wave = trim && wave == NW - 1;  // a wave with no more groups than any other
   const int et = lane >> 5, es = lane & 31;        // edge line (0: gx = -rx, 1: gx = rx) and slot of a lane
   const int exi = et ? nx - 1 : 0;
@@ -419,19 +482,21 @@ __global__ __launch_bounds__(64 * Half128::NW) void k_plane_half(int ncol, int r
     for (int h = 0; h < 2; ++h) {
       // ---- A: inverse y, the half's four groups ----
       for (int g = wave; g < ngroups; g += NW) {
-        {
-          const int xi = trim + g * GL + u2;
+#pragma unroll
+        for (int s = 0; s < GW / GL; ++s) {
+          const int xi = trim + g * GW + s * GL + u2;
           if (xi < xend) {
             const int4 xl = XL[xi];  // {first column, lowest gy, column count, 0}
             c128 v[N1];
 #pragma unroll
             for (int n1 = 0; n1 < N1; ++n1) {
+              if (!used(n1)) continue;
               const int j = freq<N>(N2 * n1 + n2) - xl.y;
               const bool ok = j >= 0 && j < xl.z;
               const c128 x = in[xl.x + (ok ? j : 0)];
               v[n1] = ok ? x : zero;
             }
-            Dft<N1, +1>::run(v);
+            Dft<N1, +1>::template run<ZM>(v);
             c128* p = L + xi * LSH + n2;
             const bool hh = h != 0;
 #pragma unroll
@@ -446,8 +511,8 @@ __global__ __launch_bounds__(64 * Half128::NW) void k_plane_half(int ncol, int r
         }
         wave_sync();
         {
-          const int xi = trim + g * GL + uq;
-          if (uq < GL && xi < xend) {
+          const int xi = trim + g * GW + uq;
+          if (uq < GW && xi < xend) {
             c128* p = L + xi * LSH + PS * aq;
             c128 v[N2];
 #pragma unroll
@@ -481,12 +546,13 @@ __global__ __launch_bounds__(64 * Half128::NW) void k_plane_half(int ncol, int r
           c128 v[N1];
 #pragma unroll
           for (int n1 = 0; n1 < N1; ++n1) {
+            if (!used(n1)) continue;
             const int gx = freq<N>(N2 * n1 + n2);
             const bool ok = gx >= -rx && gx <= rx;
             const c128 x = L[(ok ? gx + rx : 0) * LSH + py];
             v[n1] = ok ? x : zero;
           }
-          Dft<N1, +1>::run(v);
+          Dft<N1, +1>::template run<ZM>(v);
           c128* p = Rw + u2 * LS + n2;
 #pragma unroll
           for (int k1 = 0; k1 < N1; ++k1) p[PS * k1] = k1 ? cmul(v[k1], twi[k1]) : v[0];
@@ -514,6 +580,7 @@ __global__ __launch_bounds__(64 * Half128::NW) void k_plane_half(int ncol, int r
           Dft<N1, -1>::run(v);
 #pragma unroll
           for (int ka = 0; ka < N1; ++ka) {
+            if (!used(ka)) continue;
             const int gx = freq<N>(n2 + N2 * ka);
             if (gx >= -rx && gx <= rx) L[(gx + rx) * LSH + py] = v[ka];
           }
@@ -525,8 +592,8 @@ __global__ __launch_bounds__(64 * Half128::NW) void k_plane_half(int ncol, int r
       // ---- C: forward y, this half's share ----
       for (int g = wave; g < ngroups; g += NW) {
         {
-          const int xi = trim + g * GL + uq;
-          if (uq < GL && xi < xend) {
+          const int xi = trim + g * GW + uq;
+          if (uq < GW && xi < xend) {
             c128* p = L + xi * LSH + PS * aq;
             const int a = aq + H::G * h;
             c128 v[N2];
@@ -538,8 +605,9 @@ __global__ __launch_bounds__(64 * Half128::NW) void k_plane_half(int ncol, int r
           }
         }
         wave_sync();
-        {
-          const int xi = trim + g * GL + u2;
+#pragma unroll
+        for (int s = 0; s < GW / GL; ++s) {
+          const int xi = trim + g * GW + s * GL + u2;
           if (xi < xend) {
             const int4 xl = XL[xi];
             const c128* p = L + xi * LSH + n2;
@@ -553,6 +621,7 @@ __global__ __launch_bounds__(64 * Half128::NW) void k_plane_half(int ncol, int r
             Dft<H::G, -1>::run(o);  // Y[2k + 1]
 #pragma unroll
             for (int ka = 0; ka < N1; ++ka) {
+              if (!used(ka)) continue;
               const int j = freq<N>(n2 + N2 * ka) - xl.y;
               if (j >= 0 && j < xl.z) {
                 c128 yv = (ka & 1) ? o[ka >> 1] : e[ka >> 1];
@@ -1171,8 +1240,12 @@ hipError_t plane_half_launch(const FftGeom& g, const c128* tw, const double* Vt,
   const size_t lds = half128_lds(2 * g.rx + 1);
   if (lds > 160 * 1024) return hipErrorInvalidConfiguration;
   const int grid = int(std::min<long>(nitems, long(compute_units())));  // one block per CU (LDS)
-  hipLaunchKernelGGL(k_plane_half, dim3(grid), dim3(64 * Half128::NW), lds, st, g.ncol, g.rx, g.xline, tw, Vt, cin,
-                     cout, nitems);
+  if (g.narrow)
+    hipLaunchKernelGGL(k_plane_half<true>, dim3(grid), dim3(64 * Half128::NW), lds, st, g.ncol, g.rx, g.xline, tw, Vt,
+                       cin, cout, nitems);
+  else
+    hipLaunchKernelGGL(k_plane_half<false>, dim3(grid), dim3(64 * Half128::NW), lds, st, g.ncol, g.rx, g.xline, tw, Vt,
+                       cin, cout, nitems);
   return hipGetLastError();
 }
 hipError_t plane_half_launch(const FftGeom&, const c64*, const float*, const c64*, c64*, int, hipStream_t) {
@@ -1180,21 +1253,23 @@ hipError_t plane_half_launch(const FftGeom&, const c64*, const float*, const c64
 }
 
 // resident blocks of k_plane<N, T> on the device (LDS and registers): the persistent grid of the plane pass
-template <int N, typename T> int plane_resident_blocks(int rx) {
+template <int N, typename T> int plane_resident_blocks(int rx, bool narrow) {
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&k_plane<N, T>),
+  const void* kernel = narrow ? reinterpret_cast<const void*>(&k_plane<N, T, true>)
+                                   : reinterpret_cast<const void*>(&k_plane<N, T, false>);
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel,
                                                    64 * PlaneCfg<N, T>::NW, plane_lds<N, T>(2 * rx + 1)) != hipSuccess ||
       per_cu <= 0)
     per_cu = 1;
   return compute_units() * per_cu;
 }
 
-int fft_plane_blocks(int n, int rx, bool dbl) {
+int fft_plane_blocks(int n, int rx, bool narrow, bool dbl) {
   int out = compute_units();
   (void)dispatch_n(n, [&](auto nc) {
     constexpr int N = decltype(nc)::value;
     if (N == 128 && dbl) out = compute_units();  // k_plane_half: one block per CU
-    else out = dbl ? plane_resident_blocks<N, double>(rx) : plane_resident_blocks<N, float>(rx);
+    else out = dbl ? plane_resident_blocks<N, double>(rx, narrow) : plane_resident_blocks<N, float>(rx, narrow);
     return hipSuccess;
   });
   return out;
@@ -1215,9 +1290,13 @@ hipError_t fft_plane(const FftGeom& g, const cx<T>* tw, const T* Vt, const cx<T>
       // a persistent grid of as many blocks as stay resident (LDS and registers), so that no block starts its share
       // of the items late and each loads its twiddles once
       constexpr int threads = 64 * PlaneCfg<N, T>::NW;
-      const int grid = int(std::min<long>(nitems, long(plane_resident_blocks<N, T>(g.rx))));
-      hipLaunchKernelGGL((k_plane<N, T>), dim3(grid), dim3(threads), lds, st, g.ncol, g.rx, g.xline, tw, Vt, cin,
-                         cout, nitems);
+      const int grid = int(std::min<long>(nitems, long(plane_resident_blocks<N, T>(g.rx, g.narrow))));
+      if (g.narrow)
+        hipLaunchKernelGGL((k_plane<N, T, true>), dim3(grid), dim3(threads), lds, st, g.ncol, g.rx, g.xline, tw, Vt, cin,
+                           cout, nitems);
+      else
+        hipLaunchKernelGGL((k_plane<N, T, false>), dim3(grid), dim3(threads), lds, st, g.ncol, g.rx, g.xline, tw, Vt, cin,
+                           cout, nitems);
       return hipGetLastError();
     }
   });
@@ -1340,9 +1419,15 @@ hipError_t fft_prepare_attributes() {
   };
   auto each = [&](auto nc) {
     constexpr int N = decltype(nc)::value;
-    if constexpr (N == 128) set(reinterpret_cast<const void*>(&k_plane_half));
-    else set(reinterpret_cast<const void*>(&k_plane<N, double>));
-    set(reinterpret_cast<const void*>(&k_plane<N, float>));
+    if constexpr (N == 128) {
+      set(reinterpret_cast<const void*>(&k_plane_half<true>));
+      set(reinterpret_cast<const void*>(&k_plane_half<false>));
+    } else {
+      set(reinterpret_cast<const void*>(&k_plane<N, double, true>));
+      set(reinterpret_cast<const void*>(&k_plane<N, double, false>));
+    }
+    set(reinterpret_cast<const void*>(&k_plane<N, float, true>));
+    set(reinterpret_cast<const void*>(&k_plane<N, float, false>));
     if constexpr (band_box<N>()) {
       set(reinterpret_cast<const void*>(&k_band<N, double>));
       set(reinterpret_cast<const void*>(&k_band<N, float>));

@@ -134,6 +134,7 @@ struct FftGeom {
   const int4* col;  // per column: {x-line index gx + rx, y = gy mod n, first sphere entry, length}
   const int* ent;   // per sphere entry: (column << 8) | (gz mod n)
   const int4* xline;  // per x-line xi = gx + rx: {first column, lowest gy, number of columns (consecutive gy), 0}
+  bool narrow = false;  // every |gx| and |gy| <= n / 4
 };
 template <typename T>
 hipError_t fft_col_inverse(const FftGeom& g, const cx<T>* tw, const cx<T>* X, long ldx, int nb, cx<T>* colbuf,
@@ -164,7 +165,7 @@ size_t fft_xdens_lds_bytes(int n, int rx, bool dbl);
 // dynamic LDS bytes of the plane pass for box n, x-line half-width rx (0 if n unsupported)
 size_t fft_plane_lds_bytes(int n, int rx, bool dbl);
 // blocks of the plane pass resident on the current device at once (its persistent grid for large batches)
-int fft_plane_blocks(int n, int rx, bool dbl);
+int fft_plane_blocks(int n, int rx, bool narrow, bool dbl);
 // Row stride (in elements) of the disk-column buffers [band][z][column]: the column count rounded up to 16, so
 // that every z-row starts on a 128-byte line (the column passes read 16 or 32 neighbouring columns of a row)
 __host__ __device__ inline int col_stride(int ncol) { return (ncol + 15) & ~15; }
