@@ -1251,12 +1251,12 @@ template <typename T> struct Ops {
       return gemm<double, double, double, double>(GEMM_CN, n, 2 * n, n, Xc, n, TT, n, e2, gemm_pick_splits(n, 2 * n, n),
                                                   w.part, st, ROLE_SUBSPACE);
     };
-    // corrections F of the X whose products are (m1, m2) and their block maxima and the cluster flag staged in
-    // slot s, the slot's event recorded after the copies
+    // corrections F of the X whose products are (m1, m2), their block maxima and the cluster flag written to
+    // slot s, the slot's event recorded behind them. The kernel writes the pinned slot itself
     auto corrections = [&](const c128* m1, const c128* m2, long l, int s) {
-      hipError_t r = refine_update(n, m1, l, m2, l, w.F, w.lam, w.absF, w.bmax, st);
-      if (!r) r = hipMemcpyAsync(hst + s * kSlot, w.bmax, nbm * sizeof(double), hipMemcpyDeviceToHost, st);
-      if (!r) r = hipMemcpyAsync(hst + s * kSlot + kRefineBlocksMax, cflag, sizeof(int), hipMemcpyDeviceToHost, st);
+      double* const hs = hst + s * kSlot;
+      hipError_t r = refine_update(n, m1, l, m2, l, w.F, w.lam, w.absF, hs, st, cflag,
+                                   reinterpret_cast<int*>(hs + kRefineBlocksMax));
       if (!r) r = hipEventRecord(p->rr_ev[s], st);
       return r;
     };

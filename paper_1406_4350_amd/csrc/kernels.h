@@ -245,11 +245,12 @@ template <typename E> hipError_t fill_zero_real(E* p, long count, hipStream_t st
 // Warm-started refinement of H X = S X Lambda (n x n, FP64): given M1 = X^H S X, M2 = X^H H X, the correction
 // X <- X (I + F) with F_ij = (M2_ij - lam_j M1_ij)/(lam_j - lam_i), F_ii = (1 - M1_ii)/2, lam_i = M2_ii/M1_ii;
 // absF = off-diagonal |F| (1e300 for an unresolvable near-degenerate pair); bmax[b] = the maximum of block b's
-// entries (NaN if one is NaN) for b < refine_blocks(n) <= kRefineBlocksMax
+// entries (NaN if one is NaN) for b < refine_blocks(n) <= kRefineBlocksMax; with flag, *flag_out = *flag. bmax and
+// flag_out may be pinned host memory, to be read behind an event on st
 constexpr int kRefineBlocksMax = 256;
 int refine_blocks(int n);
 hipError_t refine_update(int n, const c128* M1, long ld1, const c128* M2, long ld2, c128* F, double* lam, double* absF,
-                         double* bmax, hipStream_t st);
+                         double* bmax, hipStream_t st, const int* flag = nullptr, int* flag_out = nullptr);
 // res[0] = max |M1 - I|, res[1] = max off-diagonal |M2| / max(1, max |diag M2|) (NaN if an entry is NaN); part
 // holds 3 kRefineCheckBlocks doubles of per-block maxima
 constexpr int kRefineCheckBlocks = 64;

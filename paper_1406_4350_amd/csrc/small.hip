@@ -701,7 +701,8 @@ namespace {
 __device__ __forceinline__ double max_nan(double a, double b) { return (a != a || b != b) ? a + b : fmax(a, b); }
 
 __global__ __launch_bounds__(256) void k_refine_update(int n, const c128* M1, long ld1, const c128* M2, long ld2, c128* F,
-                                                      double* lam, double* absF, double* bmax) {
+                                                      double* lam, double* absF, double* bmax, const int* flag,
+                                                      int* flag_out) {
   __shared__ double red[256];
   double mx = 0.0;
   const long total = long(n) * n;
@@ -737,7 +738,10 @@ __global__ __launch_bounds__(256) void k_refine_update(int n, const c128* M1, lo
     if (threadIdx.x < k) red[threadIdx.x] = max_nan(red[threadIdx.x], red[threadIdx.x + k]);
     __syncthreads();
   }
-  if (threadIdx.x == 0) bmax[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) {
+    bmax[blockIdx.x] = red[0];
+    if (flag && blockIdx.x == 0) *flag_out = *flag;
+  }
 }
 
 // res[0] = max |M1 - I|, res[1] = max_{i != j} |M2_ij| / max(1, max_i |M2_ii|)  (one block, fixed order)
@@ -820,8 +824,9 @@ __global__ void k_permute_scale(int n, const c128* X, const int* perm, const dou
 int refine_blocks(int n) { return nblocks(long(n) * n, 256, kRefineBlocksMax); }
 
 hipError_t refine_update(int n, const c128* M1, long ld1, const c128* M2, long ld2, c128* F, double* lam, double* absF,
-                         double* bmax, hipStream_t st) {
-  hipLaunchKernelGGL(k_refine_update, dim3(refine_blocks(n)), dim3(256), 0, st, n, M1, ld1, M2, ld2, F, lam, absF, bmax);
+                         double* bmax, hipStream_t st, const int* flag, int* flag_out) {
+  hipLaunchKernelGGL(k_refine_update, dim3(refine_blocks(n)), dim3(256), 0, st, n, M1, ld1, M2, ld2, F, lam, absF, bmax,
+                     flag, flag_out);
   return hipGetLastError();
 }
 hipError_t refine_check(int n, const c128* M1, long ld1, const c128* M2, long ld2, double* part, double* res,
