@@ -58,25 +58,6 @@ __global__ __launch_bounds__(NT) void k_col_inv(int ncol, const int4* __restrict
   }
 }
 
-// Rows of the old block-synchronous x-pass, kept for the cross-density kernel of the adjoint: about one task per
-// thread in the first stage, and the N = 128 double-precision plane inside 160 KB of LDS.
-template <int N, typename T> constexpr int xdens_rows() {
-  constexpr int N2 = LineSplit<N>::N2;
-  constexpr int r = (N == 128 && sizeof(T) == 8) ? 4 : NT / N2;
-  return r < N ? r : N;
-}
-
-// Inter-stage twiddles laid out for the lanes that use them: twA[k1 N2 + n2] = W_N^(n2 k1) is read by lanes of
-// consecutive n2, twB[kb N1 + a] = W_N^(a kb) by lanes of consecutive a (forward sign; conjugate for inverse).
-template <int N, typename T> __device__ __forceinline__ void stage_twiddles(const cx<T>* tw, cx<T>* twA, cx<T>* twB) {
-  constexpr int N1 = LineSplit<N>::N1, N2 = LineSplit<N>::N2;
-  for (int t = threadIdx.x; t < N; t += NT) {
-    const int k1 = t / N2, n2 = t - k1 * N2;
-    twA[t] = tw[(n2 * k1) % N];
-    const int kb = t / N1, a = t - kb * N1;
-    twB[t] = tw[(a * kb) % N];
-  }
-}
 template <typename T> __device__ __forceinline__ cx<T> conj_if(cx<T> w, bool c) { return c ? cx<T>{w.x, -w.y} : w; }
 
 // signed frequency of FFT index k (|result| <= (N-1)/2 for the indices the sphere uses)
@@ -779,130 +760,169 @@ __global__ __launch_bounds__((64 * PlaneCfg<N, T>::NW)) void k_dens(int ncol, in
   }
 }
 
-// ---- cross density for the adjoint: part[chunk][z][y][x] = sum_b w_b Re(conj(a_b(r)) psi_b(r)) ----------
-// Inputs are the z-transformed disk columns of both blocks (as written by the column pass). Per block: one
-// z-plane and a chunk of bands; each thread keeps its (y, x) points of every row batch in FP64 registers
-// across the bands of the chunk, so the band sum is in a fixed order.
-template <int N, typename T> constexpr int xdens_batches() { return (N + xdens_rows<N, T>() - 1) / xdens_rows<N, T>(); }
-template <int N, typename T> constexpr size_t xdens_lds(int nx) {
-  return (size_t(2 * (nx + xdens_rows<N, T>())) * line_stride<N>() + 3 * N) * sizeof(cx<T>);
-}
-
-// inverse y of one x-line block (both stages), the line ends in digit-reversed order as in k_plane
-template <int N, typename T>
-__device__ __forceinline__ void y_inverse(const cx<T>* __restrict__ in, cx<T>* L, const int4* __restrict__ xline,
-                                          const cx<T>* twA, int nx) {
-  constexpr int N1 = LineSplit<N>::N1, N2 = LineSplit<N>::N2, LS = line_stride<N>(), PS = group_stride<N>();
-  const int tid = threadIdx.x;
-  for (int task = tid; task < nx * N2; task += NT) {
-    const int xi = task / N2, n2 = task - xi * N2;
-    const int4 xl = xline[xi];
-    cx<T> v[N1];
-#pragma unroll
-    for (int n1 = 0; n1 < N1; ++n1) {
-      const int j = freq<N>(N2 * n1 + n2) - xl.y;
-      v[n1] = (j >= 0 && j < xl.z) ? cx<T>(in[xl.x + j]) : cx<T>{T(0), T(0)};
-    }
-    Dft<N1, +1>::run(v);
-#pragma unroll
-    for (int k1 = 0; k1 < N1; ++k1) L[xi * LS + PS * k1 + n2] = k1 ? cmul(v[k1], conj_if(twA[k1 * N2 + n2], true)) : v[0];
-  }
-  __syncthreads();
-  for (int task = tid; task < nx * N1; task += NT) {
-    const int xi = task / N1, a = task - xi * N1;
-    cx<T>* p = L + xi * LS + PS * a;
-    cx<T> v[N2];
-#pragma unroll
-    for (int n2 = 0; n2 < N2; ++n2) v[n2] = p[n2];
-    Dft<N2, +1>::run(v);
-#pragma unroll
-    for (int k2 = 0; k2 < N2; ++k2) p[k2] = v[k2];
-  }
-}
-
-// first inverse-x stage of rows y0 .. y0 + nrow - 1 from the x-lines in L into the row scratch S
-template <int N, typename T>
-__device__ __forceinline__ void x_inverse_stage1(const cx<T>* L, cx<T>* S, const cx<T>* twA, int rx, int y0, int nrow) {
-  constexpr int N1 = LineSplit<N>::N1, N2 = LineSplit<N>::N2, LS = line_stride<N>(), PS = group_stride<N>();
-  for (int task = threadIdx.x; task < nrow * N2; task += NT) {
-    const int yy = task / N2, n2 = task - yy * N2;
-    const int y = y0 + yy, py = PS * (y % N1) + y / N1;
-    cx<T> v[N1];
-#pragma unroll
-    for (int n1 = 0; n1 < N1; ++n1) {
-      const int gx = freq<N>(N2 * n1 + n2);
-      v[n1] = (gx >= -rx && gx <= rx) ? cx<T>(L[(gx + rx) * LS + py]) : cx<T>{T(0), T(0)};
-    }
-    Dft<N1, +1>::run(v);
-#pragma unroll
-    for (int k1 = 0; k1 < N1; ++k1) S[yy * LS + PS * k1 + n2] = k1 ? cmul(v[k1], conj_if(twA[k1 * N2 + n2], true)) : v[0];
-  }
-}
-
-template <int N, typename T>
-__global__ __launch_bounds__(NT) void k_xdens(int ncol, int rx, const int4* __restrict__ xline,
-                                              const cx<T>* __restrict__ twg, const cx<T>* __restrict__ ca,
-                                              const cx<T>* __restrict__ cb, int nband, int bpc,
-                                              const double* __restrict__ wts, double* __restrict__ part) {
-  constexpr int N1 = LineSplit<N>::N1, N2 = LineSplit<N>::N2, LS = line_stride<N>(), PS = group_stride<N>();
-  constexpr int RB = xdens_rows<N, T>(), NBT = xdens_batches<N, T>();
-  static_assert(RB * N1 <= NT, "one second-stage task per thread and row batch");
+// ---- band densities up to 64^3: part[chunk][z][y][x] = sum_b w_b Re(conj(a_b(r)) psi_b(r)), or w_b |a_b(r)|^2 if cb = ca --
+// Inputs are the z-transformed disk columns of the blocks (as written by the column pass). One z-plane and a chunk of
+// bands per block, with the wave-local stages A and B of the plane pass: a band's a is taken to real space into
+// registers (each lane keeps the points of its rows, RPW rows per wave and pass), then psi over the same LDS, and the
+// products are added up in FP64 registers across the bands of the chunk, in a fixed order. Bound by the exchanges through
+// LDS like the plane pass, and by its occupancy: with one plane in LDS instead of two, two blocks share a CU at 64^3
+// (FP64, 77 KB each). With both planes in LDS and block-wide exchanges a launch
+// at 64^3 (FP64, some 110 bands) took 254 us, now 124 us (the plane pass, of the same work, 113 us); a filter of 8 steps of
+// 512 bands with its adjoint 79.2 -> 73.7 ms.
+template <int N, typename T, bool PR>
+__global__ __launch_bounds__((64 * PlaneCfg<N, T>::NW)) void k_xdens(int rx, long cs, const int4* __restrict__ xline,
+                                                                     const cx<T>* __restrict__ twg,
+                                                                     const cx<T>* __restrict__ ca,
+                                                                     const cx<T>* __restrict__ cb, int cross, int nband,
+                                                                     int bpc, const double* __restrict__ wts,
+                                                                     double* __restrict__ part) {
+  using P = PlaneCfg<N, T>;
+  constexpr int N1 = P::N1, N2 = P::N2, PS = P::PS, LS = P::LS, NW = P::NW, GL = P::GL, RPW = P::RPW;
+  constexpr int NP = (N + NW * RPW - 1) / (NW * RPW);  // row passes
+  constexpr unsigned ZM = digit_mask<N, PR>();
+  constexpr auto used = [](int d) { return (ZM >> d & 1u) == 0u; };
   extern __shared__ unsigned char smem_raw[];
   const int nx = 2 * rx + 1;
-  cx<T>* La = reinterpret_cast<cx<T>*>(smem_raw);
-  cx<T>* Lb = La + nx * LS;
-  cx<T>* Sa = Lb + nx * LS;
-  cx<T>* Sb = Sa + RB * LS;
-  cx<T>* tw = Sb + RB * LS;
-  cx<T>* twA = tw + N;
-  cx<T>* twB = twA + N;
-  const int z = blockIdx.x, chunk = blockIdx.y, tid = threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  cx<T>* L = reinterpret_cast<cx<T>*>(smem_raw);
+  cx<T>* Rw = L + nx * LS + wave * RPW * LS;
+  int4* XL = reinterpret_cast<int4*>(smem_raw + plane_lines_bytes<N, T>(nx));
+  const cx<T> zero = {T(0), T(0)};
+  const int z = blockIdx.x, chunk = blockIdx.y;
   const int b0 = chunk * bpc, b1 = min(nband, b0 + bpc);
-  for (int t = tid; t < N; t += NT) tw[t] = twg[t];
-  __syncthreads();
-  stage_twiddles<N, T>(tw, twA, twB);
-  double acc[NBT][N2];
+  for (int t = threadIdx.x; t < nx; t += blockDim.x) XL[t] = xline[t];
+  const int u2 = lane / N2, n2 = lane - u2 * N2;
+  const int u1 = lane / N1, a1 = lane - u1 * N1;
+  cx<T> twi[N1];
 #pragma unroll
-  for (int t = 0; t < NBT; ++t)
+  for (int k = 1; k < N1; ++k) {
+    const cx<T> w = twg[(n2 * k) % N];
+    twi[k] = cx<T>{w.x, -w.y};
+  }
+  __syncthreads();
+  // one-column outermost x-lines apart, as in k_plane
+  const int trim = (P::TRIM && nx >= 3 && XL[0].z == 1 && XL[0].y == 0 && XL[nx - 1].z == 1 && XL[nx - 1].y == 0) ? 1 : 0;
+  const int xend = nx - trim;
+  const int ngroups = (xend - trim + GL - 1) / GL;
+
+  auto inverse_y = [&](const cx<T>* in) {
+    for (int g = wave; g < ngroups; g += NW) {
+      {
+        const int xi = trim + g * GL + u2;
+        if (u2 < GL && xi < xend) {
+          const int4 xl = XL[xi];
+          cx<T> v[N1];
+#pragma unroll
+          for (int n1 = 0; n1 < N1; ++n1) {
+            if (!used(n1)) continue;
+            const int j = freq<N>(N2 * n1 + n2) - xl.y;
+            const bool ok = j >= 0 && j < xl.z;
+            const cx<T> c = in[xl.x + (ok ? j : 0)];
+            v[n1] = ok ? c : zero;
+          }
+          Dft<N1, +1>::template run<ZM>(v);
+          cx<T>* p = L + xi * LS + n2;
+#pragma unroll
+          for (int k1 = 0; k1 < N1; ++k1) p[PS * k1] = k1 ? cmul(v[k1], twi[k1]) : v[0];
+        }
+      }
+      wave_sync();
+      {
+        const int xi = trim + g * GL + u1;
+        if (u1 < GL && xi < xend) {
+          cx<T>* p = L + xi * LS + PS * a1;
+          cx<T> v[N2];
+#pragma unroll
+          for (int b = 0; b < N2; ++b) v[b] = p[b];
+          Dft<N2, +1>::run(v);
+#pragma unroll
+          for (int b = 0; b < N2; ++b) p[b] = v[b];
+        }
+      }
+    }
+    if (trim && wave == NW - 1) {
+      const int exi = lane >> 5 ? nx - 1 : 0;
+      const cx<T> c = in[XL[exi].x];
+      cx<T>* p = L + exi * LS;
+      for (int e = lane & 31; e < N; e += 32) p[PS * (e / N2) + e % N2] = c;
+    }
+  };
+  // v[b] = field(x = a1 + N1 b) of this lane's row of the pass at y0
+  auto inverse_x = [&](int y0, cx<T>* v) {
+    const int nrow = min(RPW, N - y0);
+    if (u2 < nrow) {
+      const int y = y0 + u2, py = PS * (y % N1) + y / N1;
+      cx<T> w[N1];
+#pragma unroll
+      for (int n1 = 0; n1 < N1; ++n1) {
+        if (!used(n1)) continue;
+        const int gx = freq<N>(N2 * n1 + n2);
+        const bool ok = gx >= -rx && gx <= rx;
+        const cx<T> x = L[(ok ? gx + rx : 0) * LS + py];
+        w[n1] = ok ? x : zero;
+      }
+      Dft<N1, +1>::template run<ZM>(w);
+      cx<T>* p = Rw + u2 * LS + n2;
+#pragma unroll
+      for (int k1 = 0; k1 < N1; ++k1) p[PS * k1] = k1 ? cmul(w[k1], twi[k1]) : w[0];
+    }
+    wave_sync();
+    if (u1 < nrow) {
+      const cx<T>* p = Rw + u1 * LS + PS * a1;
+#pragma unroll
+      for (int b = 0; b < N2; ++b) v[b] = p[b];
+      Dft<N2, +1>::run(v);
+    }
+    wave_sync();  // the row buffers are refilled by the next pass
+  };
+
+  double acc[NP][N2];
+#pragma unroll
+  for (int t = 0; t < NP; ++t)
 #pragma unroll
     for (int b = 0; b < N2; ++b) acc[t][b] = 0.0;
-  const int yy = tid / N1, a = tid - (tid / N1) * N1;
-  __syncthreads();
   for (int band = b0; band < b1; ++band) {
     const double wt = wts ? wts[band] : 1.0;
-    const long base = long(band) * N * col_stride(ncol) + long(z) * col_stride(ncol);
-    y_inverse<N, T>(ca + base, La, xline, twA, nx);
-    y_inverse<N, T>(cb + base, Lb, xline, twA, nx);
+    const long base = (long(band) * N + z) * cs;
+    cx<T> f[NP][N2];
+    inverse_y(ca + base);
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < NBT; ++t) {
-      const int y0 = t * RB, nrow = min(RB, N - y0);
-      x_inverse_stage1<N, T>(La, Sa, twA, rx, y0, nrow);
-      x_inverse_stage1<N, T>(Lb, Sb, twA, rx, y0, nrow);
-      __syncthreads();
-      if (yy < nrow) {
-        cx<T> va[N2], vb[N2];
+    for (int t = 0; t < NP; ++t) {
 #pragma unroll
-        for (int n2 = 0; n2 < N2; ++n2) {
-          va[n2] = Sa[yy * LS + PS * a + n2];
-          vb[n2] = Sb[yy * LS + PS * a + n2];
-        }
-        Dft<N2, +1>::run(va);
-        Dft<N2, +1>::run(vb);
+      for (int b = 0; b < N2; ++b) f[t][b] = zero;
+      inverse_x((t * NW + wave) * RPW, f[t]);
+    }
+    __syncthreads();  // the next field overwrites the x-lines
+    if (cross) {
+      inverse_y(cb + base);
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < NP; ++t) {
+        cx<T> v[N2];
+#pragma unroll
+        for (int b = 0; b < N2; ++b) v[b] = zero;
+        inverse_x((t * NW + wave) * RPW, v);
 #pragma unroll
         for (int b = 0; b < N2; ++b)
-          acc[t][b] += wt * (double(va[b].x) * double(vb[b].x) + double(va[b].y) * double(vb[b].y));
+          acc[t][b] += wt * (double(f[t][b].x) * double(v[b].x) + double(f[t][b].y) * double(v[b].y));
       }
       __syncthreads();
+    } else {
+#pragma unroll
+      for (int t = 0; t < NP; ++t)
+#pragma unroll
+        for (int b = 0; b < N2; ++b)
+          acc[t][b] += wt * (double(f[t][b].x) * double(f[t][b].x) + double(f[t][b].y) * double(f[t][b].y));
     }
   }
   double* out = part + (long(chunk) * N + z) * N * N;
 #pragma unroll
-  for (int t = 0; t < NBT; ++t) {
-    const int y0 = t * RB, nrow = min(RB, N - y0);
-    if (yy < nrow) {
+  for (int t = 0; t < NP; ++t) {
+    const int y0 = (t * NW + wave) * RPW;
+    if (u1 < min(RPW, N - y0)) {
 #pragma unroll
-      for (int b = 0; b < N2; ++b) out[long(y0 + yy) * N + a + N1 * b] = acc[t][b];
+      for (int b = 0; b < N2; ++b) out[long(y0 + u1) * N + a1 + N1 * b] = acc[t][b];
     }
   }
 }
@@ -1373,10 +1393,16 @@ hipError_t cross_density(const FftGeom& g, const cx<T>* tw, const cx<T>* ca, con
   hipError_t e = dispatch_n(g.n, [&](auto nc) {
     constexpr int N = decltype(nc)::value;
     if constexpr (N <= 64) {
-      const size_t lds = xdens_lds<N, T>(2 * g.rx + 1);
+      const size_t lds = plane_lds<N, T>(2 * g.rx + 1);
       if (lds > 160 * 1024) return hipErrorInvalidConfiguration;
-      hipLaunchKernelGGL((k_xdens<N, T>), dim3(N, nchunk), dim3(NT), lds, st, g.ncol, g.rx, g.xline, tw, ca, cb, nband,
-                         bpc, wts, part);
+      const dim3 grid(N, nchunk), block(64 * PlaneCfg<N, T>::NW);
+      const int cross = ca != cb;
+      if (g.narrow)
+        hipLaunchKernelGGL((k_xdens<N, T, true>), grid, block, lds, st, g.rx, col_stride(g.ncol), g.xline, tw, ca, cb, cross,
+                           nband, bpc, wts, part);
+      else
+        hipLaunchKernelGGL((k_xdens<N, T, false>), grid, block, lds, st, g.rx, col_stride(g.ncol), g.xline, tw, ca, cb, cross,
+                           nband, bpc, wts, part);
       return hipGetLastError();
     } else {
       const size_t lds = plane_lds<N, T>(2 * g.rx + 1);
@@ -1398,6 +1424,14 @@ hipError_t cross_density(const FftGeom& g, const cx<T>* tw, const cx<T>* ca, con
 }
 
 size_t cross_density_part_doubles(int n, int nband) { return size_t(xdens_chunks(n, nband)) * n * n * n; }
+
+// The radii that the adjoint takes up to 64^3 are those at which both planes and NT / N2 rows of both fit in LDS, which is
+// more than k_xdens asks for.
+template <int N, typename T> constexpr size_t xdens_lds(int nx) {
+  constexpr int r = NT / LineSplit<N>::N2, rows = r < N ? r : N;
+  static_assert(PlaneCfg<N, T>::NW * PlaneCfg<N, T>::RPW <= 2 * rows, "k_xdens fits wherever the bound does");
+  return (size_t(2 * (nx + rows)) * line_stride<N>() + 3 * N) * sizeof(cx<T>);
+}
 
 size_t fft_xdens_lds_bytes(int n, int rx, bool dbl) {
   size_t out = 0;
@@ -1433,8 +1467,10 @@ hipError_t fft_prepare_attributes() {
       set(reinterpret_cast<const void*>(&k_band<N, float>));
     }
     if constexpr (N <= 64) {
-      set(reinterpret_cast<const void*>(&k_xdens<N, double>));
-      set(reinterpret_cast<const void*>(&k_xdens<N, float>));
+      set(reinterpret_cast<const void*>(&k_xdens<N, double, true>));
+      set(reinterpret_cast<const void*>(&k_xdens<N, double, false>));
+      set(reinterpret_cast<const void*>(&k_xdens<N, float, true>));
+      set(reinterpret_cast<const void*>(&k_xdens<N, float, false>));
     } else {
       set(reinterpret_cast<const void*>(&k_dens<N, double>));
       set(reinterpret_cast<const void*>(&k_dens<N, float>));
