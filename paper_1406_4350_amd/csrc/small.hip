@@ -625,17 +625,32 @@ hipError_t ratio_real(int nb, const c128* a, const c128* b, double* out, hipStre
 
 namespace chebfd {
 namespace {
-__global__ void k_block_grad(int dsize, const int2* __restrict__ dent, int nb, const c128* __restrict__ x, long ldx,
-                             const c128* __restrict__ y, long ldy, const double* __restrict__ wts, double alpha,
-                             double* __restrict__ out) {
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < dsize; e += gridDim.x * blockDim.x) {
+// 16 entries per block and 16 threads per entry, each with every 16th band (four in flight), their sums in a fixed order.
+// Bound by the latency of the loads: one thread per entry (4096 entries, 512 bands) left 240 CUs idle and took 235 us, and
+// the adjoint of 8 filter steps at 64^3 73.7 ms, now 71.6.
+constexpr int kGradEnt = 16, kGradSlice = 16;
+__global__ __launch_bounds__(kGradEnt* kGradSlice) void k_block_grad(int dsize, const int2* __restrict__ dent, int nb,
+                                                                     const c128* __restrict__ x, long ldx,
+                                                                     const c128* __restrict__ y, long ldy,
+                                                                     const double* __restrict__ wts, double alpha,
+                                                                     double* __restrict__ out) {
+  __shared__ double red[kGradSlice][kGradEnt];
+  const int le = threadIdx.x % kGradEnt, sl = threadIdx.x / kGradEnt;
+  const int e = blockIdx.x * kGradEnt + le;
+  double s = 0.0;
+  if (e < dsize) {
     const int k = dent[e].x, l = dent[e].y;
-    double s = 0.0;
-    for (int b = 0; b < nb; ++b) {
+#pragma unroll 4
+    for (int b = sl; b < nb; b += kGradSlice) {
       const c128 xk = x[b * ldx + k], xl = x[b * ldx + l], yk = y[b * ldy + k], yl = y[b * ldy + l];
       const double v = xk.x * yl.x + xk.y * yl.y + xl.x * yk.x + xl.y * yk.y;
       s += wts ? wts[b] * v : v;
     }
+  }
+  red[sl][le] = s;
+  __syncthreads();
+  if (sl == 0 && e < dsize) {
+    for (int k = 1; k < kGradSlice; ++k) s += red[k][le];
     out[e] += alpha * s;
   }
 }
@@ -665,7 +680,8 @@ template <typename E> __global__ void k_zero_real(E* p, long count) {
 hipError_t block_grad(int dsize, const int2* dent, int nb, const c128* x, long ldx, const c128* y, long ldy,
                       const double* wts, double alpha, double* out, hipStream_t st) {
   if (dsize <= 0 || nb <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_block_grad, dim3(nblocks(dsize)), dim3(256), 0, st, dsize, dent, nb, x, ldx, y, ldy, wts, alpha, out);
+  hipLaunchKernelGGL(k_block_grad, dim3((dsize + kGradEnt - 1) / kGradEnt), dim3(kGradEnt * kGradSlice), 0, st, dsize, dent,
+                     nb, x, ldx, y, ldy, wts, alpha, out);
   return hipGetLastError();
 }
 hipError_t weighted_adjoint(int nk, int nb, const double* w, const c128* Z, long ldz, c128* B, hipStream_t st) {

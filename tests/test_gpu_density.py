@@ -36,3 +36,21 @@ def test_band_densities(n, radius, nb):
         print(f"[check] prec={prec} dV {e:.2e}", flush=True)
         assert e < tol
         plan.close()
+
+
+@pytest.mark.parametrize("nb", [6, 16, 17, 83])
+def test_block_gradient(nb):
+    """dL/dD with band counts on either side of the 16 slices that share a block entry. Bounds as above."""
+    cfg = wl.SMALL["tiny_paw"].replace(name=f"dd{nb}", n=16, radius=4, nb=nb, seed_index=600 + nb)
+    pb = wl.make_problem(cfg)
+    ops = matfree.Operators.from_problem(pb)
+    lp = matfree.lanczos_upper_bound(ops, pb.v0, 10)[0]
+    lm = float(np.max(matfree.rayleigh_quotients(ops, pb.X0)))
+    c, r, m, nk = 0.5 * (lp + lm), 0.5 * (lp - lm), 2, 4
+    w = np.random.default_rng(13).uniform(0, 1, nk)
+    _, _, _, _, dD = grad.filter_rr_grad(ops, pb.X0, m, c, r, w, pb.D)
+    print(f"[case] nb={nb} entries={dD.size}", flush=True)
+    plan = cf.plan_from_problem(pb, cf.CHEB_FP64)
+    _, _, _, gD = plan.filter_rr_backward(cf.to_device_block(pb.X0, torch.complex128), m, c, r, w, 2)
+    assert _rel(gD.cpu().numpy(), dD) < 1e-8
+    plan.close()
