@@ -92,7 +92,8 @@ typedef struct {
 } cheb_desc;
 
 /* Size in bytes of the device buffer a plan keeps for its lifetime (index maps, twiddles, V(r), P, D, Q,
- * P^H P, capacitance inverse). */
+ * P^H P, capacitance inverse; in FP64 plans whose projector products run on the INT8 matrix cores also the residue
+ * planes of P, 90 bytes per entry, up to 64 GiB). */
 cheb_status cheb_plan_persistent_bytes(const cheb_desc* desc, size_t* bytes);
 
 /* Create a plan over a caller-provided device buffer of at least cheb_plan_persistent_bytes bytes
@@ -287,7 +288,8 @@ cheb_status cheb_filter_rr_backward(cheb_plan plan, const void* X0, int ldx, int
 /* Kernel-class timers (diagnostics). While enabled, each launch of a class below made by calls on the plan is
  * bracketed by HIP events on the call's own stream, and the algorithmic bytes and flops of the launch
  * (from its shapes: the bytes the operation must move and the flops it must do, not what the kernel
- * actually fetches) are tallied per class. */
+ * actually fetches) are tallied per class. While enabled, boxes up to 16^3 take the three FFT passes that the timers
+ * tell apart instead of the one launch per call that they take otherwise (equal up to rounding). */
 typedef enum {
   CHEB_T_FFT_COL_INV = 0,   /* sphere -> disk columns, inverse z-FFT */
   CHEB_T_FFT_PLANE = 1,     /* per z-plane inverse y, x, V(r) multiply, forward x, y */
