@@ -326,6 +326,14 @@ cheb_status cheb_gemm_splits(int M, int N, int K, int* fp64, int* fp16, int* bou
  * tm (tm + 1) / 2 for group -1) > 0, group >= 1 or -1 and the pointers non-null. */
 cheb_status cheb_gemm_block_item(int i, int total, int tm, int tn, int group, int* bx, int* by, int* bz);
 
+/* Residue arithmetic of the INT8 projector products, host arithmetic only (the operations of the kernels): for modulus
+ * number l (0 <= l < *count), its value, the largest integer magnitude *sum that the split of an operand reduces modulo
+ * it, the largest residue magnitude *residue that the accumulator bound counts on (*max_k residue^2 < 2^31, *max_k the
+ * longest product taken; modulus 256 may wrap), and the largest residue magnitude *largest that the reduction leaves of
+ * the integers x0 <= x < x1. CHEB_ERR_ARG for a null pointer, l out of range or x0 > x1. */
+cheb_status cheb_residue_limits(int l, int x0, int x1, int* count, int* modulus, int* sum, int* residue, int* max_k,
+                                int* largest);
+
 /* Message of the last failing call on `plan` ("" if none). Valid until the next call on the plan. */
 const char* cheb_last_error(cheb_plan plan);
 

@@ -2608,6 +2608,18 @@ cheb_status cheb_gemm_block_item(int i, int total, int tm, int tn, int group, in
   return host_fail(nullptr);
 }
 
+cheb_status cheb_residue_limits(int l, int x0, int x1, int* count, int* modulus, int* sum, int* residue, int* max_k,
+                                int* largest) try {
+  if (!count || !modulus || !sum || !residue || !max_k || !largest || l < 0 || l >= kRnsMods || x0 > x1) return CHEB_ERR_ARG;
+  *count = kRnsMods;
+  *max_k = kRnsMaxK;
+  rns_residue_limits(modulus, l, sum, residue);
+  *largest = rns_residue_largest(l, x0, x1);
+  return CHEB_OK;
+} catch (...) {
+  return host_fail(nullptr);
+}
+
 cheb_status cheb_locking_degrees(int nb, const double* ritz, const double* resid, double c, double r, int m_max,
                                  double tol, int32_t* degrees, int* nlocked) try {
   if (nb < 0 || m_max < 1 || !(r > 0.0) || !std::isfinite(c) || !std::isfinite(r) || !(tol >= 0.0)) return CHEB_ERR_ARG;

@@ -14,6 +14,7 @@
 // Operands arrive as int8 planes (per modulus: residues of the real parts, of the imaginary parts and of the sum),
 // K contiguous; the projectors' planes are laid out once with the plan, the other operand's per call.
 #include <algorithm>
+#include <cstdlib>
 
 #include "gemm_common.h"
 #include "kernels.h"
@@ -22,8 +23,9 @@ namespace chebfd {
 namespace {
 
 constexpr int L = kRnsMods;
-// 256, then the largest numbers below 242 that are pairwise coprime: residues of the odd ones lie within +-120, which
-// leaves the one-step reductions below (error at most 6) inside the int8 range
+// 256, then the largest numbers below 242 that are pairwise coprime. The split leaves residues of the odd ones within
+// +-kResMax (one above (p - 1) / 2 at 241: its reduction rounds in float), and the one-step reductions of their products
+// (error at most 6) stay inside the int8 range.
 constexpr int kP[15] = {256, 241, 239, 235, 233, 229, 227, 223, 221, 217, 211, 209, 199, 197, 193};
 static_assert(L <= 15, "moduli");
 
@@ -100,13 +102,20 @@ __constant__ ModTab kTab = make_tab();
 // mantissa bits. Exact up to the rounding of x to float: |result| <= p / 2 + 2^-24 |x| + |x - float(x)|.
 constexpr float kMagic = 12582912.0f;
 constexpr int kMagicBits = 0x4B400000;
-__device__ __forceinline__ int mod_step(int x, int p, float inv) {
-  const int q = __float_as_int(fmaf(float(x), inv, kMagic)) - kMagicBits;
-  return x - __mul24(q, p);
+__host__ __device__ __forceinline__ int mul24(int a, int b) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __mul24(a, b);
+#else
+  return a * b;
+#endif
+}
+__host__ __device__ __forceinline__ int mod_step(int x, int p, float inv) {
+  const int q = __builtin_bit_cast(int, fmaf(float(x), inv, kMagic)) - kMagicBits;
+  return x - mul24(q, p);
 }
 // the low byte of the same: the constant of kMagicBits drops out modulo 256
 __device__ __forceinline__ unsigned mod_byte(int x, int p, float inv) {
-  return unsigned(x - __mul24(__float_as_int(fmaf(float(x), inv, kMagic)), p));
+  return unsigned(x - mul24(__builtin_bit_cast(int, fmaf(float(x), inv, kMagic)), p));
 }
 __device__ __forceinline__ unsigned pack4(unsigned a, unsigned b, unsigned c, unsigned d) {  // low bytes
   const unsigned lo = __builtin_amdgcn_perm(b, a, 0x0c0c0400u), hi = __builtin_amdgcn_perm(d, c, 0x04000c0cu);
@@ -176,7 +185,13 @@ __device__ __forceinline__ Digits digits(double y) {
   return {int(h), int(g), int(rint(fma(-g, 0x1p22, r)))};
 }
 // residues modulo kP[l] of NV complex integers, as bytes packed by four: re, im and the sums re + im, re - im (each
-// third plane only where asked for). |d2 c2 + d1 c1 + d0| <= 2^25.1, so one step leaves at most p / 2 + 4.
+// third plane only where asked for). |d2 c2 + d1 c1 + d0| <= split_max, of which one step leaves at most kResMax modulo
+// the odd numbers (p / 2 + 4 by the bound of mod_step; over every such integer the largest is 121, modulo 241).
+constexpr int split_max(int p) {
+  const int c2 = sym_mod(1ll << 40, p), c1 = sym_mod(1ll << 22, p);
+  return ((c2 < 0 ? -c2 : c2) + (c1 < 0 ? -c1 : c1)) * (1 << 17) + (1 << 21);
+}
+constexpr int kResMax = 121;
 template <int NV, bool SUM, bool DIFF>
 __device__ __forceinline__ void residues(int l, const Digits (&re)[NV], const Digits (&im)[NV], unsigned (&pr)[NV / 4],
                                          unsigned (&pi)[NV / 4], unsigned (&ps)[NV / 4], unsigned (&pd)[NV / 4]) {
@@ -190,8 +205,8 @@ __device__ __forceinline__ void residues(int l, const Digits (&re)[NV], const Di
     for (int j = 0; j < 4; ++j) {
       const Digits& a = re[4 * g + j];
       const Digits& b = im[4 * g + j];
-      r[j] = mod_step(__mul24(a.d2, c2) + __mul24(a.d1, c1) + a.d0, p, inv);
-      i[j] = mod_step(__mul24(b.d2, c2) + __mul24(b.d1, c1) + b.d0, p, inv);
+      r[j] = mod_step(mul24(a.d2, c2) + mul24(a.d1, c1) + a.d0, p, inv);
+      i[j] = mod_step(mul24(b.d2, c2) + mul24(b.d1, c1) + b.d0, p, inv);
     }
     pr[g] = pack4(unsigned(r[0]), unsigned(r[1]), unsigned(r[2]), unsigned(r[3]));
     pi[g] = pack4(unsigned(i[0]), unsigned(i[1]), unsigned(i[2]), unsigned(i[3]));
@@ -278,11 +293,11 @@ constexpr int RT = 256;         // output tile (both ways), 4 waves of 128 x 128
 constexpr int RK = kRnsKTile;   // k per LDS stage
 constexpr int RCH = RK / 16;    // 16-byte chunks of a stage row
 constexpr int kStageBytes = 2 * RT * RK;
-// |accumulator| <= 120^2 k (modulo 256 it may wrap): K up to kRnsMaxK fits int32, and up to kDirectK the one-byte
+// |accumulator| <= kResMax^2 k (modulo 256 it may wrap): K up to kRnsMaxK fits int32, and up to kDirectK the one-byte
 // reduction takes it as it is; beyond, its upper half is folded first: |x| <= 2^15 120 + 2^16, exact as a float
-constexpr int kDirectK = 4608;
-static_assert(long(kRnsMaxK) * 120 * 120 < (1l << 31), "accumulator range");
-static_assert(long(kDirectK) * 120 * 120 <= (1l << 26), "accumulator range of the one-byte reduction");
+constexpr int kDirectK = 4480;
+static_assert(long(kRnsMaxK) * kResMax * kResMax < (1l << 31), "accumulator range");
+static_assert(long(kDirectK) * kResMax * kResMax <= (1l << 26), "accumulator range of the one-byte reduction");
 
 // chunk c of stage row r sits at chunk c ^ (r / 2 % 8): 16 consecutive rows read at one c touch all 64 LDS banks
 __device__ __forceinline__ int stage_at(int r, int c) { return r * RK + ((c ^ ((r >> 1) & 7)) << 4); }
@@ -413,7 +428,7 @@ __global__ __launch_bounds__(256, 1) void k_rns_gemm(int M, int N, int nt, RnsOp
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             int y = acc[a][b][v + j];
-            if constexpr (decltype(fold)::value) y = __mul24(y >> 16, c16) + (y & 0xffff);
+            if constexpr (decltype(fold)::value) y = mul24(y >> 16, c16) + (y & 0xffff);
             x[j] = mod_byte(y, p, inv);
           }
           const int m = 32 * a + 2 * v + 4 * fh, n = 32 * b + fr;
@@ -485,6 +500,19 @@ __global__ __launch_bounds__(256) void k_rns_finish(int M, int N, const int8_t* 
 }
 
 }  // namespace
+
+int rns_residue_largest(int l, int x0, int x1) {
+  const int p = kP[l];
+  const float inv = 1.0f / float(p);
+  int big = 0;
+  for (int x = x0; x < x1; ++x) big = std::max(big, std::abs(mod_step(x, p, inv)));
+  return big;
+}
+void rns_residue_limits(int* modulus, int l, int* sum, int* residue) {
+  *modulus = kP[l];
+  *sum = split_max(kP[l]);
+  *residue = kP[l] % 2 ? kResMax : 128 + 4;
+}
 
 // Microseconds of both routes, from what they measured: the FP64 tiles at 60 TFLOP/s executed on whole 64 x 64 tiles
 // (47 to 66 over the sizes below); the int8 tiles at 0.0140 us per k and 3.5 us for filling and emptying them, or the

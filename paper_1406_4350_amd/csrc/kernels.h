@@ -94,7 +94,7 @@ hipError_t split_planes(const c128* X, long ldx, int rows_x, int cols_x, bool tr
 // Operands as residues modulo kRnsMods coprime numbers (see gemm_rns.hip): int8 planes [2 l] (real parts) and
 // [2 l + 1] (imaginary parts) at base + i plane, the sums' (or differences') plane l at third + l third_plane; row r of a
 // plane at r ld, its K values contiguous and padded with zeros to ld = rns_ld(K). inv[r] undoes the row's scale.
-constexpr int kRnsMods = 15, kRnsKTile = 128, kRnsMaxK = 149120;
+constexpr int kRnsMods = 15, kRnsKTile = 128, kRnsMaxK = 146560;
 inline long rns_ld(long K) { return (K + kRnsKTile - 1) / kRnsKTile * kRnsKTile; }
 inline long rns_ldc(long M) { return (M + 15) / 16 * 16; }
 struct RnsOperand {
@@ -103,6 +103,10 @@ struct RnsOperand {
   long plane = 0, third_plane = 0, ld = 0;
   const double* inv = nullptr;
 };
+// Host arithmetic, the operations of the kernels: modulus number l, the largest |integer| that its split reduces and the
+// largest |residue| that kRnsMaxK counts on; the largest |residue| left of x0 <= x < x1.
+void rns_residue_limits(int* modulus, int l, int* sum, int* residue);
+int rns_residue_largest(int l, int x0, int x1);
 // whether the INT8 matrix cores are the faster ones for an M x N x K product whose A is already split
 bool rns_pays(int M, int N, int K);
 // Power-of-two scales of the columns (K x N, ldb) or rows (M x K, lda) of a matrix and their inverses; *flag = 1 (else
