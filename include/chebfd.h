@@ -93,7 +93,7 @@ typedef struct {
 
 /* Size in bytes of the device buffer a plan keeps for its lifetime (index maps, twiddles, V(r), P, D, Q,
  * P^H P, capacitance inverse; in FP64 plans whose projector products run on the INT8 matrix cores also the residue
- * planes of P, 90 bytes per entry, up to 64 GiB). */
+ * planes of P, 96 bytes per entry, up to 64 GiB). */
 cheb_status cheb_plan_persistent_bytes(const cheb_desc* desc, size_t* bytes);
 
 /* Create a plan over a caller-provided device buffer of at least cheb_plan_persistent_bytes bytes

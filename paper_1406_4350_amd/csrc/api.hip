@@ -56,6 +56,7 @@ struct cheb_plan_s {
   bool split_gemm = true;                   // mixed plans: FP16 hi/lo split MFMA for P^H x and P w
   RnsOperand rproj, rback;                  // FP64 plans: residue planes of P for P^H x and for P w (large plans)
   bool rns_ok = false;                      // the planes hold the projectors (false: P unfit, FP64 products only)
+  bool rns_flat[2] = {false, false};        // and their envelopes pass a flat vector, for P^H x and for P w
   bool rr_refine = true;                    // warm-started refinement before the library eigensolver
   // Projections carried through the recurrence (reuse trick) are recomputed from the vectors every `resync`
   // steps (0: never); drift_on measures ||p_carried - P^H psi|| / ||P^H psi|| before every step of the filter
@@ -208,7 +209,8 @@ struct Persist {
   _Float16* Hproj;  // mixed plans: FP16 hi/lo planes of P for P^H x (rows = projectors, k = plane waves)
   _Float16* Hback;  // and for P w (rows = plane waves, k = projectors)
   int8_t *Rproj, *Rback;   // large FP64 plans: residue planes of P (rows = projectors; rows = plane waves)
-  double *Rpinv, *Rbinv;   // and the inverse scales of their rows
+  double *Rpinv, *Rbinv;   // the inverse scales of their rows
+  double *Rpenv, *Rbenv;   // and the envelopes of their rows
   int* gmap; int2* gpair;  // Gamma point maps
   size_t bytes;
 };
@@ -216,7 +218,7 @@ struct Persist {
 inline long pad32(long k) { return (k + 31) / 32 * 32; }
 
 // Whether a plan holds the residue planes of its projectors: FP64 plans whose products over 1024 bands pay on the INT8
-// matrix cores, up to 64 GiB of planes (90 bytes per entry of P; 41 GB of the GPU's 288 at 137 065 x 3328). Gamma
+// matrix cores, up to 64 GiB of planes (96 bytes per entry of P; 44 GB of the GPU's 288 at 137 065 x 3328). Gamma
 // plans take one or two real products per complex one instead of three and stay on the FP64 matrix cores.
 constexpr size_t kRnsPlaneCap = size_t(64) << 30;
 bool rns_planned(int npw, int nproj, int prec, int gamma) {
@@ -252,12 +254,14 @@ Persist persist_layout(void* base, int n, int npw, int npf, int ncol, int rx, in
     l.Hback = b.take<_Float16>(4 * size_t(npw) * pad32(nproj));
   }
   l.Rproj = l.Rback = nullptr;
-  l.Rpinv = l.Rbinv = nullptr;
+  l.Rpinv = l.Rbinv = l.Rpenv = l.Rbenv = nullptr;
   if (rns_planned(npw, nproj, prec, gamma)) {
     l.Rproj = b.take<int8_t>(3 * kRnsMods * size_t(nproj) * rns_ld(npw));
     l.Rback = b.take<int8_t>(3 * kRnsMods * size_t(npw) * rns_ld(nproj));
     l.Rpinv = b.take<double>(nproj);
     l.Rbinv = b.take<double>(npw);
+    l.Rpenv = b.take<double>(npw);
+    l.Rbenv = b.take<double>(nproj);
   }
   l.gmap = gamma ? b.take<int>(npf) : nullptr;
   l.gpair = gamma ? b.take<int2>(npw) : nullptr;
@@ -282,7 +286,7 @@ size_t upper_part_elems(int N, int K) {
   return s > 1 ? size_t(s) * N * N : 0;
 }
 
-// Columns taken at a time by a product on the INT8 matrix cores, whose residue planes (45 bytes per complex entry of
+// Columns taken at a time by a product on the INT8 matrix cores, whose residue planes (48 bytes per complex entry of
 // the operand and of the result) are scratch: about equal pieces of at most kRnsChunk columns, whole tiles of 256.
 constexpr int kRnsChunk = 1024;
 constexpr int kRnsGramChunk = 512;  // and by P^H P, whose set-up has no other large scratch
@@ -319,10 +323,11 @@ struct Ws {
   c128 *cp = nullptr, *cq = nullptr, *cr = nullptr;  // iterative capacitance solve: right side, solution, residual
   c128* pfresh = nullptr;  // projections recomputed from the vectors (drift monitor)
   double* dcol = nullptr;  // per-band relative drift
-  // products on the INT8 matrix cores: flag, scales and inverse scales of the call's operand, its residue planes, the
-  // products' planes (both for at most kRnsChunk columns at a time; null where no product of the call takes them)
+  // products on the INT8 matrix cores: flags, scales and inverse scales of the columns of the call's operand, its residue
+  // planes, the products' planes (both for at most kRnsChunk columns at a time; null where no product of the call takes
+  // them). Set-up: rflag[0] for P unfit, rflag[1] and columns from rflag[2] for P^H P, 1 / norms of P's columns (rinv) and rows (rrow), rflat
   int* rflag = nullptr;
-  double *rscale = nullptr, *rinv = nullptr;
+  double *rscale = nullptr, *rinv = nullptr, *rrow = nullptr, *rflat = nullptr;
   int8_t *rB = nullptr, *rC = nullptr;
   size_t rB_bytes = 0, rC_bytes = 0;
   void* Xs = nullptr;   // band-sorted copy for the per-band degree filter
@@ -489,8 +494,11 @@ cheb_status ws_layout(cheb_plan p, int op, int nb, void* base, Ws* w) {
       if (p->rproj.base) {
         // scales, the flag, and for P^H P the sums of a piece of the projectors and its product's planes
         const size_t n = size_t(std::min(np, kRnsGramChunk));
-        w->rflag = b.take<int>(1);
+        w->rflag = b.take<int>(size_t(np) + 2);
         w->rscale = b.take<double>(std::max(np, p->npw));
+        w->rinv = b.take<double>(np);
+        w->rrow = b.take<double>(p->npw);
+        w->rflat = b.take<double>(2);
         w->rB = b.take<int8_t>(kRnsMods * n * rns_ld(p->npw));
         w->rC = b.take<int8_t>(3 * kRnsMods * n * rns_ldc(np));
       }
@@ -529,7 +537,7 @@ cheb_status ws_layout(cheb_plan p, int op, int nb, void* base, Ws* w) {
       w->rC_bytes = std::max<size_t>(w->rC_bytes, 3 * kRnsMods * n * rns_ldc(p->npw));
     }
     if (w->rB_bytes > 0) {
-      w->rflag = b.take<int>(1);
+      w->rflag = b.take<int>(nb);
       w->rscale = b.take<double>(nb);
       w->rinv = b.take<double>(nb);
       w->rB = b.take<int8_t>(w->rB_bytes);
@@ -782,19 +790,18 @@ template <typename T> struct Ops {
   // Whether a product with residue planes of the plan takes the INT8 matrix cores: where it pays and the workspace,
   // which is laid out for the call's widest block, holds its planes (a narrower block of the same call takes the FP64
   // product where the wide one did not need the planes)
-  bool use_rns(const Ws& w, int M, int nb, int K) const {
-    if (!std::is_same<T, double>::value || !w.rB || !p->rns_ok || !rns_pays(M, nb, K)) return false;
+  bool use_rns(const Ws& w, bool back, int M, int nb, int K) const {
+    if (!std::is_same<T, double>::value || !w.rB || !p->rns_ok || !p->rns_flat[back] || !rns_pays(M, nb, K)) return false;
     const size_t n = size_t(rns_chunk(nb));
     return 3 * kRnsMods * n * rns_ld(K) <= w.rB_bytes && 3 * kRnsMods * n * rns_ldc(M) <= w.rC_bytes;
   }
 
   // out = op(A) B on the INT8 matrix cores (A: residue planes of the plan, B: K x nb), with the FP64 product behind it
-  // for an operand that the flag says is not fit for the integers (every product looks at its own operand)
+  // for the columns that the flags say are not fit for it (every product looks at its own operand)
   template <typename Fallback>
   cheb_status rns(GemmMode mode, int M, int nb, int K, const RnsOperand& A, const c128* B, long ldb, Epi<double> e,
                   const Ws& w, Fallback&& fp64) {
-    HIPCHK(fill_zero_real<int>(w.rflag, 1, st));
-    HIPCHK(rns_scale_cols<double>(K, nb, B, ldb, w.rscale, w.rinv, w.rflag, st));
+    HIPCHK(rns_scale_cols<double>(K, nb, B, ldb, A.env, w.rscale, w.rinv, nullptr, w.rflag, nullptr, st));
     const long step = rns_chunk(nb), ld = rns_ld(K);
     for (long n0 = 0; n0 < nb; n0 += step) {
       const int cnt = int(std::min<long>(step, nb - n0));
@@ -803,13 +810,13 @@ template <typename T> struct Ops {
       b.base = w.rB; b.third = w.rB + 2 * kRnsMods * plane;
       b.plane = b.third_plane = plane; b.ld = ld; b.inv = w.rinv + n0;
       HIPCHK(rns_split_cols<double>(K, cnt, B + n0 * ldb, ldb, w.rscale + n0, w.rB, w.rB + 2 * kRnsMods * plane, nullptr,
-                                    plane, ld, w.rflag, st));
+                                    plane, ld, w.rflag + n0, 1, st));
       Epi<double> en = e;
       en.out += n0 * e.ldo;
       if (en.L) en.L += n0 * e.ldl;
       if (en.U) en.U += n0 * e.ldu;
       if (en.W) en.W += n0 * e.ldw;
-      HIPCHK(rns_product<double>(mode, M, cnt, K, A, b, w.rC, en, false, w.rflag, st));
+      HIPCHK(rns_product<double>(mode, M, cnt, K, A, b, w.rC, en, false, w.rflag + n0, st));
     }
     HIPCHK(fp64(w.rflag));
     return CHEB_OK;
@@ -833,7 +840,7 @@ template <typename T> struct Ops {
     const double b = sizeof(C), np = p->nproj, npw = p->npw;
     Timed t(p, st, CHEB_T_PROJECT, (npw * np + npw * nb) * b + np * nb * 16.0, 8.0 * np * nb * npw);
     if constexpr (std::is_same<T, double>::value) {
-      if (use_rns(w, p->nproj, nb, p->npw))
+      if (use_rns(w, false, p->nproj, nb, p->npw))
         return rns(GEMM_CN, p->nproj, nb, p->npw, p->rproj, X, ldx, e, w, [&](const int* pred) {
           return gemm<double, double, double, double>(GEMM_CN, p->nproj, nb, p->npw, P(), p->npw, X, ldx, e,
                                                       gemm_pick_splits(p->nproj, nb, p->npw), w.part, st, ROLE_PROJECT,
@@ -878,7 +885,7 @@ template <typename T> struct Ops {
     if (ldw <= 0) ldw = p->nproj;
     Timed t(p, st, CHEB_T_BACKPROJECT, npw * np * b + np * nb * 16.0 + vecs * npw * nb * b, 8.0 * npw * nb * np);
     if constexpr (std::is_same<T, double>::value) {
-      if (use_rns(w, p->npw, nb, p->nproj))
+      if (use_rns(w, true, p->npw, nb, p->nproj))
         return rns(GEMM_NN, p->npw, nb, p->nproj, p->rback, wv, ldw, e, w, [&](const int* pred) {
           return gemm<double, double, double, double>(GEMM_NN, p->npw, nb, p->nproj, P(), p->npw, wv, ldw, e, 1, nullptr,
                                                       st, ROLE_BACKPROJECT, false, pred);
@@ -2154,9 +2161,9 @@ cheb_status cheb_plan_create(const cheb_desc* d, void* persistent, size_t bytes,
   if (l.Rproj) {
     const long lp = rns_ld(d->npw), lb = rns_ld(nproj);
     p->rproj.base = l.Rproj; p->rproj.third = l.Rproj + 2 * kRnsMods * nproj * lp;
-    p->rproj.plane = p->rproj.third_plane = nproj * lp; p->rproj.ld = lp; p->rproj.inv = l.Rpinv;
+    p->rproj.plane = p->rproj.third_plane = nproj * lp; p->rproj.ld = lp; p->rproj.inv = l.Rpinv; p->rproj.env = l.Rpenv;
     p->rback.base = l.Rback; p->rback.third = l.Rback + 2 * kRnsMods * d->npw * lb;
-    p->rback.plane = p->rback.third_plane = d->npw * lb; p->rback.ld = lb; p->rback.inv = l.Rbinv;
+    p->rback.plane = p->rback.third_plane = d->npw * lb; p->rback.ld = lb; p->rback.inv = l.Rbinv; p->rback.env = l.Rbenv;
   }
 
   // host-side index maps
@@ -2370,25 +2377,36 @@ cheb_status cheb_set_projectors(cheb_plan p, const void* P, int ldp, const doubl
   // where the planes are laid out, residues of P: rows = projectors (with the differences, for P^H x) and rows = plane
   // waves (with the sums)
   auto mut = [](const auto* q) { return const_cast<std::remove_const_t<std::remove_pointer_t<decltype(q)>>*>(q); };
+  bool gram = false;
   if (p->rproj.base) {
-    int unfit = 0;
-    HIPCHK(fill_zero_real<int>(w.rflag, 1, st));
-    HIPCHK(rns_scale_rows<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rback.inv), w.rflag, st));
+    int unfit[2] = {0, 0};
+    double flat[2] = {0.0, 0.0};
+    HIPCHK(fill_zero_real<int>(w.rflag, 2, st));
+    HIPCHK(rns_scale_cols<double>(p->npw, np, Pd, ldp, nullptr, w.rscale, mut(p->rproj.inv), w.rinv, nullptr, w.rflag, st));
+    HIPCHK(rns_scale_rows<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rback.inv), w.rrow, w.rinv, mut(p->rproj.env),
+                                  w.rflag, st));
     HIPCHK(rns_split_rows<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rback.base), mut(p->rback.third),
                                   p->rback.plane, p->rback.ld, w.rflag, st));
-    HIPCHK(rns_scale_cols<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rproj.inv), w.rflag, st));
+    HIPCHK(rns_row_envelope<double>(p->npw, np, Pd, ldp, w.rrow, mut(p->rback.env), st));
+    HIPCHK(rns_scale_cols<double>(p->npw, np, Pd, ldp, p->rproj.env, w.rscale, mut(p->rproj.inv), nullptr, w.rflag + 2,
+                                  w.rflag + 1, st));
     HIPCHK(rns_split_cols<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rproj.base), nullptr, mut(p->rproj.third),
-                                  p->rproj.plane, p->rproj.ld, w.rflag, st));
-    HIPCHK(hipMemcpyAsync(&unfit, w.rflag, sizeof(int), hipMemcpyDeviceToHost, st));
+                                  p->rproj.plane, p->rproj.ld, w.rflag, 0, st));
+    HIPCHK(rns_flat_overlap(p->npw, p->rproj.env, w.rflat, st));
+    HIPCHK(rns_flat_overlap(np, p->rback.env, w.rflat + 1, st));
+    HIPCHK(hipMemcpyAsync(unfit, w.rflag, sizeof(unfit), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(flat, w.rflat, sizeof(flat), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    p->rns_ok = !unfit;
+    p->rns_ok = !unfit[0];
+    for (int i = 0; i < 2; ++i) p->rns_flat[i] = flat[i] >= kRnsOverlap;
+    gram = p->rns_ok && !unfit[1];
   }
-  // G = P^H P in FP64 from the caller's complex128 projectors; on the INT8 matrix cores by pieces of the columns, each
-  // down to its diagonal block (3328 projectors, 137 065 plane waves: cheb_set_projectors 87 ms, planes included, instead
+  // G = P^H P in FP64 from the caller's complex128 projectors; on the INT8 matrix cores, if every column of P is fit
+  // for it, by pieces of the columns, each down to its diagonal block (3328 projectors, 137 065 plane waves: cheb_set_projectors 87 ms, planes included, instead
   // of 169; 1664 and 57 777: 20 instead of 26)
   Epi<double> eg;
   eg.out = p->G; eg.ldo = np; eg.real_only = p->gamma != 0;
-  if (p->rns_ok && rns_pays(np, std::min(np, kRnsGramChunk), p->npw)) {
+  if (gram && rns_pays(np, std::min(np, kRnsGramChunk), p->npw)) {
     for (int n0 = 0; n0 < np; n0 += kRnsGramChunk) {
       const int cnt = std::min(kRnsGramChunk, np - n0);
       RnsOperand b = p->rproj;
@@ -2396,12 +2414,12 @@ cheb_status cheb_set_projectors(cheb_plan p, const void* P, int ldp, const doubl
       b.inv += n0;
       const long plane = cnt * b.ld;
       HIPCHK(rns_split_cols<double>(p->npw, cnt, Pd + long(n0) * ldp, ldp, w.rscale + n0, nullptr, w.rB, nullptr, plane,
-                                    b.ld, w.rflag, st));
+                                    b.ld, w.rflag, 0, st));
       b.third = w.rB;
       b.third_plane = plane;
       Epi<double> ec = eg;
       ec.out += long(n0) * np;
-      HIPCHK(rns_product<double>(GEMM_CN, n0 + cnt, cnt, p->npw, p->rproj, b, w.rC, ec, false, w.rflag, st));
+      HIPCHK(rns_product<double>(GEMM_CN, n0 + cnt, cnt, p->npw, p->rproj, b, w.rC, ec, false, w.rflag + 2 + n0, st));
     }
     HIPCHK(hermitian_lower(np, p->G, np, st));
   } else {

@@ -55,11 +55,11 @@ template <typename E> int epi_slots(Epi<E>& e) {
 // Epilogue of one wave's NI x NJ MFMA blocks of 16 x 16 (T accumulators, the combined real and imaginary parts in
 // cr, ci; rows of accumulator v given by row_of(v); column block j scaled by scale[j]). The NE operands of block
 // b + 1 are requested, at clamped in-range indices, before the stores of block b, so that every thread keeps a
-// block of loads in flight instead of waiting on each element in turn.
+// block of loads in flight instead of waiting on each element in turn. pred: only columns n with pred[n] set are stored.
 template <int NE, int NI, int NJ, typename E, typename Acc, typename RowOf>
 __device__ __forceinline__ void epi_blocks(const Epi<E>& epi, int M, int N, long mb, long nb, int li,
                                            const Acc (&cr)[NI][NJ], const Acc (&ci)[NI][NJ],
-                                           const double (&scale)[NJ], RowOf row_of) {
+                                           const double (&scale)[NJ], RowOf row_of, const int* pred = nullptr) {
   constexpr int NS = NE > 0 ? NE : 1, NBLK = NI * NJ;
   const cx<E>* src[3] = {epi.L, epi.U, epi.W};
   const long lds[3] = {epi.ldl, epi.ldu, epi.ldw};
@@ -83,6 +83,7 @@ __device__ __forceinline__ void epi_blocks(const Epi<E>& epi, int M, int N, long
       if (b + 1 < NBLK) eload(b + 1, buf[(b + 1) & 1]);
     const int i = b / NJ, j = b % NJ;
     const long n = nb + 16 * j + li;
+    const bool keep = n < N && (!pred || pred[n]);
     const double f = epi.alpha * scale[j];
     // values of all four elements first, then the guarded stores: a value computed only under the guard would
     // let the compiler move its loads there and wait on them
@@ -101,7 +102,7 @@ __device__ __forceinline__ void epi_blocks(const Epi<E>& epi, int M, int N, long
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const long m = mb + 16 * i + row_of(v);
-      if (m < M && n < N) epi.out[m + n * epi.ldo] = val[v];
+      if (m < M && keep) epi.out[m + n * epi.ldo] = val[v];
     }
   }
 }
@@ -135,7 +136,6 @@ __global__ __launch_bounds__(NT, 2) void k_gemm(int M, int N, int K, int kchunk,
   constexpr int SZ = GK * (BM + PAD);
   static_assert(BM == BN, "one stage layout");
   __shared__ cx<T> A0[SZ], B0[SZ], A1[SZ], B1[SZ];
-  if (pred && !*pred) return;
   using acc_t = typename Mfma<T>::acc;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
@@ -143,6 +143,8 @@ __global__ __launch_bounds__(NT, 2) void k_gemm(int M, int N, int K, int kchunk,
   int bx, by, bz;
   gemm_tile_of(blockIdx.x, gridDim.x, (M + BM - 1) / BM, (N + BN - 1) / BN, grp, bx, by, bz);
   const long m0 = long(bx) * BM, n0 = long(by) * BN;
+  static_assert(BN == 64, "a lane per column");
+  if (pred && !__any(n0 + lane < N && pred[min(n0 + lane, long(N) - 1)])) return;
   const int kbeg = bz * kchunk;
   const int kend = min(K, kbeg + kchunk);
   const int nt = (kend - kbeg + GK - 1) / GK;
@@ -309,7 +311,7 @@ __global__ __launch_bounds__(NT, 2) void k_gemm(int M, int N, int K, int kchunk,
         }
   } else {
     const double one[2] = {1.0, 1.0};
-    epi_blocks<NE>(epi, M, N, m0 + wm, n0 + wn, li, cr, ci, one, row_of);
+    epi_blocks<NE>(epi, M, N, m0 + wm, n0 + wn, li, cr, ci, one, row_of, pred);
   }
 }
 
@@ -317,11 +319,10 @@ __global__ __launch_bounds__(NT, 2) void k_gemm(int M, int N, int K, int kchunk,
 template <typename EO>
 __global__ __launch_bounds__(256) void k_reduce(int M, int N, int splits, const c128* __restrict__ part, Epi<EO> epi,
                                                 int upper = 0, const int* __restrict__ pred = nullptr) {
-  if (pred && !*pred) return;
   const long total = long(M) * N;
   for (long t = blockIdx.x * long(blockDim.x) + threadIdx.x; t < total; t += long(gridDim.x) * blockDim.x) {
     const long n = t / M, m = t - n * M;
-    if (upper && m / BM > n / BN) continue;
+    if ((upper && m / BM > n / BN) || (pred && !pred[n])) continue;
     double re = 0.0, im = 0.0;
     // eight partials in flight at a time, added in order
     for (int s0 = 0; s0 < splits; s0 += 8) {

@@ -1,13 +1,23 @@
 // Large FP64 complex products on the INT8 matrix cores, by exact integer arithmetic in a residue number system.
 //
 // The FP64 matrix cores do 78.6 TFLOP/s and the INT8 ones about 5 POP/s, 64 times as much. Each operand vector (a row
-// of op(A), a column of B) is scaled by a power of two to a 2-norm in (2^56, 2^57] and rounded to integers; the
+// of op(A), a column of B) is scaled by a power of two to a 2-norm in [2^60, 2^61) and rounded to integers; the
 // product of the integer matrices is computed exactly, modulo kRnsMods pairwise coprime numbers p below 2^8, as one
 // int8 x int8 -> int32 product per modulus and real product; the Chinese remainder theorem gives the integers back.
-// By Cauchy-Schwarz every entry (real or imaginary) is below 2^114 <= prod p / 4 in magnitude, so nothing overflows
-// whatever the data, and the only errors are the roundings of the operands (1/2 in integers of norm 2^56 ... 2^57) and
-// one rounding of the result: about 2^-58 |a| |b| per entry, where a chain of K / 4 FP64 MFMAs leaves about
-// 2^-53 0.3 sqrt(chain / K) |a| |b| (chain: the K range that one accumulator sums).
+// By Cauchy-Schwarz every entry (real or imaginary) is below 2^122 <= prod p / 4 in magnitude, so nothing overflows
+// whatever the data, and the only errors are the roundings of the operands (at most 1/2 in integers of norm 2^60 ... 2^61,
+// 2^-61.3 |a| |b| per entry in the mean square at most) and one rounding of the result. They are relative to the norms,
+// where those of an FP64 product follow sum |a_k b_k|: a chain of K / 4 FP64 MFMAs leaves about 2^-53 0.3 sqrt(chain / K)
+// |a| |b| (chain: the K range that one accumulator sums) where the two vectors overlap, and less where they do not. A
+// column of B therefore takes this route only if sum_k |a_k b_k| >= kRnsOverlap |a| |b| for every row a, which the
+// envelope env_k = min over the rows of |a_k| / |a|, kept with A's planes, bounds from below by sum_k env_k |b_k|: its
+// error is then at most about 2^-61 / 2^-8 = 2^-53 of sum |a_k b_k|, one rounding of the sum of the magnitudes. The other
+// columns, flagged, take the FP64 product. Blocks of a plane-wave calculation pass: the envelope bounds measured 0.03 to
+// 0.27 for P^H x (the overlaps themselves 0.16 to 0.67) and 0.007 to 0.2 for P w (0.04 to 0.46), from random smooth
+// blocks to converged ones. With 15 moduli (2^57) the entries of small overlap came out less exact than from FP64.
+//
+// The scheme (residues of scaled integers, one INT8 product per modulus, Chinese remaindering) is the one that Ozaki,
+// Uchino and Imamura published as Ozaki scheme II (arXiv:2504.08009); moduli, splitting, kernels and guard are this file's.
 //
 // A complex product takes three real ones, P1 = a_r b_r, P2 = a_i b_i, P3 = (a_r + s a_i)(b_r + b_i), re = P1 - s P2,
 // im = P3 - P1 - s P2 (s = -1 for conj(a) b, 1 for a b): exact here, since everything is modulo p.
@@ -26,8 +36,8 @@ constexpr int L = kRnsMods;
 // 256, then the largest numbers below 242 that are pairwise coprime. The split leaves residues of the odd ones within
 // +-kResMax (one above (p - 1) / 2 at 241: its reduction rounds in float), and the one-step reductions of their products
 // (error at most 6) stay inside the int8 range.
-constexpr int kP[15] = {256, 241, 239, 235, 233, 229, 227, 223, 221, 217, 211, 209, 199, 197, 193};
-static_assert(L <= 15, "moduli");
+constexpr int kP[16] = {256, 241, 239, 235, 233, 229, 227, 223, 221, 217, 211, 209, 199, 197, 193, 191};
+static_assert(L <= 16, "moduli");
 
 typedef unsigned __int128 u128;
 constexpr u128 rns_modulus() {
@@ -52,7 +62,7 @@ constexpr bool rns_coprime() {
 static_assert(rns_coprime(), "moduli must be pairwise coprime");
 // operand norms: 2^kNormExp per operand, twice that two bits below M
 constexpr int kNormExp = (rns_bits() - 1 - 2) / 2;
-static_assert(kNormExp <= 57, "the split takes integers up to 2^57");
+static_assert(kNormExp <= 61, "the split takes integers up to 2^61");
 
 constexpr double u128_to_double(u128 v) {  // exact for values of at most 53 significant bits
   double r = 0.0, f = 1.0;
@@ -60,8 +70,9 @@ constexpr double u128_to_double(u128 v) {  // exact for values of at most 53 sig
   return r;
 }
 // Weights w_l = (M / p_l) ((M / p_l)^-1 mod p_l) of the Chinese remainder theorem in two parts of 40 bits, w1 a
-// multiple of 2^(bits - 40) and w2 of 2^(bits - 80); the rest (below 2^(bits - 80)) is some 2^-8 of the rounding error
-// of the operands. Sums of kRnsMods such parts times residues (at most 384 in magnitude) are exact in FP64.
+// multiple of 2^(bits - 40) and w2 of 2^(bits - 80). What is left out (below 2^45 per weight, 2^57.6 in a sum, of results
+// up to 2^122 |a| |b|) is a few per cent of the rounding of the operands. Sums of kRnsMods such parts times residues (at
+// most 384 in magnitude) are exact in FP64.
 struct Crt {
   double w1[L], w2[L], m1, m2, minv;
 };
@@ -90,10 +101,10 @@ constexpr int sym_mod(long long v, int p) {
   return r > p / 2 ? r - p : r;
 }
 
-struct ModTab { int p[16]; float inv[16]; int c16[16]; };  // c16 = 2^16 mod p
+struct ModTab { int p[L]; float inv[L]; int c16[L]; };  // c16 = 2^16 mod p
 constexpr ModTab make_tab() {
   ModTab t{};
-  for (int l = 0; l < 15; ++l) { t.p[l] = kP[l]; t.inv[l] = 1.0f / float(kP[l]); t.c16[l] = sym_mod(1 << 16, kP[l]); }
+  for (int l = 0; l < L; ++l) { t.p[l] = kP[l]; t.inv[l] = 1.0f / float(kP[l]); t.c16[l] = sym_mod(1 << 16, kP[l]); }
   return t;
 }
 __constant__ ModTab kTab = make_tab();
@@ -123,73 +134,135 @@ __device__ __forceinline__ unsigned pack4(unsigned a, unsigned b, unsigned c, un
 }
 
 // ---- scales ------------------------------------------------------------------------------------------------
-// A vector of norm f 2^x (f in [1/2, 1)) is scaled by 2^(kNormExp - x). flag[0] = 1 for a vector with a NaN or Inf,
-// or whose largest entry is not 0 and outside [1e-130, 1e130]: its product is left to the FP64 matrix cores.
-__device__ __forceinline__ void set_scale(double ss, double mx, double* scale, double* inv, int* flag) {
+// A vector of norm f 2^x (f in [1/2, 1)) is scaled by 2^(kNormExp - x). Returns whether it is fit for the integers: not
+// one with a NaN or Inf, or whose largest entry is not 0 and outside [1e-130, 1e130].
+__device__ __forceinline__ bool set_scale(double ss, double mx, double* scale, double* inv) {
   const bool zero = mx == 0.0 && ss == 0.0;
   const bool ok = zero || (mx >= 1e-130 && mx <= 1e130 && ss < 1e300);
-  if (!ok) *flag = 1;
   int x = 0;
   if (ok && !zero) (void)frexp(sqrt(ss), &x);
   *scale = ldexp(1.0, kNormExp - x);
   *inv = ldexp(1.0, x - kNormExp);
+  return ok;
 }
+// 1 / norm, 0 for a vector of zeros (which the envelopes leave out)
+__device__ __forceinline__ double rnorm_of(double ss) { return ss > 0.0 ? 1.0 / sqrt(ss) : 0.0; }
 
+// flag[n] = 1 for a column that is not fit or, with env, whose overlap with some row of A may be below kRnsOverlap (the
+// larger component stands for the modulus); *any = 1 if one is. Bound by memory; env stays in L2.
 constexpr int NST = 1024;
 template <typename E>
-__global__ __launch_bounds__(NST) void k_rns_colnorm(long K, const cx<E>* __restrict__ B, long ldb, double* scale,
-                                                     double* inv, int* flag) {
-  __shared__ double rs[NST / 64], rm[NST / 64];
+__global__ __launch_bounds__(NST) void k_rns_colnorm(long K, const cx<E>* __restrict__ B, long ldb,
+                                                     const double* __restrict__ env, double* scale, double* inv,
+                                                     double* rnorm, int* flag, int* any) {
+  __shared__ double rs[NST / 64], rm[NST / 64], ro[NST / 64];
   const cx<E>* col = B + long(blockIdx.x) * ldb;
-  double ss = 0.0, mx = 0.0;
+  double ss = 0.0, mx = 0.0, ov = 0.0;
   for (long i = threadIdx.x; i < K; i += NST) {
     const cx<E> v = col[i];
-    const double x = double(v.x), y = double(v.y);
+    const double x = fabs(double(v.x)), y = fabs(double(v.y)), m = fmax(x, y);
     ss += x * x + y * y;
-    mx = fmax(mx, fmax(fabs(x), fabs(y)));
+    mx = fmax(mx, m);
+    if (env) ov = fma(env[i], m, ov);
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) { ss += __shfl_xor(ss, o, 64); mx = fmax(mx, __shfl_xor(mx, o, 64)); }
-  if ((threadIdx.x & 63) == 0) { rs[threadIdx.x >> 6] = ss; rm[threadIdx.x >> 6] = mx; }
+  for (int o = 32; o > 0; o >>= 1) {
+    ss += __shfl_xor(ss, o, 64);
+    mx = fmax(mx, __shfl_xor(mx, o, 64));
+    ov += __shfl_xor(ov, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) { rs[threadIdx.x >> 6] = ss; rm[threadIdx.x >> 6] = mx; ro[threadIdx.x >> 6] = ov; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < NST / 64; ++w) { ss += rs[w]; mx = fmax(mx, rm[w]); }
-    set_scale(ss, mx, scale + blockIdx.x, inv + blockIdx.x, flag);
+    for (int w = 1; w < NST / 64; ++w) { ss += rs[w]; mx = fmax(mx, rm[w]); ov += ro[w]; }
+    const int n = blockIdx.x;
+    bool ok = set_scale(ss, mx, scale + n, inv + n);
+    if (env && mx != 0.0) ok = ok && ov >= kRnsOverlap * sqrt(ss);
+    if (rnorm) rnorm[n] = rnorm_of(ss);
+    if (flag) flag[n] = ok ? 0 : 1;
+    if (any && !ok) *any = 1;
   }
 }
 
-// rows of an M x K matrix stored with the rows contiguous: one thread per row
+// rows of an M x K matrix stored with the rows contiguous: one thread per row; with the columns' 1 / norms also the
+// columns' envelope, env[m] = min_k |A[m][k]| / |column k|
 template <typename E>
 __global__ __launch_bounds__(256) void k_rns_rownorm(long M, int K, const cx<E>* __restrict__ A, long lda,
-                                                     double* scale, double* inv, int* flag) {
+                                                     double* scale, double* inv, double* rnorm,
+                                                     const double* __restrict__ cnorm, double* env, int* any) {
   const long m = long(blockIdx.x) * 256 + threadIdx.x;
   if (m >= M) return;
-  double ss = 0.0, mx = 0.0;
+  double ss = 0.0, mx = 0.0, lo = 1.0;
 #pragma unroll 8
   for (int k = 0; k < K; ++k) {
     const cx<E> v = A[m + long(k) * lda];
-    const double x = double(v.x), y = double(v.y);
-    ss += x * x + y * y;
+    const double x = double(v.x), y = double(v.y), q = x * x + y * y, c = cnorm[k];
+    ss += q;
     mx = fmax(mx, fmax(fabs(x), fabs(y)));
+    lo = c > 0.0 ? fmin(lo, q * c * c) : lo;
   }
-  set_scale(ss, mx, scale + m, inv + m, flag);
+  if (!set_scale(ss, mx, scale + m, inv + m)) *any = 1;
+  rnorm[m] = rnorm_of(ss);
+  env[m] = sqrt(lo);
+}
+// the rows' envelope, env[k] = min_m |A[m][k]| / |row m|: one block per column
+template <typename E>
+__global__ __launch_bounds__(NST) void k_rns_rowenv(long M, const cx<E>* __restrict__ A, long lda,
+                                                    const double* __restrict__ rnorm, double* env) {
+  __shared__ double red[NST / 64];
+  const cx<E>* col = A + long(blockIdx.x) * lda;
+  double lo = 1.0;
+  for (long m = threadIdx.x; m < M; m += NST) {
+    const cx<E> v = col[m];
+    const double x = double(v.x), y = double(v.y), c = rnorm[m];
+    lo = c > 0.0 ? fmin(lo, (x * x + y * y) * c * c) : lo;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) lo = fmin(lo, __shfl_xor(lo, o, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = lo;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < NST / 64; ++w) lo = fmin(lo, red[w]);
+    env[blockIdx.x] = sqrt(lo);
+  }
+}
+// the overlap that an envelope leaves a vector of K equal entries
+__global__ __launch_bounds__(NST) void k_rns_flat(long K, const double* __restrict__ env, double* out) {
+  __shared__ double red[NST / 64];
+  double s = 0.0;
+  for (long k = threadIdx.x; k < K; k += NST) s += env[k];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < NST / 64; ++w) s += red[w];
+    *out = s / sqrt(double(K));
+  }
 }
 
 // ---- operands to residues ------------------------------------------------------------------------------------
-// y = d2 2^40 + d1 2^22 + d0 with |d2|, |d1| <= 2^17, |d0| <= 2^21 for |y| <= 2^57, y rounded to an integer
-struct Digits { int d2, d1, d0; };
+// y = d3 2^48 + d2 2^32 + d1 2^16 + d0 with |d3| <= 2^13 and |d2|, |d1|, |d0| <= 2^15 for |y| <= 2^61, y rounded to an
+// integer: sums of digits times residues stay exact as floats
+struct Digits { int d3, d2, d1, d0; };
 __device__ __forceinline__ Digits digits(double y) {
-  const double h = rint(y * 0x1p-40);
-  const double r = fma(-h, 0x1p40, y);
-  const double g = rint(r * 0x1p-22);
-  return {int(h), int(g), int(rint(fma(-g, 0x1p22, r)))};
+  const double h = rint(y * 0x1p-48);
+  const double r = fma(-h, 0x1p48, y);
+  const double g = rint(r * 0x1p-32);
+  const double q = fma(-g, 0x1p32, r);
+  const double f = rint(q * 0x1p-16);
+  return {int(h), int(g), int(f), int(rint(fma(-f, 0x1p16, q)))};
 }
 // residues modulo kP[l] of NV complex integers, as bytes packed by four: re, im and the sums re + im, re - im (each
-// third plane only where asked for). |d2 c2 + d1 c1 + d0| <= split_max, of which one step leaves at most kResMax modulo
-// the odd numbers (p / 2 + 4 by the bound of mod_step; over every such integer the largest is 121, modulo 241).
+// third plane only where asked for). |sum of digits times powers| <= split_max < 2^24, of which one step leaves at most
+// kResMax modulo the odd numbers (p / 2 + 1/2 + 2^-24 split_max: 121 modulo 241).
 constexpr int split_max(int p) {
-  const int c2 = sym_mod(1ll << 40, p), c1 = sym_mod(1ll << 22, p);
-  return ((c2 < 0 ? -c2 : c2) + (c1 < 0 ? -c1 : c1)) * (1 << 17) + (1 << 21);
+  int s = 1 << 15;
+  for (int e = 1; e < 4; ++e) {
+    const int c = sym_mod(1ll << (16 * e), p);
+    s += (c < 0 ? -c : c) * (1 << (e == 3 ? 13 : 15));
+  }
+  return s;
 }
 constexpr int kResMax = 121;
 template <int NV, bool SUM, bool DIFF>
@@ -197,7 +270,7 @@ __device__ __forceinline__ void residues(int l, const Digits (&re)[NV], const Di
                                          unsigned (&pi)[NV / 4], unsigned (&ps)[NV / 4], unsigned (&pd)[NV / 4]) {
   const int p = kP[l];
   const float inv = 1.0f / float(p);
-  const int c2 = sym_mod(1ll << 40, p), c1 = sym_mod(1ll << 22, p);
+  const int c3 = sym_mod(1ll << 48, p), c2 = sym_mod(1ll << 32, p), c1 = sym_mod(1ll << 16, p);
 #pragma unroll
   for (int g = 0; g < NV / 4; ++g) {
     int r[4], i[4];
@@ -205,8 +278,8 @@ __device__ __forceinline__ void residues(int l, const Digits (&re)[NV], const Di
     for (int j = 0; j < 4; ++j) {
       const Digits& a = re[4 * g + j];
       const Digits& b = im[4 * g + j];
-      r[j] = mod_step(mul24(a.d2, c2) + mul24(a.d1, c1) + a.d0, p, inv);
-      i[j] = mod_step(mul24(b.d2, c2) + mul24(b.d1, c1) + b.d0, p, inv);
+      r[j] = mod_step(mul24(a.d3, c3) + mul24(a.d2, c2) + mul24(a.d1, c1) + a.d0, p, inv);
+      i[j] = mod_step(mul24(b.d3, c3) + mul24(b.d2, c2) + mul24(b.d1, c1) + b.d0, p, inv);
     }
     pr[g] = pack4(unsigned(r[0]), unsigned(r[1]), unsigned(r[2]), unsigned(r[3]));
     pi[g] = pack4(unsigned(i[0]), unsigned(i[1]), unsigned(i[2]), unsigned(i[3]));
@@ -220,23 +293,24 @@ __device__ __forceinline__ void residues(int l, const Digits (&re)[NV], const Di
 }
 
 // Vectors contiguous along k (columns of B, columns of A under a conjugate transpose): 4 k per thread, so a wave
-// reads 4 KB and writes 256 bytes of each plane. Bound by memory: 16 bytes read, 3 kRnsMods written per element.
+// reads 4 KB and writes 256 bytes of each plane. Bound by memory: 16 bytes read, 3 kRnsMods written per element. A column
+// n with flag[n fs] set is written as zeros.
 template <typename E, bool SUM, bool DIFF>
 __global__ __launch_bounds__(256) void k_rns_split(long K, const cx<E>* __restrict__ B, long ldb,
                                                    const double* __restrict__ scale, int8_t* __restrict__ base,
                                                    int8_t* __restrict__ sum, int8_t* __restrict__ diff, long plane,
-                                                   long ld, const int* __restrict__ flag) {
-  if (*flag) return;
+                                                   long ld, const int* __restrict__ flag, int fs) {
   const long k = (long(blockIdx.x) * 256 + threadIdx.x) * 4;
   const long n = blockIdx.y;
   if (k >= ld) return;
   const double s = scale[n];
+  const bool fit = flag[n * fs] == 0;
   const cx<E>* col = B + n * ldb;
   Digits re[4], im[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const cx<E> v = col[min(k + j, K - 1)];
-    const bool in = k + j < K;
+    const bool in = fit && k + j < K;
     re[j] = digits(in ? double(v.x) * s : 0.0);
     im[j] = digits(in ? double(v.y) * s : 0.0);
   }
@@ -316,13 +390,16 @@ __global__ __launch_bounds__(256, 1) void k_rns_gemm(int M, int N, int nt, RnsOp
                                                      int8_t* __restrict__ C, long ldc, long zc, int upper,
                                                      const int* __restrict__ flag) {
   __shared__ __align__(16) int8_t S0[kStageBytes], S1[kStageBytes];
-  if (*flag) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tm = (M + RT - 1) / RT, tn = (N + RT - 1) / RT;
   // one contiguous run of tiles per XCD, the N tile fastest: the blocks an XCD holds at once share their operands in L2
   int bx, by, z;
   gemm_tile_of(blockIdx.x, gridDim.x, tm, tn, upper ? kUpperTiles : 1, bx, by, z);
   const int m0 = bx * RT, n0 = by * RT, l = z / 3, c3 = z - 3 * l;
+  bool some = false;  // a column of the tile takes this route
+#pragma unroll
+  for (int i = 0; i < RT; i += 64) some = some || (n0 + i + lane < N && flag[n0 + i + lane] == 0);
+  if (!__any(some)) return;
   const int8_t* Az = c3 < 2 ? A.base + (2 * l + c3) * A.plane : A.third + l * A.third_plane;
   const int8_t* Bz = c3 < 2 ? B.base + (2 * l + c3) * B.plane : B.third + l * B.third_plane;
 
@@ -459,8 +536,8 @@ __global__ __launch_bounds__(256) void k_rns_finish(int M, int N, const int8_t* 
                                                     const double* __restrict__ ia, const double* __restrict__ ib,
                                                     int sg, int upper, Epi<EO> epi, const int* __restrict__ flag) {
   __shared__ c128 buf[1024];
-  if (*flag) return;
   const long mb = long(blockIdx.x) * 1024, n = blockIdx.y;
+  if (flag[n]) return;
   if (upper && mb / RT > n / RT) return;
   const int t = threadIdx.x;
   const long m4 = mb + 4 * t;
@@ -511,7 +588,7 @@ int rns_residue_largest(int l, int x0, int x1) {
 void rns_residue_limits(int* modulus, int l, int* sum, int* residue) {
   *modulus = kP[l];
   *sum = split_max(kP[l]);
-  *residue = kP[l] % 2 ? kResMax : 128 + 4;
+  *residue = kP[l] % 2 ? kResMax : 128;
 }
 
 // Microseconds of both routes, from what they measured: the FP64 tiles at 60 TFLOP/s executed on whole 64 x 64 tiles
@@ -537,37 +614,49 @@ bool rns_pays(int M, int N, int K) {
 }
 
 template <typename E>
-hipError_t rns_scale_cols(long K, int N, const cx<E>* B, long ldb, double* scale, double* inv, int* flag,
-                          hipStream_t st) {
+hipError_t rns_scale_cols(long K, int N, const cx<E>* B, long ldb, const double* env, double* scale, double* inv,
+                          double* rnorm, int* flag, int* any, hipStream_t st) {
   if (N <= 0) return hipSuccess;
-  hipLaunchKernelGGL((k_rns_colnorm<E>), dim3(N), dim3(NST), 0, st, K, B, ldb, scale, inv, flag);
+  hipLaunchKernelGGL((k_rns_colnorm<E>), dim3(N), dim3(NST), 0, st, K, B, ldb, env, scale, inv, rnorm, flag, any);
   return hipGetLastError();
 }
 
 template <typename E>
-hipError_t rns_scale_rows(long M, int K, const cx<E>* A, long lda, double* scale, double* inv, int* flag,
-                          hipStream_t st) {
+hipError_t rns_scale_rows(long M, int K, const cx<E>* A, long lda, double* scale, double* inv, double* rnorm,
+                          const double* cnorm, double* env, int* any, hipStream_t st) {
   if (M <= 0) return hipSuccess;
   hipLaunchKernelGGL((k_rns_rownorm<E>), dim3(unsigned((M + 255) / 256)), dim3(256), 0, st, M, K, A, lda, scale, inv,
-                     flag);
+                     rnorm, cnorm, env, any);
+  return hipGetLastError();
+}
+
+template <typename E>
+hipError_t rns_row_envelope(long M, int K, const cx<E>* A, long lda, const double* rnorm, double* env, hipStream_t st) {
+  if (K <= 0) return hipSuccess;
+  hipLaunchKernelGGL((k_rns_rowenv<E>), dim3(K), dim3(NST), 0, st, M, A, lda, rnorm, env);
+  return hipGetLastError();
+}
+
+hipError_t rns_flat_overlap(long K, const double* env, double* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_rns_flat, dim3(1), dim3(NST), 0, st, K, env, out);
   return hipGetLastError();
 }
 
 template <typename E>
 hipError_t rns_split_cols(long K, int N, const cx<E>* B, long ldb, const double* scale, int8_t* base, int8_t* sum,
-                          int8_t* diff, long plane, long ld, const int* flag, hipStream_t st) {
+                          int8_t* diff, long plane, long ld, const int* flag, int fs, hipStream_t st) {
   if (N <= 0) return hipSuccess;
   if (K <= 0 || N > 65535 || ld != rns_ld(K) || plane < N * ld || !(sum || diff)) return hipErrorInvalidValue;
   const dim3 grid(unsigned((ld / 4 + 255) / 256), unsigned(N));
   if (sum && diff)
     hipLaunchKernelGGL((k_rns_split<E, true, true>), grid, dim3(256), 0, st, K, B, ldb, scale, base, sum, diff, plane,
-                       ld, flag);
+                       ld, flag, fs);
   else if (sum)
     hipLaunchKernelGGL((k_rns_split<E, true, false>), grid, dim3(256), 0, st, K, B, ldb, scale, base, sum, diff, plane,
-                       ld, flag);
+                       ld, flag, fs);
   else
     hipLaunchKernelGGL((k_rns_split<E, false, true>), grid, dim3(256), 0, st, K, B, ldb, scale, base, sum, diff, plane,
-                       ld, flag);
+                       ld, flag, fs);
   return hipGetLastError();
 }
 
@@ -599,10 +688,13 @@ hipError_t rns_product(GemmMode mode, int M, int N, int K, const RnsOperand& A, 
 }
 
 #define INST(E)                                                                                                       \
-  template hipError_t rns_scale_cols<E>(long, int, const cx<E>*, long, double*, double*, int*, hipStream_t);          \
-  template hipError_t rns_scale_rows<E>(long, int, const cx<E>*, long, double*, double*, int*, hipStream_t);          \
+  template hipError_t rns_scale_cols<E>(long, int, const cx<E>*, long, const double*, double*, double*, double*, int*, \
+                                        int*, hipStream_t);                                                           \
+  template hipError_t rns_scale_rows<E>(long, int, const cx<E>*, long, double*, double*, double*, const double*,      \
+                                        double*, int*, hipStream_t);                                                  \
+  template hipError_t rns_row_envelope<E>(long, int, const cx<E>*, long, const double*, double*, hipStream_t);        \
   template hipError_t rns_split_cols<E>(long, int, const cx<E>*, long, const double*, int8_t*, int8_t*, int8_t*, long, \
-                                        long, const int*, hipStream_t);                                               \
+                                        long, const int*, int, hipStream_t);                                          \
   template hipError_t rns_split_rows<E>(long, int, const cx<E>*, long, const double*, int8_t*, int8_t*, long, long,    \
                                         const int*, hipStream_t);                                                     \
   template hipError_t rns_product<E>(GemmMode, int, int, int, const RnsOperand&, const RnsOperand&, int8_t*,          \

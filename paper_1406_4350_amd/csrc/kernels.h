@@ -32,8 +32,8 @@ enum GemmRole { ROLE_SMALL = 0, ROLE_PROJECT = 1, ROLE_BACKPROJECT = 2, ROLE_SUB
 // deterministic reduction applies the epilogue; splits == 1: the epilogue is applied directly.
 // upper = true (M = N, a Hermitian result): only the 64 x 64 output tiles with row tile <= column tile are
 // computed (the others are not written; hermitian_lower fills them), splits from gemm_upper_splits.
-// pred (device): the product is computed only where *pred is not 0 (the other route of a product that took
-// rns_product; hipErrorInvalidValue at the sizes of the small GEMM, which have no other route).
+// pred (device, N ints): only the columns n with pred[n] not 0 are computed (the others took rns_product;
+// hipErrorInvalidValue at the sizes of the small GEMM, which have no other route).
 template <typename T, typename EA, typename EB, typename EO>
 hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, const cx<EB>* B, long ldb,
                 const Epi<EO>& epi, int splits, c128* part, hipStream_t st, GemmRole role = ROLE_SMALL,
@@ -94,7 +94,7 @@ hipError_t split_planes(const c128* X, long ldx, int rows_x, int cols_x, bool tr
 // Operands as residues modulo kRnsMods coprime numbers (see gemm_rns.hip): int8 planes [2 l] (real parts) and
 // [2 l + 1] (imaginary parts) at base + i plane, the sums' (or differences') plane l at third + l third_plane; row r of a
 // plane at r ld, its K values contiguous and padded with zeros to ld = rns_ld(K). inv[r] undoes the row's scale.
-constexpr int kRnsMods = 15, kRnsKTile = 128, kRnsMaxK = 146560;
+constexpr int kRnsMods = 16, kRnsKTile = 128, kRnsMaxK = 146560;
 inline long rns_ld(long K) { return (K + kRnsKTile - 1) / kRnsKTile * kRnsKTile; }
 inline long rns_ldc(long M) { return (M + 15) / 16 * 16; }
 struct RnsOperand {
@@ -102,32 +102,42 @@ struct RnsOperand {
   const int8_t* third = nullptr;
   long plane = 0, third_plane = 0, ld = 0;
   const double* inv = nullptr;
+  const double* env = nullptr;  // A: min over its rows of |entry k| / |row|, K values
 };
+constexpr double kRnsOverlap = 1.0 / 256;  // smallest sum_k |a_k b_k| / (|a| |b|) of a column that takes the INT8 route
 // Host arithmetic, the operations of the kernels: modulus number l, the largest |integer| that its split reduces and the
 // largest |residue| that kRnsMaxK counts on; the largest |residue| left of x0 <= x < x1.
 void rns_residue_limits(int* modulus, int l, int* sum, int* residue);
 int rns_residue_largest(int l, int x0, int x1);
 // whether the INT8 matrix cores are the faster ones for an M x N x K product whose A is already split
 bool rns_pays(int M, int N, int K);
-// Power-of-two scales of the columns (K x N, ldb) or rows (M x K, lda) of a matrix and their inverses; *flag = 1 (else
-// untouched) if a vector is not fit for the integers (NaN, Inf, entries beyond 1e+-130): every rns call below then
-// returns without effect, and the product is left to gemm() with pred = flag.
+// Power-of-two scales of the columns (K x N, ldb) and their inverses, and where asked for 1 / norms (0 for a column of
+// zeros), flag[n] = 1 (else 0) for a column not fit for the integers (NaN, Inf, entries beyond 1e+-130) or, with A's
+// envelope, of too small an overlap with A's rows; *any = 1 (else untouched) if one is not. rns_product leaves flagged
+// columns to gemm() with pred = flag.
 template <typename E>
-hipError_t rns_scale_cols(long K, int N, const cx<E>* B, long ldb, double* scale, double* inv, int* flag,
-                          hipStream_t st);
+hipError_t rns_scale_cols(long K, int N, const cx<E>* B, long ldb, const double* env, double* scale, double* inv,
+                          double* rnorm, int* flag, int* any, hipStream_t st);
+// the same of the rows (M x K, lda), with the envelope of the columns, whose 1 / norms are cnorm, over the rows
 template <typename E>
-hipError_t rns_scale_rows(long M, int K, const cx<E>* A, long lda, double* scale, double* inv, int* flag,
-                          hipStream_t st);
+hipError_t rns_scale_rows(long M, int K, const cx<E>* A, long lda, double* scale, double* inv, double* rnorm,
+                          const double* cnorm, double* env, int* any, hipStream_t st);
+// the envelope of the rows over the columns; the overlap that an envelope leaves a vector of K equal entries
+template <typename E>
+hipError_t rns_row_envelope(long M, int K, const cx<E>* A, long lda, const double* rnorm, double* env, hipStream_t st);
+hipError_t rns_flat_overlap(long K, const double* env, double* out, hipStream_t st);
 // Residue planes of scaled columns (row n of a plane = column n; base null: not written) with the sums re + im, the
-// differences re - im or both (null: not written), and of scaled rows (row m = row m) with the sums.
+// differences re - im or both (null: not written), zeros for a column n with flag[n fs] set, and of scaled rows (row m =
+// row m) with the sums (nothing if *flag is set).
 template <typename E>
 hipError_t rns_split_cols(long K, int N, const cx<E>* B, long ldb, const double* scale, int8_t* base, int8_t* sum,
-                          int8_t* diff, long plane, long ld, const int* flag, hipStream_t st);
+                          int8_t* diff, long plane, long ld, const int* flag, int fs, hipStream_t st);
 template <typename E>
 hipError_t rns_split_rows(long M, int K, const cx<E>* A, long lda, const double* scale, int8_t* base, int8_t* sum,
                           long plane, long ld, const int* flag, hipStream_t st);
 // out (M x N) = conj(A)^T B (GEMM_CN, A's third planes the differences) or A B (GEMM_NN, the sums; B's always the
-// sums) with the epilogue of gemm(); upper as there. C: 3 kRnsMods N rns_ldc(M) bytes of scratch. N <= 65535.
+// sums) with the epilogue of gemm(), the columns with flag[n] set left alone; upper as there. C: 3 kRnsMods N rns_ldc(M)
+// bytes of scratch. N <= 65535.
 template <typename EO>
 hipError_t rns_product(GemmMode mode, int M, int N, int K, const RnsOperand& A, const RnsOperand& B, int8_t* C,
                        const Epi<EO>& epi, bool upper, const int* flag, hipStream_t st);
