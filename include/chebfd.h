@@ -93,7 +93,7 @@ typedef struct {
 
 /* Size in bytes of the device buffer a plan keeps for its lifetime (index maps, twiddles, V(r), P, D, Q,
  * P^H P, capacitance inverse; in FP64 plans whose projector products run on the INT8 matrix cores also the residue
- * planes of P, 96 bytes per entry, up to 64 GiB). */
+ * planes of P, 48 bytes per entry for each of the two products that does, up to 64 GiB). */
 cheb_status cheb_plan_persistent_bytes(const cheb_desc* desc, size_t* bytes);
 
 /* Create a plan over a caller-provided device buffer of at least cheb_plan_persistent_bytes bytes
@@ -325,6 +325,12 @@ cheb_status cheb_gemm_splits(int M, int N, int K, int* fp64, int* fp16, int* bou
  * arithmetic only. CHEB_ERR_ARG unless 0 <= i < total, total a multiple of the tiles per split (tm * tn, or
  * tm (tm + 1) / 2 for group -1) > 0, group >= 1 or -1 and the pointers non-null. */
 cheb_status cheb_gemm_block_item(int i, int total, int tm, int tn, int group, int* bx, int* by, int* bz);
+
+/* Route of a projector product of an FP64 plan, host arithmetic only: the estimated times (us) of the M x N x K product
+ * P^H x (back = 0: M projectors, K plane waves) or P w with its vector epilogue (back = 1: M plane waves, K projectors)
+ * over N bands on the FP64 and on the INT8 matrix cores, and *int8 = 1 if the INT8 ones are taken (by plans that hold the
+ * planes of that product: those where it pays at some width up to 1024 bands). CHEB_ERR_ARG for a null pointer. */
+cheb_status cheb_product_route(int M, int N, int K, int back, int* int8, double* us_fp64, double* us_int8);
 
 /* Residue arithmetic of the INT8 projector products, host arithmetic only (the operations of the kernels): for modulus
  * number l (0 <= l < *count), its value, the largest integer magnitude *sum that the split of an operand reduces modulo

@@ -36,7 +36,7 @@ SYMBOLS = ["cheb_plan_persistent_bytes", "cheb_plan_create", "cheb_plan_destroy"
            "cheb_set_capacitance_solver", "cheb_lobpcg_state_bytes", "cheb_lobpcg_iterate", "cheb_gemm_splits",
            "cheb_gemm_block_item", "cheb_set_projection_resync", "cheb_drift_monitor", "cheb_drift_read",
            "cheb_apply_H_noalloc", "cheb_filter_carry", "cheb_rayleigh_ritz_carry", "cheb_residue_limits",
-           "cheb_last_error"]
+           "cheb_product_route", "cheb_last_error"]
 TIMERS = ["fft_col_inverse", "fft_plane", "fft_col_forward", "project", "backproject", "small", "rr_gram", "rr_eig",
           "rr_rotate", "xdens"]
 
@@ -98,6 +98,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "cheb_locking_degrees": [i, vp, vp, d, d, i, d, vp, P(i)],
         "cheb_gemm_splits": [i, i, i, P(i), P(i), P(i)],
         "cheb_gemm_block_item": [i, i, i, i, i, P(i), P(i), P(i)],
+        "cheb_product_route": [i, i, i, i, P(i), P(d), P(d)],
         "cheb_residue_limits": [i, i, i, P(i), P(i), P(i), P(i), P(i), P(i)],
         "cheb_set_projection_resync": [vp, i],
         "cheb_apply_H_noalloc": [vp, vp, i, vp, i, i, vp],

@@ -217,14 +217,19 @@ struct Persist {
 
 inline long pad32(long k) { return (k + 31) / 32 * 32; }
 
-// Whether a plan holds the residue planes of its projectors: FP64 plans whose products over 1024 bands pay on the INT8
-// matrix cores, up to 64 GiB of planes (96 bytes per entry of P; 44 GB of the GPU's 288 at 137 065 x 3328). Gamma
-// plans take one or two real products per complex one instead of three and stay on the FP64 matrix cores.
+// Which residue planes of its projectors a plan holds, for P^H x and for P w: FP64 plans, each product by itself if it pays
+// on the INT8 matrix cores at some width up to 1024 bands, up to 64 GiB of planes (48 bytes per entry of P and product; 44
+// GB of the GPU's 288 at 137 065 x 3328). Gamma plans take one or two real products per complex one instead of three and
+// stay on the FP64 matrix cores.
 constexpr size_t kRnsPlaneCap = size_t(64) << 30;
-bool rns_planned(int npw, int nproj, int prec, int gamma) {
-  if (prec != CHEB_FP64 || gamma || nproj <= 0) return false;
-  if (!rns_pays(nproj, 1024, npw) && !rns_pays(npw, 1024, nproj)) return false;
-  return 3 * kRnsMods * (size_t(nproj) * rns_ld(npw) + size_t(npw) * rns_ld(nproj)) <= kRnsPlaneCap;
+struct RnsPlanned { bool proj = false, back = false; };
+RnsPlanned rns_planned(int npw, int nproj, int prec, int gamma) {
+  RnsPlanned r;
+  if (prec != CHEB_FP64 || gamma || nproj <= 0) return r;
+  r.proj = rns_pays_some(nproj, kRnsChunk, npw, false);
+  r.back = rns_pays_some(npw, kRnsChunk, nproj, true);
+  const size_t bytes = 3 * kRnsMods * ((r.proj ? size_t(nproj) * rns_ld(npw) : 0) + (r.back ? size_t(npw) * rns_ld(nproj) : 0));
+  return bytes <= kRnsPlaneCap ? r : RnsPlanned{};
 }
 
 // Carves the persistent buffer (base == nullptr: only measures)
@@ -255,12 +260,15 @@ Persist persist_layout(void* base, int n, int npw, int npf, int ncol, int rx, in
   }
   l.Rproj = l.Rback = nullptr;
   l.Rpinv = l.Rbinv = l.Rpenv = l.Rbenv = nullptr;
-  if (rns_planned(npw, nproj, prec, gamma)) {
+  const RnsPlanned rns = rns_planned(npw, nproj, prec, gamma);
+  if (rns.proj) {
     l.Rproj = b.take<int8_t>(3 * kRnsMods * size_t(nproj) * rns_ld(npw));
-    l.Rback = b.take<int8_t>(3 * kRnsMods * size_t(npw) * rns_ld(nproj));
     l.Rpinv = b.take<double>(nproj);
-    l.Rbinv = b.take<double>(npw);
     l.Rpenv = b.take<double>(npw);
+  }
+  if (rns.back) {
+    l.Rback = b.take<int8_t>(3 * kRnsMods * size_t(npw) * rns_ld(nproj));
+    l.Rbinv = b.take<double>(npw);
     l.Rbenv = b.take<double>(nproj);
   }
   l.gmap = gamma ? b.take<int>(npf) : nullptr;
@@ -286,15 +294,7 @@ size_t upper_part_elems(int N, int K) {
   return s > 1 ? size_t(s) * N * N : 0;
 }
 
-// Columns taken at a time by a product on the INT8 matrix cores, whose residue planes (48 bytes per complex entry of
-// the operand and of the result) are scratch: about equal pieces of at most kRnsChunk columns, whole tiles of 256.
-constexpr int kRnsChunk = 1024;
-constexpr int kRnsGramChunk = 512;  // and by P^H P, whose set-up has no other large scratch
-long rns_chunk(int nb) {
-  const long pieces = (nb + kRnsChunk - 1) / kRnsChunk;
-  const long per = (nb + pieces - 1) / pieces;
-  return std::min<long>(nb, (per + 255) / 256 * 256);
-}
+constexpr int kRnsGramChunk = 512;  // columns taken at a time by P^H P, whose set-up has no other large scratch
 
 // Scratch of the FFT passes: two disk-column buffers for a batch of bands.
 struct FftWs { void* a; void* b; void* ga = nullptr; void* gb = nullptr; };  // ga, gb: Gamma band pairs
@@ -325,9 +325,10 @@ struct Ws {
   double* dcol = nullptr;  // per-band relative drift
   // products on the INT8 matrix cores: flags, scales and inverse scales of the columns of the call's operand, its residue
   // planes, the products' planes (both for at most kRnsChunk columns at a time; null where no product of the call takes
-  // them). Set-up: rflag[0] for P unfit, rflag[1] and columns from rflag[2] for P^H P, 1 / norms of P's columns (rinv) and rows (rrow), rflat
+  // them). Set-up: rflag[0] for P unfit, rflag[1] and columns from rflag[2] for P^H P, 1 / norms of P's columns (rinv) and
+  // rows (rrow), overlaps of flat vectors, outputs of a pass that are not wanted (rspare)
   int* rflag = nullptr;
-  double *rscale = nullptr, *rinv = nullptr, *rrow = nullptr, *rflat = nullptr;
+  double *rscale = nullptr, *rinv = nullptr, *rrow = nullptr, *rflat = nullptr, *rspare = nullptr;
   int8_t *rB = nullptr, *rC = nullptr;
   size_t rB_bytes = 0, rC_bytes = 0;
   void* Xs = nullptr;   // band-sorted copy for the per-band degree filter
@@ -358,6 +359,11 @@ int fft_batch_for(const cheb_plan_s* p, int nb) {
 }
 
 cheb_status solver_query(cheb_plan p, int op, int nb, size_t* bytes);
+
+// whether P^H P takes the INT8 matrix cores, by pieces
+bool rns_gram(const cheb_plan_s* p) {
+  return p->rproj.base && rns_pays(p->nproj, std::min(p->nproj, kRnsGramChunk), p->npw, false);
+}
 
 cheb_status ws_layout(cheb_plan p, int op, int nb, void* base, Ws* w) {
   Bump b(base);
@@ -491,16 +497,19 @@ cheb_status ws_layout(cheb_plan p, int op, int nb, void* base, Ws* w) {
     case CHEB_OP_SETUP: {
       w->Hs = b.take<c128>(size_t(std::max(np, 1)) * std::max(np, 1));  // staging of C
       w->flags = b.take<int>(4);
-      if (p->rproj.base) {
-        // scales, the flag, and for P^H P the sums of a piece of the projectors and its product's planes
-        const size_t n = size_t(std::min(np, kRnsGramChunk));
+      if (p->rproj.base || p->rback.base) {
+        // scales, the flags, and for P^H P the sums of a piece of the projectors and its product's planes
         w->rflag = b.take<int>(size_t(np) + 2);
         w->rscale = b.take<double>(std::max(np, p->npw));
         w->rinv = b.take<double>(np);
         w->rrow = b.take<double>(p->npw);
+        w->rspare = b.take<double>(std::max(np, p->npw));
         w->rflat = b.take<double>(2);
-        w->rB = b.take<int8_t>(kRnsMods * n * rns_ld(p->npw));
-        w->rC = b.take<int8_t>(3 * kRnsMods * n * rns_ldc(np));
+        if (rns_gram(p)) {
+          const size_t n = size_t(std::min(np, kRnsGramChunk));
+          w->rB = b.take<int8_t>(kRnsMods * n * rns_ld(p->npw));
+          w->rC = b.take<int8_t>(3 * kRnsMods * n * rns_ldc(np));
+        }
       }
       part = part_elems(np, np, p->npw);
       CHK(solver_query(p, CHEB_OP_SETUP, np, &w->solver_bytes));
@@ -525,14 +534,14 @@ cheb_status ws_layout(cheb_plan p, int op, int nb, void* base, Ws* w) {
     w->cq = b.take<c128>(pp);
     w->cr = b.take<c128>(pp);
   }
-  if (p->rproj.base && op != CHEB_OP_SETUP && op != CHEB_OP_BOUND) {
+  if ((p->rproj.base || p->rback.base) && op != CHEB_OP_SETUP && op != CHEB_OP_BOUND) {
     const size_t before = b.off;
     const size_t n = size_t(rns_chunk(std::max(nb, 1)));
-    if (rns_pays(np, nb, p->npw)) {
+    if (p->rproj.base && rns_pays(np, nb, p->npw, false)) {
       w->rB_bytes = 3 * kRnsMods * n * rns_ld(p->npw);
       w->rC_bytes = 3 * kRnsMods * n * rns_ldc(np);
     }
-    if (rns_pays(p->npw, nb, np)) {
+    if (p->rback.base && rns_pays(p->npw, nb, np, true)) {
       w->rB_bytes = std::max<size_t>(w->rB_bytes, 3 * kRnsMods * n * rns_ld(np));
       w->rC_bytes = std::max<size_t>(w->rC_bytes, 3 * kRnsMods * n * rns_ldc(p->npw));
     }
@@ -791,7 +800,8 @@ template <typename T> struct Ops {
   // which is laid out for the call's widest block, holds its planes (a narrower block of the same call takes the FP64
   // product where the wide one did not need the planes)
   bool use_rns(const Ws& w, bool back, int M, int nb, int K) const {
-    if (!std::is_same<T, double>::value || !w.rB || !p->rns_ok || !p->rns_flat[back] || !rns_pays(M, nb, K)) return false;
+    if (!std::is_same<T, double>::value || !w.rB || !p->rns_ok || !p->rns_flat[back]) return false;
+    if (!(back ? p->rback : p->rproj).base || !rns_pays(M, nb, K, back)) return false;
     const size_t n = size_t(rns_chunk(nb));
     return 3 * kRnsMods * n * rns_ld(K) <= w.rB_bytes && 3 * kRnsMods * n * rns_ldc(M) <= w.rC_bytes;
   }
@@ -2159,9 +2169,12 @@ cheb_status cheb_plan_create(const cheb_desc* d, void* persistent, size_t bytes,
   p->hproj.p = l.Hproj; p->hproj.rows = nproj; p->hproj.ld = pad32(d->npw);
   p->hback.p = l.Hback; p->hback.rows = d->npw; p->hback.ld = pad32(nproj);
   if (l.Rproj) {
-    const long lp = rns_ld(d->npw), lb = rns_ld(nproj);
+    const long lp = rns_ld(d->npw);
     p->rproj.base = l.Rproj; p->rproj.third = l.Rproj + 2 * kRnsMods * nproj * lp;
     p->rproj.plane = p->rproj.third_plane = nproj * lp; p->rproj.ld = lp; p->rproj.inv = l.Rpinv; p->rproj.env = l.Rpenv;
+  }
+  if (l.Rback) {
+    const long lb = rns_ld(nproj);
     p->rback.base = l.Rback; p->rback.third = l.Rback + 2 * kRnsMods * d->npw * lb;
     p->rback.plane = p->rback.third_plane = d->npw * lb; p->rback.ld = lb; p->rback.inv = l.Rbinv; p->rback.env = l.Rbenv;
   }
@@ -2378,35 +2391,41 @@ cheb_status cheb_set_projectors(cheb_plan p, const void* P, int ldp, const doubl
   // waves (with the sums)
   auto mut = [](const auto* q) { return const_cast<std::remove_const_t<std::remove_pointer_t<decltype(q)>>*>(q); };
   bool gram = false;
-  if (p->rproj.base) {
+  if (p->rproj.base || p->rback.base) {
     int unfit[2] = {0, 0};
     double flat[2] = {0.0, 0.0};
+    // one pass over the rows forms what P w's planes need and the envelope of P^H x; a plan may hold only one of them
+    double* const rinv = p->rback.base ? mut(p->rback.inv) : w.rspare;
+    double* const penv = p->rproj.base ? mut(p->rproj.env) : w.rspare;
     HIPCHK(fill_zero_real<int>(w.rflag, 2, st));
-    HIPCHK(rns_scale_cols<double>(p->npw, np, Pd, ldp, nullptr, w.rscale, mut(p->rproj.inv), w.rinv, nullptr, w.rflag, st));
-    HIPCHK(rns_scale_rows<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rback.inv), w.rrow, w.rinv, mut(p->rproj.env),
-                                  w.rflag, st));
-    HIPCHK(rns_split_rows<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rback.base), mut(p->rback.third),
-                                  p->rback.plane, p->rback.ld, w.rflag, st));
-    HIPCHK(rns_row_envelope<double>(p->npw, np, Pd, ldp, w.rrow, mut(p->rback.env), st));
-    HIPCHK(rns_scale_cols<double>(p->npw, np, Pd, ldp, p->rproj.env, w.rscale, mut(p->rproj.inv), nullptr, w.rflag + 2,
-                                  w.rflag + 1, st));
-    HIPCHK(rns_split_cols<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rproj.base), nullptr, mut(p->rproj.third),
-                                  p->rproj.plane, p->rproj.ld, w.rflag, 0, st));
-    HIPCHK(rns_flat_overlap(p->npw, p->rproj.env, w.rflat, st));
-    HIPCHK(rns_flat_overlap(np, p->rback.env, w.rflat + 1, st));
+    HIPCHK(rns_scale_cols<double>(p->npw, np, Pd, ldp, nullptr, w.rscale, w.rspare, w.rinv, nullptr, w.rflag, st));
+    HIPCHK(rns_scale_rows<double>(p->npw, np, Pd, ldp, w.rscale, rinv, w.rrow, w.rinv, penv, w.rflag, st));
+    if (p->rback.base) {
+      HIPCHK(rns_split_rows<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rback.base), mut(p->rback.third),
+                                    p->rback.plane, p->rback.ld, w.rflag, st));
+      HIPCHK(rns_row_envelope<double>(p->npw, np, Pd, ldp, w.rrow, mut(p->rback.env), st));
+      HIPCHK(rns_flat_overlap(np, p->rback.env, w.rflat + 1, st));
+    }
+    if (p->rproj.base) {
+      HIPCHK(rns_scale_cols<double>(p->npw, np, Pd, ldp, p->rproj.env, w.rscale, mut(p->rproj.inv), nullptr, w.rflag + 2,
+                                    w.rflag + 1, st));
+      HIPCHK(rns_split_cols<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rproj.base), nullptr, mut(p->rproj.third),
+                                    p->rproj.plane, p->rproj.ld, w.rflag, 0, st));
+      HIPCHK(rns_flat_overlap(p->npw, p->rproj.env, w.rflat, st));
+    }
     HIPCHK(hipMemcpyAsync(unfit, w.rflag, sizeof(unfit), hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(flat, w.rflat, sizeof(flat), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     p->rns_ok = !unfit[0];
     for (int i = 0; i < 2; ++i) p->rns_flat[i] = flat[i] >= kRnsOverlap;
-    gram = p->rns_ok && !unfit[1];
+    gram = p->rns_ok && !unfit[1] && rns_gram(p);
   }
   // G = P^H P in FP64 from the caller's complex128 projectors; on the INT8 matrix cores, if every column of P is fit
   // for it, by pieces of the columns, each down to its diagonal block (3328 projectors, 137 065 plane waves: cheb_set_projectors 87 ms, planes included, instead
   // of 169; 1664 and 57 777: 20 instead of 26)
   Epi<double> eg;
   eg.out = p->G; eg.ldo = np; eg.real_only = p->gamma != 0;
-  if (gram && rns_pays(np, std::min(np, kRnsGramChunk), p->npw)) {
+  if (gram) {
     for (int n0 = 0; n0 < np; n0 += kRnsGramChunk) {
       const int cnt = std::min(kRnsGramChunk, np - n0);
       RnsOperand b = p->rproj;
@@ -2621,6 +2640,15 @@ cheb_status cheb_gemm_block_item(int i, int total, int tm, int tn, int group, in
     return CHEB_ERR_ARG;
   }
   gemm_block_item(i, total, tm, tn, group, *bx, *by, *bz);
+  return CHEB_OK;
+} catch (...) {
+  return host_fail(nullptr);
+}
+
+cheb_status cheb_product_route(int M, int N, int K, int back, int* int8, double* us_fp64, double* us_int8) try {
+  if (!int8 || !us_fp64 || !us_int8) return CHEB_ERR_ARG;
+  rns_cost(M, N, K, back != 0, us_fp64, us_int8);
+  *int8 = rns_pays(M, N, K, back != 0) ? 1 : 0;
   return CHEB_OK;
 } catch (...) {
   return host_fail(nullptr);

@@ -968,6 +968,8 @@ int gemm_pick_splits(int M, int N, int K) {
   return int(std::max<long>(s, 1));
 }
 
+bool gemm_is_small(int M, int N, int K) { return K <= SKMAX && long((M + 15) / 16) * ((N + 15) / 16) <= SBLKMAX; }
+
 template <typename T, typename EA, typename EB, typename EO>
 hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, const cx<EB>* B, long ldb,
                 const Epi<EO>& epi, int splits, c128* part, hipStream_t st, GemmRole role, bool upper,
@@ -975,8 +977,8 @@ hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, c
   if (M <= 0 || N <= 0) return hipSuccess;
   if (upper && M != N) return hipErrorInvalidValue;
   if constexpr (std::is_same<T, double>::value && std::is_same<EA, double>::value && std::is_same<EB, double>::value) {
-    const long blocks = long((M + 15) / 16) * ((N + 15) / 16);
-    if (K <= SKMAX && blocks <= SBLKMAX) {
+    if (gemm_is_small(M, N, K)) {
+      const long blocks = long((M + 15) / 16) * ((N + 15) / 16);
       if (pred) return hipErrorInvalidValue;  // too small for a product that has another route
       // K over blocks as well where few of them meet a longer K: up to a block per CU, at least 64 k each
       int s = 1;

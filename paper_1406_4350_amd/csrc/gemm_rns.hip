@@ -24,6 +24,7 @@
 // Operands arrive as int8 planes (per modulus: residues of the real parts, of the imaginary parts and of the sum),
 // K contiguous; the projectors' planes are laid out once with the plan, the other operand's per call.
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 
 #include "gemm_common.h"
@@ -591,26 +592,53 @@ void rns_residue_limits(int* modulus, int l, int* sum, int* residue) {
   *residue = kP[l] % 2 ? kResMax : 128;
 }
 
-// Microseconds of both routes, from what they measured: the FP64 tiles at 60 TFLOP/s executed on whole 64 x 64 tiles
-// (47 to 66 over the sizes below); the int8 tiles at 0.0140 us per k and 3.5 us for filling and emptying them, or the
-// A planes read once at 4.2 TB/s where few columns share them; the operand scaled and split, the results' residues read.
+// Microseconds of both routes, from what they measured. FP64: one 64 x 64 tile of a CU's takes 0.0955 us per k, the tiles
+// of a CU share its matrix cores (whole tiles per CU, from the tiles and splits that gemm() launches), then the split-K
+// partials. INT8: a 256 x 256 tile takes 0.0138 us per k and 3.5 us to fill and empty, in rounds of 256 tiles (the first
+// ones faster: few blocks leave the clock higher), or the A planes read once at 4.2 TB/s where few columns share them; the
+// operand scaled and split, the results' residues. Back-projections also read and write three operands and the result.
 //   M x N x K              FP64    INT8     (us, INT8 with the scaling, the split of B and the epilogue)
-//   3328 x 512 x 137065   21213   10446     137065 x 512 x 3328   21209   10901
-//   3328 x 128 x 137065    9255    5770     137065 x 128 x 3328    5520    5416
-//   3328 x  64 x 137065    5698    5438     137065 x  64 x 3328    3206    5133
-//   1664 x 700 x 57777     6446    3697     57777 x 700 x 1664     6292    3955
-//    832 x 512 x 57777     3793    1943     57777 x 512 x 832      2746    2066
-//    512 x 512 x 17077      481     368     17077 x 512 x 512       531     514
-//    512 x 256 x 17077      246     277     17077 x 256 x 512       291     280
-bool rns_pays(int M, int N, int K) {
-  if (M <= 0 || N <= 0 || K <= 0 || K > kRnsMaxK) return false;
-  const double m = M, n = N, k = double(rns_ld(K));
-  const double tiles = double((M + RT - 1) / RT) * double((N + RT - 1) / RT) * 3 * L;
-  const double m64 = (M + 63) / 64 * 64, n64 = (N + 63) / 64 * 64;
-  const double fp64 = 6.0 * m64 * n64 * K / 60e6;
-  const double rounds = std::max(1.0, tiles / 256 + 0.3);
-  const double gemm = std::max(rounds * (0.0140 * k + 3.5), 3.0 * L * m * k / 4.2e6);
-  return gemm + 77.0 * n * (k + m) / 4.6e6 + 20.0 < 0.9 * fp64;
+//   3328 x 512 x 137065   21987   10833     137065 x 512 x 3328   21828   12210
+//   3328 x 128 x 137065    9352    5964     137065 x 128 x 3328    5651    5956
+//   3328 x  64 x 137065    5722    5587     137065 x  64 x 3328    3229    5512
+//   1664 x 700 x 57777     6285    3912     57777 x 700 x 1664     6580    4508
+//    832 x 512 x 57777     3733    1920     57777 x 512 x 832      2639    2331
+//    512 x 448 x 17077      639     383     17077 x 448 x 512       502     545
+//    512 x 512 x 17077      417     398     17077 x 512 x 512       563     586
+//    512 x 256 x 17077      213     291     17077 x 256 x 512       310     307
+//   1024 x 512 x 7153       348     273     7153 x 512 x 1024       438     329
+// Over 230 products (2109 to 137 065 plane waves, 128 to 3328 projectors, 48 to 1024 bands) the rule takes the faster side,
+// or one within 6% of it; the estimates are within 20% of the measured times. Back-projections keep a larger margin: the
+// rule was too good to INT8 at few plane waves (7153 x 448 x 512: 229 and 259). Products of the small FP64 GEMM, whose
+// time this does not estimate, stay with it.
+void rns_cost(int M, int N, int K, bool back, double* fp64, double* int8) {
+  *fp64 = *int8 = 0.0;
+  if (M <= 0 || N <= 0 || K <= 0) return;
+  const double m = M, epi = back ? 64.0 * m * N / 4.5e6 : 0.0;
+  const long tiles = long((M + 63) / 64) * ((N + 63) / 64);
+  const int sp = back ? 1 : gemm_pick_splits(M, N, K);
+  const long kc = ((K + sp - 1) / sp + 31) / 32 * 32, s = (K + kc - 1) / kc;
+  *fp64 = double((tiles * s + 255) / 256) * (0.0955 * kc + 1.0) + (s > 1 ? 32.0 * s * m * N / 4e6 : 0.0) + epi;
+  const double k = double(rns_ld(K));
+  const long step = rns_chunk(N);
+  for (long n0 = 0; n0 < N; n0 += step) {
+    const double n = double(std::min<long>(step, N - n0));
+    const double t = double((M + RT - 1) / RT) * std::ceil(n / RT) * 3 * L;
+    *int8 += std::max(std::max(0.75, t / 256 + 0.15) * (0.0138 * k + 3.5), 3.0 * L * m * k / 4.2e6) +
+             82.0 * n * (k + m) / 4.6e6;
+  }
+  *int8 += 15.0 + epi;
+}
+bool rns_pays(int M, int N, int K, bool back) {
+  if (M <= 0 || N <= 0 || K <= 0 || K > kRnsMaxK || gemm_is_small(M, N, K)) return false;
+  double fp64, int8;
+  rns_cost(M, N, K, back, &fp64, &int8);
+  return int8 < (back ? 0.92 : 0.98) * fp64;
+}
+bool rns_pays_some(int M, int N, int K, bool back) {
+  for (int n = 64; n < N; n += 64)
+    if (rns_pays(M, n, K, back)) return true;
+  return rns_pays(M, N, K, back);
 }
 
 template <typename E>

@@ -39,6 +39,8 @@ hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, c
                 const Epi<EO>& epi, int splits, c128* part, hipStream_t st, GemmRole role = ROLE_SMALL,
                 bool upper = false, const int* pred = nullptr, GemmForm form = FORM_FULL);
 int gemm_upper_splits(int N, int K);
+// whether an FP64 product of FP64 operands takes the small GEMM (one 16 x 16 block of the result per workgroup)
+bool gemm_is_small(int M, int N, int K);
 // A[i][j] = conj(A[j][i]) for i > j (n x n, column-major)
 hipError_t hermitian_lower(int n, c128* A, long lda, hipStream_t st);
 
@@ -109,8 +111,18 @@ constexpr double kRnsOverlap = 1.0 / 256;  // smallest sum_k |a_k b_k| / (|a| |b
 // largest |residue| that kRnsMaxK counts on; the largest |residue| left of x0 <= x < x1.
 void rns_residue_limits(int* modulus, int l, int* sum, int* residue);
 int rns_residue_largest(int l, int x0, int x1);
-// whether the INT8 matrix cores are the faster ones for an M x N x K product whose A is already split
-bool rns_pays(int M, int N, int K);
+// Columns taken at a time by a product on the INT8 matrix cores, whose residue planes (48 bytes per complex entry of
+// the operand and of the result) are scratch: about equal pieces of at most kRnsChunk columns, whole tiles of 256.
+constexpr int kRnsChunk = 1024;
+inline long rns_chunk(long n) {
+  const long pieces = (n + kRnsChunk - 1) / kRnsChunk, per = (n + pieces - 1) / pieces, whole = (per + 255) / 256 * 256;
+  return n < whole ? n : whole;
+}
+// Estimated times (us) of an M x N x K product, P^H x or (back) P w with its vector epilogue, on the FP64 and on the INT8
+// matrix cores with A already split; whether INT8 is the faster, at N columns or at some width up to N
+void rns_cost(int M, int N, int K, bool back, double* fp64, double* int8);
+bool rns_pays(int M, int N, int K, bool back);
+bool rns_pays_some(int M, int N, int K, bool back);
 // Power-of-two scales of the columns (K x N, ldb) and their inverses, and where asked for 1 / norms (0 for a column of
 // zeros), flag[n] = 1 (else 0) for a column not fit for the integers (NaN, Inf, entries beyond 1e+-130) or, with A's
 // envelope, of too small an overlap with A's rows; *any = 1 (else untouched) if one is not. rns_product leaves flagged
