@@ -311,6 +311,19 @@ cheb_status cheb_profile_enable(cheb_plan plan, int on);
 cheb_status cheb_profile_read(cheb_plan plan, int timer, double* ms, int64_t* launches, double* algo_bytes,
                               double* algo_flops);
 
+/* Kernels that the projector products of a plan took: counts[r] = products of class CHEB_T_PROJECT or
+ * CHEB_T_BACKPROJECT since the plan was made or cheb_profile_enable last reset the tallies, by route (on the host's
+ * side: bands that the INT8 kernels flag take the FP64 product inside the same call). Counted with the timers on or off.
+ * counts holds CHEB_ROUTE_COUNT values. CHEB_ERR_ARG for another class or a null pointer. */
+typedef enum {
+  CHEB_ROUTE_MFMA = 0,      /* FP64 or FP32 matrix cores */
+  CHEB_ROUTE_FP16 = 1,      /* FP16 hi/lo split, 64 x 64 tiles or operands split on the fly */
+  CHEB_ROUTE_FP16_128 = 2,  /* FP16 hi/lo split, 128 x 128 tiles of pre-split operands */
+  CHEB_ROUTE_INT8 = 3,      /* INT8 residue products */
+  CHEB_ROUTE_COUNT = 4
+} cheb_route;
+cheb_status cheb_profile_routes(cheb_plan plan, int timer, int64_t* counts);
+
 /* Tiling rules of the complex GEMMs, host arithmetic only (no device call; usable without a GPU). For an
  * M x N x K product: *fp64 = the split-K count of the tiled FP64/FP32 kernel, *fp16 = that of the FP16 split
  * kernel of mixed plans, *bound = the count every workspace sizes its split-K partials by (each partial buffer

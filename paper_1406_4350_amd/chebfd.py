@@ -36,9 +36,10 @@ SYMBOLS = ["cheb_plan_persistent_bytes", "cheb_plan_create", "cheb_plan_destroy"
            "cheb_set_capacitance_solver", "cheb_lobpcg_state_bytes", "cheb_lobpcg_iterate", "cheb_gemm_splits",
            "cheb_gemm_block_item", "cheb_set_projection_resync", "cheb_drift_monitor", "cheb_drift_read",
            "cheb_apply_H_noalloc", "cheb_filter_carry", "cheb_rayleigh_ritz_carry", "cheb_residue_limits",
-           "cheb_product_route", "cheb_last_error"]
+           "cheb_product_route", "cheb_profile_routes", "cheb_last_error"]
 TIMERS = ["fft_col_inverse", "fft_plane", "fft_col_forward", "project", "backproject", "small", "rr_gram", "rr_eig",
           "rr_rotate", "xdens"]
+ROUTES = ["mfma", "fp16", "fp16_128", "int8"]
 
 
 class ChebError(RuntimeError):
@@ -98,6 +99,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "cheb_locking_degrees": [i, vp, vp, d, d, i, d, vp, P(i)],
         "cheb_gemm_splits": [i, i, i, P(i), P(i), P(i)],
         "cheb_gemm_block_item": [i, i, i, i, i, P(i), P(i), P(i)],
+        "cheb_profile_routes": [vp, i, P(ctypes.c_int64)],
         "cheb_product_route": [i, i, i, i, P(i), P(d), P(d)],
         "cheb_residue_limits": [i, i, i, P(i), P(i), P(i), P(i), P(i), P(i)],
         "cheb_set_projection_resync": [vp, i],
@@ -423,6 +425,16 @@ class Plan:
 
     def profile_enable(self, on: bool = True):
         self._check(self.lib.cheb_profile_enable(self.handle, int(bool(on))), "cheb_profile_enable")
+
+    def profile_routes(self) -> dict:
+        """{"project": {route: products}, "backproject": {...}}: kernels that the projector products took since the plan
+        was made or the last profile_enable(True)."""
+        out = {}
+        for name in ("project", "backproject"):
+            c = (ctypes.c_int64 * len(ROUTES))()
+            self._check(self.lib.cheb_profile_routes(self.handle, TIMERS.index(name), c), "cheb_profile_routes")
+            out[name] = dict(zip(ROUTES, c))
+        return out
 
     def profile_read(self) -> dict:
         """{timer name: dict(ms, launches, bytes, flops)} since the last profile_enable(True)."""

@@ -80,6 +80,7 @@ struct cheb_plan_s {
   std::vector<std::pair<hipEvent_t, hipEvent_t>> prof_free;
   double prof_ms[CHEB_T_COUNT] = {}, prof_bytes[CHEB_T_COUNT] = {}, prof_flops[CHEB_T_COUNT] = {};
   int64_t prof_n[CHEB_T_COUNT] = {};
+  int64_t routes[2][CHEB_ROUTE_COUNT] = {};  // projections, back-projections by kernel
 };
 
 // Scratch of cheb_apply_H_noalloc, for callers that cannot allocate device memory: a file-scope device array, of
@@ -850,14 +851,17 @@ template <typename T> struct Ops {
     const double b = sizeof(C), np = p->nproj, npw = p->npw;
     Timed t(p, st, CHEB_T_PROJECT, (npw * np + npw * nb) * b + np * nb * 16.0, 8.0 * np * nb * npw);
     if constexpr (std::is_same<T, double>::value) {
-      if (use_rns(w, false, p->nproj, nb, p->npw))
+      if (use_rns(w, false, p->nproj, nb, p->npw)) {
+        p->routes[0][CHEB_ROUTE_INT8] += 1;
         return rns(GEMM_CN, p->nproj, nb, p->npw, p->rproj, X, ldx, e, w, [&](const int* pred) {
           return gemm<double, double, double, double>(GEMM_CN, p->nproj, nb, p->npw, P(), p->npw, X, ldx, e,
                                                       gemm_pick_splits(p->nproj, nb, p->npw), w.part, st, ROLE_PROJECT,
                                                       false, pred);
         });
+      }
     }
     if (exact) {
+      p->routes[0][CHEB_ROUTE_MFMA] += 1;
       HIPCHK((gemm<double, T, T, double>(GEMM_CN, p->nproj, nb, p->npw, P(), p->npw, X, ldx, e,
                                          gemm_pick_splits(p->nproj, nb, p->npw), w.part, st, ROLE_PROJECT, false,
                                          nullptr, re_form())));
@@ -872,15 +876,18 @@ template <typename T> struct Ops {
           xp.p = w.hx;
           xp.rows = nb;
           xp.ld = w.hx_ld;
+          p->routes[0][gemm_h_pre_128(p->nproj, nb, p->npw, splits) ? CHEB_ROUTE_FP16_128 : CHEB_ROUTE_FP16] += 1;
           HIPCHK((gemm_h_pre<double>(GEMM_CN, p->nproj, nb, p->npw, p->hproj, xp, w.bsc, e, splits, w.part, st,
                                      ROLE_PROJECT)));
         } else {
+          p->routes[0][CHEB_ROUTE_FP16] += 1;
           HIPCHK(column_scales<float>(p->npw, nb, X, ldx, w.bsc, st));
           HIPCHK((gemm_h<float, double>(GEMM_CN, p->nproj, nb, p->npw, p->hproj, X, ldx, w.bsc, e, splits, w.part,
                                         st, ROLE_PROJECT)));
         }
       }
     } else {
+      p->routes[0][CHEB_ROUTE_MFMA] += 1;
       HIPCHK((gemm<T, T, T, double>(GEMM_CN, p->nproj, nb, p->npw, P(), p->npw, X, ldx, e,
                                     gemm_pick_splits(p->nproj, nb, p->npw), w.part, st, ROLE_PROJECT, false, nullptr,
                                     re_form())));
@@ -895,11 +902,13 @@ template <typename T> struct Ops {
     if (ldw <= 0) ldw = p->nproj;
     Timed t(p, st, CHEB_T_BACKPROJECT, npw * np * b + np * nb * 16.0 + vecs * npw * nb * b, 8.0 * npw * nb * np);
     if constexpr (std::is_same<T, double>::value) {
-      if (use_rns(w, true, p->npw, nb, p->nproj))
+      if (use_rns(w, true, p->npw, nb, p->nproj)) {
+        p->routes[1][CHEB_ROUTE_INT8] += 1;
         return rns(GEMM_NN, p->npw, nb, p->nproj, p->rback, wv, ldw, e, w, [&](const int* pred) {
           return gemm<double, double, double, double>(GEMM_NN, p->npw, nb, p->nproj, P(), p->npw, wv, ldw, e, 1, nullptr,
                                                       st, ROLE_BACKPROJECT, false, pred);
         });
+      }
     }
     if (use_split()) {
       if constexpr (std::is_same<T, float>::value) {
@@ -910,10 +919,12 @@ template <typename T> struct Ops {
         bp.p = w.hb;
         bp.rows = nb;
         bp.ld = w.hb_ld;
+        p->routes[1][gemm_h_pre_128(p->npw, nb, p->nproj, 1) ? CHEB_ROUTE_FP16_128 : CHEB_ROUTE_FP16] += 1;
         HIPCHK((gemm_h_pre<float>(GEMM_NN, p->npw, nb, p->nproj, p->hback, bp, w.bsc, e, 1, nullptr, st,
                                   ROLE_BACKPROJECT)));
       }
     } else {
+      p->routes[1][CHEB_ROUTE_MFMA] += 1;
       HIPCHK((gemm<T, T, double, T>(GEMM_NN, p->npw, nb, p->nproj, P(), p->npw, wv, ldw, e, 1, nullptr, st,
                                     ROLE_BACKPROJECT, false, nullptr, b_form())));
     }
@@ -2298,8 +2309,19 @@ cheb_status cheb_profile_enable(cheb_plan p, int on) try {
   CHK(prof_collect(p));
   if (on) {
     for (int k = 0; k < CHEB_T_COUNT; ++k) { p->prof_ms[k] = 0; p->prof_bytes[k] = 0; p->prof_flops[k] = 0; p->prof_n[k] = 0; }
+    for (auto& r : p->routes)
+      for (int64_t& v : r) v = 0;
   }
   p->prof_on = on != 0;
+  return CHEB_OK;
+} catch (...) {
+  return host_fail(p);
+}
+
+cheb_status cheb_profile_routes(cheb_plan p, int timer, int64_t* counts) try {
+  if (!p) return CHEB_ERR_ARG;
+  if ((timer != CHEB_T_PROJECT && timer != CHEB_T_BACKPROJECT) || !counts) return fail(p, CHEB_ERR_ARG, "no such class of products");
+  for (int r = 0; r < CHEB_ROUTE_COUNT; ++r) counts[r] = p->routes[timer == CHEB_T_BACKPROJECT][r];
   return CHEB_OK;
 } catch (...) {
   return host_fail(p);

@@ -1138,6 +1138,12 @@ int gemm_h_pick_splits(int M, int N, int K) {
   return s;
 }
 
+bool gemm_h_pre_128(int M, int N, int K, int splits) {
+  int tb = 64, s = 1;
+  h_plan(M, N, K, splits > 1, &tb, &s);
+  return tb == 128;
+}
+
 template <typename EB, typename EO>
 hipError_t gemm_h(GemmMode mode, int M, int N, int K, const HalfPlanes& A, const cx<EB>* B, long ldb,
                   const float* bscale, const Epi<EO>& epi, int splits, c128* part, hipStream_t st, GemmRole role) {

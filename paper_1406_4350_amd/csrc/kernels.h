@@ -78,6 +78,8 @@ template <typename EO>
 hipError_t gemm_h_pre(GemmMode mode, int M, int N, int K, const HalfPlanes& A, const HalfPlanes& Bp,
                       const float* bscale, const Epi<EO>& epi, int splits, c128* part, hipStream_t st, GemmRole role);
 int gemm_h_pick_splits(int M, int N, int K);
+// whether gemm_h_pre takes its 128 x 128 tiles with these splits
+bool gemm_h_pre_128(int M, int N, int K, int splits);
 // upper bound of both split rules, for sizing split-K partial buffers
 int gemm_split_bound(int M, int N, int K);
 // the work item (M tile bx, N tile by, split bz) the tiled kernels give block i of a `total`-block launch

@@ -1,0 +1,148 @@
+"""The kernels that projector products take (cheb_profile_routes), and the special cases of the INT8 route on blocks that
+are shown to take it: padded rows, scaled and zero bands, bands and projectors that are not fit for the integers."""
+import ctypes
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_1406_4350_amd import chebfd as cf  # noqa: E402
+from paper_1406_4350_amd import workload as wl  # noqa: E402
+
+CFG = wl.Config("routes64", 64, 16, 16.0, "sc", 4, 64, "2s2p1d", True, 8, 4, 1, 4, 151)  # 17 077 plane waves, 832 projectors
+
+
+@pytest.fixture(scope="module")
+def problem():
+    pb = wl.make_problem(CFG)
+    plan = cf.plan_from_problem(pb, cf.CHEB_FP64)
+    yield pb, plan, torch.from_numpy(np.ascontiguousarray(pb.P.T)).cuda(), torch.from_numpy(pb.Q).cuda()
+    plan.close()
+
+
+def _block(npw, nb, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.randn((nb, npw), dtype=torch.complex128, device="cuda", generator=g)
+
+
+def _s(X, P, Q):
+    return X + ((X @ P.conj().T) * Q) @ P
+
+
+def _rel(Y, ref):
+    return float((torch.linalg.vector_norm(Y - ref, dim=1) / torch.linalg.vector_norm(ref, dim=1)).max())
+
+
+def _took(plan, fn):
+    """(routes of the projections, of the back-projections) of the products inside fn()."""
+    a = plan.profile_routes()
+    fn()
+    b = plan.profile_routes()
+    return [{r: b[k][r] - a[k][r] for r in cf.ROUTES if b[k][r] != a[k][r]} for k in ("project", "backproject")]
+
+
+def _rule(pb, nb):
+    v, x, y = ctypes.c_int(), ctypes.c_double(), ctypes.c_double()
+    out = []
+    for M, K, back in ((CFG.natom * 13, pb.npw, 0), (pb.npw, CFG.natom * 13, 1)):
+        cf.load_library().cheb_product_route(M, nb, K, back, ctypes.byref(v), ctypes.byref(x), ctypes.byref(y))
+        out.append({"int8" if v.value else "mfma": 1})
+    return out
+
+
+@pytest.mark.parametrize("nb", [16, 300, 320, 511, 512, 513, 768, 1025, 1537])
+def test_operators_take_the_route_of_the_rule(problem, nb):
+    """S X on either route: sums of 17 077 and 832 terms in FP64, a few sqrt(17 077) eps = 3e-14."""
+    pb, plan, P, Q = problem
+    print(f"[case] routes64 nb={nb}", flush=True)
+    X = _block(pb.npw, nb, nb)
+    Y = torch.empty_like(X)
+    assert _took(plan, lambda: plan.apply_S(X, Y)) == _rule(pb, nb)
+    assert _rel(Y, _s(X, P, Q)) < 1e-13
+
+
+def test_padded_rows_and_scaled_bands_on_int8(problem):
+    """Leading dimension above npw; bands 2^332 and 2^-332 times as large, a zero band, a band whose one entry dominates:
+    every band is scaled by itself, so powers of two scale its result exactly and no band changes another's bits."""
+    pb, plan, P, Q = problem
+    nb = 512
+    wide = torch.zeros((nb, pb.npw + 37), dtype=torch.complex128, device="cuda")
+    X = wide[:, :pb.npw]
+    X.copy_(_block(pb.npw, nb, 5))
+    base = plan.apply_S(X.contiguous())
+    X[1] *= 2.0 ** 332
+    X[2] *= 2.0 ** -332
+    X[3] = 0.0
+    X[4, 7] = 1e12
+    Y = torch.empty_like(wide)[:, :pb.npw]
+    assert _took(plan, lambda: plan.apply_S(X, Y)) == [{"int8": 1}, {"int8": 1}]
+    assert torch.equal(Y[0], base[0]) and torch.equal(Y[5:], base[5:])
+    assert torch.equal(Y[1], base[1] * 2.0 ** 332) and torch.equal(Y[2], base[2] * 2.0 ** -332)
+    assert float(Y[3].abs().max()) == 0.0
+    assert _rel(Y[4:5], _s(X[4:5].contiguous(), P, Q)) < 1e-13
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), 1e200, 1e-200])
+def test_unfit_band_on_int8(problem, value):
+    """A band with a NaN, an Inf or beyond the integers' range takes the FP64 product inside the call, alone: the other
+    bands keep their bits, the band its NaN or, with finite entries, its value."""
+    pb, plan, P, Q = problem
+    X = _block(pb.npw, 512, 9)
+    base = plan.apply_S(X)
+    if value == 1e-200:
+        X[17] *= value
+    else:
+        X[17, 11] = complex(value, 0.0)
+    Y = torch.empty_like(X)
+    assert _took(plan, lambda: plan.apply_S(X, Y)) == [{"int8": 1}, {"int8": 1}]
+    keep = [i for i in range(512) if i != 17]
+    assert torch.equal(Y[keep], base[keep])
+    if value in (1e200, 1e-200):
+        assert _rel(Y[17:18] / value, _s(X[17:18] / value, P, Q)) < 1e-13
+    else:
+        assert not bool(torch.isfinite(torch.view_as_real(Y[17])).all())
+
+
+@pytest.mark.parametrize("value", [1e200, 1e-200, 0.0])
+def test_unfit_projector_turns_the_route_off(problem, value):
+    """A projector scaled beyond the integers' range, where every product takes the FP64 matrix cores, and a projector of
+    zeros, which is fit: H X = P D P^H X (no kinetic term and potential)."""
+    pb, _, P, _ = problem
+    plan = cf.Plan(pb.gidx, np.zeros(pb.npw), 64, pb.proj_off, False)
+    plan.set_potential(torch.zeros((64,) * 3, dtype=torch.float64))
+    Pu = P.clone()
+    Pu[100] *= value
+    plan.set_projectors(Pu, None)
+    D = torch.eye(13, dtype=torch.float64).repeat(CFG.natom, 1, 1)
+    if value == 1e200:  # its square would overflow FP64
+        D[100 // 13, 100 % 13, 100 % 13] = 0.0
+    plan.set_D(D.reshape(-1))
+    X = _block(pb.npw, 512, 21)
+    Y = torch.empty_like(X)
+    route = "int8" if value == 0.0 else "mfma"
+    assert _took(plan, lambda: plan.apply_H(X, Y)) == [{route: 1}, {route: 1}]
+    Pr = Pu.clone()
+    Pr[100] = 0.0
+    assert _rel(Y, (X @ Pr.conj().T) @ Pr) < 1e-13
+    plan.close()
+
+
+def test_mixed_routes_and_reset(problem):
+    """Mixed plans count their FP16 products by tile; profile_enable resets the counts; other classes are refused."""
+    pb, _, _, _ = problem
+    plan = cf.plan_from_problem(pb, cf.CHEB_MIXED)
+    X = _block(pb.npw, 512, 2).to(torch.complex64)
+    plan.filter(X, 2, 10.0, 30.0)
+    r = plan.profile_routes()
+    assert sum(r["project"].values()) == 3 and sum(r["backproject"].values()) == 2
+    assert r["project"]["int8"] == r["project"]["mfma"] == r["backproject"]["mfma"] == 0
+    assert r["backproject"]["fp16_128"] == 2  # 134 x 4 tiles of 128
+    plan.profile_enable(True)
+    plan.profile_enable(False)
+    assert not any(plan.profile_routes()["project"].values())
+    c = (ctypes.c_int64 * 4)()
+    assert plan.lib.cheb_profile_routes(plan.handle, cf.TIMERS.index("small"), c) == cf.CHEB_ERR_ARG
+    assert plan.lib.cheb_profile_routes(plan.handle, cf.TIMERS.index("project"), None) == cf.CHEB_ERR_ARG
+    plan.close()
