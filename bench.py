@@ -28,7 +28,7 @@ sys.path.insert(0, ROOT)
 
 METRIC = "H·ψ band-applications/s (FP32-MFMA vs FP64) at ≤1e-6 Ha; % HBM/MFMA roofline"
 HBM_PEAK_GBS = 8000.0
-PEAK_TFLOPS = {"f64": 78.6, "f32": 157.3, "f16x3": 2500.0, "i8x45": 5000.0}
+PEAK_TFLOPS = {"f64": 78.6, "f32": 157.3, "f16x3": 2500.0, "i8x48": 5000.0}
 # vector ALU peaks (FMA = 2 flops): FP64 78.6; FP32 157.3 with packed FP32 instructions, which the build disables,
 # so the FP32 kernels here issue at most half of it
 VECTOR_PEAK_TFLOPS = {"f64": 78.6, "f32": 157.3}
@@ -92,6 +92,8 @@ def run_path(cf, pb, prec, lam_plus, steps, warmup, resync=None):
     torch.cuda.synchronize()
     t1 = time.perf_counter()
     prof = plan.profile_read()
+    for name, routes in plan.profile_routes().items():
+        prof[name]["routes"] = routes
     plan.profile_enable(False)
     rr_stats = plan.rr_stats()
 
@@ -134,20 +136,22 @@ def class_roofline(name, d, kind, n):
     (whose timers also count its transform arithmetic) against the vector ALU peak where that fraction is the larger. Achieved = algorithmic flops (8 per
     complex multiply-add; 5 n log2 n per length-n transform) or bytes per launch / average launch time."""
     per_launch_s = d["ms"] * 1e-3 / d["launches"]
-    alu = False
+    alu, route = False, None
     if name in GEMM_CLASSES:
         achieved = d["flops"] / d["launches"] / per_launch_s / 1e12
         dt = "f16x3" if (kind == "f32" and name in ("project", "backproject")) else "f64"
-        # FP64 projector products faster than three-product complex arithmetic can run on the FP64 matrix cores are the
-        # INT8 residue products: 3 int8 GEMMs for each of 15 moduli
-        if dt == "f64" and name in ("project", "backproject") and achieved * 0.75 > PEAK_TFLOPS["f64"]:
-            dt = "i8x45"
+        # the kernel that most products of the class took, from the plan's counts (INT8 residue products: 3 int8 GEMMs
+        # for each of 16 moduli)
+        routes = d.get("routes") or {}
+        route = max(routes, key=routes.get) if any(routes.values()) else None
+        if route == "int8":
+            dt = "i8x48"
         peak = PEAK_TFLOPS[dt]
         out = {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "mfma_dtype": dt}
         # flops the matrix cores execute per algorithmic flop: the FP64 tiles take 3 real products per complex
         # product (6 of the 8 counted flops), the FP16 split products 3 FP16 products per useful one, the residue
-        # products 45 integer multiply-adds per complex one
-        out["executed_frac"] = achieved * {"f64": 0.75, "f16x3": 3.0, "i8x45": 90.0 / 8.0}[dt] / peak
+        # products 48 integer multiply-adds per complex one
+        out["executed_frac"] = achieved * {"f64": 0.75, "f16x3": 3.0, "i8x48": 96.0 / 8.0}[dt] / peak
     else:
         achieved = d["bytes"] / d["launches"] / per_launch_s / 1e9
         out = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s"}
@@ -163,10 +167,8 @@ def class_roofline(name, d, kind, n):
     out["frac"] = out["achieved"] / out["peak"]
     tmpl = KERNEL_NAMES.get(name)
     out["kernel"] = tmpl[0 if kind == "f64" else 1].format(n=n) if tmpl else name
-    if out.get("mfma_dtype") == "i8x45":
-        out["kernel"] = "k_rns_gemm"
-    elif kind == "f32" and name in ("project", "backproject") and n >= 96:
-        out["kernel"] = "k_gemm_hp"  # 128 x 128 tiles from pre-split operands, where they fill a round of blocks
+    if name in ("project", "backproject") and route in ("int8", "fp16_128"):
+        out["kernel"] = {"int8": "k_rns_gemm", "fp16_128": "k_gemm_hp"}[route]
     if name == "fft_plane" and kind == "f64" and n == 128:
         out["kernel"] = "k_plane_half"  # the FP64 128^3 plane pass runs in two halves of the y residues
     out["avg_launch_us"] = per_launch_s * 1e6
