@@ -538,11 +538,13 @@ cheb_status ws_layout(cheb_plan p, int op, int nb, void* base, Ws* w) {
   if ((p->rproj.base || p->rback.base) && op != CHEB_OP_SETUP && op != CHEB_OP_BOUND) {
     const size_t before = b.off;
     const size_t n = size_t(rns_chunk(std::max(nb, 1)));
-    if (p->rproj.base && rns_pays(np, nb, p->npw, false)) {
+    // blocks that shrink inside the call may take a product that the whole block does not
+    const auto pays = op == CHEB_OP_FILTER_DEGREES || op == CHEB_OP_LOBPCG ? rns_pays_some : rns_pays;
+    if (p->rproj.base && pays(np, nb, p->npw, false)) {
       w->rB_bytes = 3 * kRnsMods * n * rns_ld(p->npw);
       w->rC_bytes = 3 * kRnsMods * n * rns_ldc(np);
     }
-    if (p->rback.base && rns_pays(p->npw, nb, np, true)) {
+    if (p->rback.base && pays(p->npw, nb, np, true)) {
       w->rB_bytes = std::max<size_t>(w->rB_bytes, 3 * kRnsMods * n * rns_ld(np));
       w->rC_bytes = std::max<size_t>(w->rC_bytes, 3 * kRnsMods * n * rns_ldc(p->npw));
     }
@@ -797,23 +799,30 @@ template <typename T> struct Ops {
     return CHEB_OK;
   }
 
-  // Whether a product with residue planes of the plan takes the INT8 matrix cores: where it pays and the workspace,
-  // which is laid out for the call's widest block, holds its planes (a narrower block of the same call takes the FP64
-  // product where the wide one did not need the planes)
-  bool use_rns(const Ws& w, bool back, int M, int nb, int K) const {
-    if (!std::is_same<T, double>::value || !w.rB || !p->rns_ok || !p->rns_flat[back]) return false;
-    if (!(back ? p->rback : p->rproj).base || !rns_pays(M, nb, K, back)) return false;
-    const size_t n = size_t(rns_chunk(nb));
-    return 3 * kRnsMods * n * rns_ld(K) <= w.rB_bytes && 3 * kRnsMods * n * rns_ldc(M) <= w.rC_bytes;
+  // Columns at a time of a product with residue planes of the plan on the INT8 matrix cores, 0 where it takes the FP64
+  // ones: where INT8 does not pay, or the workspace does not hold planes of that product. The workspace is laid out for
+  // the pieces of the call's widest block, which may be narrower than a smaller block's (1100 bands: two of 768 at most,
+  // 1000 bands: one); that one takes equal pieces of whole tiles that fit.
+  long rns_cols(const Ws& w, bool back, int M, int nb, int K) const {
+    if (!std::is_same<T, double>::value || !w.rB || !p->rns_ok || !p->rns_flat[back]) return 0;
+    if (!(back ? p->rback : p->rproj).base || !rns_pays(M, nb, K, back)) return 0;
+    const long step = rns_chunk(nb);
+    const size_t ub = 3 * kRnsMods * size_t(rns_ld(K)), uc = 3 * kRnsMods * size_t(rns_ldc(M));
+    const long held = long(std::min(w.rB_bytes / ub, w.rC_bytes / uc));
+    if (held >= step) return step;
+    const long most = held / 256 * 256;
+    if (most == 0) return 0;
+    const long pieces = (nb + most - 1) / most, per = (nb + pieces - 1) / pieces;
+    return (per + 255) / 256 * 256;
   }
 
   // out = op(A) B on the INT8 matrix cores (A: residue planes of the plan, B: K x nb), with the FP64 product behind it
   // for the columns that the flags say are not fit for it (every product looks at its own operand)
   template <typename Fallback>
   cheb_status rns(GemmMode mode, int M, int nb, int K, const RnsOperand& A, const c128* B, long ldb, Epi<double> e,
-                  const Ws& w, Fallback&& fp64) {
+                  const Ws& w, long step, Fallback&& fp64) {
     HIPCHK(rns_scale_cols<double>(K, nb, B, ldb, A.env, w.rscale, w.rinv, nullptr, w.rflag, nullptr, st));
-    const long step = rns_chunk(nb), ld = rns_ld(K);
+    const long ld = rns_ld(K);
     for (long n0 = 0; n0 < nb; n0 += step) {
       const int cnt = int(std::min<long>(step, nb - n0));
       const long plane = cnt * ld;
@@ -851,9 +860,9 @@ template <typename T> struct Ops {
     const double b = sizeof(C), np = p->nproj, npw = p->npw;
     Timed t(p, st, CHEB_T_PROJECT, (npw * np + npw * nb) * b + np * nb * 16.0, 8.0 * np * nb * npw);
     if constexpr (std::is_same<T, double>::value) {
-      if (use_rns(w, false, p->nproj, nb, p->npw)) {
+      if (const long step = rns_cols(w, false, p->nproj, nb, p->npw)) {
         p->routes[0][CHEB_ROUTE_INT8] += 1;
-        return rns(GEMM_CN, p->nproj, nb, p->npw, p->rproj, X, ldx, e, w, [&](const int* pred) {
+        return rns(GEMM_CN, p->nproj, nb, p->npw, p->rproj, X, ldx, e, w, step, [&](const int* pred) {
           return gemm<double, double, double, double>(GEMM_CN, p->nproj, nb, p->npw, P(), p->npw, X, ldx, e,
                                                       gemm_pick_splits(p->nproj, nb, p->npw), w.part, st, ROLE_PROJECT,
                                                       false, pred);
@@ -902,9 +911,9 @@ template <typename T> struct Ops {
     if (ldw <= 0) ldw = p->nproj;
     Timed t(p, st, CHEB_T_BACKPROJECT, npw * np * b + np * nb * 16.0 + vecs * npw * nb * b, 8.0 * npw * nb * np);
     if constexpr (std::is_same<T, double>::value) {
-      if (use_rns(w, true, p->npw, nb, p->nproj)) {
+      if (const long step = rns_cols(w, true, p->npw, nb, p->nproj)) {
         p->routes[1][CHEB_ROUTE_INT8] += 1;
-        return rns(GEMM_NN, p->npw, nb, p->nproj, p->rback, wv, ldw, e, w, [&](const int* pred) {
+        return rns(GEMM_NN, p->npw, nb, p->nproj, p->rback, wv, ldw, e, w, step, [&](const int* pred) {
           return gemm<double, double, double, double>(GEMM_NN, p->npw, nb, p->nproj, P(), p->npw, wv, ldw, e, 1, nullptr,
                                                       st, ROLE_BACKPROJECT, false, pred);
         });

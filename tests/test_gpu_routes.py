@@ -129,6 +129,34 @@ def test_unfit_projector_turns_the_route_off(problem, value):
     plan.close()
 
 
+@pytest.mark.parametrize("nb", [1100, 2100])
+def test_shrinking_blocks_keep_the_route(problem, nb):
+    """A filter with a degree per band whose active blocks pass through widths above the pieces that the workspace of the
+    widest block is laid out for: every product whose block the rule gives to INT8 takes it, and every band equals the
+    plain filter of its degree (two filters whose products sum in different orders: 1e-11 after 6 steps)."""
+    pb, plan, _, _ = problem
+    X = _block(pb.npw, nb, nb)
+    width = [nb, nb - 50, 1000 if nb < 2000 else 1900, 900 if nb < 2000 else 1000, 800, 300]  # active at step 1, 2, ...
+    deg = np.array([sum(b < k for k in width) for b in range(nb)], dtype=np.int32)
+    lp = plan.upper_bound(X[0], 10)
+    c, r = 0.55 * lp, 0.45 * lp
+    Y = X.clone()
+    took = _took(plan, lambda: plan.filter_degrees(Y, deg, c, r))
+    want = [{}, {}]
+    for k in [nb] + width:  # the projections of the start block and of each step
+        route = next(iter(_rule(pb, k)[0]))
+        want[0][route] = want[0].get(route, 0) + 1
+    for k in width:
+        route = next(iter(_rule(pb, k)[1]))
+        want[1][route] = want[1].get(route, 0) + 1
+    assert took == want and want[0] == {"int8": 7}
+    for m in range(1, 7):
+        some = [b for b in range(nb) if deg[b] == m][:40]
+        Z = X[some].clone()
+        plan.filter(Z, m, c, r)
+        assert _rel(Y[some], Z) < 1e-11
+
+
 def test_mixed_routes_and_reset(problem):
     """Mixed plans count their FP16 products by tile; profile_enable resets the counts; other classes are refused."""
     pb, _, _, _ = problem
