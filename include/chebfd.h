@@ -95,9 +95,13 @@ typedef struct {
  * P^H P, capacitance inverse; in FP64 plans whose projector products run on the INT8 matrix cores also the residue
  * planes of P, 48 bytes per entry for each of the two products that does, up to 64 GiB). */
 cheb_status cheb_plan_persistent_bytes(const cheb_desc* desc, size_t* bytes);
+/* The same without the residue planes: a plan made over a buffer of at least these bytes, and fewer than
+ * cheb_plan_persistent_bytes, computes its projector products on the FP64 matrix cores, and the workspaces of its calls
+ * hold no residue planes either. For programs that keep several plans on one GPU. */
+cheb_status cheb_plan_persistent_bytes_min(const cheb_desc* desc, size_t* bytes);
 
-/* Create a plan over a caller-provided device buffer of at least cheb_plan_persistent_bytes bytes
- * (256-byte aligned). Copies the host arrays of desc; synchronizes `stream`. */
+/* Create a plan over a caller-provided device buffer of at least cheb_plan_persistent_bytes bytes (256-byte aligned;
+ * fewer, but at least cheb_plan_persistent_bytes_min: a plan without residue planes). Copies the host arrays of desc; synchronizes `stream`. */
 cheb_status cheb_plan_create(const cheb_desc* desc, void* persistent_dev, size_t bytes, hipStream_t stream,
                              cheb_plan* out);
 cheb_status cheb_plan_destroy(cheb_plan plan);

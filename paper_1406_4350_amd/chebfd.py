@@ -28,7 +28,7 @@ CHEB_FP64, CHEB_MIXED = 0, 1
  CHEB_OP_LOBPCG) = range(8)
 
 # exported symbols, as declared in include/chebfd.h
-SYMBOLS = ["cheb_plan_persistent_bytes", "cheb_plan_create", "cheb_plan_destroy", "cheb_set_potential",
+SYMBOLS = ["cheb_plan_persistent_bytes", "cheb_plan_persistent_bytes_min", "cheb_plan_create", "cheb_plan_destroy", "cheb_set_potential",
            "cheb_set_projectors", "cheb_set_D", "cheb_workspace_bytes", "cheb_apply_H", "cheb_apply_S",
            "cheb_apply_Sinv", "cheb_filter", "cheb_rayleigh_ritz", "cheb_rayleigh_quotients", "cheb_upper_bound",
            "cheb_profile_enable", "cheb_profile_read", "cheb_backward_workspace_bytes", "cheb_filter_rr_backward",
@@ -70,6 +70,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     P = ctypes.POINTER
     sig = {
         "cheb_plan_persistent_bytes": [P(cheb_desc), P(sz)],
+        "cheb_plan_persistent_bytes_min": [P(cheb_desc), P(sz)],
         "cheb_plan_create": [P(cheb_desc), vp, sz, vp, P(vp)],
         "cheb_plan_destroy": [vp],
         "cheb_set_potential": [vp, vp, vp],
@@ -143,10 +144,11 @@ def _stream() -> int:
 
 
 class Plan:
-    """A plan over one problem (sphere, box, atoms, precision); owns its persistent device buffer."""
+    """A plan over one problem (sphere, box, atoms, precision); owns its persistent device buffer. residue_planes = False:
+    a smaller buffer without the planes of the INT8 products (see cheb_plan_persistent_bytes_min)."""
 
     def __init__(self, gidx: np.ndarray, kin: np.ndarray, n: int, proj_off: np.ndarray, has_overlap: bool,
-                 prec: int = CHEB_FP64, device: str = "cuda", gamma: bool = False):
+                 prec: int = CHEB_FP64, device: str = "cuda", gamma: bool = False, residue_planes: bool = True):
         self.lib = load_library()
         if not torch.cuda.is_available():
             raise RuntimeError("chebfd needs a GPU (torch.cuda.is_available() is False)")
@@ -164,8 +166,8 @@ class Plan:
                               self._off.ctypes.data if self.natom > 0 else None, int(bool(has_overlap)), prec,
                               int(self.gamma))
         nbytes = ctypes.c_size_t()
-        self._check(self.lib.cheb_plan_persistent_bytes(ctypes.byref(self.desc), ctypes.byref(nbytes)),
-                    "cheb_plan_persistent_bytes", plan=False)
+        size = "cheb_plan_persistent_bytes" if residue_planes else "cheb_plan_persistent_bytes_min"
+        self._check(getattr(self.lib, size)(ctypes.byref(self.desc), ctypes.byref(nbytes)), size, plan=False)
         self.persistent = torch.empty(nbytes.value, dtype=torch.uint8, device=self.device)
         h = ctypes.c_void_p()
         self._check(self.lib.cheb_plan_create(ctypes.byref(self.desc), self.persistent.data_ptr(), nbytes.value,

@@ -233,9 +233,9 @@ RnsPlanned rns_planned(int npw, int nproj, int prec, int gamma) {
   return bytes <= kRnsPlaneCap ? r : RnsPlanned{};
 }
 
-// Carves the persistent buffer (base == nullptr: only measures)
+// Carves the persistent buffer (base == nullptr: only measures), with the residue planes or without
 Persist persist_layout(void* base, int n, int npw, int npf, int ncol, int rx, int nproj, size_t dsize, int overlap,
-                       int prec, int gamma) {
+                       int prec, int gamma, bool planes) {
   Bump b(base);
   Persist l{};
   const bool mixed = prec == CHEB_MIXED;
@@ -261,7 +261,7 @@ Persist persist_layout(void* base, int n, int npw, int npf, int ncol, int rx, in
   }
   l.Rproj = l.Rback = nullptr;
   l.Rpinv = l.Rbinv = l.Rpenv = l.Rbenv = nullptr;
-  const RnsPlanned rns = rns_planned(npw, nproj, prec, gamma);
+  const RnsPlanned rns = planes ? rns_planned(npw, nproj, prec, gamma) : RnsPlanned{};
   if (rns.proj) {
     l.Rproj = b.take<int8_t>(3 * kRnsMods * size_t(nproj) * rns_ld(npw));
     l.Rpinv = b.take<double>(nproj);
@@ -279,8 +279,8 @@ Persist persist_layout(void* base, int n, int npw, int npf, int ncol, int rx, in
 }
 
 size_t persist_bytes(int n, int npw, int npf, int ncol, int rx, int nproj, size_t dsize, int overlap, int prec,
-                     int gamma) {
-  return persist_layout(nullptr, n, npw, npf, ncol, rx, nproj, dsize, overlap, prec, gamma).bytes;
+                     int gamma, bool planes) {
+  return persist_layout(nullptr, n, npw, npf, ncol, rx, nproj, dsize, overlap, prec, gamma, planes).bytes;
 }
 
 // split-K partials of an M x N x K product: enough for either GEMM kernel (FP64/FP32 MFMA or FP16 split),
@@ -2143,7 +2143,7 @@ static cheb_status validate_desc(const cheb_desc* d, int* ncol_out, int* rx_out,
   return CHEB_OK;
 }
 
-cheb_status cheb_plan_persistent_bytes(const cheb_desc* d, size_t* bytes) try {
+static cheb_status persistent_bytes(const cheb_desc* d, bool planes, size_t* bytes) {
   if (!bytes) return CHEB_ERR_ARG;
   int ncol = 0, rx = 0;
   size_t dsize = 0;
@@ -2153,8 +2153,17 @@ cheb_status cheb_plan_persistent_bytes(const cheb_desc* d, size_t* bytes) try {
   if (s != CHEB_OK) return s;
   const int nproj = d->natom > 0 ? d->proj_off_host[d->natom] : 0;
   const int npf = d->gamma ? int(fs.gmap.size()) : d->npw;
-  *bytes = persist_bytes(d->n, d->npw, npf, ncol, rx, nproj, dsize, d->has_overlap ? 1 : 0, d->prec, d->gamma);
+  *bytes = persist_bytes(d->n, d->npw, npf, ncol, rx, nproj, dsize, d->has_overlap ? 1 : 0, d->prec, d->gamma, planes);
   return CHEB_OK;
+}
+
+cheb_status cheb_plan_persistent_bytes(const cheb_desc* d, size_t* bytes) try {
+  return persistent_bytes(d, true, bytes);
+} catch (...) {
+  return host_fail(nullptr);
+}
+cheb_status cheb_plan_persistent_bytes_min(const cheb_desc* d, size_t* bytes) try {
+  return persistent_bytes(d, false, bytes);
 } catch (...) {
   return host_fail(nullptr);
 }
@@ -2171,9 +2180,11 @@ cheb_status cheb_plan_create(const cheb_desc* d, void* persistent, size_t bytes,
   const int nproj = d->natom > 0 ? d->proj_off_host[d->natom] : 0;
   const int npf = d->gamma ? int(fs.gmap.size()) : d->npw;
   const int32_t* G = d->gamma ? fs.g.data() : d->gidx_host;  // the sphere of the FFTs
-  const size_t need = persist_bytes(d->n, d->npw, npf, ncol, rx, nproj, dsize, d->has_overlap ? 1 : 0, d->prec,
-                                    d->gamma);
-  if (!persistent || bytes < need || reinterpret_cast<uintptr_t>(persistent) % kAlign) return CHEB_ERR_WORKSPACE;
+  auto need = [&](bool planes) {
+    return persist_bytes(d->n, d->npw, npf, ncol, rx, nproj, dsize, d->has_overlap ? 1 : 0, d->prec, d->gamma, planes);
+  };
+  const bool planes = bytes >= need(true);  // a smaller buffer does without the residue planes
+  if (!persistent || bytes < need(false) || reinterpret_cast<uintptr_t>(persistent) % kAlign) return CHEB_ERR_WORKSPACE;
 
   std::unique_ptr<cheb_plan_s> owner(new cheb_plan_s);  // handed to the caller only on success
   cheb_plan p = owner.get();
@@ -2182,7 +2193,8 @@ cheb_status cheb_plan_create(const cheb_desc* d, void* persistent, size_t bytes,
   p->gamma = d->gamma; p->npf = npf; p->h0 = fs.h0;
   p->resync = d->prec == CHEB_MIXED ? kMixedResync : 0;
   p->proj_off.assign(d->proj_off_host, d->proj_off_host + (d->natom > 0 ? d->natom + 1 : 0));
-  Persist l = persist_layout(persistent, d->n, d->npw, npf, ncol, rx, nproj, dsize, p->has_overlap, d->prec, d->gamma);
+  Persist l = persist_layout(persistent, d->n, d->npw, npf, ncol, rx, nproj, dsize, p->has_overlap, d->prec, d->gamma,
+                             planes);
   p->gmap = l.gmap; p->gpair = l.gpair;
   p->col = l.col; p->ent = l.ent; p->xline = l.xline; p->pinfo = l.pinfo; p->dent = l.dent; p->tw = l.tw; p->kin = l.kin; p->Vt = l.Vt; p->P = l.P;
   p->D = l.D; p->Q = l.Q; p->G = l.G; p->Cinv = l.Cinv; p->Cmat = l.Cmat; p->Minv = l.Minv;

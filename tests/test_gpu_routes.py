@@ -157,6 +157,30 @@ def test_shrinking_blocks_keep_the_route(problem, nb):
         assert _rel(Y[some], Z) < 1e-11
 
 
+def test_plan_without_residue_planes(problem):
+    """A plan over the smaller buffer holds no planes, neither do its workspaces, and its products are FP64 ones, equal
+    to the INT8 ones up to rounding; a buffer one byte short is refused."""
+    pb, plan, P, Q = problem
+    lean = cf.Plan(pb.gidx, pb.kin, 64, pb.proj_off, True, residue_planes=False)
+    planes = 48 * P.numel()  # of one product; the plan holds those of both
+    assert plan.persistent.numel() - lean.persistent.numel() > 2 * planes
+    lean.set_potential(torch.from_numpy(np.ascontiguousarray(pb.V)))
+    lean.set_projectors(P, Q)
+    lean.set_D(torch.from_numpy(pb.D_packed))
+    X = _block(pb.npw, 512, 31)
+    Y = torch.empty_like(X)
+    assert _took(lean, lambda: lean.apply_S(X, Y)) == [{"mfma": 1}, {"mfma": 1}]
+    assert _rel(plan.apply_S(X), Y) < 1e-13
+    assert plan.workspace(cf.CHEB_OP_SINV, 512).numel() - lean.workspace(cf.CHEB_OP_SINV, 512).numel() > 48 * X.numel()
+    h, buf = ctypes.c_void_p(), torch.empty_like(lean.persistent)
+    for size, status in ((lean.persistent.numel(), cf.CHEB_OK), (lean.persistent.numel() - 1, cf.CHEB_ERR_WORKSPACE)):
+        st = lean.lib.cheb_plan_create(ctypes.byref(lean.desc), buf.data_ptr(), size, None, ctypes.byref(h))
+        assert st == status
+        if st == cf.CHEB_OK:
+            lean.lib.cheb_plan_destroy(h)
+    lean.close()
+
+
 def test_mixed_routes_and_reset(problem):
     """Mixed plans count their FP16 products by tile; profile_enable resets the counts; other classes are refused."""
     pb, _, _, _ = problem
