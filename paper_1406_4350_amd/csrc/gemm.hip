@@ -352,7 +352,9 @@ __global__ __launch_bounds__(256) void k_reduce(int M, int N, int splits, const 
 //
 // Few blocks with a longer K (the projections and Grams of the small spheres) leave the chip idle while each block pulls
 // its whole K through one CU: K is then split over blocks too, and the partial blocks summed by k_reduce (65 x 41 x 925,
-// 15 blocks: 15.1 us in one launch, also with 16 waves per block; 8.4 us with 14 splits, the reduction included).
+// 15 blocks: 15.1 us in one launch, also with 16 waves per block; 8.4 us with 14 splits, the reduction included). Filters of
+// 4 steps at 24^3, 4 to 130 projectors and 1 to 100 bands, take 145 to 206 us instead of 150 to 238; Rayleigh-Ritz of 1 to
+// 100 bands there 231 to 272 instead of 276 to 319; with 832 projectors (their K in projector space) 1 to 8 bands gain 1%.
 constexpr int SKG = 16, SKMAX = 1024, SBLKMAX = 1024, SLD = 17, SW = 4;  // 8 waves per block measured slower at 256^3
 static_assert(SW >= 4, "the epilogue takes one thread per element of the 16 x 16 block");
 
