@@ -50,6 +50,7 @@ struct cheb_plan_s {
   bool cap_blocks_ok = false;  // atom blocks inverted (all of size <= 32)
   bool have_V = false, have_P = false, have_D = false;
   int fft_batch = 1;
+  int max_atom = 0;        // projectors of the largest atom
   bool narrow = false;     // every |gx| and |gy| of the sphere <= n / 4 (pruned plane pass)
   bool band_fits = false;  // small boxes: the transforms of a band in one launch (fft_band)
   HalfPlanes hproj, hback;                  // mixed plans: split planes of P (set with the projectors)
@@ -1055,7 +1056,7 @@ template <typename T> struct Ops {
     long ldw = l2;
     if (p->has_overlap) {
       // u = Q^-1 D p - p_loc comes out of the projection's epilogue, over Q^-1 D p
-      if (!opened) HIPCHK(overlap_open(np, nb, p->pinfo, p->D, p->Q, pcur, np, dp, pl, l2, st));
+      if (!opened) HIPCHK(overlap_open(np, nb, p->max_atom, p->pinfo, p->D, p->Q, pcur, np, dp, pl, l2, st));
       CHK(project(loc, npw, nb, pl, w, false, l2, pl));
       CHK(cinv(pl, l2, nb, w.w, np, w));
       wv = w.w;
@@ -1073,7 +1074,7 @@ template <typename T> struct Ops {
     CHK(backproject(wv, nb, e, w, ldw));
     if (p->has_overlap) {
       // p^i = s1 (Q^-1 (D p - w) - c p^(i-1)) - s2 p^(i-2)
-      HIPCHK(overlap_close(np, nb, p->pinfo, p->D, p->Q, dp, pl, l2, w.w, np, s1, c, pcur, np, s2,
+      HIPCHK(overlap_close(np, nb, p->max_atom, p->pinfo, p->D, p->Q, dp, pl, l2, w.w, np, s1, c, pcur, np, s2,
                            i > 1 ? pprev : nullptr, np, pout, np, open_next, st));
       return CHEB_OK;
     }
@@ -2247,6 +2248,7 @@ cheb_status cheb_plan_create(const cheb_desc* d, void* persistent, size_t bytes,
   std::vector<int2> dent(std::max<size_t>(dsize, 1), int2{0, 0});
   for (int a = 0; a < d->natom; ++a) {
     const int o = d->proj_off_host[a], na = d->proj_off_host[a + 1] - o;
+    p->max_atom = std::max(p->max_atom, na);
     for (int i = 0; i < na; ++i) pinfo[o + i] = int4{o, na, int(doff), 0};
     for (int i = 0; i < na; ++i)
       for (int j = 0; j < na; ++j) dent[doff + size_t(i) * na + j] = int2{o + i, o + j};

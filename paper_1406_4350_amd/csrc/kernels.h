@@ -221,11 +221,11 @@ hipError_t diag_apply(int nproj, int nb, const double* d, const c128* in, long l
                       hipStream_t st);
 // Projector space of a filter step with an overlap (S = I + P Q P^H, Q diagonal, C = Q^-1 + P^H P): open: dp = D cur and
 // qdp = Q^-1 D cur (both ld ldd); close: out = s1 (Q^-1 (dp - w) - c cur) - s2 prev (prev may be null or out), and with
-// next the open of out for the following step.
-hipError_t overlap_open(int nproj, int nb, const int4* pinfo, const double* D, const double* Q, const c128* cur,
-                        long ldc, c128* dp, c128* qdp, long ldd, hipStream_t st);
-hipError_t overlap_close(int nproj, int nb, const int4* pinfo, const double* D, const double* Q, c128* dp, c128* qdp,
-                         long ldd, const c128* w, long ldw, double s1, double c, const c128* cur, long ldc, double s2,
+// next the open of out for the following step. atom: projectors of the largest atom.
+hipError_t overlap_open(int nproj, int nb, int atom, const int4* pinfo, const double* D, const double* Q,
+                        const c128* cur, long ldc, c128* dp, c128* qdp, long ldd, hipStream_t st);
+hipError_t overlap_close(int nproj, int nb, int atom, const int4* pinfo, const double* D, const double* Q, c128* dp,
+                         c128* qdp, long ldd, const c128* w, long ldw, double s1, double c, const c128* cur, long ldc, double s2,
                          const c128* prev, long ldp, c128* out, long ldo, bool next, hipStream_t st);
 // out = a x + b y (+ c z), complex, any storage type
 template <typename E>

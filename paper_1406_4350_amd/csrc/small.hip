@@ -104,21 +104,35 @@ __global__ void k_block_diag_c(int nproj, int nb, const int4* __restrict__ pinfo
 }
 
 // Projector space of a filter step with an overlap (u = Q^-1 D p - P^H loc, w = C^-1 u, and the recurrence of the carried
-// projections p). The recurrence closes one step and D p and Q^-1 D p open the next one, of the same p: one kernel, one
-// block per band with the band's new p in LDS for the block-diagonal D (an atom's block needs p of all its projectors).
-// Bound by its launch at the small sizes (D p, u and the recurrence as kernels of their own took 4.8 us each at 256 x 256
-// and 256 bands, this one 5.0); u itself comes out of the projection's epilogue.
+// projections p). The recurrence closes one step and D p and Q^-1 D p open the next one, of the same p: one kernel, whose
+// blocks keep a band's new p in LDS for the block-diagonal D (an atom's block needs p of all its projectors). Bound by its
+// launch at the small sizes (D p, u and the recurrence as kernels of their own took 4.8 us each at 256 x 256 and 256
+// bands, this one 5.0); u itself comes out of the projection's epilogue.
+// A band's projectors are dealt to `pieces` blocks at the boundaries of atoms (piece q: the atoms that begin in rows
+// [q rows, (q + 1) rows)), several where the bands alone would leave the chip idle: a mixed filter of 4 steps with 3328
+// projectors and 1 to 32 bands takes 2.49 to 2.91 ms (one block per band 2.67 to 3.05, kernels of their own 2.56 to 2.89).
+// Atoms of more than 256 projectors take blocks of 1024 threads: with two atoms of 512 and 1 to 32 bands 0.69 to 0.86 ms
+// (one block of 256 threads per band 1.00 to 1.16, apart 0.90 to 1.06).
 constexpr int kStepProj = 4096;  // projectors whose p fits 64 KB of LDS
-template <bool RECUR, bool DIAG>
-__global__ __launch_bounds__(256) void k_overlap_step(int nproj, const int4* __restrict__ pinfo,
+constexpr int kStepAtom = 1024;  // largest atom
+template <bool RECUR, bool DIAG, int NTH>
+__global__ __launch_bounds__(NTH) void k_overlap_step(int nproj, int rows, int pieces, const int4* __restrict__ pinfo,
                                                       const double* __restrict__ D, const double* __restrict__ Q,
                                                       c128* dp, c128* qdp, long ldd, const c128* __restrict__ w,
                                                       long ldw, double s1, double c, const c128* __restrict__ cur,
                                                       long ldc, double s2, const c128* prev, long ldp, c128* out,
                                                       long ldo) {
   extern __shared__ c128 pcol[];
-  const long b = blockIdx.x;
-  for (int i = threadIdx.x; i < nproj; i += 256) {
+  const long b = blockIdx.x / pieces;
+  const int i0 = int(blockIdx.x - b * pieces) * rows;
+  auto bound = [&](int i) {  // the first atom that begins at row i or after it
+    if (i >= nproj) return nproj;
+    if constexpr (!DIAG) return i;
+    const int4 pi = pinfo[i];
+    return pi.x == i ? i : pi.x + pi.y;
+  };
+  const int r0 = bound(i0), r1 = bound(i0 + rows);
+  for (int i = r0 + threadIdx.x; i < r1; i += NTH) {
     const c128 x = cur[b * ldc + i];
     if constexpr (RECUR) {  // out = s1 (Q^-1 (D p - w) - c cur) - s2 prev (prev may be null, and may be out)
       const c128 d = dp[b * ldd + i], v = w[b * ldw + i];
@@ -130,19 +144,19 @@ __global__ __launch_bounds__(256) void k_overlap_step(int nproj, const int4* __r
         im -= s2 * y.y;
       }
       out[b * ldo + i] = c128{re, im};
-      if constexpr (DIAG) pcol[i] = c128{re, im};
+      if constexpr (DIAG) pcol[i - r0] = c128{re, im};
     } else {
-      pcol[i] = x;
+      pcol[i - r0] = x;
     }
   }
   if constexpr (DIAG) {
     __syncthreads();
-    for (int i = threadIdx.x; i < nproj; i += 256) {
+    for (int i = r0 + threadIdx.x; i < r1; i += NTH) {
       const int4 pi = pinfo[i];  // {atom's first row, block size, block offset, 0}
       const double* Drow = D + pi.z + long(i - pi.x) * pi.y;
       double re = 0.0, im = 0.0;
       for (int j = 0; j < pi.y; ++j) {
-        const c128 x = pcol[pi.x + j];
+        const c128 x = pcol[pi.x - r0 + j];
         re += Drow[j] * x.x;
         im += Drow[j] * x.y;
       }
@@ -153,7 +167,7 @@ __global__ __launch_bounds__(256) void k_overlap_step(int nproj, const int4* __r
   }
 }
 
-// qdp = Q^-1 dp (more projectors than kStepProj)
+// qdp = Q^-1 dp (atoms larger than kStepAtom)
 __global__ void k_overlap_scale(int nproj, int nb, const double* __restrict__ Q, const c128* __restrict__ dp,
                                 c128* __restrict__ qdp, long ldd) {
   const long total = long(nproj) * nb;
@@ -397,32 +411,47 @@ hipError_t block_diag_apply_c(int nproj, int nb, const int4* pinfo, const c128* 
                      out, ldo, accumulate ? 1 : 0);
   return hipGetLastError();
 }
-hipError_t overlap_open(int nproj, int nb, const int4* pinfo, const double* D, const double* Q, const c128* cur,
-                        long ldc, c128* dp, c128* qdp, long ldd, hipStream_t st) {
+namespace {
+// rows and pieces per band of k_overlap_step, and its launch
+template <bool RECUR, bool DIAG>
+hipError_t overlap_step(int nproj, int nb, int atom, const int4* pinfo, const double* D, const double* Q, c128* dp,
+                        c128* qdp, long ldd, const c128* w, long ldw, double s1, double c, const c128* cur, long ldc,
+                        double s2, const c128* prev, long ldp, c128* out, long ldo, hipStream_t st) {
+  int pieces = std::max(1, std::min((nproj + 255) / 256, 256 / nb));
+  if (DIAG) pieces = std::max(pieces, (nproj + kStepProj - atom - 1) / (kStepProj - atom));
+  const int rows = (nproj + pieces - 1) / pieces;
+  const size_t lds = DIAG ? size_t(std::min(rows + atom, nproj)) * sizeof(c128) : 0;
+  const dim3 grid(unsigned(nb) * unsigned(pieces));
+  if (DIAG && atom > 256)
+    hipLaunchKernelGGL((k_overlap_step<RECUR, DIAG, 1024>), grid, dim3(1024), lds, st, nproj, rows, pieces, pinfo, D, Q, dp,
+                       qdp, ldd, w, ldw, s1, c, cur, ldc, s2, prev, ldp, out, ldo);
+  else
+    hipLaunchKernelGGL((k_overlap_step<RECUR, DIAG, 256>), grid, dim3(256), lds, st, nproj, rows, pieces, pinfo, D, Q, dp,
+                       qdp, ldd, w, ldw, s1, c, cur, ldc, s2, prev, ldp, out, ldo);
+  return hipGetLastError();
+}
+}  // namespace
+hipError_t overlap_open(int nproj, int nb, int atom, const int4* pinfo, const double* D, const double* Q,
+                        const c128* cur, long ldc, c128* dp, c128* qdp, long ldd, hipStream_t st) {
   if (nproj <= 0 || nb <= 0) return hipSuccess;
-  if (nproj <= kStepProj) {
-    hipLaunchKernelGGL((k_overlap_step<false, true>), dim3(nb), dim3(256), size_t(nproj) * sizeof(c128), st, nproj, pinfo,
-                       D, Q, dp, qdp, ldd, nullptr, 0L, 0.0, 0.0, cur, ldc, 0.0, nullptr, 0L, nullptr, 0L);
-    return hipGetLastError();
-  }
+  if (atom <= kStepAtom)
+    return overlap_step<false, true>(nproj, nb, atom, pinfo, D, Q, dp, qdp, ldd, nullptr, 0L, 0.0, 0.0, cur, ldc, 0.0,
+                                     nullptr, 0L, nullptr, 0L, st);
   const hipError_t e = block_diag_apply(nproj, nb, pinfo, D, cur, ldc, dp, ldd, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_overlap_scale, dim3(nblocks(long(nproj) * nb)), dim3(256), 0, st, nproj, nb, Q, dp, qdp, ldd);
   return hipGetLastError();
 }
-hipError_t overlap_close(int nproj, int nb, const int4* pinfo, const double* D, const double* Q, c128* dp, c128* qdp,
-                         long ldd, const c128* w, long ldw, double s1, double c, const c128* cur, long ldc, double s2,
-                         const c128* prev, long ldp, c128* out, long ldo, bool next, hipStream_t st) {
+hipError_t overlap_close(int nproj, int nb, int atom, const int4* pinfo, const double* D, const double* Q, c128* dp,
+                         c128* qdp, long ldd, const c128* w, long ldw, double s1, double c, const c128* cur, long ldc,
+                         double s2, const c128* prev, long ldp, c128* out, long ldo, bool next, hipStream_t st) {
   if (nproj <= 0 || nb <= 0) return hipSuccess;
-  if (next && nproj <= kStepProj) {
-    hipLaunchKernelGGL((k_overlap_step<true, true>), dim3(nb), dim3(256), size_t(nproj) * sizeof(c128), st, nproj, pinfo,
-                       D, Q, dp, qdp, ldd, w, ldw, s1, c, cur, ldc, s2, prev, ldp, out, ldo);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL((k_overlap_step<true, false>), dim3(nb), dim3(256), 0, st, nproj, pinfo, D, Q, dp, qdp, ldd, w, ldw,
-                     s1, c, cur, ldc, s2, prev, ldp, out, ldo);
-  const hipError_t e = hipGetLastError();
-  return e != hipSuccess || !next ? e : overlap_open(nproj, nb, pinfo, D, Q, out, ldo, dp, qdp, ldd, st);
+  if (next && atom <= kStepAtom)
+    return overlap_step<true, true>(nproj, nb, atom, pinfo, D, Q, dp, qdp, ldd, w, ldw, s1, c, cur, ldc, s2, prev, ldp, out,
+                                    ldo, st);
+  const hipError_t e = overlap_step<true, false>(nproj, nb, atom, pinfo, D, Q, dp, qdp, ldd, w, ldw, s1, c, cur, ldc, s2,
+                                                 prev, ldp, out, ldo, st);
+  return e != hipSuccess || !next ? e : overlap_open(nproj, nb, atom, pinfo, D, Q, out, ldo, dp, qdp, ldd, st);
 }
 hipError_t diag_apply(int nproj, int nb, const double* d, const c128* in, long ldi, c128* out, long ldo,
                       hipStream_t st) {
