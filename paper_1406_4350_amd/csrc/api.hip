@@ -838,14 +838,14 @@ template <typename T> struct Ops {
       RnsOperand b;
       b.base = w.rB; b.third = w.rB + 2 * kRnsMods * plane;
       b.plane = b.third_plane = plane; b.ld = ld; b.inv = w.rinv + n0;
-      HIPCHK(rns_split_cols<double>(K, cnt, B + n0 * ldb, ldb, w.rscale + n0, w.rB, w.rB + 2 * kRnsMods * plane, nullptr,
+      HIPCHK(rns_split_cols<double>(K, cnt, B + n0 * ldb, ldb, w.rscale + n0, w.rB, w.rB + 2 * kRnsMods * plane, false,
                                     plane, ld, w.rflag + n0, 1, st));
       Epi<double> en = e;
       en.out += n0 * e.ldo;
       if (en.L) en.L += n0 * e.ldl;
       if (en.U) en.U += n0 * e.ldu;
       if (en.W) en.W += n0 * e.ldw;
-      HIPCHK(rns_product<double>(mode, M, cnt, K, A, b, w.rC, en, false, w.rflag + n0, st));
+      HIPCHK(rns_product<double>(mode, M, cnt, K, A, b, w.rC, en, w.rflag + n0, st));
     }
     HIPCHK(fp64(w.rflag));
     return CHEB_OK;
@@ -2462,7 +2462,7 @@ cheb_status cheb_set_projectors(cheb_plan p, const void* P, int ldp, const doubl
     if (p->rproj.base) {
       HIPCHK(rns_scale_cols<double>(p->npw, np, Pd, ldp, p->rproj.env, w.rscale, mut(p->rproj.inv), nullptr, w.rflag + 2,
                                     w.rflag + 1, st));
-      HIPCHK(rns_split_cols<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rproj.base), nullptr, mut(p->rproj.third),
+      HIPCHK(rns_split_cols<double>(p->npw, np, Pd, ldp, w.rscale, mut(p->rproj.base), mut(p->rproj.third), true,
                                     p->rproj.plane, p->rproj.ld, w.rflag, 0, st));
       HIPCHK(rns_flat_overlap(p->npw, p->rproj.env, w.rflat, st));
     }
@@ -2485,13 +2485,13 @@ cheb_status cheb_set_projectors(cheb_plan p, const void* P, int ldp, const doubl
       b.base += long(n0) * b.ld;
       b.inv += n0;
       const long plane = cnt * b.ld;
-      HIPCHK(rns_split_cols<double>(p->npw, cnt, Pd + long(n0) * ldp, ldp, w.rscale + n0, nullptr, w.rB, nullptr, plane,
+      HIPCHK(rns_split_cols<double>(p->npw, cnt, Pd + long(n0) * ldp, ldp, w.rscale + n0, nullptr, w.rB, false, plane,
                                     b.ld, w.rflag, 0, st));
       b.third = w.rB;
       b.third_plane = plane;
       Epi<double> ec = eg;
       ec.out += long(n0) * np;
-      HIPCHK(rns_product<double>(GEMM_CN, n0 + cnt, cnt, p->npw, p->rproj, b, w.rC, ec, false, w.rflag + 2 + n0, st));
+      HIPCHK(rns_product<double>(GEMM_CN, n0 + cnt, cnt, p->npw, p->rproj, b, w.rC, ec, w.rflag + 2 + n0, st));
     }
     HIPCHK(hermitian_lower(np, p->G, np, st));
   } else {

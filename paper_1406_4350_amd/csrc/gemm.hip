@@ -978,6 +978,7 @@ hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, c
                 const int* pred, GemmForm form) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (upper && M != N) return hipErrorInvalidValue;
+  if (role == ROLE_PROJECT ? mode != GEMM_CN : role == ROLE_BACKPROJECT && mode != GEMM_NN) return hipErrorInvalidValue;
   if constexpr (std::is_same<T, double>::value && std::is_same<EA, double>::value && std::is_same<EB, double>::value) {
     if (gemm_is_small(M, N, K)) {
       const long blocks = long((M + 15) / 16) * ((N + 15) / 16);
@@ -1030,19 +1031,19 @@ hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, c
       else if (ne == 1) go(modec, rolec, std::integral_constant<int, 1>{}, formc);
       else go(modec, rolec, std::integral_constant<int, 3>{}, formc);
     };
-    if constexpr (sizeof(T) == 8 && RO != 0) {
-      // real parts of conjugate products (projections, Grams), real right sides of plain ones (back-projection,
-      // rotation)
-      if (MO == GEMM_CN && form == FORM_RE) return by_ne(std::integral_constant<int, MO == GEMM_CN ? FORM_RE : FORM_FULL>{});
-      if (MO == GEMM_NN && form == FORM_B_REAL) return by_ne(std::integral_constant<int, MO == GEMM_NN ? FORM_B_REAL : FORM_FULL>{});
+    // real parts of projections and Grams, real right sides of back-projections
+    if constexpr (sizeof(T) == 8 && MO == GEMM_CN && (RO == ROLE_PROJECT || RO == ROLE_SUBSPACE)) {
+      if (form == FORM_RE) return by_ne(std::integral_constant<int, FORM_RE>{});
+    } else if constexpr (sizeof(T) == 8 && RO == ROLE_BACKPROJECT) {
+      if (form == FORM_B_REAL) return by_ne(std::integral_constant<int, FORM_B_REAL>{});
     }
     by_ne(std::integral_constant<int, FORM_FULL>{});
   };
   using CN = std::integral_constant<int, GEMM_CN>;
   using NNm = std::integral_constant<int, GEMM_NN>;
   switch (role) {
-    case ROLE_PROJECT: mode == GEMM_CN ? launch(CN{}, std::integral_constant<int, 1>{}) : launch(NNm{}, std::integral_constant<int, 1>{}); break;
-    case ROLE_BACKPROJECT: mode == GEMM_CN ? launch(CN{}, std::integral_constant<int, 2>{}) : launch(NNm{}, std::integral_constant<int, 2>{}); break;
+    case ROLE_PROJECT: launch(CN{}, std::integral_constant<int, ROLE_PROJECT>{}); break;
+    case ROLE_BACKPROJECT: launch(NNm{}, std::integral_constant<int, ROLE_BACKPROJECT>{}); break;
     case ROLE_SUBSPACE: mode == GEMM_CN ? launch(CN{}, std::integral_constant<int, 3>{}) : launch(NNm{}, std::integral_constant<int, 3>{}); break;
     default: mode == GEMM_CN ? launch(CN{}, std::integral_constant<int, 0>{}) : launch(NNm{}, std::integral_constant<int, 0>{}); break;
   }
@@ -1186,8 +1187,8 @@ hipError_t gemm_h(GemmMode mode, int M, int N, int K, const HalfPlanes& A, const
     if (tb == 128) launch(std::integral_constant<int, 128>{}, modec, rolec);
     else launch(std::integral_constant<int, 64>{}, modec, rolec);
   };
-  if (role == ROLE_BACKPROJECT) mode == GEMM_CN ? by_tile(CN{}, R2{}) : by_tile(NNm{}, R2{});
-  else mode == GEMM_CN ? by_tile(CN{}, R1{}) : by_tile(NNm{}, R1{});
+  if (mode == GEMM_CN) by_tile(CN{}, R1{});
+  else by_tile(NNm{}, R2{});
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !use_part) return e;
   const long total = long(M) * N;
@@ -1259,8 +1260,8 @@ hipError_t gemm_h_pre(GemmMode mode, int M, int N, int K, const HalfPlanes& A, c
     if (tb == 128) launch(std::integral_constant<int, 128>{}, modec, rolec);
     else launch(std::integral_constant<int, 64>{}, modec, rolec);
   };
-  if (role == ROLE_BACKPROJECT) mode == GEMM_CN ? by_tile(CN{}, R2{}) : by_tile(NNm{}, R2{});
-  else mode == GEMM_CN ? by_tile(CN{}, R1{}) : by_tile(NNm{}, R1{});
+  if (mode == GEMM_CN) by_tile(CN{}, R1{});
+  else by_tile(NNm{}, R2{});
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !use_part) return e;
   const long total = long(M) * N;
@@ -1295,12 +1296,8 @@ hipError_t split_planes(const c128* X, long ldx, int rows_x, int cols_x, bool tr
   return hipGetLastError();
 }
 
-template hipError_t gemm_h<float, float>(GemmMode, int, int, int, const HalfPlanes&, const c64*, long, const float*,
-                                         const Epi<float>&, int, c128*, hipStream_t, GemmRole);
 template hipError_t gemm_h<float, double>(GemmMode, int, int, int, const HalfPlanes&, const c64*, long, const float*,
                                           const Epi<double>&, int, c128*, hipStream_t, GemmRole);
-template hipError_t gemm_h<double, float>(GemmMode, int, int, int, const HalfPlanes&, const c128*, long,
-                                          const float*, const Epi<float>&, int, c128*, hipStream_t, GemmRole);
 template hipError_t gemm_h_pre<float>(GemmMode, int, int, int, const HalfPlanes&, const HalfPlanes&, const float*,
                                        const Epi<float>&, int, c128*, hipStream_t, GemmRole);
 template hipError_t gemm_h_pre<double>(GemmMode, int, int, int, const HalfPlanes&, const HalfPlanes&, const float*,

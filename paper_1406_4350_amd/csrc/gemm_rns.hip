@@ -254,8 +254,7 @@ __device__ __forceinline__ Digits digits(double y) {
   const double f = rint(q * 0x1p-16);
   return {int(h), int(g), int(f), int(rint(fma(-f, 0x1p16, q)))};
 }
-// residues modulo kP[l] of NV complex integers, as bytes packed by four: re, im and the sums re + im, re - im (each
-// third plane only where asked for). |sum of digits times powers| <= split_max < 2^24, of which one step leaves at most
+// residues modulo kP[l] of NV complex integers, as bytes packed by four: re, im and re + im or (DIFF) re - im. |sum of digits times powers| <= split_max < 2^24, of which one step leaves at most
 // kResMax modulo the odd numbers (p / 2 + 1/2 + 2^-24 split_max: 121 modulo 241).
 constexpr int split_max(int p) {
   int s = 1 << 15;
@@ -266,9 +265,9 @@ constexpr int split_max(int p) {
   return s;
 }
 constexpr int kResMax = 121;
-template <int NV, bool SUM, bool DIFF>
+template <int NV, bool DIFF>
 __device__ __forceinline__ void residues(int l, const Digits (&re)[NV], const Digits (&im)[NV], unsigned (&pr)[NV / 4],
-                                         unsigned (&pi)[NV / 4], unsigned (&ps)[NV / 4], unsigned (&pd)[NV / 4]) {
+                                         unsigned (&pi)[NV / 4], unsigned (&pt)[NV / 4]) {
   const int p = kP[l];
   const float inv = 1.0f / float(p);
   const int c3 = sym_mod(1ll << 48, p), c2 = sym_mod(1ll << 32, p), c1 = sym_mod(1ll << 16, p);
@@ -284,23 +283,20 @@ __device__ __forceinline__ void residues(int l, const Digits (&re)[NV], const Di
     }
     pr[g] = pack4(unsigned(r[0]), unsigned(r[1]), unsigned(r[2]), unsigned(r[3]));
     pi[g] = pack4(unsigned(i[0]), unsigned(i[1]), unsigned(i[2]), unsigned(i[3]));
-    if constexpr (SUM)
-      ps[g] = pack4(mod_byte(r[0] + i[0], p, inv), mod_byte(r[1] + i[1], p, inv), mod_byte(r[2] + i[2], p, inv),
-                    mod_byte(r[3] + i[3], p, inv));
-    if constexpr (DIFF)
-      pd[g] = pack4(mod_byte(r[0] - i[0], p, inv), mod_byte(r[1] - i[1], p, inv), mod_byte(r[2] - i[2], p, inv),
-                    mod_byte(r[3] - i[3], p, inv));
+    int t[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t[j] = DIFF ? r[j] - i[j] : r[j] + i[j];
+    pt[g] = pack4(mod_byte(t[0], p, inv), mod_byte(t[1], p, inv), mod_byte(t[2], p, inv), mod_byte(t[3], p, inv));
   }
 }
 
 // Vectors contiguous along k (columns of B, columns of A under a conjugate transpose): 4 k per thread, so a wave
 // reads 4 KB and writes 256 bytes of each plane. Bound by memory: 16 bytes read, 3 kRnsMods written per element. A column
 // n with flag[n fs] set is written as zeros.
-template <typename E, bool SUM, bool DIFF>
+template <typename E, bool DIFF>
 __global__ __launch_bounds__(256) void k_rns_split(long K, const cx<E>* __restrict__ B, long ldb,
                                                    const double* __restrict__ scale, int8_t* __restrict__ base,
-                                                   int8_t* __restrict__ sum, int8_t* __restrict__ diff, long plane,
-                                                   long ld, const int* __restrict__ flag, int fs) {
+                                                   int8_t* __restrict__ third, long plane, long ld, const int* __restrict__ flag, int fs) {
   const long k = (long(blockIdx.x) * 256 + threadIdx.x) * 4;
   const long n = blockIdx.y;
   if (k >= ld) return;
@@ -318,14 +314,13 @@ __global__ __launch_bounds__(256) void k_rns_split(long K, const cx<E>* __restri
   const long at = n * ld + k;
 #pragma unroll
   for (int l = 0; l < L; ++l) {
-    unsigned pr[1], pi[1], ps[1], pd[1];
-    residues<4, SUM, DIFF>(l, re, im, pr, pi, ps, pd);
+    unsigned pr[1], pi[1], pt[1];
+    residues<4, DIFF>(l, re, im, pr, pi, pt);
     if (base) {
       *reinterpret_cast<unsigned*>(base + (2 * l) * plane + at) = pr[0];
       *reinterpret_cast<unsigned*>(base + (2 * l + 1) * plane + at) = pi[0];
     }
-    if constexpr (SUM) *reinterpret_cast<unsigned*>(sum + l * plane + at) = ps[0];
-    if constexpr (DIFF) *reinterpret_cast<unsigned*>(diff + l * plane + at) = pd[0];
+    *reinterpret_cast<unsigned*>(third + l * plane + at) = pt[0];
   }
 }
 
@@ -352,8 +347,8 @@ __global__ __launch_bounds__(256) void k_rns_split_rows(long M, int K, const cx<
   const long at = m * ld + k0;
 #pragma unroll
   for (int l = 0; l < L; ++l) {
-    unsigned pr[4], pi[4], ps[4], pd[4];
-    residues<16, true, false>(l, re, im, pr, pi, ps, pd);
+    unsigned pr[4], pi[4], ps[4];
+    residues<16, false>(l, re, im, pr, pi, ps);
     *reinterpret_cast<uint4*>(base + (2 * l) * plane + at) = uint4{pr[0], pr[1], pr[2], pr[3]};
     *reinterpret_cast<uint4*>(base + (2 * l + 1) * plane + at) = uint4{pi[0], pi[1], pi[2], pi[3]};
     *reinterpret_cast<uint4*>(sum + l * plane + at) = uint4{ps[0], ps[1], ps[2], ps[3]};
@@ -388,14 +383,14 @@ __device__ __forceinline__ int stage_at(int r, int c) { return r * RK + ((c ^ ((
 // the next output tile's operands during the last k tiles of this one left too few registers for the reduction of the
 // accumulators and took 31 instead of 22 us per tile at 1024 k.
 __global__ __launch_bounds__(256, 1) void k_rns_gemm(int M, int N, int nt, RnsOperand A, RnsOperand B,
-                                                     int8_t* __restrict__ C, long ldc, long zc, int upper,
+                                                     int8_t* __restrict__ C, long ldc, long zc,
                                                      const int* __restrict__ flag) {
   __shared__ __align__(16) int8_t S0[kStageBytes], S1[kStageBytes];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tm = (M + RT - 1) / RT, tn = (N + RT - 1) / RT;
   // one contiguous run of tiles per XCD, the N tile fastest: the blocks an XCD holds at once share their operands in L2
   int bx, by, z;
-  gemm_tile_of(blockIdx.x, gridDim.x, tm, tn, upper ? kUpperTiles : 1, bx, by, z);
+  gemm_tile_of(blockIdx.x, gridDim.x, tm, tn, 1, bx, by, z);
   const int m0 = bx * RT, n0 = by * RT, l = z / 3, c3 = z - 3 * l;
   bool some = false;  // a column of the tile takes this route
 #pragma unroll
@@ -535,11 +530,10 @@ static_assert(kStageBytes == 4 * 128 * 128, "the output bytes of a block fill on
 template <typename EO>
 __global__ __launch_bounds__(256) void k_rns_finish(int M, int N, const int8_t* __restrict__ C, long ldc, long zc,
                                                     const double* __restrict__ ia, const double* __restrict__ ib,
-                                                    int sg, int upper, Epi<EO> epi, const int* __restrict__ flag) {
+                                                    int sg, Epi<EO> epi, const int* __restrict__ flag) {
   __shared__ c128 buf[1024];
   const long mb = long(blockIdx.x) * 1024, n = blockIdx.y;
   if (flag[n]) return;
-  if (upper && mb / RT > n / RT) return;
   const int t = threadIdx.x;
   const long m4 = mb + 4 * t;
   if (m4 < ldc) {
@@ -569,7 +563,7 @@ __global__ __launch_bounds__(256) void k_rns_finish(int M, int N, const int8_t* 
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const long m = mb + 256 * j + t;
-    if (m < M && !(upper && m / RT > n / RT)) {
+    if (m < M) {
       const double s = ia[m];
       const c128 v = buf[256 * j + t];
       epi_store(epi, m, n, v.x * s * sb, v.y * s * sb);
@@ -671,20 +665,15 @@ hipError_t rns_flat_overlap(long K, const double* env, double* out, hipStream_t 
 }
 
 template <typename E>
-hipError_t rns_split_cols(long K, int N, const cx<E>* B, long ldb, const double* scale, int8_t* base, int8_t* sum,
-                          int8_t* diff, long plane, long ld, const int* flag, int fs, hipStream_t st) {
+hipError_t rns_split_cols(long K, int N, const cx<E>* B, long ldb, const double* scale, int8_t* base, int8_t* third,
+                          bool diff, long plane, long ld, const int* flag, int fs, hipStream_t st) {
   if (N <= 0) return hipSuccess;
-  if (K <= 0 || N > 65535 || ld != rns_ld(K) || plane < N * ld || !(sum || diff)) return hipErrorInvalidValue;
+  if (K <= 0 || N > 65535 || ld != rns_ld(K) || plane < N * ld || !third) return hipErrorInvalidValue;
   const dim3 grid(unsigned((ld / 4 + 255) / 256), unsigned(N));
-  if (sum && diff)
-    hipLaunchKernelGGL((k_rns_split<E, true, true>), grid, dim3(256), 0, st, K, B, ldb, scale, base, sum, diff, plane,
-                       ld, flag, fs);
-  else if (sum)
-    hipLaunchKernelGGL((k_rns_split<E, true, false>), grid, dim3(256), 0, st, K, B, ldb, scale, base, sum, diff, plane,
-                       ld, flag, fs);
+  if (diff)
+    hipLaunchKernelGGL((k_rns_split<E, true>), grid, dim3(256), 0, st, K, B, ldb, scale, base, third, plane, ld, flag, fs);
   else
-    hipLaunchKernelGGL((k_rns_split<E, false, true>), grid, dim3(256), 0, st, K, B, ldb, scale, base, sum, diff, plane,
-                       ld, flag, fs);
+    hipLaunchKernelGGL((k_rns_split<E, false>), grid, dim3(256), 0, st, K, B, ldb, scale, base, third, plane, ld, flag, fs);
   return hipGetLastError();
 }
 
@@ -700,18 +689,17 @@ hipError_t rns_split_rows(long M, int K, const cx<E>* A, long lda, const double*
 
 template <typename EO>
 hipError_t rns_product(GemmMode mode, int M, int N, int K, const RnsOperand& A, const RnsOperand& B, int8_t* C,
-                       const Epi<EO>& epi, bool upper, const int* flag, hipStream_t st) {
+                       const Epi<EO>& epi, const int* flag, hipStream_t st) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  if (K <= 0 || K > kRnsMaxK || N > 65535 || A.ld != rns_ld(K) || B.ld != A.ld || (upper && M != N)) return hipErrorInvalidValue;
+  if (K <= 0 || K > kRnsMaxK || N > 65535 || A.ld != rns_ld(K) || B.ld != A.ld) return hipErrorInvalidValue;
   const long ldc = rns_ldc(M), zc = ldc * N;
   const long tm = (M + RT - 1) / RT, tn = (N + RT - 1) / RT;
-  const long tiles = upper ? tm * (tm + 1) / 2 : tm * tn;
-  hipLaunchKernelGGL(k_rns_gemm, dim3(unsigned(tiles * 3 * L)), dim3(256), 0, st, M, N, int(A.ld / RK), A, B, C, ldc,
-                     zc, upper ? 1 : 0, flag);
+  hipLaunchKernelGGL(k_rns_gemm, dim3(unsigned(tm * tn * 3 * L)), dim3(256), 0, st, M, N, int(A.ld / RK), A, B, C, ldc,
+                     zc, flag);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_rns_finish<EO>), dim3(unsigned((M + 1023) / 1024), unsigned(N)), dim3(256), 0, st, M, N, C, ldc,
-                     zc, A.inv, B.inv, mode == GEMM_CN ? -1 : 1, upper ? 1 : 0, epi, flag);
+                     zc, A.inv, B.inv, mode == GEMM_CN ? -1 : 1, epi, flag);
   return hipGetLastError();
 }
 
@@ -721,12 +709,12 @@ hipError_t rns_product(GemmMode mode, int M, int N, int K, const RnsOperand& A, 
   template hipError_t rns_scale_rows<E>(long, int, const cx<E>*, long, double*, double*, double*, const double*,      \
                                         double*, int*, hipStream_t);                                                  \
   template hipError_t rns_row_envelope<E>(long, int, const cx<E>*, long, const double*, double*, hipStream_t);        \
-  template hipError_t rns_split_cols<E>(long, int, const cx<E>*, long, const double*, int8_t*, int8_t*, int8_t*, long, \
+  template hipError_t rns_split_cols<E>(long, int, const cx<E>*, long, const double*, int8_t*, int8_t*, bool, long,    \
                                         long, const int*, int, hipStream_t);                                          \
   template hipError_t rns_split_rows<E>(long, int, const cx<E>*, long, const double*, int8_t*, int8_t*, long, long,    \
                                         const int*, hipStream_t);                                                     \
   template hipError_t rns_product<E>(GemmMode, int, int, int, const RnsOperand&, const RnsOperand&, int8_t*,          \
-                                     const Epi<E>&, bool, const int*, hipStream_t);
+                                     const Epi<E>&, const int*, hipStream_t);
 INST(double)
 #undef INST
 

@@ -18,10 +18,10 @@ template <typename E> struct Epi {
 
 enum GemmMode { GEMM_CN = 0, GEMM_NN = 1 };
 // FORM_RE: the caller keeps only the real part of conj(A)^T B (the imaginary part of the result is 0); FORM_B_REAL: the
-// imaginary part of B in A B is 0 or to be taken as 0. Two real products per complex one instead of three; taken by the
-// tiled FP64 products of the matching mode, ignored (the full product) by the others.
+// imaginary part of B in A B is 0 or to be taken as 0. Two real products per complex one instead of three; FORM_RE is taken
+// by the tiled FP64 projections and Grams, FORM_B_REAL by the back-projections, both ignored (the full product) elsewhere.
 enum GemmForm { FORM_FULL = 0, FORM_RE = 1, FORM_B_REAL = 2 };
-// separate kernel instances per use, so that profiles tell them apart
+// separate kernel instances per use, so that profiles tell them apart; projections are GEMM_CN, back-projections GEMM_NN
 enum GemmRole { ROLE_SMALL = 0, ROLE_PROJECT = 1, ROLE_BACKPROJECT = 2, ROLE_SUBSPACE = 3 };
 
 // C (M x N) = op(A) B, complex, column-major operands.
@@ -140,21 +140,21 @@ hipError_t rns_scale_rows(long M, int K, const cx<E>* A, long lda, double* scale
 template <typename E>
 hipError_t rns_row_envelope(long M, int K, const cx<E>* A, long lda, const double* rnorm, double* env, hipStream_t st);
 hipError_t rns_flat_overlap(long K, const double* env, double* out, hipStream_t st);
-// Residue planes of scaled columns (row n of a plane = column n; base null: not written) with the sums re + im, the
-// differences re - im or both (null: not written), zeros for a column n with flag[n fs] set, and of scaled rows (row m =
-// row m) with the sums (nothing if *flag is set).
+// Residue planes of scaled columns (row n of a plane = column n; base null: not written) with the sums re + im or, with
+// diff, the differences re - im as third planes, zeros for a column n with flag[n fs] set, and of scaled rows (row m = row
+// m) with the sums (nothing if *flag is set).
 template <typename E>
-hipError_t rns_split_cols(long K, int N, const cx<E>* B, long ldb, const double* scale, int8_t* base, int8_t* sum,
-                          int8_t* diff, long plane, long ld, const int* flag, int fs, hipStream_t st);
+hipError_t rns_split_cols(long K, int N, const cx<E>* B, long ldb, const double* scale, int8_t* base, int8_t* third,
+                          bool diff, long plane, long ld, const int* flag, int fs, hipStream_t st);
 template <typename E>
 hipError_t rns_split_rows(long M, int K, const cx<E>* A, long lda, const double* scale, int8_t* base, int8_t* sum,
                           long plane, long ld, const int* flag, hipStream_t st);
 // out (M x N) = conj(A)^T B (GEMM_CN, A's third planes the differences) or A B (GEMM_NN, the sums; B's always the
-// sums) with the epilogue of gemm(), the columns with flag[n] set left alone; upper as there. C: 3 kRnsMods N rns_ldc(M)
-// bytes of scratch. N <= 65535.
+// sums) with the epilogue of gemm(), the columns with flag[n] set left alone. C: 3 kRnsMods N rns_ldc(M) bytes of
+// scratch. N <= 65535.
 template <typename EO>
 hipError_t rns_product(GemmMode mode, int M, int N, int K, const RnsOperand& A, const RnsOperand& B, int8_t* C,
-                       const Epi<EO>& epi, bool upper, const int* flag, hipStream_t st);
+                       const Epi<EO>& epi, const int* flag, hipStream_t st);
 
 // ---- FFT passes (per batch of bands) -------------------------------------------------------------------
 struct FftGeom {
