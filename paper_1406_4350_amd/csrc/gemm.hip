@@ -55,8 +55,8 @@ template <typename E> int epi_slots(Epi<E>& e) {
 // Epilogue of one wave's NI x NJ MFMA blocks of 16 x 16 (T accumulators, the combined real and imaginary parts in
 // cr, ci; rows of accumulator v given by row_of(v); column block j scaled by scale[j]). The NE operands of block
 // b + 1 are requested, at clamped in-range indices, before the stores of block b, so that every thread keeps a
-// block of loads in flight instead of waiting on each element in turn. pred: only columns n with pred[n] set are stored.
-template <int NE, int NI, int NJ, typename E, typename Acc, typename RowOf>
+// block of loads in flight instead of waiting on each element in turn. PRED: only columns n with pred[n] set are stored.
+template <int NE, bool PRED = false, int NI, int NJ, typename E, typename Acc, typename RowOf>
 __device__ __forceinline__ void epi_blocks(const Epi<E>& epi, int M, int N, long mb, long nb, int li,
                                            const Acc (&cr)[NI][NJ], const Acc (&ci)[NI][NJ],
                                            const double (&scale)[NJ], RowOf row_of, const int* pred = nullptr) {
@@ -83,7 +83,8 @@ __device__ __forceinline__ void epi_blocks(const Epi<E>& epi, int M, int N, long
       if (b + 1 < NBLK) eload(b + 1, buf[(b + 1) & 1]);
     const int i = b / NJ, j = b % NJ;
     const long n = nb + 16 * j + li;
-    const bool keep = n < N && (!pred || pred[n]);
+    bool keep = n < N;
+    if constexpr (PRED) keep = keep && pred[n];
     const double f = epi.alpha * scale[j];
     // values of all four elements first, then the guarded stores: a value computed only under the guard would
     // let the compiler move its loads there and wait on them
@@ -126,7 +127,7 @@ __device__ __forceinline__ void epi_blocks(const Epi<E>& epi, int M, int N, long
 // ROLE only separates kernel names per use (projection, back-projection, small, subspace) for profiling.
 constexpr int GK = 16;
 static_assert(BK % GK == 0, "splits are whole tiles");
-template <typename T, typename EA, typename EB, typename EO, int MODE, int ROLE, int NE, int FORM>
+template <typename T, typename EA, typename EB, typename EO, int MODE, int ROLE, int NE, int FORM, bool PRED>
 __global__ __launch_bounds__(NT, 2) void k_gemm(int M, int N, int K, int kchunk, const cx<EA>* __restrict__ A,
                                              long lda, const cx<EB>* __restrict__ B, long ldb, Epi<EO> epi,
                                              c128* __restrict__ part, int grp,
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(NT, 2) void k_gemm(int M, int N, int K, int kchunk,
   gemm_tile_of(blockIdx.x, gridDim.x, (M + BM - 1) / BM, (N + BN - 1) / BN, grp, bx, by, bz);
   const long m0 = long(bx) * BM, n0 = long(by) * BN;
   static_assert(BN == 64, "a lane per column");
-  if (pred && !__any(n0 + lane < N && pred[min(n0 + lane, long(N) - 1)])) return;
+  if (PRED && !__any(n0 + lane < N && pred[min(n0 + lane, long(N) - 1)])) return;
   const int kbeg = bz * kchunk;
   const int kend = min(K, kbeg + kchunk);
   const int nt = (kend - kbeg + GK - 1) / GK;
@@ -311,7 +312,7 @@ __global__ __launch_bounds__(NT, 2) void k_gemm(int M, int N, int K, int kchunk,
         }
   } else {
     const double one[2] = {1.0, 1.0};
-    epi_blocks<NE>(epi, M, N, m0 + wm, n0 + wn, li, cr, ci, one, row_of, pred);
+    epi_blocks<NE, PRED>(epi, M, N, m0 + wm, n0 + wn, li, cr, ci, one, row_of, pred);
   }
 }
 
@@ -489,7 +490,7 @@ template <int TB> struct HTile {
 
 // The 16x16x32 FP16 MFMA takes, in lane l, row l % 16 of A and column l % 16 of B at k = 8 (l / 16) ...
 // 8 (l / 16) + 7, and returns row 4 (l / 16) + v, column l % 16 in accumulator element v.
-// BPRE: B arrives as pre-split planes Bp [4][brows][bld] (see split_columns) and is copied to LDS as it is.
+// BPRE: B arrives as pre-split planes Bp [4][brows][bld] (see scale_split_columns) and is copied to LDS as it is.
 template <int TB, typename EB, typename EO, int MODE, int ROLE, int NE, bool BPRE>
 __global__ __launch_bounds__(HTile<TB>::NT) void k_gemm_h(int M, int N, int K, int kchunk,
                                                            const _Float16* __restrict__ Ap, long arows, long ald,
@@ -979,6 +980,8 @@ hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, c
   if (M <= 0 || N <= 0) return hipSuccess;
   if (upper && M != N) return hipErrorInvalidValue;
   if (role == ROLE_PROJECT ? mode != GEMM_CN : role == ROLE_BACKPROJECT && mode != GEMM_NN) return hipErrorInvalidValue;
+  constexpr bool kPred = std::is_same<T, double>::value && std::is_same<EA, double>::value && std::is_same<EB, double>::value;
+  if (pred && !(kPred && form == FORM_FULL && (role == ROLE_PROJECT || role == ROLE_BACKPROJECT))) return hipErrorInvalidValue;
   if constexpr (std::is_same<T, double>::value && std::is_same<EA, double>::value && std::is_same<EB, double>::value) {
     if (gemm_is_small(M, N, K)) {
       const long blocks = long((M + 15) / 16) * ((N + 15) / 16);
@@ -1018,26 +1021,32 @@ hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, c
   c128* pp = use_part ? part : nullptr;
   Epi<EO> en = epi;
   const int ne = epi_slots(en);
-  auto go = [&](auto modec, auto rolec, auto nec, auto formc) {
+  auto go = [&](auto modec, auto rolec, auto nec, auto formc, auto predc) {
     constexpr int MO = decltype(modec)::value, RO = decltype(rolec)::value, NEC = decltype(nec)::value,
                   FO = decltype(formc)::value;
-    hipLaunchKernelGGL((k_gemm<T, EA, EB, EO, MO, RO, NEC, FO>), grid, dim3(NT), 0, st, M, N, K, kchunk, A, lda, B, ldb,
+    constexpr bool PR = decltype(predc)::value;
+    hipLaunchKernelGGL((k_gemm<T, EA, EB, EO, MO, RO, NEC, FO, PR>), grid, dim3(NT), 0, st, M, N, K, kchunk, A, lda, B, ldb,
                        en, pp, grp, pred);
   };
   auto launch = [&](auto modec, auto rolec) {
     constexpr int MO = decltype(modec)::value, RO = decltype(rolec)::value;
-    auto by_ne = [&](auto formc) {
-      if (ne == 0 || use_part) go(modec, rolec, std::integral_constant<int, 0>{}, formc);
-      else if (ne == 1) go(modec, rolec, std::integral_constant<int, 1>{}, formc);
-      else go(modec, rolec, std::integral_constant<int, 3>{}, formc);
+    auto by_ne = [&](auto formc, auto predc) {
+      if (ne == 0 || use_part) go(modec, rolec, std::integral_constant<int, 0>{}, formc, predc);
+      else if (ne == 1) go(modec, rolec, std::integral_constant<int, 1>{}, formc, predc);
+      else go(modec, rolec, std::integral_constant<int, 3>{}, formc, predc);
     };
+    // the FP64 side of the INT8 products
+    if constexpr (std::is_same<EA, double>::value && std::is_same<EB, double>::value &&
+                  (RO == ROLE_PROJECT || RO == ROLE_BACKPROJECT)) {
+      if (pred) return by_ne(std::integral_constant<int, FORM_FULL>{}, std::true_type{});
+    }
     // real parts of projections and Grams, real right sides of back-projections
     if constexpr (sizeof(T) == 8 && MO == GEMM_CN && (RO == ROLE_PROJECT || RO == ROLE_SUBSPACE)) {
-      if (form == FORM_RE) return by_ne(std::integral_constant<int, FORM_RE>{});
+      if (form == FORM_RE) return by_ne(std::integral_constant<int, FORM_RE>{}, std::false_type{});
     } else if constexpr (sizeof(T) == 8 && RO == ROLE_BACKPROJECT) {
-      if (form == FORM_B_REAL) return by_ne(std::integral_constant<int, FORM_B_REAL>{});
+      if (form == FORM_B_REAL) return by_ne(std::integral_constant<int, FORM_B_REAL>{}, std::false_type{});
     }
-    by_ne(std::integral_constant<int, FORM_FULL>{});
+    by_ne(std::integral_constant<int, FORM_FULL>{}, std::false_type{});
   };
   using CN = std::integral_constant<int, GEMM_CN>;
   using NNm = std::integral_constant<int, GEMM_NN>;

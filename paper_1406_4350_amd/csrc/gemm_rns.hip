@@ -377,7 +377,7 @@ __device__ __forceinline__ int stage_at(int r, int c) { return r * RK + ((c ^ ((
 // 128 k. While tile t is multiplied, tile t + 1 goes from registers to the other stage and tile t + 2 is requested
 // from memory, one 16-byte access behind each MFMA (sched_group_barrier), and the fragments of the next 32 k are read
 // one step ahead, across the one barrier of the tile: the MFMAs never wait on a whole group of loads. Measured at
-// 3328 x 512 x 32768, 45 products: 2070 TOP/s against 1890 without the two stages as separate arrays (the compiler
+// 3328 x 512 x 32768, 45 products (15 moduli): 2070 TOP/s against 1890 without the two stages as separate arrays (the compiler
 // then orders reads behind writes), 1560 without the interleaving, and 3100 for the MFMAs alone: power is
 // the limit (matrix cores 70% busy at 1.5 GHz). Loads straight to LDS measured 5% slower; persistent blocks that request
 // the next output tile's operands during the last k tiles of this one left too few registers for the reduction of the

@@ -33,7 +33,8 @@ enum GemmRole { ROLE_SMALL = 0, ROLE_PROJECT = 1, ROLE_BACKPROJECT = 2, ROLE_SUB
 // upper = true (M = N, a Hermitian result): only the 64 x 64 output tiles with row tile <= column tile are
 // computed (the others are not written; hermitian_lower fills them), splits from gemm_upper_splits.
 // pred (device, N ints): only the columns n with pred[n] not 0 are computed (the others took rns_product;
-// hipErrorInvalidValue at the sizes of the small GEMM, which have no other route).
+// full FP64 projections and back-projections; hipErrorInvalidValue elsewhere and at the sizes of the small GEMM, which
+// have no other route).
 template <typename T, typename EA, typename EB, typename EO>
 hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, const cx<EB>* B, long ldb,
                 const Epi<EO>& epi, int splits, c128* part, hipStream_t st, GemmRole role = ROLE_SMALL,
@@ -73,7 +74,8 @@ template <typename E>
 hipError_t scale_split_columns(int K, int N, const cx<E>* B, long ldb, float* bscale, _Float16* planes, long pld,
                                hipStream_t st);
 // gemm_h with B given as such planes (Bp.rows = N, Bp.ld = pld, Bp.inv_scale unused); splits > 1 sums split-K
-// partials in part as gemm_h does (same results as gemm_h with the same splits)
+// partials in part as gemm_h does. The products are those of gemm_h; its 64 x 64 tiles sum them in the same order, the
+// 128 x 128 tiles (k_gemm_hp) in another, so that results agree to the rounding of the FP32 sums.
 template <typename EO>
 hipError_t gemm_h_pre(GemmMode mode, int M, int N, int K, const HalfPlanes& A, const HalfPlanes& Bp,
                       const float* bscale, const Epi<EO>& epi, int splits, c128* part, hipStream_t st, GemmRole role);

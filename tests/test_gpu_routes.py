@@ -157,6 +157,27 @@ def test_shrinking_blocks_keep_the_route(problem, nb):
         assert _rel(Y[some], Z) < 1e-11
 
 
+def test_int8_route_in_a_graph(problem):
+    """S X on INT8 captured once and replayed on new inputs, with a band that is unfit in some of them (its flag is set on
+    the device): the bits of the eager call each time."""
+    pb, plan, _, _ = problem
+    X, Y = _block(pb.npw, 512, 41), torch.empty((512, pb.npw), dtype=torch.complex128, device="cuda")
+    plan.apply_S(X, Y)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        assert _took(plan, lambda: plan.apply_S(X, Y)) == [{"int8": 1}, {"int8": 1}]
+    for k in range(4):
+        X.copy_(_block(pb.npw, 512, 42 + k))
+        if k % 2:
+            X[100 + k, 3] = float("nan")
+        graph.replay()
+        torch.cuda.synchronize()
+        eager = plan.apply_S(X)
+        assert torch.equal(Y.isnan(), eager.isnan()) and torch.equal(Y.nan_to_num(0.0), eager.nan_to_num(0.0))
+        assert int(Y.isnan().any(1).sum()) == k % 2
+
+
 def test_plan_without_residue_planes(problem):
     """A plan over the smaller buffer holds no planes, neither do its workspaces, and its products are FP64 ones, equal
     to the INT8 ones up to rounding; a buffer one byte short is refused."""
