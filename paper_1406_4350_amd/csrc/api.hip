@@ -332,6 +332,7 @@ struct Ws {
   int* rflag = nullptr;
   double *rscale = nullptr, *rinv = nullptr, *rrow = nullptr, *rflat = nullptr, *rspare = nullptr;
   int8_t *rB = nullptr, *rC = nullptr;
+  c128* rpart = nullptr;  // split-K partials of the FP64 side of a projection
   size_t rB_bytes = 0, rC_bytes = 0;
   void* Xs = nullptr;   // band-sorted copy for the per-band degree filter
   int* lidx = nullptr;  // its gather / scatter indices (3 nb)
@@ -361,6 +362,11 @@ int fft_batch_for(const cheb_plan_s* p, int nb) {
 }
 
 cheb_status solver_query(cheb_plan p, int op, int nb, size_t* bytes);
+
+// K splits of the FP64 product behind a projection on INT8: those of a product of 64 bands, since most often a band or
+// none is left to it (512 bands, 57 777 plane waves, 1664 projectors, one band alone flagged: S X 7.3 instead of 9.3 ms
+// with the 2 splits of 512 bands; all of them 10.7 instead of 11.3, without INT8 10.9)
+int rns_fp64_splits(const cheb_plan_s* p) { return gemm_pick_splits(p->nproj, 64, p->npw); }
 
 // whether P^H P takes the INT8 matrix cores, by pieces
 bool rns_gram(const cheb_plan_s* p) {
@@ -555,11 +561,13 @@ cheb_status ws_layout(cheb_plan p, int op, int nb, void* base, Ws* w) {
       w->rinv = b.take<double>(nb);
       w->rB = b.take<int8_t>(w->rB_bytes);
       w->rC = b.take<int8_t>(w->rC_bytes);
+      w->rpart = b.take<c128>(size_t(rns_fp64_splits(p)) * pp);
       // cheb_apply_H_noalloc lends a fixed scratch: what fits it without these buffers is computed without them,
       // there and in cheb_apply_H alike
       if (op == CHEB_OP_H && before <= kNoAllocScratchBytes && b.off > kNoAllocScratchBytes) {
         b.off = before;
         w->rB = w->rC = nullptr;
+        w->rpart = nullptr;
         w->rB_bytes = w->rC_bytes = 0;
       }
     }
@@ -873,7 +881,7 @@ template <typename T> struct Ops {
         p->routes[0][CHEB_ROUTE_INT8] += 1;
         return rns(GEMM_CN, p->nproj, nb, p->npw, p->rproj, X, ldx, e, w, step, [&](const int* pred) {
           return gemm<double, double, double, double>(GEMM_CN, p->nproj, nb, p->npw, P(), p->npw, X, ldx, e,
-                                                      gemm_pick_splits(p->nproj, nb, p->npw), w.part, st, ROLE_PROJECT,
+                                                      rns_fp64_splits(p), w.rpart, st, ROLE_PROJECT,
                                                       false, pred);
         });
       }

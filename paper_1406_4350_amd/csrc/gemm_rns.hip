@@ -292,22 +292,21 @@ __device__ __forceinline__ void residues(int l, const Digits (&re)[NV], const Di
 
 // Vectors contiguous along k (columns of B, columns of A under a conjugate transpose): 4 k per thread, so a wave
 // reads 4 KB and writes 256 bytes of each plane. Bound by memory: 16 bytes read, 3 kRnsMods written per element. A column
-// n with flag[n fs] set is written as zeros.
+// n with flag[n fs] set is left unwritten (its products are not used).
 template <typename E, bool DIFF>
 __global__ __launch_bounds__(256) void k_rns_split(long K, const cx<E>* __restrict__ B, long ldb,
                                                    const double* __restrict__ scale, int8_t* __restrict__ base,
                                                    int8_t* __restrict__ third, long plane, long ld, const int* __restrict__ flag, int fs) {
   const long k = (long(blockIdx.x) * 256 + threadIdx.x) * 4;
   const long n = blockIdx.y;
-  if (k >= ld) return;
+  if (k >= ld || flag[n * fs]) return;
   const double s = scale[n];
-  const bool fit = flag[n * fs] == 0;
   const cx<E>* col = B + n * ldb;
   Digits re[4], im[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const cx<E> v = col[min(k + j, K - 1)];
-    const bool in = fit && k + j < K;
+    const bool in = k + j < K;
     re[j] = digits(in ? double(v.x) * s : 0.0);
     im[j] = digits(in ? double(v.y) * s : 0.0);
   }

@@ -143,7 +143,7 @@ template <typename E>
 hipError_t rns_row_envelope(long M, int K, const cx<E>* A, long lda, const double* rnorm, double* env, hipStream_t st);
 hipError_t rns_flat_overlap(long K, const double* env, double* out, hipStream_t st);
 // Residue planes of scaled columns (row n of a plane = column n; base null: not written) with the sums re + im or, with
-// diff, the differences re - im as third planes, zeros for a column n with flag[n fs] set, and of scaled rows (row m = row
+// diff, the differences re - im as third planes, nothing for a column n with flag[n fs] set, and of scaled rows (row m = row
 // m) with the sums (nothing if *flag is set).
 template <typename E>
 hipError_t rns_split_cols(long K, int N, const cx<E>* B, long ldb, const double* scale, int8_t* base, int8_t* third,
