@@ -656,7 +656,7 @@ __global__ __launch_bounds__(HTile<TB>::NT) void k_gemm_h(int M, int N, int K, i
 // tile t is multiplied, tile t + 1 goes from registers to the other stage and tile t + 2 is requested from memory, one
 // 16-byte access behind each MFMA or two (sched_group_barrier), and the fragments of the next 16 k are read one step
 // ahead, across the one barrier of the tile. The epilogue passes through LDS so that its operands are read and written
-// with m across the lanes. Bound by power: the matrix cores are 62% busy at 1.5 to 1.6 GHz (8 waves of 64 x 32 tiles
+// with m across the lanes. Bound by power: the matrix cores are 63 to 67% busy at 1.57 to 1.65 GHz (8 waves of 64 x 32 tiles
 // without the interleaving: 45 to 50% at 1.9 to 2.0 GHz), 1.06 PFLOP/s executed. 3328 x 1024 x 137065 12.0 -> 10.6 ms,
 // 137065 x 1024 x 3328 with three epilogue operands 12.4 -> 10.6 ms.
 constexpr int PT = 128, PKB = 2 * HBK;       // output tile; bytes of a stage row

@@ -11,10 +11,13 @@
 // |a| |b| (chain: the K range that one accumulator sums) where the two vectors overlap, and less where they do not. A
 // column of B therefore takes this route only if sum_k |a_k b_k| >= kRnsOverlap |a| |b| for every row a, which the
 // envelope env_k = min over the rows of |a_k| / |a|, kept with A's planes, bounds from below by sum_k env_k |b_k|: its
-// error is then at most about 2^-61 / 2^-8 = 2^-53 of sum |a_k b_k|, one rounding of the sum of the magnitudes. The other
+// error is then in the mean square at most 2^-61.3 / 2^-8 = 2^-53.3 of sum |a_k b_k|, what FP64 leaves too. The other
 // columns, flagged, take the FP64 product. Blocks of a plane-wave calculation pass: the envelope bounds measured 0.03 to
 // 0.27 for P^H x (the overlaps themselves 0.16 to 0.67) and 0.007 to 0.2 for P w (0.04 to 0.46), from random smooth
-// blocks to converged ones. With 15 moduli (2^57) the entries of small overlap came out less exact than from FP64.
+// blocks to converged ones. There, entry by entry against extended precision (17 077 plane waves, 832 projectors, 512
+// bands), in units of 2^-53 sum |a_k b_k|: largest error 0.06 to 0.25 and 0.018 to 0.032 in the mean square (mostly the
+// rounding of the result), from the FP64 product 3.1 to 20 and 0.58 to 1.5. With 15 moduli (2^57) the same bound would
+// need an overlap 16 times as large, which the envelope bounds of P w do not reach.
 //
 // The scheme (residues of scaled integers, one INT8 product per modulus, Chinese remaindering) is the one that Ozaki,
 // Uchino and Imamura published as Ozaki scheme II (arXiv:2504.08009); moduli, splitting, kernels and guard are this file's.
@@ -378,7 +381,8 @@ __device__ __forceinline__ int stage_at(int r, int c) { return r * RK + ((c ^ ((
 // one step ahead, across the one barrier of the tile: the MFMAs never wait on a whole group of loads. Measured at
 // 3328 x 512 x 32768, 45 products (15 moduli): 2070 TOP/s against 1890 without the two stages as separate arrays (the compiler
 // then orders reads behind writes), 1560 without the interleaving, and 3100 for the MFMAs alone: power is
-// the limit (matrix cores 70% busy at 1.5 GHz). Loads straight to LDS measured 5% slower; persistent blocks that request
+// the limit (in a filter of 2048 bands at 128^3 the matrix cores are 81% busy at 1.36 GHz in P^H x and 64% at 1.61 GHz in
+// P w, whose tiles of 3328 k are short). Loads straight to LDS measured 5% slower; persistent blocks that request
 // the next output tile's operands during the last k tiles of this one left too few registers for the reduction of the
 // accumulators and took 31 instead of 22 us per tile at 1024 k.
 __global__ __launch_bounds__(256, 1) void k_rns_gemm(int M, int N, int nt, RnsOperand A, RnsOperand B,
