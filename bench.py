@@ -185,22 +185,23 @@ def roofline(prof, kind, n):
     dom = max(cands, key=lambda k: cands[k]["ms"])
     out = class_roofline(dom, cands[dom], kind, n)
     out["kernel_class"] = dom
-    out["traffic"] = load_traffic(out["kernel"], n)
+    out["traffic"] = load_traffic(out["kernel"], n, dom)
     out["by_class"] = {k: {kk: (round(vv, 4) if isinstance(vv, float) else vv)
                            for kk, vv in class_roofline(k, v, kind, n).items()} for k, v in cands.items()}
     return out
 
 
-def load_traffic(kernel, n):
-    """HBM bytes per launch from the committed rocprofv3 FETCH_SIZE/WRITE_SIZE summary, if it covers this
-    kernel at this box size and the kernel source it was taken on is unchanged; else None."""
+def load_traffic(kernel, n, cls=None):
+    """HBM bytes per launch from the committed rocprofv3 FETCH_SIZE/WRITE_SIZE summary, if it covers this kernel (of
+    this timer class, where one kernel serves several) at this box size and the kernel source it was taken on is
+    unchanged; else None."""
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
         return None
     try:
         with open(path) as f:
             data = json.load(f)
-        ent = data.get(kernel)
+        ent = data.get(f"{kernel} {cls}") or data.get(kernel)
         if not ent or int(ent.get("n", n)) != int(n):
             return None
         import hashlib

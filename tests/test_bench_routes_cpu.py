@@ -1,4 +1,7 @@
 """bench.py names the kernel and the peak of the projector products by the routes that the plan counted."""
+import hashlib
+import json
+
 import pytest
 
 import bench
@@ -27,3 +30,17 @@ def test_fp64_products_stay_fp64_whatever_their_rate():
 def test_mixed_products_by_their_tile(n, routes, kernel):
     r = bench.class_roofline("project", _cls(200.0, routes), "f32", n)
     assert r["kernel"] == kernel and r["mfma_dtype"] == "f16x3"
+
+
+def test_traffic_of_a_kernel_that_serves_two_classes(tmp_path, monkeypatch):
+    csrc = tmp_path / "paper_1406_4350_amd" / "csrc"
+    csrc.mkdir(parents=True)
+    (csrc / "k.hip").write_text("kernel")
+    h = hashlib.sha256(b"kernel").hexdigest()
+    (tmp_path / "profiles").mkdir()
+    ent = {"n": 128, "source": "k.hip", "source_sha256": h}
+    (tmp_path / "profiles" / "traffic.json").write_text(json.dumps(
+        {"k project": dict(ent, bytes_per_launch=1.0), "k backproject": dict(ent, bytes_per_launch=2.0)}))
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    assert bench.load_traffic("k", 128, "project") == 1.0 and bench.load_traffic("k", 128, "backproject") == 2.0
+    assert bench.load_traffic("k", 128) is None and bench.load_traffic("k", 128, "small") is None
