@@ -202,6 +202,23 @@ def test_plan_without_residue_planes(problem):
     lean.close()
 
 
+def test_planes_of_one_product(problem):
+    """256 projectors: P^H x pays on INT8 at some widths, P w at none, so the plan holds the planes of P^H x only."""
+    pb = wl.make_problem(wl.Config("routes64b", 64, 16, 16.0, "sc", 4, 64, "sp", True, 8, 4, 1, 4, 152))
+    plan = cf.plan_from_problem(pb, cf.CHEB_FP64)
+    lean = cf.Plan(pb.gidx, pb.kin, 64, pb.proj_off, True, residue_planes=False)
+    planes = plan.persistent.numel() - lean.persistent.numel()
+    assert 48 * pb.P.size < planes < 60 * pb.P.size
+    P, Q = torch.from_numpy(np.ascontiguousarray(pb.P.T)).cuda(), torch.from_numpy(pb.Q).cuda()
+    X = _block(pb.npw, 513, 51)
+    Y = torch.empty_like(X)
+    assert _took(plan, lambda: plan.apply_S(X, Y)) == [{"int8": 1}, {"mfma": 1}]
+    assert _rel(Y, _s(X, P, Q)) < 1e-13
+    assert _rel(plan.apply_Sinv(Y), X) < 1e-12
+    plan.close()
+    lean.close()
+
+
 def test_mixed_routes_and_reset(problem):
     """Mixed plans count their FP16 products by tile; profile_enable resets the counts; other classes are refused."""
     pb, _, _, _ = problem
