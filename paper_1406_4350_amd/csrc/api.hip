@@ -716,14 +716,6 @@ template <typename T> struct Ops {
   using C = cx<T>;
   cheb_plan p;
   hipStream_t st;
-  bool single = false;  // one operator per call (cheb_apply_H, _S, _Sinv, cheb_rayleigh_quotients)
-  // K splits of an FP64 product. The small GEMM of a call that applies one operator does not split K over blocks: the
-  // reduction is one launch more where a call is three or four, and a program that issues such calls in a row is held by
-  // their launches (S X at 24^3 with 65 projectors and 8 bands: 17.0 us a call without the split, 21.1 with it; waited for
-  // one by one 33.8 and 29.8). In the chains of a filter, Rayleigh-Ritz or Lanczos step the split pays (k_gemm_s).
-  int splits(int M, int N, int K) const {
-    return single && std::is_same<T, double>::value && gemm_is_small(M, N, K) ? 1 : gemm_pick_splits(M, N, K);
-  }
   FftGeom geom() const { return FftGeom{p->n, p->ncol, p->npw, p->rx, p->col, p->ent, p->xline, p->narrow}; }
   // algorithmic flops of one band's plane pass: on each of the n z-planes, 2 (2 rx + 1) y-transforms of the
   // nonzero x-lines and 2 n x-transforms of the rows, 5 n log2 n flops per complex length-n transform, and the
@@ -915,10 +907,27 @@ template <typename T> struct Ops {
     } else {
       p->routes[0][CHEB_ROUTE_MFMA] += 1;
       HIPCHK((gemm<T, T, T, double>(GEMM_CN, p->nproj, nb, p->npw, P(), p->npw, X, ldx, e,
-                                    splits(p->nproj, nb, p->npw), w.part, st, ROLE_PROJECT, false, nullptr,
-                                    re_form())));
+                                    gemm_pick_splits(p->nproj, nb, p->npw), w.part, st, ROLE_PROJECT, false,
+                                    nullptr, re_form())));
     }
     return CHEB_OK;
+  }
+
+  // P^H X for a kernel that adds split-K partials itself: *parts > 1 of them in w.part, else the projections in w.p0
+  cheb_status project_parts(const C* X, long ldx, int nb, const Ws& w, int* parts) {
+    *parts = 1;
+    if constexpr (std::is_same<T, double>::value) {
+      const int np = p->nproj, npw = p->npw;
+      if (gemm_is_small(np, nb, npw)) *parts = gemm_small_splits(np, nb, npw, gemm_pick_splits(np, nb, npw));
+      if (*parts > 1) {
+        Timed t(p, st, CHEB_T_PROJECT, (double(npw) * np + double(npw) * nb) * sizeof(C) + double(np) * nb * 16.0,
+                8.0 * np * nb * double(npw));
+        p->routes[0][CHEB_ROUTE_MFMA] += 1;
+        HIPCHK(gemm_small_parts(GEMM_CN, np, nb, npw, P(), npw, X, ldx, *parts, w.part, st));
+        return CHEB_OK;
+      }
+    }
+    return project(X, ldx, nb, w.p0, w);
   }
 
   // out = alpha P wv + bL L (+ bU U + bW W): back-projection with the vector epilogue
@@ -962,8 +971,8 @@ template <typename T> struct Ops {
     const int np = p->nproj;
     const double vecs = 2.0 + (e.L ? 1 : 0) + (e.U ? 1 : 0) + (e.W ? 1 : 0);
     Timed t(p, st, CHEB_T_SMALL, double(np) * K * 16.0 + vecs * np * nb * 16.0, 8.0 * np * double(K) * nb);
-    HIPCHK((gemm<double, double, double, double>(GEMM_NN, np, nb, K, A, lda, x, ldx, e, splits(np, nb, K), part,
-                                                 st)));
+    HIPCHK((gemm<double, double, double, double>(GEMM_NN, np, nb, K, A, lda, x, ldx, e, gemm_pick_splits(np, nb, K),
+                                                 part, st)));
     return CHEB_OK;
   }
   cheb_status small(const c128* M, const c128* x, int nb, Epi<double> e, c128* part) {
@@ -995,8 +1004,12 @@ template <typename T> struct Ops {
   cheb_status apply_H(const C* X, long ldx, C* Y, long ldy, int nb, const Ws& w) {
     CHK(hloc(X, ldx, nb, Y, ldy, w.fft));
     if (p->nproj == 0) return CHEB_OK;
-    CHK(project(X, ldx, nb, w.p0, w));
-    HIPCHK(block_diag_apply(p->nproj, nb, p->pinfo, p->D, w.p0, p->nproj, w.Dp, p->nproj, st));
+    int parts = 1;
+    CHK(project_parts(X, ldx, nb, w, &parts));
+    if (parts > 1)
+      HIPCHK(block_diag_parts(p->nproj, nb, p->pinfo, p->D, parts, w.part, p->gamma != 0, w.Dp, p->nproj, st));
+    else
+      HIPCHK(block_diag_apply(p->nproj, nb, p->pinfo, p->D, w.p0, p->nproj, w.Dp, p->nproj, st));
     Epi<T> e;
     e.out = Y; e.ldo = ldy; e.alpha = 1.0;
     e.L = Y; e.ldl = ldy; e.bL = 1.0;
@@ -1008,8 +1021,10 @@ template <typename T> struct Ops {
       HIPCHK((convert_copy<T, T>(p->npw, nb, X, ldx, Y, ldy, st)));
       return CHEB_OK;
     }
-    CHK(project(X, ldx, nb, w.p0, w));
-    HIPCHK(diag_apply(p->nproj, nb, p->Q, w.p0, p->nproj, w.Dp, p->nproj, st));
+    int parts = 1;
+    CHK(project_parts(X, ldx, nb, w, &parts));
+    if (parts > 1) HIPCHK(diag_parts(p->nproj, nb, p->Q, parts, w.part, p->gamma != 0, w.Dp, p->nproj, st));
+    else HIPCHK(diag_apply(p->nproj, nb, p->Q, w.p0, p->nproj, w.Dp, p->nproj, st));
     Epi<T> e;
     e.out = Y; e.ldo = ldy; e.alpha = 1.0;
     e.L = X; e.ldl = ldx; e.bL = 1.0;
@@ -1021,8 +1036,16 @@ template <typename T> struct Ops {
       HIPCHK((convert_copy<T, T>(p->npw, nb, X, ldx, Y, ldy, st)));
       return CHEB_OK;
     }
-    CHK(project(X, ldx, nb, w.p0, w));
-    CHK(cinv(w.p0, p->nproj, nb, w.Dp, p->nproj, w));
+    int parts = 1;
+    if (p->nproj <= kDensePartsProj && p->cap_iters <= 0) CHK(project_parts(X, ldx, nb, w, &parts));
+    else CHK(project(X, ldx, nb, w.p0, w));
+    if (parts > 1) {
+      const double np = p->nproj;
+      Timed t(p, st, CHEB_T_SMALL, np * np * 16.0 + 2.0 * np * nb * 16.0, 8.0 * np * np * nb);
+      HIPCHK(dense_parts(p->nproj, nb, p->Cinv, parts, w.part, p->gamma != 0, w.Dp, p->nproj, st));
+    } else {
+      CHK(cinv(w.p0, p->nproj, nb, w.Dp, p->nproj, w));
+    }
     Epi<T> e;
     e.out = Y; e.ldo = ldy; e.alpha = -1.0;
     e.L = X; e.ldl = ldx; e.bL = 1.0;
@@ -2555,7 +2578,6 @@ static cheb_status apply_common(cheb_plan p, int which, const void* X, int ldx, 
     using C = typename decltype(ops)::C;
     const C* x = static_cast<const C*>(X);
     C* y = static_cast<C*>(Y);
-    ops.single = true;
     if (which == 0) return ops.apply_H(x, ldx, y, ldy, nb, w);
     if (which == 1) return ops.apply_S(x, ldx, y, ldy, nb, w);
     return ops.apply_Sinv(x, ldx, y, ldy, nb, w);
@@ -2798,7 +2820,6 @@ cheb_status cheb_rayleigh_quotients(cheb_plan p, const void* X, int ldx, int nb,
   OP_PRELUDE(CHEB_OP_RR, nb);
   return with_prec(p, st, [&](auto ops) {
     using C = typename decltype(ops)::C;
-    ops.single = true;
     return ops.rayleigh_quotients(static_cast<const C*>(X), ldx, nb, rq, w);
   });
 } catch (...) {

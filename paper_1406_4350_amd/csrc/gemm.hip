@@ -352,7 +352,8 @@ __global__ __launch_bounds__(256) void k_reduce(int M, int N, int splits, const 
 // order): the 4 lanes of one B column (and of one A column for conj(A)^T) read 64 contiguous bytes per load.
 //
 // Few blocks with a longer K (the projections and Grams of the small spheres) leave the chip idle while each block pulls
-// its whole K through one CU: K is then split over blocks too, and the partial blocks summed by k_reduce (65 x 41 x 925,
+// its whole K through one CU: K is then split over blocks too, and the partial blocks summed by k_reduce, or by the kernel
+// that reads the product next where it can (gemm_small_parts) (65 x 41 x 925,
 // 15 blocks: 15.1 us in one launch, also with 16 waves per block; 8.4 us with 14 splits, the reduction included). Filters of
 // 4 steps at 24^3, 4 to 130 projectors and 1 to 100 bands, take 145 to 206 us instead of 150 to 238; Rayleigh-Ritz of 1 to
 // 100 bands there 231 to 272 instead of 276 to 319; with 832 projectors (their K in projector space) 1 to 8 bands gain 1%.
@@ -973,6 +974,37 @@ int gemm_pick_splits(int M, int N, int K) {
 
 bool gemm_is_small(int M, int N, int K) { return K <= SKMAX && long((M + 15) / 16) * ((N + 15) / 16) <= SBLKMAX; }
 
+// K of a wave with s splits, and K over blocks as well where few of them meet a longer K: up to a block per CU, at least
+// 64 k each
+static int gemm_small_chunk(int K, int s) {
+  const int kc = (std::max(K, 0) + SW * s - 1) / (SW * s);
+  return std::max(SKG, ((kc + SKG - 1) / SKG) * SKG);
+}
+int gemm_small_splits(int M, int N, int K, int splits) {
+  const long blocks = long((M + 15) / 16) * ((N + 15) / 16);
+  if (K < 512 || blocks > 64) return 1;
+  const int s = int(std::min<long>({long(std::max(splits, 1)), 256 / blocks, long(K / 64)}));
+  const int kc = gemm_small_chunk(K, s);
+  return std::max(1, (K + SW * kc - 1) / (SW * kc));
+}
+template <typename EO>
+static hipError_t gemm_small_launch(GemmMode mode, int M, int N, int K, const c128* A, long lda, const c128* B, long ldb,
+                                    int s, const Epi<EO>& epi, c128* part, hipStream_t st) {
+  const dim3 grid(unsigned(long((M + 15) / 16) * ((N + 15) / 16) * s));
+  const int kc = gemm_small_chunk(K, s);
+  if (mode == GEMM_CN)
+    hipLaunchKernelGGL((k_gemm_s<EO, GEMM_CN>), grid, dim3(64 * SW), 0, st, M, N, K, kc, A, lda, B, ldb, epi, part);
+  else
+    hipLaunchKernelGGL((k_gemm_s<EO, GEMM_NN>), grid, dim3(64 * SW), 0, st, M, N, K, kc, A, lda, B, ldb, epi, part);
+  return hipGetLastError();
+}
+hipError_t gemm_small_parts(GemmMode mode, int M, int N, int K, const c128* A, long lda, const c128* B, long ldb,
+                            int count, c128* part, hipStream_t st) {
+  if (M <= 0 || N <= 0) return hipSuccess;
+  if (!part || !gemm_is_small(M, N, K)) return hipErrorInvalidValue;
+  return gemm_small_launch<double>(mode, M, N, K, A, lda, B, ldb, count, Epi<double>{}, part, st);
+}
+
 template <typename T, typename EA, typename EB, typename EO>
 hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, const cx<EB>* B, long ldb,
                 const Epi<EO>& epi, int splits, c128* part, hipStream_t st, GemmRole role, bool upper,
@@ -984,27 +1016,12 @@ hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, c
   if (pred && !(kPred && form == FORM_FULL && (role == ROLE_PROJECT || role == ROLE_BACKPROJECT))) return hipErrorInvalidValue;
   if constexpr (std::is_same<T, double>::value && std::is_same<EA, double>::value && std::is_same<EB, double>::value) {
     if (gemm_is_small(M, N, K)) {
-      const long blocks = long((M + 15) / 16) * ((N + 15) / 16);
       if (pred) return hipErrorInvalidValue;  // too small for a product that has another route
-      // K over blocks as well where few of them meet a longer K: up to a block per CU, at least 64 k each
-      int s = 1;
-      if (part && K >= 512 && blocks <= 64) s = int(std::min<long>({long(std::max(splits, 1)), 256 / blocks, long(K / 64)}));
-      int kc = (std::max(K, 0) + SW * s - 1) / (SW * s);
-      kc = std::max(SKG, ((kc + SKG - 1) / SKG) * SKG);
-      s = std::max(1, (K + SW * kc - 1) / (SW * kc));
-      c128* pp = s > 1 ? part : nullptr;
-      if (mode == GEMM_CN)
-        hipLaunchKernelGGL((k_gemm_s<EO, GEMM_CN>), dim3(unsigned(blocks * s)), dim3(64 * SW), 0, st, M, N, K, kc, A, lda,
-                           B, ldb, epi, pp);
-      else
-        hipLaunchKernelGGL((k_gemm_s<EO, GEMM_NN>), dim3(unsigned(blocks * s)), dim3(64 * SW), 0, st, M, N, K, kc, A, lda,
-                           B, ldb, epi, pp);
-      if (s > 1) {
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        const long total = long(M) * N;
-        hipLaunchKernelGGL((k_reduce<EO>), dim3(unsigned((total + 255) / 256)), dim3(256), 0, st, M, N, s, part, epi);
-      }
+      const int s = part ? gemm_small_splits(M, N, K, splits) : 1;
+      const hipError_t e = gemm_small_launch(mode, M, N, K, A, lda, B, ldb, s, epi, s > 1 ? part : nullptr, st);
+      if (e != hipSuccess || s == 1) return e;
+      const long total = long(M) * N;
+      hipLaunchKernelGGL((k_reduce<EO>), dim3(unsigned((total + 255) / 256)), dim3(256), 0, st, M, N, s, part, epi);
       return hipGetLastError();
     }
   }

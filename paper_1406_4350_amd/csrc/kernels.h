@@ -42,6 +42,11 @@ hipError_t gemm(GemmMode mode, int M, int N, int K, const cx<EA>* A, long lda, c
 int gemm_upper_splits(int N, int K);
 // whether an FP64 product of FP64 operands takes the small GEMM (one 16 x 16 block of the result per workgroup)
 bool gemm_is_small(int M, int N, int K);
+// The splits that such a product takes where `splits` partials have room, and the product left as that many partials
+// (count x M x N in part, ld M) for a kernel that adds them itself (diag_parts, block_diag_parts).
+int gemm_small_splits(int M, int N, int K, int splits);
+hipError_t gemm_small_parts(GemmMode mode, int M, int N, int K, const c128* A, long lda, const c128* B, long ldb,
+                            int count, c128* part, hipStream_t st);
 // A[i][j] = conj(A[j][i]) for i > j (n x n, column-major)
 hipError_t hermitian_lower(int n, c128* A, long lda, hipStream_t st);
 
@@ -221,6 +226,17 @@ hipError_t block_diag_apply_c(int nproj, int nb, const int4* pinfo, const c128* 
                               long ldo, bool accumulate, hipStream_t st);
 hipError_t diag_apply(int nproj, int nb, const double* d, const c128* in, long ldi, c128* out, long ldo,
                       hipStream_t st);
+// The same (d, blockdiag(D), and a dense nproj x nproj A up to kDensePartsProj) of a sum of `parts` partials (nproj x nb each, ld nproj), their real parts with real_only
+hipError_t diag_parts(int nproj, int nb, const double* d, int parts, const c128* part, bool real_only, c128* out,
+                      long ldo, hipStream_t st);
+hipError_t block_diag_parts(int nproj, int nb, const int4* pinfo, const double* D, int parts, const c128* part,
+                            bool real_only, c128* out, long ldo, hipStream_t st);
+// 192: one block per band pulls all of A through its CU. S^-1 X at 24^3, 8 bands, waited for one by one (and in a row), with
+// this kernel and with a reduction launch and k_gemm_s: 29.3 and 32.0 us (16.4, 19.5) at 65 projectors, 32.9 and 34.3 (16.7,
+// 19.8) at 169, 35.1 and 33.8 (18.1, 19.7) at 208.
+constexpr int kDensePartsProj = 192;
+hipError_t dense_parts(int nproj, int nb, const c128* A, int parts, const c128* part, bool real_only, c128* out, long ldo,
+                       hipStream_t st);
 // Projector space of a filter step with an overlap (S = I + P Q P^H, Q diagonal, C = Q^-1 + P^H P): open: dp = D cur and
 // qdp = Q^-1 D cur (both ld ldd); close: out = s1 (Q^-1 (dp - w) - c cur) - s2 prev (prev may be null or out), and with
 // next the open of out for the following step. atom: projectors of the largest atom.

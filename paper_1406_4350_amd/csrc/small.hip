@@ -189,6 +189,86 @@ __global__ void k_diag(int nproj, int nb, const double* __restrict__ d, const c1
   }
 }
 
+// A band's sum v of split-K partials, one projector per thread and one band per block, eight partials in flight and added in
+// order: the reduction of a small split projection inside the kernel that follows it, since operators of three or four
+// kernels at these sizes are held by their launches (925 plane waves, 65 projectors, 8 bands, with a reduction launch and
+// with these: S X 29.8 and 27.4 us, H X 43.3 and 40.8, S^-1 X 32.0 and 29.3 waited for one by one; S X in a row 19.5 and 16.4).
+__device__ inline c128 sum_parts(const c128* __restrict__ v, int parts, long total, int real_only) {
+  double re = 0.0, im = 0.0;
+  for (int s0 = 0; s0 < parts; s0 += 8) {
+    c128 x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = v[long(min(s0 + j, parts - 1)) * total];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      re = s0 + j < parts ? re + x[j].x : re;
+      im = s0 + j < parts ? im + x[j].y : im;
+    }
+  }
+  return c128{re, real_only ? 0.0 : im};
+}
+
+// d .* v or blockdiag(D) v
+constexpr int kPartsProj = 1024;  // a split product of at most 64 blocks of 16 x 16 has no more rows
+template <bool BLOCK>
+__global__ __launch_bounds__(kPartsProj) void k_diag_parts(int nproj, long total, const int4* __restrict__ pinfo,
+                                                    const double* __restrict__ D, int parts,
+                                                    const c128* __restrict__ part, int real_only,
+                                                    c128* __restrict__ out, long ldo) {
+  __shared__ c128 col[BLOCK ? kPartsProj : 1];
+  const long b = blockIdx.x;
+  const int i = threadIdx.x;
+  c128 v{0.0, 0.0};
+  if (i < nproj) v = sum_parts(part + b * nproj + i, parts, total, real_only);
+  if constexpr (BLOCK) {
+    if (i < nproj) col[i] = v;
+    __syncthreads();
+    if (i < nproj) {
+      const int4 pi = pinfo[i];  // {atom's first row, block size, block offset, 0}
+      const double* Drow = D + pi.z + long(i - pi.x) * pi.y;
+      double re = 0.0, im = 0.0;
+      for (int j = 0; j < pi.y; ++j) {
+        re += Drow[j] * col[pi.x + j].x;
+        im += Drow[j] * col[pi.x + j].y;
+      }
+      out[b * ldo + i] = c128{re, im};
+    }
+  } else if (i < nproj) {
+    out[b * ldo + i] = c128{D[i] * v.x, D[i] * v.y};
+  }
+}
+
+// A v, A nproj x nproj (ld nproj): threads (projector, part of the columns of A), the parts added in LDS
+__global__ __launch_bounds__(1024) void k_dense_parts(int nproj, long total, const c128* __restrict__ A, int parts,
+                                                      const c128* __restrict__ part, int real_only,
+                                                      c128* __restrict__ out, long ldo) {
+  __shared__ c128 col[kDensePartsProj];
+  __shared__ c128 red[1024];
+  const long b = blockIdx.x;
+  const int i = threadIdx.x, g = threadIdx.y;
+  if (g == 0 && i < nproj) col[i] = sum_parts(part + b * nproj + i, parts, total, real_only);
+  __syncthreads();
+  const int per = (nproj + blockDim.y - 1) / blockDim.y, j1 = min(nproj, (g + 1) * per);
+  double re = 0.0, im = 0.0;
+  if (i < nproj) {
+#pragma unroll 8
+    for (int j = g * per; j < j1; ++j) {
+      const c128 a = A[long(j) * nproj + i], v = col[j];
+      re += a.x * v.x - a.y * v.y;
+      im += a.x * v.y + a.y * v.x;
+    }
+  }
+  red[g * blockDim.x + i] = c128{re, im};
+  __syncthreads();
+  if (g == 0 && i < nproj) {
+    for (int h = 1; h < int(blockDim.y); ++h) {
+      re += red[h * blockDim.x + i].x;
+      im += red[h * blockDim.x + i].y;
+    }
+    out[b * ldo + i] = c128{re, im};
+  }
+}
+
 template <typename E>
 __global__ void k_axpbypcz(long rows, int nb, double a, const cx<E>* x, long ldx, double b, const cx<E>* y, long ldy,
                            double c, const cx<E>* z, long ldz, cx<E>* out, long ldo) {
@@ -399,6 +479,31 @@ hipError_t block_diag_apply(int nproj, int nb, const int4* pinfo, const double* 
   return hipGetLastError();
 }
 
+hipError_t diag_parts(int nproj, int nb, const double* d, int parts, const c128* part, bool real_only, c128* out,
+                      long ldo, hipStream_t st) {
+  if (nproj <= 0 || nb <= 0) return hipSuccess;
+  if (nproj > kPartsProj) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_diag_parts<false>), dim3(nb), dim3((nproj + 63) / 64 * 64), 0, st, nproj, long(nproj) * nb, nullptr, d, parts, part,
+                     real_only ? 1 : 0, out, ldo);
+  return hipGetLastError();
+}
+hipError_t block_diag_parts(int nproj, int nb, const int4* pinfo, const double* D, int parts, const c128* part,
+                            bool real_only, c128* out, long ldo, hipStream_t st) {
+  if (nproj <= 0 || nb <= 0) return hipSuccess;
+  if (nproj > kPartsProj) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_diag_parts<true>), dim3(nb), dim3((nproj + 63) / 64 * 64), 0, st, nproj, long(nproj) * nb, pinfo, D, parts, part,
+                     real_only ? 1 : 0, out, ldo);
+  return hipGetLastError();
+}
+hipError_t dense_parts(int nproj, int nb, const c128* A, int parts, const c128* part, bool real_only, c128* out, long ldo,
+                       hipStream_t st) {
+  if (nproj <= 0 || nb <= 0) return hipSuccess;
+  if (nproj > kDensePartsProj) return hipErrorInvalidValue;
+  const int px = (nproj + 63) / 64 * 64;
+  hipLaunchKernelGGL(k_dense_parts, dim3(nb), dim3(px, 1024 / px), 0, st, nproj, long(nproj) * nb, A, parts, part,
+                     real_only ? 1 : 0, out, ldo);
+  return hipGetLastError();
+}
 hipError_t block_inverse(int nproj, const int4* pinfo, const c128* C, long ldc, c128* Minv, int* bad, hipStream_t st) {
   if (nproj <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_block_inverse, dim3(nproj), dim3(256), 0, st, nproj, pinfo, C, ldc, Minv, bad);
